@@ -211,7 +211,7 @@ struct GemmGroup {   // problems that go into one phase (no dependencies among t
     std::vector<GemmProblem> probs;
 };
 
-int tile_edge(int cfg) { return cfg == 0 ? 128 : 64; }
+int tile_edge(int cfg) { return cfg == 0 ? 128 : cfg == 2 ? 32 : 64; }
 
 // Rough time model (matrix-pipe cycles) of one problem under a tile configuration: the
 // matrix instructions of the workgroups resident on a CU serialise per SIMD, and a lone
@@ -251,6 +251,45 @@ void finish_problem(GemmProblem &P)
     if (P.ones == 0) P.ones = P.K;
 }
 
+// Whether a phase of plain fp32 products (three-plane mode) runs through the direct kernel of gemm_direct.hip, and with
+// which tile: 2 (32 x 32), 3 (64 x 64), or -1: the staged kernels of gemm_nt.hip with the configurations already chosen.
+// All problems of the phase go into one launch then.  Microseconds, fitted to launches of 1 to 30 products of
+// 33 ... 2304 rows (gfx950): a fixed part, then either the contraction of one workgroup (latency) or all tile steps
+// spread over the chip (throughput).  The 32-tile moves twice the operand bytes per flop and ends at 55 TFLOP/s, but
+// 288 x 288 x 288 takes 6.5 us instead of 13 (symmetric, with beta: 8 instead of 16) and 576 x 576 x 576 13.7 instead
+// of 21.5; the 64-tile without LDS staging has a shorter fixed part and K loop than the staged one at the same rate
+// (1152 x 1152 x 1152 symmetric: 28 us instead of 40).
+int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun, bool allow_split)
+{
+    double wgk[4] = {0, 0, 0, 0}, kmax[4] = {0, 0, 0, 0}, kall = 0;
+    bool split = false;
+    for (const GemmProblem &P : probs) {
+        if (P.a.hw <= P.K || P.b.hw <= P.K || (P.flags & (GEMM_BORDER | GEMM_TRANS))) return -1;
+        auto tiles = [&](int B) {
+            const double tm = (P.M + B - 1) / B, tn = (P.N + B - 1) / B;
+            return (P.flags & GEMM_SYM) ? tm * (tm + 1) / 2 : tm * tn;
+        };
+        double k_wg = P.K;
+        if (allow_split) {
+            const int want = (int)((tun.target_wgs + tiles(tile_edge(P.tile_cfg)) - 1) / tiles(tile_edge(P.tile_cfg)));
+            const int s = std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(want, P.K / tun.min_k_per_split));
+            if (s > 1) { k_wg = P.K / s; split = true; }
+        }
+        wgk[P.tile_cfg] += tiles(tile_edge(P.tile_cfg)) * P.K;
+        kmax[P.tile_cfg] = std::max(kmax[P.tile_cfg], k_wg);
+        wgk[2] += tiles(32) * P.K;
+        wgk[3] += tiles(64) * P.K;
+        kall = std::max(kall, (double)P.K);
+    }
+    double staged = split ? 6.0 : 0.0;   // the reduction launch
+    if (kmax[0] > 0) staged += 12.0 + std::max(0.050 * kmax[0], 2.0e-4 * wgk[0]);
+    if (kmax[1] > 0) staged += 5.0 + std::max(0.0265 * kmax[1], 8.3e-5 * wgk[1]);
+    const double d32 = 5.0 + std::max(0.0066 * kall, 3.65e-5 * wgk[2]);
+    const double d64 = 8.0 + std::max(0.013 * kall, 8.0e-5 * wgk[3]);
+    if (staged <= std::min(d32, d64)) return -1;
+    return d32 <= d64 ? 2 : 3;
+}
+
 // Emits the launches of one phase: per tile configuration one GEMM launch, plus one
 // reduction launch if any problem was split along K (appended to `deferred` instead, if given:
 // the caller then places the reductions after all the matrix launches, on a stream it chooses).
@@ -283,13 +322,18 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
         }
         finish_problem(P);
     }
-    for (int cfg = 0; cfg < 2; ++cfg) {
+    if (dtype == 0 && tun.split && !tun.force_tile && !tun.worst_case_splits) {   // (no scratch: the workspace bound leaves it out)
+        const int cfg = choose_direct(probs, tun, allow_split);
+        if (cfg >= 0)
+            for (auto &P : probs) { P.tile_cfg = cfg; finish_problem(P); }
+    }
+    for (int cfg = 0; cfg < 4; ++cfg) {
         std::vector<GemmProblem> sel;
         for (auto &P : probs)
             if (P.tile_cfg == cfg) sel.push_back(P);
         if (sel.empty()) continue;
         const int B = tile_edge(cfg);
-        if (allow_split) {
+        if (allow_split && cfg < 2) {
             // Per problem (independent of what else is in the launch, so that the workspace need of
             // a layer list does not depend on which of its inputs are present): enough splits for
             // target_wgs workgroups and at most max_k_per_wg of contraction each.
@@ -1482,8 +1526,10 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
         }
         switch (L.kind) {
             case L_GEMM:
-                e = launch_gemm((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b), L.n,
-                                L.total_wgs, L.cfg, L.dtype, ls);
+                e = L.cfg >= 2 ? launch_gemm_direct((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b),
+                                                    L.n, L.total_wgs, L.cfg, ls)
+                               : launch_gemm((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b), L.n,
+                                             L.total_wgs, L.cfg, L.dtype, ls);
                 break;
             case L_REDUCE:
                 e = launch_gemm_reduce((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b),

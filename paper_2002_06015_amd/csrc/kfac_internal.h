@@ -54,7 +54,7 @@ struct GemmProblem {
     int tiles_m, tiles_n, n_tiles;
     int splits, k_per_split;  // k_per_split is a multiple of 32
     int flags;
-    int tile_cfg;             // 0: 128x128 tiles, 1: 64x64 tiles
+    int tile_cfg;             // 0: 128x128 tiles, 1: 64x64 tiles; direct kernel: 2: 32x32, 3: 64x64
     float alpha, beta;        // C = alpha * acc + beta * C   (beta == 0: C is not read)
 };
 
@@ -258,6 +258,9 @@ __device__ __forceinline__ void split_pair(float x0, float x1, unsigned &h, unsi
 // ---- launchers (implemented in the kernel files) -----------------------------------
 hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs,
                        int total_wgs, int tile_cfg, int dtype, hipStream_t s);
+// small products of plain fp32 matrices (tile_cfg 2, 3), three-plane product mode
+hipError_t launch_gemm_direct(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, int total_wgs,
+                              int tile_cfg, hipStream_t s);
 hipError_t launch_gemm_reduce(const GemmProblem *probs_dev, const int *red_start_dev, int n_probs,
                               int total_wgs, hipStream_t s);
 hipError_t launch_patch(const PatchJob *jobs_dev, int n_jobs, int total_wgs, hipStream_t s);
