@@ -191,359 +191,498 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ blocked leaf inverse on the matrix cores
-// (X + damp I)^-1 for n <= 288 by one 1024-thread workgroup, as a symmetric block sweep with
-// 32x32 blocks.  The matrix is first scaled to unit diagonal (s_i = 1/sqrt(x_ii), undone at
-// the end), which makes every pivot of the elimination lie in (0, 1].  The workgroup holds
-// N = -(scaled matrix), lower-triangle 32x32 tiles only, each tile in the accumulator layout of
-// v_mfma_f32_32x32x2_f32 in the registers of one wavefront (tile t -> wavefront t % 16).
-// Sweeping block k (all i, j != k; D = (-N_kk)^-1; the column panel R_i = N_ik, taken from
-// tile (i,k) for i > k and from the transpose of tile (k,i) for i < k):
-//     P_i   = R_i D             ->  new N_ik (and N_ki = P_i^T)
-//     N_ij += P_i R_j^T         (symmetric: tiles i >= j only)
+// (X + damp I)^-1 for n <= 288 by one 1024-thread workgroup, as a symmetric block sweep with 32x32 blocks.  The matrix
+// is first scaled to unit diagonal (s_i = 1/sqrt(x_ii), undone at the end), which makes every pivot of the elimination
+// lie in (0, 1].  The workgroup holds N = -(scaled matrix), one 32x32 tile per unordered pair of block indices, in the
+// accumulator layout of the 32x32 matrix instructions in the registers of one wavefront.  Sweeping block k
+// (D = (-N_kk)^-1; R_i = N_ik, the column panel):
+//     P_i   = R_i D             ->  new N_ik
+//     N_ij += P_i R_j^T         (i, j != k)
 //     N_kk  = D
-// After all blocks N = X^-1 (the usual sweep operator, written for -X so that every update
-// is an accumulation).  R and P go through LDS; the products are MFMA.
-// D comes from a scalar sweep of the 32x32 diagonal tile inside its owner wavefront, also on
-// the matrix core: pivot p is the rank-1 update S += a b^T with b = row p (one accumulator
-// register across the lanes) and a = -row p / d (the tile is symmetric), patched so that the
-// same update leaves row and column p divided by d (a_p = 1/d - 1, b_p = d - 1; no cancellation
-// because d <= 1); two pivots share one 32x32x2 instruction.  A non-positive pivot is reported.
+// After all blocks N = X^-1 (the usual sweep operator, written for -X so that every update is an accumulation).
+//
+// The kernel is a latency chain on one compute unit: 9 dependent blocks for n = 288.  What it does about that:
+//   - One wavefront (the chain wavefront) holds no tile.  In step k it takes R_{k+1} and the diagonal tile of block
+//     k + 1 as the previous step left them, forms P_{k+1}, brings that tile up to date and sweeps it, all out of its own
+//     registers, while the other fifteen do the rest of step k.  D of the next block is ready when they are.
+//   - The tiles are dealt out as stars: a wavefront's tiles (at most three) share one block index v, so it needs one
+//     P_v only and forms it itself.  It forms the transpose, D R_v^T: its accumulator layout (lane: row of block v,
+//     registers: k) is, split into planes, the operand layout of the update R_j P_v^T, with the contraction index in the
+//     order the registers have.  Every operand uses that order; P never goes through LDS and one barrier per step is left.
+//   - A tile is (registers: row of block j, lanes: row of block v).  For the panel of step k a tile with j = k is stored
+//     as the fragments its readers load (three planes, 16 bytes a lane: form F), a tile with v = k as [k][row] rows that
+//     are read with the transposing LDS read (form T); no 2-byte stores.  The panels of two steps alternate.
+// n = 288: 49 us (77 us with two barriers per step, P and R through LDS and the sweep between the products of its
+// wavefront); 224: 34 (51), 160: 20.5 (31), 64: 9 (15).  In-kernel times at n = 288: the chain needs about 7400 cycles a
+// block (sweep 3700 to 3900, D into planes 850, operand reads 320, P 500, update 1250), the other wavefronts 10700, most
+// of it the 192 matrix instructions of a SIMD (6100 cycles) and the conversions around them.  Loads and stores: 6 us.
+//
+// Products are in the three-plane mode (x = h + m + l exactly, see split_pair; six bf16 matrix instructions per
+// 16-wide step, fp32 accumulation).
 typedef float lb_floatx16 __attribute__((ext_vector_type(16)));
 typedef float lb_floatx4 __attribute__((ext_vector_type(4)));
-constexpr int LB_MAXN = 288;
+typedef __bf16 lb_bf16x8 __attribute__((ext_vector_type(8)));
+typedef short lb_shortx4 __attribute__((ext_vector_type(4)));
+typedef short lb_shortx8 __attribute__((ext_vector_type(8)));
+typedef lb_shortx4 __attribute__((address_space(3))) *lb_lds_shortx4_ptr;
+constexpr int LB_MAXT = 9;
+constexpr int LB_CHAIN = 15;                            // the chain wavefront
+constexpr int LB_TROW = 72;                             // bytes per k row of form T (32 bf16 + 8 bytes: spreads the banks)
+constexpr int LB_BLK = 32 * LB_TROW;                    // bytes of one plane of one panel block (form F needs 2048)
+constexpr int LB_IDENT = LB_MAXT;                       // a panel block that always holds the identity, form F
+constexpr int LB_PLANE = (LB_MAXT + 1) * LB_BLK;        // bytes of one plane of a panel
+constexpr int LB_PANEL = 3 * LB_PLANE;                  // one panel: [plane][block]
+constexpr int LB_DP = 3 * 2048;                         // planes of D, form F
+constexpr int LB_LDS_D = 2 * LB_PANEL, LB_LDS_DIAG = LB_LDS_D + 2 * LB_DP,
+              LB_LDS_SC = LB_LDS_DIAG + 2 * 4096, LB_LDS_BYTES = LB_LDS_SC + 32 * LB_MAXT * 4;
+static_assert(LB_LDS_BYTES <= 160 * 1024 - 64, "one compute unit's LDS");
+static_assert(LB_LDS_D >= 15 * 32 * 33 * 4, "the staging tiles of the final store fit into the panels");
+
+// Tiles of 6 .. 9 blocks dealt to the wavefronts as stars {v; j, j, j} (-1: none), found by a search that minimises the
+// matrix instructions of the busiest SIMD (wavefront % 4, the chain's included) summed over the steps, with v = k + 1 for
+// the tile of blocks k + 1 and k (the chain reads form F only).  Up to 5 blocks: one tile per wavefront, v the larger index.
+__constant__ signed char kLeafStar[4][15][4] = {
+    {{2, 1, 4, -1}, {3, 5, 1, -1}, {1, 1, 0, -1}, {5, 4, -1, -1}, {5, 5, 0, -1}, {4, 4, 3, -1}, {2, 2, 0, -1},
+     {4, 0, -1, -1}, {3, 3, 2, -1}, {0, 0, 3, -1}, {1, 5, 4, -1}, {2, 5, -1, -1}, {-1, -1, -1, -1}, {-1, -1, -1,
+     -1}, {-1, -1, -1, -1}},
+    {{5, 2, 3, -1}, {0, 0, 6, -1}, {4, 0, 1, -1}, {3, 0, 1, -1}, {6, 1, 4, -1}, {3, 3, 2, -1}, {6, 5, 3, -1},
+     {4, 4, 3, -1}, {2, 0, 1, -1}, {5, 5, 4, -1}, {1, 1, 5, -1}, {2, 2, 4, -1}, {5, 0, -1, -1}, {1, 0, -1, -1},
+     {6, 6, 2, -1}},
+    {{4, 4, 0, 6}, {6, 0, 1, -1}, {7, 3, 0, -1}, {3, 6, 2, -1}, {0, 0, 5, 2}, {5, 5, 7, 2}, {1, 7, 0, -1}, {2,
+     2, 6, 7}, {6, 6, 5, -1}, {1, 1, 5, -1}, {5, 4, 3, -1}, {7, 7, 6, -1}, {2, 4, 1, -1}, {4, 3, 7, 1}, {3, 3,
+     1, 0}},
+    {{4, 4, 3, 0}, {1, 1, 0, 3}, {6, 6, 0, 4}, {2, 4, 0, 7}, {1, 6, 7, 4}, {8, 0, 7, 2}, {7, 0, 3, 4}, {0, 0, 3,
+     5}, {8, 8, 6, 1}, {2, 2, 5, 1}, {7, 7, 6, 5}, {8, 5, 3, 4}, {5, 5, 4, 1}, {6, 5, 2, 3}, {3, 3, 2, 5}},
+};
+// bit i of [blocks - 6][k]: the tile of blocks i and k is held with v = i (panel form F in step k), else with v = k (T)
+__constant__ unsigned short kLeafForm[4][9] = {
+    {0x36, 0xc, 0x8, 0x11, 0x26, 0xe, 0x0, 0x0, 0x0},
+    {0x3e, 0x5c, 0x68, 0x70, 0x64, 0x42, 0x1, 0x0, 0x0},
+    {0xda, 0x5c, 0x29, 0xb0, 0x24, 0x43, 0x9c, 0x36, 0x0},
+    {0x1d6, 0x124, 0x148, 0x1d3, 0x1e6, 0x1cd, 0x182, 0x106, 0x0},
+};
 
 __device__ __forceinline__ float lb_readlane(float x, int lane)
 {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
-// The panels live in LDS as three bf16 planes per value (x = h + m + l exactly, see split_pair): rows of
-// LB_LQ bf16 (32 + 8 pad: 80-byte rows, conflict-free 16-byte fragment reads), plane stride given.
-typedef __bf16 lb_bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short lb_ushortx8 __attribute__((ext_vector_type(8)));
-constexpr int LB_LQ = 40;
-constexpr int LB_PLANE = LB_MAXN * LB_LQ;     // plane stride of the R and P panels (bf16 elements)
-constexpr int LB_DPLANE = 32 * LB_LQ;         // of D
+struct LbFrag { lb_bf16x8 h, m, l; };
 
-// acc += A B^T for two 32 x 32 blocks given as plane rows: `pa`, `pb` point at the h plane of the lane's
-// row (lane % 32) plus 8 * (lane / 32), the half-wave's part of each 16-wide k step.  Six bf16 matrix
-// instructions per step form the product to fp32 accuracy: h h' + h m' + h l' + m h' + m m' + l h'.
-__device__ __forceinline__ void lb_mma_planes(lb_floatx16 &acc, const unsigned short *pa, int plane_a,
-                                              const unsigned short *pb, int plane_b)
+// eight accumulator registers (8 u .. 8 u + 7) of a tile as an operand fragment of step u
+__device__ __forceinline__ LbFrag lb_split8(const lb_floatx16 &t, int u)
 {
-    auto rd = [](const unsigned short *p) { return __builtin_bit_cast(lb_bf16x8, *(const lb_ushortx8 *)p); };
+    uint4 h, m, l;
+    split_pair(t[8 * u + 0], t[8 * u + 1], h.x, m.x, l.x);
+    split_pair(t[8 * u + 2], t[8 * u + 3], h.y, m.y, l.y);
+    split_pair(t[8 * u + 4], t[8 * u + 5], h.z, m.z, l.z);
+    split_pair(t[8 * u + 6], t[8 * u + 7], h.w, m.w, l.w);
+    return {__builtin_bit_cast(lb_bf16x8, h), __builtin_bit_cast(lb_bf16x8, m), __builtin_bit_cast(lb_bf16x8, l)};
+}
+__device__ __forceinline__ void lb_mma(lb_floatx16 &acc, const LbFrag &a, const LbFrag &b)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc, 0, 0, 0);
+}
+// form F: fragments as they are read, plane stride given; [u][lane] 16 bytes each
+__device__ __forceinline__ LbFrag lb_read_f(const char *blk, int plane, int u, int lane)
+{
+    auto rd = [&](int q) { return __builtin_bit_cast(lb_bf16x8, *(const lb_shortx8 *)(blk + q * plane + u * 1024 + lane * 16)); };
+    return {rd(0), rd(1), rd(2)};
+}
+__device__ __forceinline__ void lb_store_f(char *blk, int plane, int u, const LbFrag &f, int lane)
+{
+    *(lb_shortx8 *)(blk + u * 1024 + lane * 16) = __builtin_bit_cast(lb_shortx8, f.h);
+    *(lb_shortx8 *)(blk + plane + u * 1024 + lane * 16) = __builtin_bit_cast(lb_shortx8, f.m);
+    *(lb_shortx8 *)(blk + 2 * plane + u * 1024 + lane * 16) = __builtin_bit_cast(lb_shortx8, f.l);
+}
+// form T: [k][row]; the tile's lanes are k and its registers rows.  The transposing read gives lane i of 16 element i % 4
+// of the 8-byte groups addressed by lanes i / 4, i / 4 + 4, i / 4 + 8, i / 4 + 12: four adjacent k of row i.
+__device__ __forceinline__ LbFrag lb_read_t(const char *blk, int u, int lane)
+{
+    const int i = lane & 15, row0 = lane & 16, half = lane >> 5;
+    const char *p = blk + (16 * u + 4 * half + (i >> 2)) * LB_TROW + 2 * (row0 + 4 * (i & 3));
+    auto rd = [&](int q) {
+        const lb_shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lb_lds_shortx4_ptr)(p + q * LB_PLANE));
+        const lb_shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lb_lds_shortx4_ptr)(p + q * LB_PLANE + 8 * LB_TROW));
+        return __builtin_bit_cast(lb_bf16x8, lb_shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    };
+    return {rd(0), rd(1), rd(2)};
+}
+__device__ __forceinline__ void lb_store_t(char *blk, const lb_floatx16 &t, int lane)
+{
+    char *d = blk + (lane & 31) * LB_TROW + 8 * (lane >> 5);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const lb_bf16x8 ah = rd(pa + 16 * u), am = rd(pa + plane_a + 16 * u), al = rd(pa + 2 * plane_a + 16 * u);
-        const lb_bf16x8 bh = rd(pb + 16 * u), bm = rd(pb + plane_b + 16 * u), bl = rd(pb + 2 * plane_b + 16 * u);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bm, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bh, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bm, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
+    for (int g = 0; g < 4; ++g) {   // rows 8 g + 4 half .. + 3
+        uint2 h, m, l;
+        split_pair(t[4 * g], t[4 * g + 1], h.x, m.x, l.x);
+        split_pair(t[4 * g + 2], t[4 * g + 3], h.y, m.y, l.y);
+        *(uint2 *)(d + 16 * g) = h;
+        *(uint2 *)(d + LB_PLANE + 16 * g) = m;
+        *(uint2 *)(d + 2 * LB_PLANE + 16 * g) = l;
+    }
+}
+// both fragments of panel block i
+__device__ __forceinline__ void lb_read_panel(LbFrag (&f)[2], const char *panel, int i, bool form_f, int lane)
+{
+    const char *blk = panel + i * LB_BLK;
+    if (form_f) {
+        f[0] = lb_read_f(blk, LB_PLANE, 0, lane);
+        f[1] = lb_read_f(blk, LB_PLANE, 1, lane);
+    } else {
+        f[0] = lb_read_t(blk, 0, lane);
+        f[1] = lb_read_t(blk, 1, lane);
     }
 }
 
-// A 32 x 32 tile held in the accumulator layout (register v: row 8 (v / 4) + 4 h + v % 4, lane % 32: column)
-// into plane rows, split on the way.
-//   lb_store_rows: tile element (row, column) goes to panel row row0 + row, position column  (2-byte stores)
-//   lb_store_cols: ... to panel row row0 + column, position row: the transposed tile; the four rows of a
-//                  register group are four adjacent positions, one 8-byte store per plane
-__device__ __forceinline__ void lb_store_rows(unsigned short *panel, int plane, int row0, const lb_floatx16 &t, int l32, int h)
+// The chain wavefront keeps the diagonal tile in an order that puts consecutive pivots 2 m, 2 m + 1 into the two half-waves
+// of one accumulator register: tile row (and column) 8 g + 4 h + e holds row 8 g + 2 e + h of the block.
+__device__ __forceinline__ int lb_row(int q, int h) { return 8 * (q >> 2) + 2 * (q & 3) + h; }              // of register q
+__device__ __forceinline__ int lb_row_of(int r) { return (r & 24) | ((r & 3) << 1) | ((r >> 2) & 1); }       // of tile row r
+__device__ __forceinline__ int lb_tile_row(int m) { return (m & 24) | ((m & 1) << 2) | ((m >> 1) & 3); }     // its inverse
+// register q of that order -> the accumulator layout of the plain order (rows only): registers 4 g + e and 4 g + e + 2
+// exchange half-waves (swap(x, y): upper half of x with the lower half of y)
+__device__ __forceinline__ lb_floatx16 lb_plain_rows(const lb_floatx16 &t)
 {
+    lb_floatx16 o;
 #pragma unroll
-    for (int v = 0; v < 16; v += 2) {
-        unsigned hh, mm, ll;
-        split_pair(t[v], t[v + 1], hh, mm, ll);
-        unsigned short *d = panel + (row0 + 8 * (v >> 2) + 4 * h + (v & 3)) * LB_LQ + l32;
-        d[0] = (unsigned short)hh; d[LB_LQ] = (unsigned short)(hh >> 16);
-        d[plane] = (unsigned short)mm; d[plane + LB_LQ] = (unsigned short)(mm >> 16);
-        d[2 * plane] = (unsigned short)ll; d[2 * plane + LB_LQ] = (unsigned short)(ll >> 16);
-    }
-}
-__device__ __forceinline__ void lb_store_cols(unsigned short *panel, int plane, int row0, const lb_floatx16 &t, int l32, int h)
-{
+    for (int g = 0; g < 4; ++g)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        uint2 hh, mm, ll;
-        split_pair(t[4 * g], t[4 * g + 1], hh.x, mm.x, ll.x);
-        split_pair(t[4 * g + 2], t[4 * g + 3], hh.y, mm.y, ll.y);
-        unsigned short *d = panel + (row0 + l32) * LB_LQ + 8 * g + 4 * h;
-        *(uint2 *)d = hh;
-        *(uint2 *)(d + plane) = mm;
-        *(uint2 *)(d + 2 * plane) = ll;
-    }
+        for (int e = 0; e < 2; ++e) {
+            const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[4 * g + e]), __float_as_uint(t[4 * g + e + 2]), false, false);
+            o[4 * g + 2 * e] = __uint_as_float(s[0]);
+            o[4 * g + 2 * e + 1] = __uint_as_float(s[1]);
+        }
+    return o;
 }
 
-// Scalar sweep of the 32x32 diagonal tile of block k inside the wavefront that holds it
-// (register slot `slot`): leaves D = (-N_kk)^-1 in the slot and in Dq.  Returns the 1-based
-// index (within the matrix) of the first non-positive pivot, or 0.
-template <int NSLOT>
-__device__ __forceinline__ int lb_sweep_diag(lb_floatx16 (&acc)[NSLOT], int slot, int k, int l32, int h, unsigned short *Dq)
+// The eight k slots of a half-wave as the product of one fp32 value per lane with another: h h' + h m' + m h' + m m' +
+// h l' + l h' + m l' + l m' (all but l l', 2^-32 of the product).
+__device__ __forceinline__ lb_bf16x8 lb_terms_a(float a)
 {
-    lb_floatx16 sg;
+    const unsigned hb = __float_as_uint(a);
+    const float r = a - __uint_as_float(hb & 0xFFFF0000u);
+    const unsigned mb = __float_as_uint(r);
+    const unsigned lb = __float_as_uint(r - __uint_as_float(mb & 0xFFFF0000u));
+    return __builtin_bit_cast(lb_bf16x8, uint4{__builtin_amdgcn_perm(hb, hb, 0x07060302u), __builtin_amdgcn_perm(mb, mb, 0x07060302u),
+                                               __builtin_amdgcn_perm(lb, hb, 0x07060302u), __builtin_amdgcn_perm(lb, mb, 0x07060302u)});
+}
+__device__ __forceinline__ lb_bf16x8 lb_terms_b(float b)
+{
+    const unsigned hb = __float_as_uint(b);
+    const float r = b - __uint_as_float(hb & 0xFFFF0000u);
+    const unsigned mb = __float_as_uint(r);
+    const unsigned lb = __float_as_uint(r - __uint_as_float(mb & 0xFFFF0000u));
+    const unsigned hm = __builtin_amdgcn_perm(mb, hb, 0x07060302u);
+    return __builtin_bit_cast(lb_bf16x8, uint4{hm, hm, __builtin_amdgcn_perm(hb, lb, 0x07060302u), __builtin_amdgcn_perm(mb, lb, 0x07060302u)});
+}
+
+// Scalar sweep of a 32x32 diagonal tile N (symmetric, negative definite, unit-diagonal scale) inside one wavefront, on the
+// matrix core, two pivots per instruction: register v holds both pivot rows, one in each half-wave, and a half-wave is
+// eight k slots of the instruction, which hold the terms of its pivot's rank-1 update.  With the pivots' block
+// [[a, b], [b, c]], its negated inverse Q and the rows x0, x1 of the tile as it stands, y = Q x, the update
+// N += a0 b0^T + a1 b1^T with
+//     a_i = y_i,  b_j = x_j   outside the pivots, and at them   a0 = (Q00 - 1, Q01), a1 = (Q01, Q11 - 1),
+//     b0 = (1 + a, b), b1 = (b, 1 + c)
+// adds x^T Q x, leaves the rows and columns of the pivots as Q x and the block itself as Q - 2 I.  (Pivots lie in [-1, 0):
+// the patches are sums of equal-signed terms.)  No later pivot reads the block (pivot q reads row q only, and adds to it),
+// so the 2 is put back once, at the end.
+// The patched rows b0, b1 give the patched a0, a1 by the same formula as all others: with r = -1 / det the first half-wave
+// has a0_i = r (c b0_i - b b1_i), which is r c - 1 and -r b at the two pivots.
+// What bounds it is the issue of one wavefront: about 45 instructions for two pivots.  The chain from one pair to the
+// next does not go through the matrix instruction (the next pair's rows are brought up to date with fmas from the tile as
+// it was before) and meets the reciprocal of the determinant in its last fma only.
+// On return the tile is (-N)^-1.  Returns the 1-based index of the first non-positive pivot of -N, or 0.
+__device__ __forceinline__ int leaf_chain_sweep(lb_floatx16 &t, int lane)
+{
+    const int z = (lane & 31) - 4 * (lane >> 5);
+    const bool h = lane >= 32;
+    float pa[16], pd[16], worst = 1.f;              // the pivots (first one and determinant of each pair)
+    float x = t[0];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        float x = acc[0][v];
-#pragma unroll
-        for (int s = 1; s < NSLOT; ++s) x = (slot == s) ? acc[s][v] : x;
-        sg[v] = -x;
-    }
-    // Pivot p is the rank-1 update S += a b^T with
-    //     a_i = -x_i / d (i != p),  a_p = 1/d - 1;    b_j = x_j (j != p),  b_p = d - 1
-    // where x = row p and d = x_p: besides S_ij -= x_i x_j / d this leaves row and column p multiplied by
-    // 1/d (sums of equal-signed terms, because d <= 1) and S_pp = 2 - 1/d instead of -1/d.  No later pivot
-    // reads S_pp (pivot q reads row q only, and adds to S_pp), so the 2 is taken off once, at the end.
-    // A wavefront cannot issue its vector arithmetic beside its own matrix instruction, so the pivots go
-    // two per instruction: the rows of pivots p and p + 1 (p even: both in the same half-wave) are brought up
-    // to date with fmas, row p + 1 by pivot p, and the two updates ride in the two k slots of one
-    // 32x32x2 instruction (one half-wave each; v_permlane32_swap puts the second pair of vectors there).  The
-    // row of pivot p + 2 is read from the tile as the previous instruction left it and corrected by both.
-    int badl = 0;
-    float xcur = sg[0];                 // row 0, valid in the half-wave that holds it
-#pragma unroll
-    for (int p = 0; p < 32; p += 2) {
-        const int hp = (p >> 2) & 1;    // half-wave holding rows p and p + 1
-        // pivot p
-        const float d0 = lb_readlane(xcur, p + 32 * hp);
-        badl = (badl == 0 && !(d0 > 0.f)) ? 32 * k + p + 1 : badl;
-        const float r0 = __builtin_amdgcn_rcpf(d0);
-        const float xr0 = xcur * r0;
-        float b0 = l32 == p ? d0 - 1.f : xcur;
-        float a0 = l32 == p ? r0 - 1.f : -xr0;
-        // row p + 1 after pivot p, then pivot p + 1
-        const int v1 = 4 * ((p + 1) >> 3) + ((p + 1) & 3);
-        const float x1 = fmaf(-lb_readlane(xr0, p + 1 + 32 * hp), b0, sg[v1]);
-        const float d1 = lb_readlane(x1, p + 1 + 32 * hp);
-        badl = (badl == 0 && !(d1 > 0.f)) ? 32 * k + p + 2 : badl;
-        const float r1 = __builtin_amdgcn_rcpf(d1);
-        const float xr1 = x1 * r1;
-        float b1 = l32 == p + 1 ? d1 - 1.f : x1;
-        float a1 = l32 == p + 1 ? r1 - 1.f : -xr1;
-        float xnext = 0.f;
-        if (p + 2 < 32) {
-            const int hn = ((p + 2) >> 2) & 1;
-            const int v2 = 4 * ((p + 2) >> 3) + ((p + 2) & 3);
-            const float al0 = lb_readlane(xr0, p + 2 + 32 * hp), al1 = lb_readlane(xr1, p + 2 + 32 * hp);
-            float c0 = b0, c1 = b1;
-            if (hn != hp) {             // row p + 2 lives in the other half-wave: the two b vectors go there
-                const auto s0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(b0), __float_as_uint(b0), false, false);
-                const auto s1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(b1), __float_as_uint(b1), false, false);
-                c0 = __uint_as_float(hp == 0 ? s0[0] : s0[1]);
-                c1 = __uint_as_float(hp == 0 ? s1[0] : s1[1]);
-            }
-            xnext = fmaf(-al1, c1, fmaf(-al0, c0, sg[v2]));
+        const int p = 8 * (v >> 2) + (v & 3);       // tile row of the first pivot; the second one is p + 4
+        const float a = lb_readlane(x, p), b = lb_readlane(x, p + 4), c = lb_readlane(x, p + 36);
+        const float det = fmaf(a, c, -(b * b));
+        const float r = -__builtin_amdgcn_rcpf(det);
+        const float fb = z == p ? x + 1.f : x;
+        // b0 and b1 in both half-waves (swap(x, y) exchanges the upper half of x with the lower half of y)
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(fb), __float_as_uint(fb), false, false);
+        const float b0 = __uint_as_float(s[0]), b1 = __uint_as_float(s[1]);
+        const float g0 = fmaf(c, b0, -(b * b1)), g1 = fmaf(a, b1, -(b * b0));
+        const float g = h ? g1 : g0;
+        float next = 0.f;
+        if (v + 1 < 16) {
+            const int q = 8 * ((v + 1) >> 2) + ((v + 1) & 3);
+            const float w0 = fmaf(lb_readlane(g, q + 32), b1, lb_readlane(g, q) * b0);
+            const float w1 = fmaf(lb_readlane(g, q + 36), b1, lb_readlane(g, q + 4) * b0);
+            next = fmaf(r, h ? w1 : w0, t[v + 1]);
         }
-        // operands: the half-wave that holds the rows keeps pivot p, the other one receives pivot p + 1
-        // (swap(x, y) exchanges the upper half of x with the lower half of y)
-        float a, b;
-        if (hp == 0) {
-            const auto sa = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0), __float_as_uint(a1), false, false);
-            const auto sb = __builtin_amdgcn_permlane32_swap(__float_as_uint(b0), __float_as_uint(b1), false, false);
-            a = __uint_as_float(sa[0]); b = __uint_as_float(sb[0]);
-        } else {
-            const auto sa = __builtin_amdgcn_permlane32_swap(__float_as_uint(a1), __float_as_uint(a0), false, false);
-            const auto sb = __builtin_amdgcn_permlane32_swap(__float_as_uint(b1), __float_as_uint(b0), false, false);
-            a = __uint_as_float(sa[1]); b = __uint_as_float(sb[1]);
-        }
-        sg = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, sg, 0, 0, 0);
-        xcur = xnext;
+        const float fa = r * g;
+        pa[v] = a;
+        pd[v] = det;
+        worst = fminf(fminf(worst, -a), det);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lb_terms_a(fa), lb_terms_b(fb), t, 0, 0, 0);
+        x = next;
     }
-    // sg = -(that tile)^-1 + 2 I = 2 I - D;  D is symmetric, so its planes can be written transposed (8-byte stores)
-    const int drow = l32 - 4 * h;       // register v holds the diagonal element of its lane where this is 8 (v / 4) + v % 4
+    // register v holds the diagonal element of its lane where z is 8 (v / 4) + v % 4
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        sg[v] = (drow == 8 * (v >> 2) + (v & 3) ? 2.f : 0.f) - sg[v];
+    for (int v = 0; v < 16; ++v) t[v] += z == 8 * (v >> 2) + (v & 3) ? 2.f : 0.f;
+    // (a NaN anywhere has reached the last determinant)
+    if (__builtin_amdgcn_readfirstlane((int)(worst > 0.f && pd[15] > 0.f))) return 0;
+    int first = 0;
 #pragma unroll
-        for (int s = 0; s < NSLOT; ++s) acc[s][v] = (slot == s) ? sg[v] : acc[s][v];
-    }
-    lb_store_cols(Dq, LB_DPLANE, 0, sg, l32, h);
-    return badl;
+    for (int v = 15; v >= 0; --v) first = !(pa[v] < 0.f) ? 2 * v + 1 : !(pd[v] > 0.f) ? 2 * v + 2 : first;
+    return first;
 }
-
-// Which wavefront holds which tile.  In step k the tiles of block row / column k only form the
-// panel P, the other 36 (of 45, for 9 blocks) take 12 matrix instructions each, and the wavefront
-// that holds the diagonal tile of block k + 1 updates and then sweeps it, which is the longest
-// chain of the step.  The table below (found by annealing over assignments with at most 3 tiles per
-// wavefront) gives every diagonal tile a wavefront of its own, lets the owner of diagonal tile b
-// hold nothing else but tiles of block row / column b - 1 (idle while it sweeps), puts at most two
-// panel tiles of a step on one wavefront and spreads the rest evenly over the four SIMDs (wavefront
-// % 4).  Other sizes keep the plain order (tile t to wavefront t % 16).
-__constant__ signed char kLeafTile9[16][3] = {{20, 25, -1}, {2, 3, 10}, {15, 23, 28}, {6, 14, 39}, {32, 43, 44}, {19, 29, 42},
-                                              {4, 9, 12}, {11, 17, 21}, {27, 41, -1}, {0, 8, 36}, {5, 7, 37}, {22, 30, 38},
-                                              {26, 35, -1}, {16, 24, 31}, {18, 34, 40}, {1, 13, 33}};
-__constant__ signed char kLeafWave9[45] = {9, 15, 1, 1, 6, 10, 3, 10, 9, 6, 1, 7, 6, 15, 3, 2, 13, 7, 14, 5, 0, 7, 11,
-                                           2, 13, 0, 12, 8, 2, 5, 11, 13, 4, 15, 14, 12, 9, 10, 11, 3, 14, 8, 5, 4, 4};
-__constant__ signed char kLeafSlot9[45] = {0, 0, 0, 1, 0, 0, 0, 1, 1, 1, 2, 0, 2, 1, 1, 0, 0, 1, 0, 0, 0, 2, 0,
-                                           1, 1, 1, 0, 0, 2, 1, 1, 2, 0, 2, 1, 1, 2, 2, 2, 2, 2, 1, 2, 1, 2};
 
 template <int NSLOT>
 __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restrict__ jobs,
                                                           const float *__restrict__ damp,
                                                           int32_t *__restrict__ info)
 {
-    extern __shared__ __attribute__((aligned(16))) float lb_lds[];
-    unsigned short *Rq = (unsigned short *)lb_lds;   // [3][LB_MAXN][LB_LQ] column panel R, three bf16 planes
-    unsigned short *Pq = Rq + 3 * LB_PLANE;          // [3][LB_MAXN][LB_LQ] P = R D
-    unsigned short *Dq = Pq + 3 * LB_PLANE;          // [3][32][LB_LQ]      D
-    float *sc = (float *)(Dq + 3 * LB_DPLANE);       // [LB_MAXN]           diagonal scaling
-    __shared__ int bad_s;
+    extern __shared__ __attribute__((aligned(16))) char lb_lds[];
+    float *sc = (float *)(lb_lds + LB_LDS_SC);       // [32 T] diagonal scaling
 
     const LeafJob J = jobs[blockIdx.x];
     const int n = J.n;
     const int T = (n + 31) >> 5;
-    const int ntiles = T * (T + 1) / 2;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32_ = lane & 31, h_ = lane >> 5;
     const float d = (J.damp_idx >= 0) ? damp[J.damp_idx] : 0.f;
     const unsigned lds = (unsigned)J.lds, ldd = (unsigned)J.ldd;
 
-    // my tiles: tile t is block (ti, tj), ti >= tj, in row-major order of the lower triangle; slot s
-    // of wavefront w holds tile w + 16 s, or what the balanced table says for 9 blocks.
-    // The raw loads are issued first; the scaling needs the diagonal (through LDS) and comes after.
-    const bool balanced = NSLOT == 3 && T == 9;
-    auto diag_owner = [&](int b) { const int t = b * (b + 1) / 2 + b; return balanced ? (int)kLeafWave9[t] : (t & 15); };
-    auto diag_slot = [&](int b) { const int t = b * (b + 1) / 2 + b; return balanced ? (int)kLeafSlot9[t] : (t >> 4); };
-    lb_floatx16 acc[NSLOT];
-    int ti[NSLOT], tj[NSLOT];
+    // my tiles: (rows of block j[s]: registers, rows of block v: lanes)
+    int v_ = -1, j_[NSLOT];
 #pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-        int t = w + 16 * s;
-        if (balanced) { t = kLeafTile9[w][s < 3 ? s : 0]; t = t < 0 ? ntiles : t; }
+    for (int s = 0; s < NSLOT; ++s) j_[s] = -1;
+    if (NSLOT == 1 || T < 6) {
         int r = 0;
-        while ((r + 1) * (r + 2) / 2 <= t) ++r;
-        ti[s] = t < ntiles ? r : -1;
-        tj[s] = t - r * (r + 1) / 2;
+        while ((r + 1) * (r + 2) / 2 <= w) ++r;
+        if (w < T * (T + 1) / 2 && w != LB_CHAIN) { v_ = r; j_[0] = w - r * (r + 1) / 2; }
+    } else if (w != LB_CHAIN) {
+        v_ = kLeafStar[T - 6][w][0];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int i = 32 * r + 8 * (v >> 2) + 4 * h_ + (v & 3), j = 32 * tj[s] + l32_;
-            float x = 0.f;
-            if (t < ntiles && i < n && j < n) x = J.src[(unsigned)i * lds + (unsigned)j];
-            acc[s][v] = x;
-        }
+        for (int s = 0; s < NSLOT; ++s) j_[s] = kLeafStar[T - 6][w][1 + s];
     }
-    if (tid < 32 * T) {
-        float v = 1.f;
-        if (tid < n) {
-            const float a = J.src[(unsigned)tid * lds + (unsigned)tid] + d;
-            v = a > 0.f ? rsqrtf(a) : 1.f;   // a non-positive diagonal shows up as a non-positive pivot
-        }
-        sc[tid] = v;
-    }
-    if (tid == 0) bad_s = 0;
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int i = 32 * ti[s] + 8 * (v >> 2) + 4 * h_ + (v & 3), j = 32 * tj[s] + l32_;
-            float x = acc[s][v];
-            if (ti[s] >= 0 && i < n && j < n) x = -(x + (i == j ? d : 0.f)) * sc[i] * sc[j];
-            else x = (i == j) ? -1.f : 0.f;     // identity padding (of -X)
-            acc[s][v] = x;
-        }
-    }
+    // bit i: the panel block i of step k is in form F
+    auto form_mask = [&](int k) { return (NSLOT == 1 || T < 6) ? ~((2u << k) - 1u) : (unsigned)kLeafForm[T - 6][k]; };
 
-    // The diagonal tile of block k + 1 is swept by its owner during the trailing update of
-    // block k (right after the owner has brought that tile up to date), so that the serial
-    // sweep runs beside the other wavefronts' products instead of in front of them.
-    if (w == diag_owner(0)) {
-        int l32 = l32_, h = h_;
-        asm volatile("" : "+v"(l32), "+v"(h));
-        const int badl = lb_sweep_diag<NSLOT>(acc, diag_slot(0), 0, l32, h, Dq);
-        if (badl != 0 && lane == 0) bad_s = badl;
-    }
-    __syncthreads();   // D of block 0 is in LDS
-    for (int k = 0; k < T; ++k) {
-        // (per-step copies of the lane coordinates: as loop invariants, the 32 lane masks of the
-        // sweep and the LDS addresses below would be hoisted and kept live across the whole loop)
-        int l32 = l32_, h = h_;
-        asm volatile("" : "+v"(l32), "+v"(h));
-        // ---- column panel R of block k into LDS (planes): R_i = N_ik, from tile (i,k) for i > k and from
-        // the transpose of tile (k,i) for i < k
+    // the chain wavefront loads the first diagonal tile, the others their tiles; the scaling needs the diagonal
+    auto load_tile = [&](lb_floatx16 &t, int bi, int bj, bool chain) {
 #pragma unroll
-        for (int s = 0; s < NSLOT; ++s) {
-            if (ti[s] < 0) continue;
-            if (tj[s] == k && ti[s] > k) lb_store_rows(Rq, LB_PLANE, 32 * ti[s], acc[s], l32, h);
-            else if (ti[s] == k && tj[s] < k) lb_store_cols(Rq, LB_PLANE, 32 * tj[s], acc[s], l32, h);
+        for (int q = 0; q < 16; ++q) {
+            const int i = 32 * bi + (chain ? lb_row(q, h_) : 8 * (q >> 2) + 4 * h_ + (q & 3)), j = 32 * bj + (chain ? lb_row_of(l32_) : l32_);
+            t[q] = J.src[(unsigned)min(i, n - 1) * lds + (unsigned)min(j, n - 1)];   // (outside: replaced when it is scaled)
         }
-        // A wavefront forms P from the panel rows it has just written itself and from D (in LDS since the
-        // barrier that ended the previous step or the prologue): its own LDS accesses stay in order, so no
-        // workgroup barrier is needed here, only the guarantee that they are not reordered.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // ---- the tiles of block row / column k take their new value P_i = R_i D (tile (i,k)) or its transpose
-        // D R_i^T (tile (k,i)) straight from the product, and put P into LDS for everybody else
+    };
+    // scales of the tile's rows (by register) and of its lane's column
+    auto tile_scales = [&](float (&si)[16], float &sj, int bi, int bj, bool chain) {
 #pragma unroll
-        for (int s = 0; s < NSLOT; ++s) {
-            if (ti[s] < 0) continue;
-            if (tj[s] == k && ti[s] > k) {
+        for (int g = 0; g < 4; ++g) {
+            if (chain) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[s][v] = 0.f;
-                lb_mma_planes(acc[s], Rq + (32 * ti[s] + l32) * LB_LQ + 8 * h, LB_PLANE, Dq + l32 * LB_LQ + 8 * h, LB_DPLANE);
-                lb_store_rows(Pq, LB_PLANE, 32 * ti[s], acc[s], l32, h);
-            } else if (ti[s] == k && tj[s] < k) {
+                for (int e = 0; e < 4; ++e) si[4 * g + e] = sc[32 * bi + 8 * g + 2 * e + h_];
+            } else {
+                const lb_floatx4 x = *(const lb_floatx4 *)(sc + 32 * bi + 8 * g + 4 * h_);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[s][v] = 0.f;
-                lb_mma_planes(acc[s], Dq + l32 * LB_LQ + 8 * h, LB_DPLANE, Rq + (32 * tj[s] + l32) * LB_LQ + 8 * h, LB_PLANE);
-                lb_store_cols(Pq, LB_PLANE, 32 * tj[s], acc[s], l32, h);
+                for (int e = 0; e < 4; ++e) si[4 * g + e] = x[e];
             }
         }
-        __syncthreads();   // P is in LDS; D of block k is no longer needed
-        // ---- every other tile N_ij += P_i R_j^T
-        const bool sweeps_next = k + 1 < T && w == diag_owner(k + 1);   // holds the diagonal tile of block k + 1
-        if (sweeps_next) {
-            const int slot = diag_slot(k + 1);
-            // the update of that tile and its sweep are one long dependent chain and bound the step: they issue
-            // ahead of the other wavefronts' products, which also leave the first LDS reads to this wavefront
-            __builtin_amdgcn_s_setprio(3);
+        sj = sc[32 * bj + (chain ? lb_row_of(l32_) : l32_)];
+    };
+    auto whole = [&](int bi, int bj) { return 32 * (max(bi, bj) + 1) <= n; };
+    auto scale_tile = [&](lb_floatx16 &t, int bi, int bj, bool chain) {
+        float si[16], sj;
+        tile_scales(si, sj, bi, bj, chain);
+        const float dd = bi == bj ? d : 0.f;
+        // (the diagonal lies at the same registers and lanes in either order)
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s)
-                if (s == slot)
-                    lb_mma_planes(acc[s], Pq + (32 * (k + 1) + l32) * LB_LQ + 8 * h, LB_PLANE,
-                                  Rq + (32 * (k + 1) + l32) * LB_LQ + 8 * h, LB_PLANE);
-            const int badl = lb_sweep_diag<NSLOT>(acc, slot, k + 1, l32, h, Dq);
-            __builtin_amdgcn_s_setprio(0);
-            if (badl != 0 && lane == 0 && bad_s == 0) bad_s = badl;   // blocks are swept in order: the first one stays
-        } else if (k + 1 < T) {
-            __builtin_amdgcn_s_sleep(3);
+        for (int q = 0; q < 16; ++q) t[q] = -(t[q] + (8 * (q >> 2) + 4 * h_ + (q & 3) == l32_ ? dd : 0.f)) * si[q] * sj;
+        if (!whole(bi, bj)) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int i = 32 * bi + (chain ? lb_row(q, h_) : 8 * (q >> 2) + 4 * h_ + (q & 3)), j = 32 * bj + (chain ? lb_row_of(l32_) : l32_);
+                t[q] = (i < n && j < n) ? t[q] : (i == j ? -1.f : 0.f);     // identity padding (of -X)
+            }
         }
+    };
+    auto scales = [&]() {
+        if (tid < 32 * T) {
+            float v = 1.f;
+            if (tid < n) {
+                const float a = J.src[(unsigned)tid * lds + (unsigned)tid] + d;
+                v = a > 0.f ? rsqrtf(a) : 1.f;   // a non-positive diagonal shows up as a non-positive pivot
+            }
+            sc[tid] = v;
+        }
+    };
+
+    // The two roles run loops of their own with the same barriers: one after the scales, one per step, one at the end.
+    if (w == LB_CHAIN) {
+        lb_floatx16 t;
+        load_tile(t, 0, 0, true);
+        __syncthreads();
+        scale_tile(t, 0, 0, true);
+        __builtin_amdgcn_s_setprio(3);
+        int bad = 0;
+        for (int k = 0; k < T; ++k) {
+            // t: the diagonal tile of block k, up to date
+            int l64 = lane;
+            asm volatile("" : "+v"(l64));
+            const int b = leaf_chain_sweep(t, l64);
+            if (bad == 0 && b != 0) bad = 32 * k + b;
+            char *Dq = lb_lds + LB_LDS_D + (k & 1) * LB_DP;
+            {
+                const lb_floatx16 dt = lb_plain_rows(t);       // lanes (D is symmetric: its rows) in the chain's order yet
+                const int at = (l64 & 32) | lb_row_of(l64 & 31);
+                lb_store_f(Dq, 2048, 0, lb_split8(dt, 0), at);
+                lb_store_f(Dq, 2048, 1, lb_split8(dt, 1), at);
+            }
+            __syncthreads();   // D and panel of step k, diagonal tile of block k + 1
+            if (k + 1 == T) break;
+            // rows of R in the chain's order (lanes), its columns and D in the plain one
+            const char *blk = lb_lds + (k & 1) * LB_PANEL + (k + 1) * LB_BLK;
+            const int from = (l64 & 32) | lb_row_of(l64 & 31);
+            const LbFrag r[2] = {lb_read_f(blk, LB_PLANE, 0, from), lb_read_f(blk, LB_PLANE, 1, from)};
+            const LbFrag d0 = lb_read_f(Dq, 2048, 0, l64), d1 = lb_read_f(Dq, 2048, 1, l64);
+            const lb_floatx4 *o = (const lb_floatx4 *)(lb_lds + LB_LDS_DIAG + ((k + 1) & 1) * 4096);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const lb_floatx4 x = o[g * 64 + l64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t[4 * g + e] = x[e];
+            }
+            lb_floatx16 p;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) p[q] = 0.f;
+            lb_mma(p, d0, r[0]);      // P^T = D R^T
+            lb_mma(p, d1, r[1]);
+            lb_mma(t, r[0], lb_split8(p, 0));
+            lb_mma(t, r[1], lb_split8(p, 1));
+        }
+        if (bad != 0 && lane == 0 && info && J.info_idx >= 0) atomicCAS(&info[J.info_idx], 0, J.pivot_base + bad);
+        __syncthreads();
+        return;
+    }
+
+    lb_floatx16 acc[NSLOT];
+#pragma unroll
+    for (int s = 0; s < NSLOT; ++s)
+        if (j_[s] >= 0) load_tile(acc[s], j_[s], v_, false);
+    scales();
+    if (w < 12) {   // the identity: wavefront w writes step fragments w % 2 of plane (w / 2) % 3 of panel w / 6
+        const int u = w & 1, q = (w >> 1) % 3;
+        lb_shortx8 e;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) e[x] = (q == 0 && 16 * u + 8 * (x >> 2) + 4 * h_ + (x & 3) == l32_) ? (short)0x3F80 : (short)0;
+        *(lb_shortx8 *)(lb_lds + (w / 6) * LB_PANEL + q * LB_PLANE + LB_IDENT * LB_BLK + u * 1024 + lane * 16) = e;
+    }
+    __syncthreads();
+    // panel of step kk from the tiles that have an index kk, and the diagonal tile of block kk + 1 for the chain
+    auto publish = [&](int kk, int l64) {
+        char *panel = lb_lds + (kk & 1) * LB_PANEL;
 #pragma unroll
         for (int s = 0; s < NSLOT; ++s) {
-            if (ti[s] < 0) continue;
-            const int i = ti[s], j = tj[s];
-            if (i == k || j == k) continue;
-            if (sweeps_next && i == k + 1 && j == k + 1) continue;
-            lb_mma_planes(acc[s], Pq + (32 * i + l32) * LB_LQ + 8 * h, LB_PLANE, Rq + (32 * j + l32) * LB_LQ + 8 * h, LB_PLANE);
+            const int j = j_[s];
+            if (j < 0) continue;
+            if (v_ == kk && j != kk) lb_store_t(panel + j * LB_BLK, acc[s], l64);
+            else if (j == kk && v_ != kk) {
+                lb_store_f(panel + v_ * LB_BLK, LB_PLANE, 0, lb_split8(acc[s], 0), l64);
+                lb_store_f(panel + v_ * LB_BLK, LB_PLANE, 1, lb_split8(acc[s], 1), l64);
+            }
+            if (j == v_ && v_ == kk + 1) {
+                // in the chain's order: row 8 g + 4 half + e is its register 4 g + 2 half + e / 2 of half-wave e % 2
+                float *o = (float *)(lb_lds + LB_LDS_DIAG + ((kk + 1) & 1) * 4096) + 4 * lb_tile_row(l64 & 31) + 2 * (l64 >> 5);
+#pragma unroll
+                for (int q = 0; q < 16; ++q) o[(q >> 2) * 256 + 128 * (q & 1) + ((q >> 1) & 1)] = acc[s][q];
+            }
         }
-        __syncthreads();
-    }
-    if (tid == 0 && bad_s != 0 && info && J.info_idx >= 0) atomicCAS(&info[J.info_idx], 0, J.pivot_base + bad_s);
+    };
+#pragma unroll
+    for (int s = 0; s < NSLOT; ++s)
+        if (j_[s] >= 0) scale_tile(acc[s], j_[s], v_, false);
+    publish(0, lane);
 
-    // undo the scaling; the lower triangle is written and mirrored, so the result is exactly
-    // symmetric.  The mirror image goes through a per-wavefront 32x33 LDS tile (the panels are
-    // dead by now) so that it is written along rows as well.
-    float *stage = lb_lds + w * (32 * 33);
+    for (int k = 0; k < T; ++k) {
+        // (per-step copy of the lane index: as loop invariants, LDS addresses would be kept live throughout)
+        int l64 = lane;
+        asm volatile("" : "+v"(l64));
+        const unsigned fm = form_mask(k);
+        const char *panel = lb_lds + (k & 1) * LB_PANEL, *Dq = lb_lds + LB_LDS_D + (k & 1) * LB_DP;
+        __syncthreads();   // D and panel of step k
+        __builtin_amdgcn_s_sleep(2);   // the chain's reads first
+        if (v_ >= 0) {
+            // One path for all tiles: N_jv (+)= R_j P_v^T with the identity for R_v where v = k (P = D) and for R_j where
+            // j = k, and a zero start for the tiles of block k (I P = P_v^T, R_j D, I D: exact, h + m + l).  The diagonal
+            // tile of block k + 1 is the chain's: what is left in it here is replaced in the next step.
+            LbFrag f[2], dq[2];
+            lb_read_panel(f, panel, v_ == k ? LB_IDENT : v_, v_ == k || ((fm >> v_) & 1), l64);
+            dq[0] = lb_read_f(Dq, 2048, 0, l64);
+            dq[1] = lb_read_f(Dq, 2048, 1, l64);
+            lb_floatx16 p;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) p[q] = 0.f;
+            lb_mma(p, dq[0], f[0]);
+            lb_mma(p, dq[1], f[1]);
+            const LbFrag p0 = lb_split8(p, 0), p1 = lb_split8(p, 1);
+#pragma unroll
+            for (int s = 0; s < NSLOT; ++s) {
+                const int j = j_[s];
+                if (j < 0) break;                       // (the slots of a star are filled from the front)
+                lb_read_panel(f, panel, j == k ? LB_IDENT : j, j == k || ((fm >> j) & 1), l64);
+                if (v_ == k || j == k) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) acc[s][q] = 0.f;
+                }
+                lb_mma(acc[s], f[0], p0);
+                lb_mma(acc[s], f[1], p1);
+            }
+        }
+        if (k + 1 < T) publish(k + 1, l64);
+    }
+    __syncthreads();   // the panels are dead: staging tiles
+
+    // undo the scaling; every off-diagonal tile is written twice, as it is and (through a per-wavefront 32x33 LDS tile, so
+    // that it goes along rows as well) transposed; of a diagonal tile the lower half is written and mirrored: exactly symmetric
+    if (v_ < 0) return;
+    float *stage = (float *)lb_lds + w * (32 * 33);
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) {
-        if (ti[s] < 0) continue;
+        const int bi = j_[s], bj = v_;
+        if (bi < 0) continue;
+        float si[16], sj;
+        tile_scales(si, sj, bi, bj, false);
+        lb_floatx16 x, y;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + 4 * h_ + (v & 3);
-            const int i = 32 * ti[s] + r, j = 32 * tj[s] + l32_;
-            float x = 0.f;
-            if (i < n && j < n) x = acc[s][v] * sc[i] * sc[j];
-            if (i < n && j <= i) J.dst[(unsigned)i * ldd + (unsigned)j] = x;
-            stage[l32_ * 33 + r] = x;          // transposed
+        for (int q = 0; q < 16; ++q) {
+            x[q] = acc[s][q] * si[q] * sj;
+            stage[l32_ * 33 + 8 * (q >> 2) + 4 * h_ + (q & 3)] = x[q];          // transposed
         }
-        // rows of the transposed tile: element (r, c) is X[32 ti + c][32 tj + r], goes to dst[32 tj + r][32 ti + c]
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + 4 * h_ + (v & 3);
-            const int i = 32 * ti[s] + l32_, j = 32 * tj[s] + r;
-            if (i < n && j < i) J.dst[(unsigned)j * ldd + (unsigned)i] = stage[r * 33 + l32_];
+        for (int q = 0; q < 16; ++q) y[q] = stage[(8 * (q >> 2) + 4 * h_ + (q & 3)) * 33 + l32_];
+        float *dx = J.dst + (unsigned)(32 * bi) * ldd + (unsigned)(32 * bj + l32_);   // rows of block bi
+        float *dy = J.dst + (unsigned)(32 * bj) * ldd + (unsigned)(32 * bi + l32_);   // the mirror image
+        if (bi != bj && whole(bi, bj)) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) dx[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = x[q];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) dy[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = y[q];
+        } else {
+            const int room_i = n - 32 * bi, room_j = n - 32 * bj;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int r = 8 * (q >> 2) + 4 * h_ + (q & 3);
+                // of a diagonal tile the elements below and on the diagonal, and those above from their mirror image
+                const float z = (bi != bj || l32_ <= r) ? x[q] : y[q];
+                if (r < room_i && l32_ < room_j) dx[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = z;
+                if (bi != bj && r < room_j && l32_ < room_i) dy[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = y[q];
+            }
         }
     }
 }
@@ -552,8 +691,7 @@ template <int NSLOT>
 static hipError_t launch_leaf_block(const LeafJob *jobs_dev, int n_jobs, const float *damp_dev, int32_t *info,
                                     hipStream_t s)
 {
-    constexpr size_t lds_bytes = (size_t)(6 * LB_PLANE + 3 * LB_DPLANE) * sizeof(unsigned short) + LB_MAXN * sizeof(float);
-    static_assert(lds_bytes >= (size_t)16 * 32 * 33 * sizeof(float), "the per-wavefront staging tiles of the final store fit");
+    constexpr size_t lds_bytes = LB_LDS_BYTES;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute((const void *)leaf_block_kernel<NSLOT>,

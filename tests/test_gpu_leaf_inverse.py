@@ -1,0 +1,56 @@
+"""The one-workgroup inverse at the edges of its 32-row blocks, size classes and tile deals, against numpy in float64, and the
+pivot it names when a matrix is not positive definite."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2002_06015_amd import kfac, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [1, 2, 31, 32, 33, 63, 65, 96, 127, 129, 160, 161, 191, 193, 224, 225, 255, 257, 287, 288]
+
+
+def _invert(A, G, gamma):
+    layers = [wl.fc_layer(4, A.shape[0], G.shape[0], 0)]
+    ctx = kfac.Context(layers)
+    dA, dG = torch.from_numpy(A).cuda(), torch.from_numpy(G).cuda()
+    Ai, Gi = torch.full_like(dA, 3.0), torch.full_like(dG, 3.0)
+    pi, info = torch.zeros(1, device="cuda"), torch.full((2,), -1, dtype=torch.int32, device="cuda")
+    kfac.kfac_invert(ctx, layers, [dA], [dG], gamma, [Ai], [Gi], pi, info)
+    torch.cuda.synchronize()
+    ctx.close()
+    return Ai.cpu().numpy(), Gi.cpu().numpy(), float(pi), info.tolist()
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_inverse(n):
+    rng = np.random.default_rng(n)
+    X = []
+    for scale in (1.0, 1e-6):
+        b = rng.standard_normal((2 * n + 8, n))
+        s = np.exp(rng.uniform(-2, 2, n))          # rows of different magnitude
+        x = (b.T @ b / len(b) * s[:, None] * s[None, :] * scale).astype(np.float32)
+        X.append(np.ascontiguousarray((x + x.T) / np.float32(2)))
+    Ai, Gi, pi, info = _invert(X[0], X[1], 1e-3)
+    assert info == [0, 0]
+    for x, got, damp in ((X[0], Ai, pi * 1e-3), (X[1], Gi, 1e-3 / pi)):
+        d = x.astype(np.float64) + damp * np.eye(n)
+        ref = np.linalg.inv(d)
+        s = 1 / np.sqrt(np.diag(d))
+        kappa = np.linalg.cond(d * s[:, None] * s[None, :])     # of the unit-diagonal matrix the kernel eliminates
+        assert np.array_equal(got, got.T)
+        # element-wise in the unit-diagonal scale: n kappa 2^-24 of the largest element there
+        err = np.abs(got - ref) / s[:, None] / s[None, :]
+        assert err.max() <= n * kappa * 2.0 ** -24 * (np.abs(ref) / s[:, None] / s[None, :]).max() + 1e-12
+
+
+@pytest.mark.parametrize("n,bad", [(1, 0), (32, 0), (32, 1), (33, 32), (100, 6), (100, 7), (160, 159), (224, 101), (288, 8), (288, 271), (288, 287)])
+def test_first_non_positive_pivot(n, bad):
+    rng = np.random.default_rng(n + bad)
+    b = rng.standard_normal((2 * n + 8, n))
+    x = (b.T @ b / len(b)).astype(np.float32)
+    x = np.ascontiguousarray((x + x.T) / np.float32(2))
+    x[bad, bad] = -1.0
+    _, _, _, info = _invert(x, np.eye(4, dtype=np.float32), 0.0)
+    assert info == [bad + 1, 0]
