@@ -85,10 +85,13 @@ __device__ __forceinline__ void gd_mma(gd_floatx16 (&acc)[TM][TN], const gd_floa
 
 // partial sums of four wavefronts in LDS, [wave][v][lane] per 32 x 32 block in the accumulator layout
 // (column = lane % 32, row = 8 * (v / 4) + 4 * (lane / 32) + v % 4)
-template <int BLOCKS>
-__device__ __forceinline__ float gd_sum(const float *part, int blk, int r, int c)
+__device__ __forceinline__ int gd_place(int blk, int r, int c)
 {
-    const int e = blk * 1024 + (4 * (r >> 3) + (r & 3)) * 64 + c + 32 * ((r >> 2) & 1);
+    return blk * 1024 + (4 * (r >> 3) + (r & 3)) * 64 + c + 32 * ((r >> 2) & 1);
+}
+template <int BLOCKS>
+__device__ __forceinline__ float gd_sum(const float *part, int e)
+{
     constexpr int W = BLOCKS * 1024;
     return (part[e] + part[e + W]) + (part[e + 2 * W] + part[e + 3 * W]);
 }
@@ -102,8 +105,7 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__r
     const int wg = blockIdx.x;
     const int pi = find_problem(tile_start, n_probs, wg);
     const GemmProblem &P = probs[pi];
-    const int tile = xcd_remap(wg - tile_start[pi], (P.n_tiles + 7) & ~7);
-    if (tile >= P.n_tiles) return;
+    const int tile = xcd_remap(wg - tile_start[pi], P.n_tiles);
     int tm, tn;
     decode_tile(P, tile, tm, tn);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -164,43 +166,46 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__r
     const float alpha = P.alpha, beta = P.beta;
     // direct pass: a thread owns 4 adjacent columns of one row of every block; old values of all blocks requested first
     const int q8 = 4 * (tid & 7), r32 = tid >> 3;
-    float *mbase = sym ? P.C : P.Ct;
+    float *mbase = !sym ? P.Ct : i0 - j0 - (32 * TN - 1) < P.mirror_band ? P.C : nullptr;
     const long long ldm = sym ? P.ldc : P.ldct;
-    const float mbeta = sym ? beta : 0.0f;
-    gd_floatx4 old[BLOCKS], mold[BLOCKS];
+    gd_floatx4 old[BLOCKS];
 #pragma unroll
-    for (int b = 0; b < BLOCKS; ++b) {
-        old[b] = gd_floatx4{0.f, 0.f, 0.f, 0.f};
-        mold[b] = gd_floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int b = 0; b < BLOCKS; ++b) old[b] = gd_floatx4{0.f, 0.f, 0.f, 0.f};
     if (beta != 0.0f) {
 #pragma unroll
         for (int b = 0; b < BLOCKS; ++b) {
             const int i = i0 + 32 * (b / TN) + r32, j = j0 + 32 * (b % TN) + q8;
             if (i < P.M && j + 3 <= min(diag_tile ? i : P.N - 1, P.N - 1)) old[b] = *(const gd_floatx4_u *)(P.C + (long long)i * P.ldc + j);
-            const int mi = i0 + 32 * (b / TN) + q8, mj = j0 + 32 * (b % TN) + r32;
-            if (sym && mj < P.N && mi + 4 <= P.M && !(diag_tile && mj >= mi)) mold[b] = *(const gd_floatx4_u *)(mbase + (long long)mj * ldm + mi);
         }
     }
 #pragma unroll
     for (int b = 0; b < BLOCKS; ++b) {
         const int i = i0 + 32 * (b / TN) + r32, j = j0 + 32 * (b % TN) + q8;
         const int jmax = min(diag_tile ? i : P.N - 1, P.N - 1);   // last column this row may write
-        if (!P.C || i >= P.M || j > jmax) continue;
+        if (i >= P.M || j > jmax) continue;
         float *dst = P.C + (long long)i * P.ldc + j;
         gd_floatx4 v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = alpha * gd_sum<BLOCKS>(part, b, r32, q8 + e);
-        if (j + 3 <= jmax) {
-            if (beta != 0.0f)
+        for (int e = 0; e < 4; ++e) v[e] = alpha * gd_sum<BLOCKS>(part, gd_place(b, r32, q8 + e));
+        if (beta != 0.0f) {
+            if (j + 3 <= jmax)
                 for (int e = 0; e < 4; ++e) v[e] = fmaf(beta, old[b][e], v[e]);
-            *(gd_floatx4_u *)dst = v;
-        } else {
-            for (int e = 0; e < 4 && j + e <= jmax; ++e) dst[e] = beta != 0.0f ? fmaf(beta, dst[e], v[e]) : v[e];
+            else
+                for (int e = 0; e < 4 && j + e <= jmax; ++e) v[e] = fmaf(beta, dst[e], v[e]);
         }
+        if (P.C) {
+            if (j + 3 <= jmax) *(gd_floatx4_u *)dst = v;
+            else
+                for (int e = 0; e < 4 && j + e <= jmax; ++e) dst[e] = v[e];
+        }
+        if (mbase)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[gd_place(b, r32, q8 + e)] = v[e];
     }
-    // mirrored / transposed pass: a thread owns 4 adjacent rows of one column, which are adjacent in the mirror image
+    // mirrored / transposed pass over the values of the direct pass, left in the first wavefront's place: a thread owns 4
+    // adjacent rows of one column, which are adjacent in the mirror image
     if (mbase) {
+        __syncthreads();
 #pragma unroll
         for (int b = 0; b < BLOCKS; ++b) {
             const int i = i0 + 32 * (b / TN) + q8, j = j0 + 32 * (b % TN) + r32;
@@ -209,14 +214,10 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__r
             float *dst = mbase + (long long)j * ldm + i;
             gd_floatx4 v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = alpha * gd_sum<BLOCKS>(part, b, q8 + e, r32);
-            if (e0 == 0 && e1 == 4) {
-                if (mbeta != 0.0f)
-                    for (int e = 0; e < 4; ++e) v[e] = fmaf(mbeta, mold[b][e], v[e]);
-                *(gd_floatx4_u *)dst = v;
-            } else {
-                for (int e = e0; e < e1; ++e) dst[e] = mbeta != 0.0f ? fmaf(mbeta, dst[e], v[e]) : v[e];
-            }
+            for (int e = 0; e < 4; ++e) v[e] = part[gd_place(b, q8 + e, r32)];
+            if (e0 == 0 && e1 == 4) *(gd_floatx4_u *)dst = v;
+            else
+                for (int e = e0; e < e1; ++e) dst[e] = v[e];
         }
     }
 }

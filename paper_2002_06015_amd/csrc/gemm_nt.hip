@@ -34,21 +34,19 @@ constexpr int LDF = 36;     // LDS row length in floats (32 + 4 pad: conflict-fr
 // j <= i is written directly and j < i mirrored, which makes the result exactly symmetric),
 // plus the optional transposed copy Ct[j][i].  Both passes write whole row segments with
 // adjacent lanes on adjacent addresses; the transposition happens in the LDS reads.
-// The mirror pass relies on the old C being exactly symmetric (it reads beta's operand at
-// the mirrored position); Ct requires beta == 0.
+// Of the old C (beta != 0) only the lower triangle is read.  Ct requires beta == 0.
 typedef float floatx4_st __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int ROWS, int COLS>
-__device__ __forceinline__ void store_slab(const GemmProblem &P, const float *T, int gi0, int gj0, bool diag_tile,
-                                           int tid)
+__device__ __forceinline__ void store_slab(const GemmProblem &P, float *T, int gi0, int gj0, bool diag_tile, int tid)
 {
     constexpr int LDT = COLS + 1;
     const bool sym = (P.flags & GEMM_SYM) != 0;
     const float alpha = P.alpha, beta = P.beta;
-    // The old values (beta != 0) of all rows of a pass are requested before the first store of
-    // the pass: a load issued behind a store to the same matrix waits for it, and a pass of
-    // load - store pairs then costs one memory round trip per row.
-    // direct pass: a thread owns 4 adjacent columns of one row
+    float *mbase = !sym ? P.Ct : gi0 - gj0 - (COLS - 1) < P.mirror_band ? P.C : nullptr;
+    // direct pass: a thread owns 4 adjacent columns of one row.  The old values (beta != 0) of all its rows are requested
+    // before the first store: a load issued behind a store to the same matrix waits for it, and load - store pairs then
+    // cost one memory round trip per row.
     {
         constexpr int TPR = COLS / 4, RPP = 256 / TPR, NIT = (ROWS + RPP - 1) / RPP;
         const int c = (tid % TPR) * 4, rr = tid / TPR;
@@ -70,40 +68,32 @@ __device__ __forceinline__ void store_slab(const GemmProblem &P, const float *T,
             const int jmax = min(diag_tile ? i : P.N - 1, P.N - 1);   // last column this row may write
             if (j > jmax) continue;
             float *dst = P.C + (long long)i * P.ldc + j;
-            const float *t = T + r * LDT + c;
+            float *t = T + r * LDT + c;
             if (j + 3 <= jmax) {
                 floatx4 v = {alpha * t[0], alpha * t[1], alpha * t[2], alpha * t[3]};
                 if (beta != 0.0f)
                     for (int e = 0; e < 4; ++e) v[e] = fmaf(beta, old[q][e], v[e]);   // same rounding in every path
                 *(floatx4_st *)dst = v;
+                if (mbase)
+                    for (int e = 0; e < 4; ++e) t[e] = v[e];
             } else {
                 for (int e = 0; e < 4 && j + e <= jmax; ++e) {
                     float v = alpha * t[e];
                     if (beta != 0.0f) v = fmaf(beta, dst[e], v);
                     dst[e] = v;
+                    t[e] = v;
                 }
             }
         }
     }
-    // mirrored / transposed pass: a thread owns 4 adjacent rows i of one column j, which are
-    // 4 adjacent addresses of row j of the mirror image
-    float *mbase = sym ? P.C : P.Ct;
+    // mirrored / transposed pass over the values of the direct pass, left in T: a thread owns 4 adjacent rows i of one
+    // column j, which are 4 adjacent addresses of row j of the mirror image
     if (mbase) {
+        __syncthreads();
         const long long ldm = sym ? P.ldc : P.ldct;
-        const float mbeta = sym ? beta : 0.0f;
         constexpr int TPR = ROWS / 4, RPP = 256 / TPR, NIT = (COLS + RPP - 1) / RPP;
         const int r = (tid % TPR) * 4, cc = tid / TPR;
         const int i = gi0 + r;
-        floatx4 old[NIT];
-        if (mbeta != 0.0f) {
-#pragma unroll
-            for (int q = 0; q < NIT; ++q) {
-                const int c = cc + q * RPP, j = gj0 + c;
-                const int e0 = (sym && diag_tile) ? max(0, j + 1 - i) : 0;
-                old[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (c < COLS && j < P.N && e0 == 0 && i + 4 <= P.M) old[q] = *(const floatx4_st *)(mbase + (long long)j * ldm + i);
-            }
-        }
 #pragma unroll
         for (int q = 0; q < NIT; ++q) {
             const int c = cc + q * RPP, j = gj0 + c;
@@ -114,18 +104,9 @@ __device__ __forceinline__ void store_slab(const GemmProblem &P, const float *T,
             if (e0 >= e1) continue;
             float *dst = mbase + (long long)j * ldm + i;
             const float *t = T + r * LDT + c;
-            if (e0 == 0 && e1 == 4) {
-                floatx4 v = {alpha * t[0], alpha * t[LDT], alpha * t[2 * LDT], alpha * t[3 * LDT]};
-                if (mbeta != 0.0f)
-                    for (int e = 0; e < 4; ++e) v[e] = fmaf(mbeta, old[q][e], v[e]);
-                *(floatx4_st *)dst = v;
-            } else {
-                for (int e = e0; e < e1; ++e) {
-                    float v = alpha * t[e * LDT];
-                    if (mbeta != 0.0f) v = fmaf(mbeta, dst[e], v);
-                    dst[e] = v;
-                }
-            }
+            if (e0 == 0 && e1 == 4) *(floatx4_st *)dst = floatx4{t[0], t[LDT], t[2 * LDT], t[3 * LDT]};
+            else
+                for (int e = e0; e < e1; ++e) dst[e] = t[e * LDT];
         }
     }
 }
@@ -866,18 +847,13 @@ __device__ __forceinline__ void gemm_nt_f32_body(const GemmProblem *__restrict__
     const int wg = blockIdx.x;
     const int pi = find_problem(tile_start, n_probs, wg);
     const GemmProblem &P = probs[pi];
-    // every problem starts at a multiple of 8 workgroups (padded with idle ones), so the XCD
-    // of a workgroup is its local index % 8; neighbours in the logical order are
-    // neighbouring tiles of the same K range
-    const int n_local = P.n_tiles * P.splits;
-    const int local = xcd_remap(wg - tile_start[pi], (n_local + 7) & ~7);
-    if (local >= n_local) return;
-    const int split = local / P.n_tiles;
-    const int tile = local - split * P.n_tiles;
-    int tm, tn;
+    const int local = wg - tile_start[pi];
+    if (local >= n_workgroups(P)) return;   // padding up to the next problem
+    int tile, split, tm, tn;
+    const bool part_of_k = locate_tile(P, local, tile, split);   // neighbours: neighbouring tiles of the same K range
     decode_tile(P, tile, tm, tn);
     const int k0 = split * P.k_per_split;
-    const int k1 = min(P.K, k0 + P.k_per_split);
+    const int k1 = part_of_k ? min(P.K, k0 + P.k_per_split) : P.K;
     const int tid = threadIdx.x;
 
     LoaderF32<BM> la;
@@ -949,8 +925,8 @@ __device__ __forceinline__ void gemm_nt_f32_body(const GemmProblem *__restrict__
 
     // accumulator layout of the 32x32 block: column = lane % 32,
     // row = 8 * (v / 4) + 4 * (lane / 32) + v % 4 for register v = 0..15
-    if (P.splits > 1) {
-        float *part = P.partial + ((long long)tile * P.splits + split) * (BM * BN);
+    if (part_of_k) {
+        float *part = P.partial + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1462,12 +1438,11 @@ template <int TM, int TN, bool TAIL, bool TRANS = false>
 __device__ __forceinline__ void gemm_nt_bf16_body(const GemmProblem &P, int local, float *lds)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
-    const int split = local / P.n_tiles;
-    const int tile = local - split * P.n_tiles;
-    int tm, tn;
+    int tile, split, tm, tn;
+    const bool part_of_k = locate_tile(P, local, tile, split);
     decode_tile(P, tile, tm, tn);
     const int k0 = split * P.k_per_split;
-    const int k1 = min(P.K, k0 + P.k_per_split);
+    const int k1 = part_of_k ? min(P.K, k0 + P.k_per_split) : P.K;
     const int tid = threadIdx.x;
 
     LoaderBF16<BM, TAIL> la;
@@ -1528,8 +1503,8 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmProblem &P, int loca
         }
     }
 
-    if (P.splits > 1) {
-        float *part = P.partial + ((long long)tile * P.splits + split) * (BM * BN);
+    if (part_of_k) {
+        float *part = P.partial + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1567,7 +1542,7 @@ template <int B>
 __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int slab, int tm, int tn, float *T)
 {
     const bool diag_tile = (P.flags & GEMM_SYM) && tm == tn;
-    const float *part = P.partial + (long long)tile * P.splits * (B * B) + slab * 32 * B;
+    const float *part = P.partial + (long long)(tile - P.split_from) * P.splits * (B * B) + slab * 32 * B;
     // 32 * B elements, 4 per thread per pass.  Split q goes into partial sum q % 4 of its element;
     // the four are combined in a fixed order: as reproducible as one running sum, with the loads
     // of four splits and all passes in flight at once (the partial tiles are read exactly once)
@@ -1626,8 +1601,8 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmProblem *__r
     const int B = (P.tile_cfg == 0) ? 128 : 64;
     const int slabs = B / 32;
     const int local = wg - red_start[pi];
-    const int tile = local / slabs;
-    const int slab = local - tile * slabs;
+    const int tile = P.split_from + local / slabs;
+    const int slab = local % slabs;
     int tm, tn;
     decode_tile(P, tile, tm, tn);
     if (tm * B + slab * 32 >= P.M) return;
@@ -1646,9 +1621,8 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const GemmProblem *__
     const int wg = blockIdx.x;
     const int pi = find_problem(tile_start, n_probs, wg);
     const GemmProblem &P = probs[pi];
-    const int n_local = P.n_tiles * P.splits;
-    const int local = xcd_remap(wg - tile_start[pi], (n_local + 7) & ~7);
-    if (local >= n_local) return;
+    const int local = wg - tile_start[pi];
+    if (local >= n_workgroups(P)) return;
     if (P.a.tail | P.b.tail) gemm_nt_bf16_body<TM, TN, true>(P, local, lds);
     else                     gemm_nt_bf16_body<TM, TN, false>(P, local, lds);
 }
@@ -1660,9 +1634,8 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_trans_kernel(const GemmProbl
     const int wg = blockIdx.x;
     const int pi = find_problem(tile_start, n_probs, wg);
     const GemmProblem &P = probs[pi];
-    const int n_local = P.n_tiles * P.splits;
-    const int local = xcd_remap(wg - tile_start[pi], (n_local + 7) & ~7);
-    if (local >= n_local) return;
+    const int local = wg - tile_start[pi];
+    if (local >= n_workgroups(P)) return;
     gemm_nt_bf16_body<TM, TN, false, true>(P, local, lds);
 }
 

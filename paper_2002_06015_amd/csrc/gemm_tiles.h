@@ -26,6 +26,22 @@ __device__ __forceinline__ int xcd_remap(int wg, int total)
     return x * base + min(x, rem) + q;
 }
 
+// Workgroups of a problem, and which tile and which part of its contraction the local-th of them works on.  The whole
+// tiles and the split ones are dealt to the XCDs separately, so that every XCD gets its share of either kind.  A problem may
+// start at any workgroup (residues modulo 8 are only renamed then); where the problems of a launch read the same tensors, they
+// start at multiples of 8, so that the same part of the contraction lands on the same XCD in all of them.
+__device__ __forceinline__ int n_workgroups(const GemmProblem &P) { return P.split_from + (P.n_tiles - P.split_from) * P.splits; }
+__device__ __forceinline__ bool locate_tile(const GemmProblem &P, int local, int &tile, int &split)   // true: one of several parts
+{
+    split = 0;
+    if (local < P.split_from) { tile = xcd_remap(local, P.split_from); return false; }
+    const int n = P.n_tiles - P.split_from;
+    const int u = xcd_remap(local - P.split_from, n * P.splits);
+    split = u / n;
+    tile = P.split_from + u - split * n;
+    return P.splits > 1;
+}
+
 __device__ __forceinline__ void tri_decode(int t, int &tm, int &tn)
 {
     int r = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);

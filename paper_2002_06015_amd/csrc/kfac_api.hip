@@ -246,9 +246,11 @@ void finish_problem(GemmProblem &P)
     P.n_tiles = (P.flags & GEMM_SYM) ? P.tiles_m * (P.tiles_m + 1) / 2 : P.tiles_m * P.tiles_n;
     P.splits = 1;
     P.k_per_split = std::max(32, (P.K + 31) / 32 * 32);
+    P.split_from = 0;
     P.partial = nullptr;
     P.partial_rs = nullptr;
     if (P.ones == 0) P.ones = P.K;
+    if (P.mirror_band == 0) P.mirror_band = INT_MAX;
 }
 
 // Whether a phase of plain fp32 products (three-plane mode) runs through the direct kernel of gemm_direct.hip, and with
@@ -259,7 +261,7 @@ void finish_problem(GemmProblem &P)
 // 288 x 288 x 288 takes 6.5 us instead of 13 (symmetric, with beta: 8 instead of 16) and 576 x 576 x 576 13.7 instead
 // of 21.5; the 64-tile without LDS staging has a shorter fixed part and K loop than the staged one at the same rate
 // (1152 x 1152 x 1152 symmetric: 28 us instead of 40).
-int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun, bool allow_split)
+int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun)
 {
     double wgk[4] = {0, 0, 0, 0}, kmax[4] = {0, 0, 0, 0}, kall = 0;
     bool split = false;
@@ -270,11 +272,9 @@ int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun, bo
             return (P.flags & GEMM_SYM) ? tm * (tm + 1) / 2 : tm * tn;
         };
         double k_wg = P.K;
-        if (allow_split) {
-            const int want = (int)((tun.target_wgs + tiles(tile_edge(P.tile_cfg)) - 1) / tiles(tile_edge(P.tile_cfg)));
-            const int s = std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(want, P.K / tun.min_k_per_split));
-            if (s > 1) { k_wg = P.K / s; split = true; }
-        }
+        const int want = (int)((tun.target_wgs + tiles(tile_edge(P.tile_cfg)) - 1) / tiles(tile_edge(P.tile_cfg)));
+        const int s = std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(want, P.K / tun.min_k_per_split));
+        if (s > 1) { k_wg = P.K / s; split = true; }
         wgk[P.tile_cfg] += tiles(tile_edge(P.tile_cfg)) * P.K;
         kmax[P.tile_cfg] = std::max(kmax[P.tile_cfg], k_wg);
         wgk[2] += tiles(32) * P.K;
@@ -290,18 +290,63 @@ int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun, bo
     return d32 <= d64 ? 2 : 3;
 }
 
-// Emits the launches of one phase: per tile configuration one GEMM launch, plus one
-// reduction launch if any problem was split along K (appended to `deferred` instead, if given:
-// the caller then places the reductions after all the matrix launches, on a stream it chooses).
+// One GEMM launch of problems that share a tile configuration, in the given order, plus the reduction launch if any of them
+// is split along K (appended to `deferred` instead, if given: the caller then places the reductions after all the matrix
+// launches, on a stream it chooses).
+// align: every problem starts at a multiple of that many workgroups (8: see locate_tile; not where the padding could push a
+// launch past a whole number of rounds).
+void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmProblem> &sel, int cfg, int dtype, int align,
+                      std::vector<Launch> *deferred = nullptr)
+{
+    if (sel.empty()) return;
+    const int B = tile_edge(cfg);
+    std::vector<int> start(sel.size() + 1, 0), rstart(sel.size() + 1, 0);
+    bool any_split = false;
+    for (size_t i = 0; i < sel.size(); ++i) {
+        const GemmProblem &P = sel[i];
+        start[i + 1] = start[i] + (P.split_from + (P.n_tiles - P.split_from) * P.splits + align - 1) / align * align;
+        rstart[i + 1] = rstart[i] + (P.splits > 1 ? (P.n_tiles - P.split_from) * (B / 32) : 0);
+        any_split |= P.splits > 1;
+    }
+    Launch L{};
+    L.kind = L_GEMM;
+    for (auto &P : sel)
+        if (P.flags & GEMM_SYM) {
+            const double d = P.M + ((P.flags & GEMM_BORDER) ? 1.0 : 0.0);
+            L.flops += (double)P.K * d * (d + 1.0);
+        } else {
+            L.flops += 2.0 * P.M * (double)P.N * P.K;
+        }
+    L.off_a = plan.tab.add(sel.data(), sel.size() * sizeof(GemmProblem));
+    L.off_b = plan.tab.add(start.data(), start.size() * sizeof(int));
+    L.n = (int)sel.size();
+    L.total_wgs = start.back();
+    L.cfg = cfg;
+    L.dtype = (dtype == 0 && tun.split) ? 2 : dtype;
+    plan.launches.push_back(L);
+    if (any_split) {
+        Launch R{};
+        R.kind = L_REDUCE;
+        R.off_a = L.off_a;
+        R.off_b = plan.tab.add(rstart.data(), rstart.size() * sizeof(int));
+        R.n = (int)sel.size();
+        R.total_wgs = rstart.back();
+        for (auto &P : sel)   // partial tiles read, the sum written
+            if (P.splits > 1) R.bytes += 4.0 * (P.n_tiles - P.split_from) * B * B * (P.splits + 1.0);
+        if (deferred) deferred->push_back(R);
+        else plan.launches.push_back(R);
+    }
+}
+
+// Emits the launches of one phase of factor products: per tile configuration one GEMM launch and its reduction.
 void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<GemmProblem> &probs,
-                     int dtype, bool allow_split, bool phase_boost = false, std::vector<Launch> *deferred = nullptr)
+                     int dtype, std::vector<Launch> *deferred)
 {
     if (probs.empty()) return;
     // Tile configuration per problem.  When the phase as a whole keeps the GPU busy with 128x128
     // tiles, each problem takes the configuration with less padded work (the big tile moves half the
-    // operand bytes per flop, worth ~15 %; up to 1.5x the work for the rectangular products of the
-    // preconditioning, measured: -7 %; for the symmetric products of the factors -- 256 x 256 is 3 big
-    // tiles or 10 small ones, 1.2x -- it costs the same either way); otherwise the latency model decides.
+    // operand bytes per flop, worth ~15 %; 256 x 256, symmetric, is 3 big tiles or 10 small ones, 1.2x:
+    // it costs the same either way); otherwise the latency model decides.
     double tile_steps128 = 0;   // 128x128 tiles times 32-wide K steps: the work of the phase
     for (auto &P : probs) {
         const double tm = (P.M + 127) / 128, tn = (P.N + 127) / 128;
@@ -316,14 +361,14 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
                 const double tm = (P.M + B - 1) / B, tn = (P.N + B - 1) / B;
                 return (sym ? tm * (tm + 1) / 2 : tm * tn) * B * B;
             };
-            P.tile_cfg = work(128) <= (phase_boost ? 1.5 : 1.15) * work(64) ? 0 : 1;
+            P.tile_cfg = work(128) <= 1.15 * work(64) ? 0 : 1;
         } else {
             P.tile_cfg = choose_tile_cfg(P.M, P.N, P.K, sym);
         }
         finish_problem(P);
     }
     if (dtype == 0 && tun.split && !tun.force_tile && !tun.worst_case_splits) {   // (no scratch: the workspace bound leaves it out)
-        const int cfg = choose_direct(probs, tun, allow_split);
+        const int cfg = choose_direct(probs, tun);
         if (cfg >= 0)
             for (auto &P : probs) { P.tile_cfg = cfg; finish_problem(P); }
     }
@@ -333,7 +378,8 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
             if (P.tile_cfg == cfg) sel.push_back(P);
         if (sel.empty()) continue;
         const int B = tile_edge(cfg);
-        if (allow_split && cfg < 2) {
+        int align = 1;
+        if (cfg < 2) {
             // Per problem (independent of what else is in the launch, so that the workspace need of
             // a layer list does not depend on which of its inputs are present): enough splits for
             // target_wgs workgroups and at most max_k_per_wg of contraction each.
@@ -342,98 +388,170 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
             // workspace bound is computed with the per-problem rule, which needs the most scratch.
             long long base_wgs = 0;
             for (auto &P : sel) base_wgs += (long long)P.n_tiles * ((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg);
+            // A launch of fewer workgroups also keeps its problems aligned (64 channels, fp32: 13 correlations of one tensor,
+            // 102 us against 107); one that goes through the chip several times is better off with an even deal to the XCDs
+            // (ResNet-50, bf16: 2.12 ms against 2.18).
             const bool launch_is_full = !tun.worst_case_splits && base_wgs >= (cfg == 0 ? 1024 : 2048);
-            auto splits_for = [&](const GemmProblem &P, int boost, int *kps_out) {
-                const int want = std::max(boost, launch_is_full ? 1 : (tun.target_wgs + P.n_tiles - 1) / P.n_tiles);
-                int splits = std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg,
-                                      std::min(want, P.K / tun.min_k_per_split));
-                int kps = std::max(32, (P.K + 31) / 32 * 32);
-                if (splits > 1) {
-                    kps = ((P.K + splits - 1) / splits + 31) / 32 * 32;
-                    splits = (P.K + kps - 1) / kps;
-                }
-                *kps_out = kps;
-                return std::max(1, splits);
-            };
-            // A heavy phase with only a few rounds of workgroups (a CU holds two 128x128 or four
-            // 64x64 workgroups) loses a large part of its last round: 1026 equal tiles on 512 slots
-            // take 3 rounds, not 2.004.  Splitting every problem `boost` times further shortens the
-            // rounds; the boost with the shortest modelled makespan wins (each extra split charged
-            // 2 % for the partial tiles and their reduction).  Only for phases whose problem set is
-            // fixed by the layer list.
-            int boost = 1;
-            if (phase_boost) {
-                const double slots = cfg == 0 ? 512.0 : 1024.0;
-                double ksteps = 0;
-                for (auto &P : sel) ksteps += (double)P.n_tiles * ((P.K + 31) / 32);
-                if (ksteps >= slots * 24) {
-                    double best = 0;
-                    for (int cand = 1; cand <= 8; ++cand) {
-                        double work = 0, longest = 0;
-                        for (auto &P : sel) {
-                            int kps;
-                            const int sp = splits_for(P, cand, &kps);
-                            const double len = kps / 32 + 6.0;   // K steps plus the fixed part of a workgroup
-                            work += (double)P.n_tiles * sp * len;
-                            longest = std::max(longest, len);
-                        }
-                        const double makespan = std::ceil(work / (longest * slots)) * longest * (1.0 + 0.02 * (cand - 1));
-                        if (cand == 1 || makespan < best) { best = makespan; boost = cand; }
-                    }
-                }
-            }
+            if (!launch_is_full) align = 8;
             for (auto &P : sel) {
-                int kps;
-                const int splits = splits_for(P, boost, &kps);
-                if (splits > 1) {
-                    P.splits = splits;
-                    P.k_per_split = kps;
-                    P.partial = (float *)arena.take((size_t)P.n_tiles * splits * B * B * sizeof(float));
-                    if (P.flags & GEMM_BORDER)
-                        P.partial_rs = (float *)arena.take((size_t)P.tiles_m * splits * B * sizeof(float));
-                }
+                const int want = launch_is_full ? 1 : (tun.target_wgs + P.n_tiles - 1) / P.n_tiles;
+                const int splits = std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(want, P.K / tun.min_k_per_split));
+                if (splits <= 1) continue;
+                P.k_per_split = ((P.K + splits - 1) / splits + 31) / 32 * 32;
+                P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
+                if (P.splits == 1) continue;
+                P.partial = (float *)arena.take((size_t)P.n_tiles * P.splits * B * B * sizeof(float));
+                if (P.flags & GEMM_BORDER)
+                    P.partial_rs = (float *)arena.take((size_t)P.tiles_m * P.splits * B * sizeof(float));
             }
         }
         // longest workgroups first
         std::stable_sort(sel.begin(), sel.end(), [](const GemmProblem &x, const GemmProblem &y) {
             return std::min(x.K, x.k_per_split) > std::min(y.K, y.k_per_split);
         });
-        std::vector<int> start(sel.size() + 1, 0), rstart(sel.size() + 1, 0);
-        bool any_split = false;
-        for (size_t i = 0; i < sel.size(); ++i) {
-            start[i + 1] = start[i] + ((sel[i].n_tiles * sel[i].splits + 7) & ~7);   // XCD-aligned
-            rstart[i + 1] = rstart[i] + (sel[i].splits > 1 ? sel[i].n_tiles * (B / 32) : 0);
-            any_split |= sel[i].splits > 1;
-        }
-        Launch L{};
-        L.kind = L_GEMM;
-        for (auto &P : sel)
-            if (P.flags & GEMM_SYM) {
-                const double d = P.M + ((P.flags & GEMM_BORDER) ? 1.0 : 0.0);
-                L.flops += (double)P.K * d * (d + 1.0);
-            } else {
-                L.flops += 2.0 * P.M * (double)P.N * P.K;
-            }
-        L.off_a = plan.tab.add(sel.data(), sel.size() * sizeof(GemmProblem));
-        L.off_b = plan.tab.add(start.data(), start.size() * sizeof(int));
-        L.n = (int)sel.size();
-        L.total_wgs = start.back();
-        L.cfg = cfg;
-        L.dtype = (dtype == 0 && tun.split) ? 2 : dtype;
-        plan.launches.push_back(L);
-        if (any_split) {
-            Launch R{};
-            R.kind = L_REDUCE;
-            R.off_a = L.off_a;
-            R.off_b = plan.tab.add(rstart.data(), rstart.size() * sizeof(int));
-            R.n = (int)sel.size();
-            R.total_wgs = rstart.back();
-            for (auto &P : sel)
-                if (P.splits > 1) R.bytes += 4.0 * P.n_tiles * B * B * (P.splits + 1.0);   // partial tiles read, the sum written
-            if (deferred) deferred->push_back(R);
-            else plan.launches.push_back(R);
-        }
+        push_gemm_launch(plan, tun, sel, cfg, dtype, align, deferred);
     }
+}
+
+// ---- products of plain fp32 matrices (the inversion's and the preconditioning's): which kernel takes a phase
+// Estimated microseconds of one launch of `ps` per kernel, fitted to launches of 1 to 30 products of 33 ... 4096 rows on
+// gfx950.  They are measured shapes, not a theory: what they have to get right is which kernel is faster.
+//   128-tile, staged: a compute unit holds two workgroups.  One alone takes 1.7 us a K step of 32 (it waits for its own loads
+//     and barriers), two together 3.0 us a step for both, where the matrix cores' power limit lies (171 TFLOP/s).
+//   64-tile, staged / direct: latency of one workgroup (the direct one halves it: its wavefronts split K), then
+//     100 to 120 TFLOP/s.
+//   32-tile, direct: a quarter of the latency again and half the rate.
+struct PhaseCost { double us; int cfg, tail_parts; };
+struct Shape {                                      // what the estimate knows of a product
+    double tiles[4], K, steps;                      // tiles per configuration, contraction length, K steps of 32
+    const GemmProblem *P;
+};
+
+constexpr int kSlots128 = 512;                      // workgroups of the 128-tile kernel resident at once
+constexpr int kMaxTailParts = 8, kMaxTailWgs = 1024;
+
+// (Shapes in falling order of K.)  The workgroups of a 128-tile launch beyond a whole number of rounds (512) leave most of
+// the chip idle: 513 equal tiles take as long as 768.  Their contractions are cut into `tail_parts`, and a reduction adds
+// the parts up (9 us and 128 KB of traffic per part).
+PhaseCost cost_128(const Shape *first, const Shape *last)
+{
+    double n = 0, work = 0;
+    for (const Shape *q = first; q != last; ++q) { n += q->tiles[0]; work += q->tiles[0] * q->steps; }
+    const double r = n - kSlots128 * std::floor(n / kSlots128);
+    double tail_work = 0, left = r;
+    for (const Shape *q = last; q != first && left > 0;) {
+        --q;
+        const double c = std::min(left, q->tiles[0]);
+        tail_work += c * q->steps;
+        left -= c;
+    }
+    auto round = [](double q, double steps) {       // q workgroups of `steps` each
+        const double full = std::floor(q / kSlots128), rest = q - kSlots128 * full;
+        const double slope = rest == 0 ? 0.0 : rest <= 256 ? 1.7 + 0.5 * rest / 256 : 2.6 + 0.4 * (rest - 256) / 256;
+        return (3.0 * full + slope) * steps;
+    };
+    const double head = 11.0 + 3.0 * (work - tail_work) / kSlots128;
+    PhaseCost best{head + (r > 0 ? round(r, tail_work / r) : 0.0), 0, 1};
+    for (int s = 2; s <= kMaxTailParts && r > 0 && r * s <= kMaxTailWgs && (last - 1)->steps >= 4.0 * s; ++s) {
+        const double us = head + round(r * s, tail_work / r / s + 1.5) + 9.0 + 0.03 * r * s;
+        if (us < best.us) best = {us, 0, s};
+    }
+    return best;
+}
+
+PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last)
+{
+    double nk[4] = {0, 0, 0, 0}, n64 = 0;
+    for (const Shape *q = first; q != last; ++q) {
+        for (int c = 1; c < 4; ++c) nk[c] += q->tiles[c] * q->K;
+        n64 += q->tiles[1];
+    }
+    const double kmax = first->K;
+    const PhaseCost c64{6.0 + std::max(0.0265 * kmax, 0.0065 * kmax + 6.45e-5 * nk[1]), 1, 1};
+    if (tun.force_tile == 64) return c64;
+    PhaseCost best = cost_128(first, last);
+    if (tun.force_tile == 128) return best;
+    if (c64.us < best.us) best = c64;
+    if (tun.split) {
+        const PhaseCost d32{5.0 + std::max(0.0066 * kmax, 3.65e-5 * nk[2]), 2, 1};
+        const double per_cu = n64 / 256;
+        const PhaseCost d64{8.0 + std::max((per_cu <= 1 ? 0.013 + 0.006 * per_cu : 0.034) * kmax, 0.0035 * kmax + 6.45e-5 * nk[3]), 3, 1};
+        if (d32.us < best.us) best = d32;
+        if (d64.us < best.us) best = d64;
+    }
+    return best;
+}
+
+// Emits a phase of independent plain products: through one kernel, or through two launches, where the products with the
+// longer contractions take one kernel and the others another, or where 128-tiles take those they fit and another kernel
+// the rest, whichever the estimate prefers.
+void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::vector<GemmProblem> &probs)
+{
+    if (probs.empty()) return;
+    std::vector<Shape> all;
+    for (auto &P : probs) {
+        Shape q{{0, 0, 0, 0}, (double)P.K, std::ceil(P.K / 32.0), &P};
+        for (int c = 0; c < 4; ++c) {
+            const int B = tile_edge(c), tm = (P.M + B - 1) / B, tn = (P.N + B - 1) / B;
+            q.tiles[c] = (P.flags & GEMM_SYM) ? 0.5 * tm * (tm + 1.0) : (double)tm * tn;
+        }
+        all.push_back(q);
+    }
+    std::stable_sort(all.begin(), all.end(), [](const Shape &x, const Shape &y) { return x.K > y.K; });
+    const Shape *first = all.data(), *last = first + all.size(), *cut = last;
+    PhaseCost cost[2] = {best_kernel(tun, first, last), {0, 0, 1}};
+    auto consider = [&](const Shape *a, const Shape *b, const Shape *c) {   // [a, b) in one launch, [b, c) in another
+        const PhaseCost x = best_kernel(tun, a, b), y = best_kernel(tun, b, c);
+        if (x.us + y.us >= cost[0].us + cost[1].us) return;
+        cost[0] = x; cost[1] = y;
+        first = a; cut = b; last = c;
+    };
+    std::vector<Shape> by_fit;
+    if (!tun.force_tile) {
+        const Shape *end = last;
+        for (const Shape *q = all.data() + 1; q < end; ++q)
+            if (q->K != q[-1].K) consider(all.data(), q, end);
+        by_fit = all;
+        const size_t fit = std::stable_partition(by_fit.begin(), by_fit.end(), [](const Shape &q) { return 4.0 * q.tiles[0] <= 1.5 * q.tiles[1]; }) - by_fit.begin();
+        if (fit > 0 && fit < by_fit.size()) consider(by_fit.data(), by_fit.data() + fit, by_fit.data() + by_fit.size());
+    }
+    for (int q = 0; q < 2; ++q) {
+        std::vector<GemmProblem> sel;
+        long long n = 0;
+        for (const Shape *t = q ? cut : first; t != (q ? last : cut); ++t) {
+            sel.push_back(*t->P);
+            sel.back().tile_cfg = cost[q].cfg;
+            finish_problem(sel.back());
+            n += sel.back().n_tiles;
+        }
+        const int s = cost[q].tail_parts;
+        long long left = s > 1 ? n % kSlots128 : 0;   // the last tiles of the launch, those beyond whole rounds
+        for (size_t i = sel.size(); i-- > 0 && left > 0;) {
+            GemmProblem &P = sel[i];
+            const int split_tiles = (int)std::min<long long>(left, P.n_tiles);
+            left -= split_tiles;
+            P.k_per_split = ((P.K + s - 1) / s + 31) / 32 * 32;
+            P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
+            if (P.splits == 1) continue;
+            P.split_from = P.n_tiles - split_tiles;
+            if (!tun.worst_case_splits)               // (the workspace bound adds max_tail_bytes instead)
+                P.partial = (float *)arena.take((size_t)split_tiles * P.splits * 128 * 128 * sizeof(float));
+        }
+        push_gemm_launch(plan, tun, sel, cost[q].cfg, 0, 1);
+    }
+}
+
+// Upper bound of the scratch of one such phase on matrices with n rows each.
+size_t max_tail_bytes(const std::vector<int> &n)
+{
+    double tiles = 0, parts = 1;
+    for (int d : n) {
+        const double t = (d + 127) / 128;
+        tiles += t * t;
+        parts = std::max(parts, std::min<double>(kMaxTailParts, (d + 31) / 32 / 4));   // (cost_128: at least 4 steps a part)
+    }
+    if (parts < 2) return 0;
+    return (size_t)std::min<double>(tiles * parts, kMaxTailWgs) * 128 * 128 * sizeof(float) + n.size() * kAlign;
 }
 
 Operand plain_operand(const float *base, long long ld, int rows, int K)
@@ -809,7 +927,7 @@ void plan_stats(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &
     {
         const int nchunk = split ? std::max(1, split->gemm_chunks) : 1;
         if (nchunk <= 1) {
-            emit_gemm_phase(plan, arena, tun, probs, a.in == KFAC_BF16 ? 1 : 0, true, false, post > 0 ? &reductions : nullptr);
+            emit_gemm_phase(plan, arena, tun, probs, a.in == KFAC_BF16 ? 1 : 0, post > 0 ? &reductions : nullptr);
         } else {
             // chunks of similar work (largest problems first, each to the lightest chunk)
             std::vector<size_t> order(probs.size());
@@ -825,9 +943,9 @@ void plan_stats(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &
                 load[g] += work(probs[i]);
             }
             for (auto &c : chunks)
-                emit_gemm_phase(plan, arena, tun, c, a.in == KFAC_BF16 ? 1 : 0, true, false, post > 0 ? &reductions : nullptr);
+                emit_gemm_phase(plan, arena, tun, c, a.in == KFAC_BF16 ? 1 : 0, post > 0 ? &reductions : nullptr);
         }
-        emit_gemm_phase(plan, arena, tun, tprobs, a.in == KFAC_BF16 ? 4 : 3, true, false, post > 0 ? &reductions : nullptr);
+        emit_gemm_phase(plan, arena, tun, tprobs, a.in == KFAC_BF16 ? 4 : 3, post > 0 ? &reductions : nullptr);
     }
     if (post > 0) {
         plan.sync(L_RECORD, split->ev_gemm, 0);
@@ -924,8 +1042,6 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         P.C = Y; P.ldc = ldy; P.Ct = W; P.ldct = ldw;
         P.M = n2; P.N = n1; P.K = n1; P.flags = 0;
         P.alpha = 1.f; P.beta = 0.f;
-        P.tile_cfg = choose_tile_cfg(P.M, P.N, P.K, (P.flags & GEMM_SYM) != 0);
-        finish_problem(P);
         ops.push_back(op);
     }
     {
@@ -936,9 +1052,8 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         P.b = plain_operand(X21, ld, n2, n1);
         P.C = X22; P.ldc = ld; P.Ct = nullptr;
         P.M = n2; P.N = n2; P.K = n1; P.flags = GEMM_SYM;
+        P.mirror_band = rec_leaf;   // above the diagonal only the leaf inversion reads its source
         P.alpha = -1.f; P.beta = 1.f;
-        P.tile_cfg = choose_tile_cfg(P.M, P.N, P.K, (P.flags & GEMM_SYM) != 0);
-        finish_problem(P);
         ops.push_back(op);
     }
     const int l2 = build_inverse(ops, arena, X, ld, o + n1, n2, l1 + 2, info_idx, rec_leaf);
@@ -951,8 +1066,6 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         P.C = X12; P.ldc = ld; P.Ct = X21; P.ldct = ld;
         P.M = n1; P.N = n2; P.K = n2; P.flags = 0;
         P.alpha = -1.f; P.beta = 0.f;
-        P.tile_cfg = choose_tile_cfg(P.M, P.N, P.K, (P.flags & GEMM_SYM) != 0);
-        finish_problem(P);
         ops.push_back(op);
     }
     {
@@ -964,8 +1077,6 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         P.C = X11; P.ldc = ld; P.Ct = nullptr;
         P.M = n1; P.N = n1; P.K = n2; P.flags = GEMM_SYM;
         P.alpha = -1.f; P.beta = 1.f;
-        P.tile_cfg = choose_tile_cfg(P.M, P.N, P.K, (P.flags & GEMM_SYM) != 0);
-        finish_problem(P);
         ops.push_back(op);
     }
     return l2 + 2;
@@ -1017,7 +1128,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             C.border = m.bias ? 1 : 0;
             C.wg_start = copy_wgs;
             copy_wgs += (core + 7) / 8;
-            copy_bytes += 8.0 * core * core;   // every element read once and written once
+            copy_bytes += 4.0 * core * (core + 1.0 + 2.0 * std::min(core, kLeafMax));   // the elements up to kLeafMax past the diagonal, read and written
             cjobs.push_back(C);
             build_inverse(ops, arena, m.dst, m.n, 0, core, 0, m.info_idx, tun.rec_leaf);
             if (m.bias) {
@@ -1064,7 +1175,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             if (op.level == lv && op.kind == OP_GEMM) gp.push_back(op.gemm);
         // split-K scratch of one level is dead once the level's launches are enqueued (in order)
         const size_t mark = arena.used;
-        emit_gemm_phase(plan, arena, tun, gp, 0, true, true);
+        emit_plain_phase(plan, arena, tun, gp);
         arena.release_to(mark);
     }
     if (!bjobs.empty()) {
@@ -1234,8 +1345,6 @@ void plan_precondition(Plan &plan, Arena &arena, const Tunables &tun, const Prec
         P.C = Vt; P.ldc = ldv; P.Ct = nullptr;
         P.M = dA; P.N = dG; P.K = dA; P.flags = 0;
         P.alpha = 1.f; P.beta = 0.f;
-        P.tile_cfg = choose_tile_cfg(P.M, P.N, P.K, (P.flags & GEMM_SYM) != 0);
-        finish_problem(P);
         p1.push_back(P);
         GemmProblem Q{};
         Q.a = plain_operand(dry ? nullptr : a.G_inv[l], dG, dG, dG);
@@ -1243,12 +1352,13 @@ void plan_precondition(Plan &plan, Arena &arena, const Tunables &tun, const Prec
         Q.C = dry ? nullptr : a.out[l]; Q.ldc = dA; Q.Ct = nullptr;
         Q.M = dG; Q.N = dA; Q.K = dG; Q.flags = 0;
         Q.alpha = 1.f; Q.beta = 0.f;
-        Q.tile_cfg = choose_tile_cfg(Q.M, Q.N, Q.K, false);
-        finish_problem(Q);
         p2.push_back(Q);
     }
-    emit_gemm_phase(plan, arena, tun, p1, 0, true, true);
-    emit_gemm_phase(plan, arena, tun, p2, 0, true, true);
+    const size_t mark = arena.used;
+    emit_plain_phase(plan, arena, tun, p1);
+    arena.release_to(mark);
+    emit_plain_phase(plan, arena, tun, p2);
+    arena.release_to(mark);
 }
 
 // ---------------------------------------------------------------- fused step planner
@@ -1705,6 +1815,17 @@ size_t kfac_workspace_bytes_opt(const kfac_layer *L, int32_t n_layers, kfac_dtyp
             best = std::max(best, std::max(arena.peak, sum_peaks + sum_peaks / 4));
         }
     }
+    // the split tails of the plain products: up to four chains and the preconditioning have one phase each under way
+    {
+        std::vector<int> dims;
+        for (int l = 0; l < n_layers; ++l) {
+            int dA, dG;
+            layer_ok(L[l], &dA, &dG, nullptr, nullptr);
+            dims.push_back(dA);
+            dims.push_back(dG);
+        }
+        best += (1 + std::min(4, n_layers)) * max_tail_bytes(dims);
+    }
     // im2col of a single layer and the BatchNorm calls need table space only
     best = std::max(best, (size_t)1 << 20);
     return align_up(best + 4096, kAlign);
@@ -2093,7 +2214,8 @@ bool bn_full_dims_ok(int32_t n_layers, int32_t N, const int32_t *C)
 size_t bn_full_workspace_bytes(int32_t n_layers, int32_t N, const int32_t *C)
 {
     if (!bn_full_dims_ok(n_layers, N, C)) return 0;
-    const Tunables tun(default_options());
+    Tunables tun(default_options());
+    tun.worst_case_splits = true;
     BnFullArgs a{};
     a.n_layers = n_layers; a.N = N; a.C = C;
     size_t all = 0, single = 0;
@@ -2103,8 +2225,8 @@ size_t bn_full_workspace_bytes(int32_t n_layers, int32_t N, const int32_t *C)
         arena.take_tail(plan.tab.buf.size() + 16);
         all = arena.peak;
     }
-    // a partial mask changes which products share a launch and hence their split-K scratch: the
-    // largest single-layer plan on top covers that; the call itself checks the size in any case
+    // a partial mask changes which matrices share a group: the largest single-layer plan on top, and the split tails of
+    // one phase of every group, cover that; the call itself checks the size in any case
     std::vector<uint8_t> mask(n_layers, 0);
     a.invert_mask = mask.data();
     for (int l = 0; l < n_layers; ++l) {
@@ -2117,7 +2239,9 @@ size_t bn_full_workspace_bytes(int32_t n_layers, int32_t N, const int32_t *C)
         single = std::max(single, arena.peak);
         mask[l] = 0;
     }
-    return align_up(all + single + 4096, kAlign);
+    std::vector<int> dims;
+    for (int l = 0; l < n_layers; ++l) dims.push_back(2 * C[l]);
+    return align_up(all + single + 4 * max_tail_bytes(dims) + 4096, kAlign);
 }
 
 kfac_status bn_full_precondition(kfac_ctx *ctx, int32_t n_layers, int32_t N, const int32_t *C,

@@ -46,13 +46,16 @@ struct GemmProblem {
     Operand a, b;
     float *C;        // [M, N], leading dimension ldc (may be null if only Ct is wanted)
     float *Ct;       // optional transposed copy Ct[j][i], leading dimension ldct (or null)
-    float *partial;  // split-K scratch: [tiles][splits][BM*BN] (null if splits == 1)
+    float *partial;  // split-K scratch: [split tiles][splits][BM*BN] (null if splits == 1)
     float *partial_rs;  // split-K scratch of the border row sums: [tiles_m][splits][BM] (GEMM_BORDER, splits > 1)
     long long ldc, ldct;
     int M, N, K;
     int ones;                 // GEMM_BORDER: the sum of the all-ones row with itself (K, unless the contraction includes padding)
     int tiles_m, tiles_n, n_tiles;
     int splits, k_per_split;  // k_per_split is a multiple of 32
+    int split_from;           // tiles below this number are not split (0 with GEMM_BORDER): the workgroups of the whole tiles
+                              // come first, then splits workgroups for each of the others
+    int mirror_band;          // GEMM_SYM: a tile is mirrored only if it has an element with i - j < mirror_band
     int flags;
     int tile_cfg;             // 0: 128x128 tiles, 1: 64x64 tiles; direct kernel: 2: 32x32, 3: 64x64
     float alpha, beta;        // C = alpha * acc + beta * C   (beta == 0: C is not read)
@@ -134,7 +137,7 @@ struct TraceJob {   // one per layer
     int idx;        // layer index: damp[3*idx .. 3*idx+2] and pi_out[idx] are written
 };
 
-struct CopyJob {    // dst[i][j] = src[i][j] + (i == j) * damp[damp_idx]   (i, j < n)
+struct CopyJob {    // dst[i][j] = src[i][j] + (i == j) * damp[damp_idx]   (i < n, j < min(n, i + kLeafMax))
     const float *src;
     float *dst;
     long long lds, ldd;
