@@ -1535,56 +1535,72 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmProblem &P, int loca
 }
 
 // ------------------------------------------------------------------ split-K reduction + epilogue
-// One workgroup per 32-row slab of a partial tile: sums the partial tiles in split order
-// (fixed order, so results are reproducible bit for bit) into LDS and applies the same
-// row-wise epilogue.  red_start counts slabs.
-template <int B>
-__device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int slab, int tm, int tn, float *T)
+// One workgroup per slab of rows of a partial tile: sums the partial tiles in a fixed order (reproducible bit for bit) into
+// LDS and applies the same row-wise epilogue.  red_start counts slabs.  A chain of load latencies where the splits are many
+// and the tiles few (13 tiles of 147 parts for the 64-channel correlations): slabs of 8 rows then (red_rows), the splits dealt
+// to the thread groups a slab leaves, 8 loads in flight a thread: 13 tiles 54 -> XX us, ResNet-50's 64-row tiles 79 -> XX us.
+// Few splits stream at the memory's rate and keep slabs of 32 rows, whose mirror image is written in 128-byte pieces.
+template <int B, int ROWS>
+__device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int slab, int tm, int tn, float *T, floatx4 *sums)
 {
     const bool diag_tile = (P.flags & GEMM_SYM) && tm == tn;
-    const float *part = P.partial + (long long)(tile - P.split_from) * P.splits * (B * B) + slab * 32 * B;
-    // 32 * B elements, 4 per thread per pass.  Split q goes into partial sum q % 4 of its element;
-    // the four are combined in a fixed order: as reproducible as one running sum, with the loads
-    // of four splits and all passes in flight at once (the partial tiles are read exactly once)
-    constexpr int PASSES = 32 * B / 1024;
-    floatx4 acc[PASSES][4];
+    const float *part = P.partial + (long long)(tile - P.split_from) * P.splits * (B * B) + slab * ROWS * B;
+    // ROWS * B elements, 4 per thread per pass; where they are fewer than 4 per thread, `groups` groups of threads take every
+    // groups-th split.  A thread's U splits in flight go into U partial sums.
+    constexpr int VECS = ROWS * B / 4, PASSES = VECS >= 256 ? VECS / 256 : 1, GROUPS = VECS >= 256 ? 1 : 256 / VECS;
+    constexpr int U = PASSES > 1 ? 4 : 8;
+    const int group = GROUPS > 1 ? (int)threadIdx.x / VECS : 0, vec = GROUPS > 1 ? (int)threadIdx.x % VECS : (int)threadIdx.x;
+    floatx4 acc[PASSES][U];
 #pragma unroll
     for (int p = 0; p < PASSES; ++p)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[p][k] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int q = 0; q < P.splits; q += 4) {
-        floatx4 v[PASSES][4];
+        for (int k = 0; k < U; ++k) acc[p][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int q = group; q < P.splits; q += U * GROUPS) {
+        floatx4 v[PASSES][U];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < U; ++k)
 #pragma unroll
             for (int p = 0; p < PASSES; ++p) {
                 v[p][k] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (q + k < P.splits)
-                    v[p][k] = __builtin_nontemporal_load((const floatx4 *)(part + (long long)(q + k) * (B * B) + threadIdx.x * 4 + p * 1024));
+                if (q + k * GROUPS < P.splits)
+                    v[p][k] = __builtin_nontemporal_load((const floatx4 *)(part + (long long)(q + k * GROUPS) * (B * B) + vec * 4 + p * 1024));
             }
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < U; ++k)
 #pragma unroll
-            for (int p = 0; p < PASSES; ++p)
-                if (q + k < P.splits) acc[p][k] += v[p][k];
+            for (int p = 0; p < PASSES; ++p) acc[p][k] += v[p][k];
     }
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
-        const floatx4 s = (acc[p][0] + acc[p][1]) + (acc[p][2] + acc[p][3]);
-        const int e = threadIdx.x * 4 + p * 1024;
+#pragma unroll
+        for (int d = U / 2; d > 0; d /= 2)
+#pragma unroll
+            for (int k = 0; k < d; ++k) acc[p][k] += acc[p][k + d];
+        floatx4 s = acc[p][0];
+        if constexpr (GROUPS > 1) {
+            sums[threadIdx.x] = s;
+            __syncthreads();
+            if (group == 0)
+#pragma unroll
+                for (int g = 1; g < GROUPS; ++g) s += sums[g * VECS + vec];
+        }
+        const int e = vec * 4 + p * 1024;
         const int r = e / B, c = e - r * B;
         float *t = T + r * (B + 1) + c;
-        t[0] = s[0]; t[1] = s[1]; t[2] = s[2]; t[3] = s[3];
+        if (group == 0) { t[0] = s[0]; t[1] = s[1]; t[2] = s[2]; t[3] = s[3]; }
     }
     __syncthreads();
-    store_slab<32, B>(P, T, tm * B + slab * 32, tn * B, diag_tile, threadIdx.x);
+    store_slab<ROWS, B>(P, T, tm * B + slab * ROWS, tn * B, diag_tile, threadIdx.x);
     if (diag_tile && (P.flags & GEMM_BORDER)) {
-        const int row = tm * B + slab * 32 + threadIdx.x;
-        if (threadIdx.x < 32 && row < P.M) {
-            const float *prs = P.partial_rs + (long long)tm * P.splits * B + slab * 32 + threadIdx.x;
-            float sum = 0.f;
-            for (int q = 0; q < P.splits; ++q) sum += prs[(long long)q * B];
-            store_border(P, row, sum);
+        const int row = tm * B + slab * ROWS + threadIdx.x;
+        if (threadIdx.x < ROWS && row < P.M) {
+            const float *prs = P.partial_rs + (long long)tm * P.splits * B + slab * ROWS + threadIdx.x;
+            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int q = 0; q < P.splits; q += 4)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (q + k < P.splits) sum[k] += prs[(long long)(q + k) * B];
+            store_border(P, row, (sum[0] + sum[1]) + (sum[2] + sum[3]));
         }
         if (tile == 0 && slab == 0 && threadIdx.x == 0) store_corner(P);
     }
@@ -1594,23 +1610,27 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmProblem *__r
                                                           const int *__restrict__ red_start, int n_probs)
 {
     __shared__ float T[32 * 129];
+    __shared__ floatx4 sums[256];
     const int wg = blockIdx.x;
     const int pi = find_problem(red_start, n_probs, wg);
     const GemmProblem &P = probs[pi];
     if (P.splits <= 1) return;
     const int B = (P.tile_cfg == 0) ? 128 : 64;
-    const int slabs = B / 32;
+    const int rows = red_rows(P.splits), slabs = B / rows;
     const int local = wg - red_start[pi];
     const int tile = P.split_from + local / slabs;
     const int slab = local % slabs;
     int tm, tn;
     decode_tile(P, tile, tm, tn);
-    if (tm * B + slab * 32 >= P.M) return;
-    if (B == 128) reduce_slab<128>(P, tile, slab, tm, tn, T);
-    else          reduce_slab<64>(P, tile, slab, tm, tn, T);
+    if (tm * B + slab * rows >= P.M) return;
+    if (rows == 32) {
+        if (B == 128) reduce_slab<128, 32>(P, tile, slab, tm, tn, T, sums);
+        else          reduce_slab<64, 32>(P, tile, slab, tm, tn, T, sums);
+    } else {
+        if (B == 128) reduce_slab<128, 8>(P, tile, slab, tm, tn, T, sums);
+        else          reduce_slab<64, 8>(P, tile, slab, tm, tn, T, sums);
+    }
 }
-
-// LDS per workgroup: two operand stages, reused for the (BM x BN+1) fp32 output tile.
 
 template <int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(const GemmProblem *__restrict__ probs,

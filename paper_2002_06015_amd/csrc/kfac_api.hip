@@ -305,7 +305,7 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
     for (size_t i = 0; i < sel.size(); ++i) {
         const GemmProblem &P = sel[i];
         start[i + 1] = start[i] + (P.split_from + (P.n_tiles - P.split_from) * P.splits + align - 1) / align * align;
-        rstart[i + 1] = rstart[i] + (P.splits > 1 ? (P.n_tiles - P.split_from) * (B / 32) : 0);
+        rstart[i + 1] = rstart[i] + (P.splits > 1 ? (P.n_tiles - P.split_from) * (B / red_rows(P.splits)) : 0);
         any_split |= P.splits > 1;
     }
     Launch L{};
@@ -344,9 +344,9 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
 {
     if (probs.empty()) return;
     // Tile configuration per problem.  When the phase as a whole keeps the GPU busy with 128x128
-    // tiles, each problem takes the configuration with less padded work (the big tile moves half the
-    // operand bytes per flop, worth ~15 %; 256 x 256, symmetric, is 3 big tiles or 10 small ones, 1.2x:
-    // it costs the same either way); otherwise the latency model decides.
+    // tiles, each problem takes the big tile unless that is more than 1.5x the work (it moves half the operand
+    // bytes per flop and runs at 183 TFLOP/s against 113, bf16 at 490 to 620 against 200 to 310; 256 x 256, symmetric, is
+    // 3 big tiles or 10 small ones, 1.2x; a 64-row problem 4x); otherwise the latency model decides.
     double tile_steps128 = 0;   // 128x128 tiles times 32-wide K steps: the work of the phase
     for (auto &P : probs) {
         const double tm = (P.M + 127) / 128, tn = (P.N + 127) / 128;
@@ -361,7 +361,7 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
                 const double tm = (P.M + B - 1) / B, tn = (P.N + B - 1) / B;
                 return (sym ? tm * (tm + 1) / 2 : tm * tn) * B * B;
             };
-            P.tile_cfg = work(128) <= 1.15 * work(64) ? 0 : 1;
+            P.tile_cfg = work(128) <= 1.5 * work(64) ? 0 : 1;
         } else {
             P.tile_cfg = choose_tile_cfg(P.M, P.N, P.K, sym);
         }

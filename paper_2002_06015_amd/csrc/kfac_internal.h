@@ -61,6 +61,9 @@ struct GemmProblem {
     float alpha, beta;        // C = alpha * acc + beta * C   (beta == 0: C is not read)
 };
 
+// Rows of a partial tile that one workgroup of the reduction sums up.
+__host__ __device__ inline int red_rows(int splits) { return splits > 8 ? 8 : 32; }
+
 // ---- patch extraction ------------------------------------------------------------
 struct PatchJob {
     const void *src;  // [N, c_in, h_in, w_in]
