@@ -1156,16 +1156,18 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
     int max_level = -1;
     for (auto &op : ops) max_level = std::max(max_level, op.level);
     for (int lv = 0; lv <= max_level; ++lv) {
-        for (int c = 0; c < kNumLeafClasses; ++c) {
-            std::vector<LeafJob> lj;
-            for (auto &op : ops)
-                if (op.level == lv && op.kind == OP_LEAF && leaf_class(op.leaf.n) == c) lj.push_back(op.leaf);
-            if (lj.empty()) continue;
+        // One launch per level, by the kernel of its largest leaf and the largest first: a leaf is a serial chain on one compute
+        // unit, and one launch per size class ran chains of 21, 34 and 41 us one after the other that fit beside each other.
+        std::vector<LeafJob> lj;
+        for (auto &op : ops)
+            if (op.level == lv && op.kind == OP_LEAF) lj.push_back(op.leaf);
+        if (!lj.empty()) {
+            std::stable_sort(lj.begin(), lj.end(), [](const LeafJob &x, const LeafJob &y) { return x.n > y.n; });
             Launch Lf{};
             Lf.kind = L_LEAF;
             Lf.off_a = plan.tab.add(lj.data(), lj.size() * sizeof(LeafJob));
             Lf.n = (int)lj.size();
-            Lf.cfg = c;
+            Lf.cfg = leaf_class(lj.front().n);
             Lf.p0 = damp;
             Lf.p1 = info;
             plan.launches.push_back(Lf);

@@ -55,3 +55,25 @@ def test_first_non_positive_pivot(n, bad):
     x[bad, bad] = -1.0
     _, _, _, info = _invert(x, np.eye(4, dtype=np.float32), 0.0)
     assert info == [bad + 1, 0]
+
+
+def test_leaves_of_all_sizes_in_one_call():
+    """One launch takes the leaves of all sizes: the same bits as a call per size."""
+    X = {}
+    for n in SIZES:
+        rng = np.random.default_rng(n)
+        b = rng.standard_normal((2 * n + 8, n))
+        x = (b.T @ b / len(b)).astype(np.float32)
+        X[n] = np.ascontiguousarray((x + x.T) / np.float32(2))
+    layers = [wl.fc_layer(4, n, n, 0) for n in SIZES]
+    ctx = kfac.Context(layers)
+    A = [torch.from_numpy(X[n]).cuda() for n in SIZES]
+    Ai, Gi = [torch.zeros_like(a) for a in A], [torch.zeros_like(a) for a in A]
+    pi, info = torch.zeros(len(SIZES), device="cuda"), torch.full((2 * len(SIZES),), -1, dtype=torch.int32, device="cuda")
+    kfac.kfac_invert(ctx, layers, A, A, 1e-3, Ai, Gi, pi, info)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert not info.any()
+    for q, n in enumerate(SIZES):
+        one = _invert(X[n], X[n], 1e-3)
+        assert np.array_equal(Ai[q].cpu().numpy(), one[0]) and np.array_equal(Gi[q].cpu().numpy(), one[1]), n
