@@ -2084,7 +2084,7 @@ kfac_status bn_unitwise_precondition(kfac_ctx *ctx, int32_t n_layers, int32_t N,
         J.F_ema = F_ema[l]; J.out_gamma = out_gamma[l]; J.out_beta = out_beta[l];
         J.C = C[l];
         J.wg_start = wgs;
-        wgs += (C[l] + 255) / 256;
+        wgs += (C[l] + 63) / 64;
         jobs.push_back(J);
     }
     Plan plan; Arena arena(ctx->ws);
@@ -2272,7 +2272,7 @@ static kfac_status bn_reduce_call(int nhwc, kfac_ctx *ctx, int32_t n_layers, int
     if (!ctx || n_layers < 1 || n_layers > 65536 || N < 1 || !C || !HW) return KFAC_ERR_INVALID;
     if (!dy || !xhat || !g_gamma || !g_beta) return KFAC_ERR_INVALID;
     std::vector<BnReduceJob> jobs;
-    long long wgs = 0;
+    long long wgs = 0, size = 0;
     for (int l = 0; l < n_layers; ++l) {
         if (C[l] < 1 || C[l] > (1 << 24) || HW[l] < 1 || HW[l] > (1 << 24)) return KFAC_ERR_INVALID;
         if (!dy[l] || !xhat[l] || !g_gamma[l] || !g_beta[l]) return KFAC_ERR_INVALID;
@@ -2280,8 +2280,9 @@ static kfac_status bn_reduce_call(int nhwc, kfac_ctx *ctx, int32_t n_layers, int
         J.dy = dy[l]; J.xhat = xhat[l]; J.g_gamma = g_gamma[l]; J.g_beta = g_beta[l];
         J.C = C[l]; J.HW = HW[l];
         J.wg_start = (int)wgs;
-        wgs += nhwc ? (long long)N * ((C[l] + 63) / 64) : ((long long)N * C[l] + 3) / 4;
-        if (wgs > (1LL << 30)) return KFAC_ERR_INVALID;
+        wgs += nhwc ? (long long)N * ((C[l] + 63) / 64) : ((long long)N * C[l] + bn_rows(HW[l]) - 1) / bn_rows(HW[l]);
+        size += nhwc ? (long long)N * ((C[l] + 63) / 64) : ((long long)N * C[l] + 3) / 4;
+        if (size > (1LL << 30)) return KFAC_ERR_INVALID;
         jobs.push_back(J);
     }
     Plan plan; Arena arena(ctx->ws);

@@ -187,8 +187,9 @@ struct BnReduceJob {
     const float *dy, *xhat;
     float *g_gamma, *g_beta;
     int C, HW;
-    int wg_start;   // NCHW: one wave per (n, c) row, 4 rows per workgroup; NHWC: one workgroup per sample and 64 channels
+    int wg_start;   // NCHW: bn_rows(HW) rows (n, c) per workgroup; NHWC: one workgroup per sample and 64 channels
 };
+__host__ __device__ inline int bn_rows(int HW) { return HW <= 64 ? 64 : HW <= 128 ? 32 : HW <= 256 ? 16 : 4; }
 
 // One tensor [N, HW, C] -> [N, C, HW] (NHWC -> NCHW).
 struct LayoutJob {
@@ -298,7 +299,7 @@ hipError_t launch_update(const UpdateJob *jobs_dev, int n_jobs, int total_wgs, i
                          float eps, hipStream_t s);
 hipError_t launch_staleness(const StaleJob *jobs_dev, int n_jobs, int total_wgs, int pass, hipStream_t s);
 
-// leaf size classes: a class value B serves n <= 32*B (one launch per class and level)
+// leaf size classes: the kernel of class value B serves n <= 32*B
 static const int kLeafClasses[] = {5, 7, 9};
 static const int kNumLeafClasses = 3;
 static const int kLeafMax = 288;
