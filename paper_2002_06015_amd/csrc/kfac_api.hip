@@ -583,7 +583,10 @@ struct StatsArgs {
 int patch_job_wgs(const PatchJob &J)
 {
     const int hw = J.h * J.w;
-    if (J.flat) return J.c_in * ((J.N * hw + 255) / 256);
+    if (J.flat) {   // 16 bytes per thread, rows packed into workgroups (patch_flat)
+        const int v = 16 / J.esize;
+        return (int)(((long long)J.c_in * ((J.N * hw + v - 1) / v) + 255) / 256);
+    }
     return ((J.N * J.c_in + 3) / 4) * ((hw + 1023) / 1024);
 }
 

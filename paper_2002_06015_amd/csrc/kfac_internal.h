@@ -71,7 +71,7 @@ struct PatchJob {
     long long ld;
     int N, c_in, k, stride, pad, h_in, w_in, h, w;
     int esize;        // 4 (f32) or 2 (bf16)
-    int flat;         // 1: k == 1, stride 1, no padding, tiny planes: one thread per output element
+    int flat;         // 1: k == 1, stride 1, no padding, tiny planes: one thread per 16 bytes of the output
     unsigned magic_w; // floor(2^32 / w) + 1: t / w == mulhi(t, magic_w) for t, w < 2^16
     int wg_start;     // first workgroup of this job in the grouped launch
 };
