@@ -215,9 +215,10 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s)
 //     as the fragments its readers load (three planes, 16 bytes a lane: form F), a tile with v = k as [k][row] rows that
 //     are read with the transposing LDS read (form T); no 2-byte stores.  The panels of two steps alternate.
 // n = 288: 49 us (77 us with two barriers per step, P and R through LDS and the sweep between the products of its
-// wavefront); 224: 34 (51), 160: 20.5 (31), 64: 9 (15).  In-kernel times at n = 288: the chain needs about 7400 cycles a
-// block (sweep 3700 to 3900, D into planes 850, operand reads 320, P 500, update 1250), the other wavefronts 10700, most
-// of it the 192 matrix instructions of a SIMD (6100 cycles) and the conversions around them.  Loads and stores: 6 us.
+// wavefront); 224: 33 (51), 160: 20.5 (31), 64: 8.5 (15).  In-kernel times at n = 288, cycles a block: the chain 8800 to 9700
+// (sweep 3500 alone on its SIMD, 6000 to 7300 beside the others; D into planes 900, operand reads 300, P and update 1300), the
+// other wavefronts up to 10900, most of it the 192 matrix instructions of a SIMD (6100) and the conversions around them.
+// Loads and stores: 6 us.
 //
 // Products are in the three-plane mode (x = h + m + l exactly, see split_pair; six bf16 matrix instructions per
 // 16-wide step, fp32 accumulation).
@@ -362,83 +363,65 @@ __device__ __forceinline__ lb_floatx16 lb_plain_rows(const lb_floatx16 &t)
     return o;
 }
 
-// The eight k slots of a half-wave as the product of one fp32 value per lane with another: h h' + h m' + m h' + m m' +
-// h l' + l h' + m l' + l m' (all but l l', 2^-32 of the product).
-__device__ __forceinline__ lb_bf16x8 lb_terms_a(float a)
-{
-    const unsigned hb = __float_as_uint(a);
-    const float r = a - __uint_as_float(hb & 0xFFFF0000u);
-    const unsigned mb = __float_as_uint(r);
-    const unsigned lb = __float_as_uint(r - __uint_as_float(mb & 0xFFFF0000u));
-    return __builtin_bit_cast(lb_bf16x8, uint4{__builtin_amdgcn_perm(hb, hb, 0x07060302u), __builtin_amdgcn_perm(mb, mb, 0x07060302u),
-                                               __builtin_amdgcn_perm(lb, hb, 0x07060302u), __builtin_amdgcn_perm(lb, mb, 0x07060302u)});
-}
-__device__ __forceinline__ lb_bf16x8 lb_terms_b(float b)
-{
-    const unsigned hb = __float_as_uint(b);
-    const float r = b - __uint_as_float(hb & 0xFFFF0000u);
-    const unsigned mb = __float_as_uint(r);
-    const unsigned lb = __float_as_uint(r - __uint_as_float(mb & 0xFFFF0000u));
-    const unsigned hm = __builtin_amdgcn_perm(mb, hb, 0x07060302u);
-    return __builtin_bit_cast(lb_bf16x8, uint4{hm, hm, __builtin_amdgcn_perm(hb, lb, 0x07060302u), __builtin_amdgcn_perm(mb, lb, 0x07060302u)});
-}
-
 // Scalar sweep of a 32x32 diagonal tile N (symmetric, negative definite, unit-diagonal scale) inside one wavefront, on the
-// matrix core, two pivots per instruction: register v holds both pivot rows, one in each half-wave, and a half-wave is
-// eight k slots of the instruction, which hold the terms of its pivot's rank-1 update.  With the pivots' block
-// [[a, b], [b, c]], its negated inverse Q and the rows x0, x1 of the tile as it stands, y = Q x, the update
-// N += a0 b0^T + a1 b1^T with
-//     a_i = y_i,  b_j = x_j   outside the pivots, and at them   a0 = (Q00 - 1, Q01), a1 = (Q01, Q11 - 1),
-//     b0 = (1 + a, b), b1 = (b, 1 + c)
-// adds x^T Q x, leaves the rows and columns of the pivots as Q x and the block itself as Q - 2 I.  (Pivots lie in [-1, 0):
-// the patches are sums of equal-signed terms.)  No later pivot reads the block (pivot q reads row q only, and adds to it),
-// so the 2 is put back once, at the end.
-// The patched rows b0, b1 give the patched a0, a1 by the same formula as all others: with r = -1 / det the first half-wave
-// has a0_i = r (c b0_i - b b1_i), which is r c - 1 and -r b at the two pivots.
-// What bounds it is the issue of one wavefront: about 45 instructions for two pivots.  The chain from one pair to the
-// next does not go through the matrix instruction (the next pair's rows are brought up to date with fmas from the tile as
-// it was before) and meets the reciprocal of the determinant in its last fma only.
+// matrix core, two pivots per instruction: register v holds both pivot rows, one in each half-wave, and a half-wave is one
+// k slot of the fp32 instruction, which takes its pivot's rank-1 update.  The pivots are eliminated one after the other:
+// with x0, x1 their rows in the tile as it stands and a = x0[0], b = x0[1] = x1[0], c = x1[1] (index: the pivot),
+//     q0 = -1 / a,  u0 = x0 with 1 + a at the first pivot,
+//     d1 = c + q0 b b (the second pivot after the first one),  q1 = -1 / d1,
+//     u1 = (x1 with 1 + c at the second pivot) + q0 b u0,
+// and N += q0 u0 u0^T + q1 u1 u1^T.  That adds the two terms of the elimination, leaves the rows and columns of the pivots
+// as those of the swept tile and their block as Q - 2 I, Q = -[[a, b], [b, c]]^-1.  (Pivots lie in [-1, 0): the patches are
+// sums of equal-signed terms.)  No later pivot reads the block (pivot q reads row q only, and adds to it), so the 2 is put
+// back once, at the end.
+// u1 has to be formed before it is used: it is small where the rows are nearly parallel (neighbouring taps of a patch), so
+// that q1 = O(1 / d1) meets a small vector only.  Solving the pair by its determinant and adding terms in the full rows is
+// the same in exact arithmetic and one reciprocal shorter, but its rounding errors are 2^-24 / d1 instead of 2^-24: pairs
+// correlated by 0.9995 (0.99995) came out 12 (150) times less accurate, and by 0.99999 as not positive definite.
+// What bounds it is the issue of one wavefront, 28 vector instructions for two pivots.  The chain from one pair to the next
+// (two dependent reciprocals) does not go through the matrix instruction of its own pair: the next rows are brought up to
+// date with fmas from the tile as it was before.  The products in one fp32 instruction (64 cycles) are exact; as eight bf16
+// terms of their planes (32 cycles, 14 instructions to make them) they cost 23.6 us at n = 160 instead of 22.8.
 // On return the tile is (-N)^-1.  Returns the 1-based index of the first non-positive pivot of -N, or 0.
 __device__ __forceinline__ int leaf_chain_sweep(lb_floatx16 &t, int lane)
 {
     const int z = (lane & 31) - 4 * (lane >> 5);
     const bool h = lane >= 32;
-    float pa[16], pd[16], worst = 1.f;              // the pivots (first one and determinant of each pair)
+    float pa[16], pd[16], worst = -1.f;             // the pivots
     float x = t[0];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int p = 8 * (v >> 2) + (v & 3);       // tile row of the first pivot; the second one is p + 4
         const float a = lb_readlane(x, p), b = lb_readlane(x, p + 4), c = lb_readlane(x, p + 36);
-        const float det = fmaf(a, c, -(b * b));
-        const float r = -__builtin_amdgcn_rcpf(det);
-        const float fb = z == p ? x + 1.f : x;
-        // b0 and b1 in both half-waves (swap(x, y) exchanges the upper half of x with the lower half of y)
-        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(fb), __float_as_uint(fb), false, false);
-        const float b0 = __uint_as_float(s[0]), b1 = __uint_as_float(s[1]);
-        const float g0 = fmaf(c, b0, -(b * b1)), g1 = fmaf(a, b1, -(b * b0));
-        const float g = h ? g1 : g0;
+        const float q0 = -__builtin_amdgcn_rcpf(a), m = q0 * b;
+        const float d1 = fmaf(m, b, c), q1 = -__builtin_amdgcn_rcpf(d1);
+        const float y = z == p ? x + 1.f : x;
+        // both patched rows in both half-waves (swap(x, y) exchanges the upper half of x with the lower half of y)
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+        const float u0 = __uint_as_float(s[0]), u1 = fmaf(m, u0, __uint_as_float(s[1]));
+        const float fb = h ? u1 : u0;
+        const float fa = (h ? q1 : q0) * fb;
         float next = 0.f;
         if (v + 1 < 16) {
             const int q = 8 * ((v + 1) >> 2) + ((v + 1) & 3);
-            const float w0 = fmaf(lb_readlane(g, q + 32), b1, lb_readlane(g, q) * b0);
-            const float w1 = fmaf(lb_readlane(g, q + 36), b1, lb_readlane(g, q + 4) * b0);
-            next = fmaf(r, h ? w1 : w0, t[v + 1]);
+            const float n0 = fmaf(lb_readlane(fa, q + 32), u1, fmaf(lb_readlane(fa, q), u0, t[v + 1]));
+            const float n1 = fmaf(lb_readlane(fa, q + 36), u1, fmaf(lb_readlane(fa, q + 4), u0, t[v + 1]));
+            next = h ? n1 : n0;
         }
-        const float fa = r * g;
         pa[v] = a;
-        pd[v] = det;
-        worst = fminf(fminf(worst, -a), det);
-        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lb_terms_a(fa), lb_terms_b(fb), t, 0, 0, 0);
+        pd[v] = d1;
+        worst = fmaxf(fmaxf(worst, a), d1);
+        t = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb, t, 0, 0, 0);
         x = next;
     }
     // register v holds the diagonal element of its lane where z is 8 (v / 4) + v % 4
 #pragma unroll
     for (int v = 0; v < 16; ++v) t[v] += z == 8 * (v >> 2) + (v & 3) ? 2.f : 0.f;
-    // (a NaN anywhere has reached the last determinant)
-    if (__builtin_amdgcn_readfirstlane((int)(worst > 0.f && pd[15] > 0.f))) return 0;
+    // (a NaN anywhere has reached the last pivot)
+    if (__builtin_amdgcn_readfirstlane((int)(worst < 0.f && pd[15] < 0.f))) return 0;
     int first = 0;
 #pragma unroll
-    for (int v = 15; v >= 0; --v) first = !(pa[v] < 0.f) ? 2 * v + 1 : !(pd[v] > 0.f) ? 2 * v + 2 : first;
+    for (int v = 15; v >= 0; --v) first = !(pa[v] < 0.f) ? 2 * v + 1 : !(pd[v] < 0.f) ? 2 * v + 2 : first;
     return first;
 }
 

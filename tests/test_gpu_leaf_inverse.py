@@ -57,6 +57,56 @@ def test_first_non_positive_pivot(n, bad):
     assert info == [bad + 1, 0]
 
 
+def _parallel_pairs(rng, n, rho):
+    """Second moments of variables whose neighbours 2 m and 2 m + 1 are correlated by rho."""
+    x = rng.standard_normal((4 * n, n))
+    second = x[:, 1::2]
+    second[:] = rho * x[:, 0:2 * (n // 2):2] + np.sqrt(1 - rho * rho) * second
+    return x.T @ x / len(x)
+
+
+def _smooth_patches(rng, channels, k, damp):
+    """Second moments of the k x k patches of smooth images."""
+    hw, f = 28, np.fft.fftfreq(28)
+    cols = []
+    for _ in range(8):
+        spectrum = np.fft.fft2(rng.standard_normal((channels, hw, hw))) / (0.002 + f[:, None] ** 2 + f[None, :] ** 2)
+        image = np.fft.ifft2(spectrum).real
+        image = np.maximum(image / image.std(), 0.0)
+        image = np.pad(image, ((0, 0), (k // 2, k // 2), (k // 2, k // 2)))
+        cols.append([image[c, y:y + hw, x:x + hw].ravel() for c in range(channels) for y in range(k) for x in range(k)])
+    m = np.concatenate(cols, axis=1)
+    return m @ m.T / m.shape[1] + damp * np.eye(len(m))
+
+
+# one tile (whole and with a remainder); several; all of a leaf; leaves behind products (577: 288 and 289, which is 160 and 129)
+@pytest.mark.parametrize("kind,n,value", [("pairs", n, rho) for n in (31, 32) for rho in (0.995, 0.9995, 0.99995)] +
+                         [("pairs", n, 0.995) for n in (70, 288, 577)] + [("chain", 32, 0.9999), ("patches", (3, 7), 1e-2),
+                          ("patches", (3, 7), 1e-3), ("patches", (32, 3), 1e-2), ("patches", (50, 3), 1e-3)])
+def test_correlated_neighbours(kind, n, value):
+    """Neighbouring taps of a patch (and gamma_i, beta_i of a BatchNorm layer) are strongly correlated variables: the rows
+    of two successive pivots are nearly parallel, and the second pivot is small beside the first."""
+    rng = np.random.default_rng(7)
+    if kind == "pairs":
+        x = _parallel_pairs(rng, n, value)
+    elif kind == "chain":
+        x = value ** np.abs(np.arange(n)[:, None] - np.arange(n)[None, :])
+    else:
+        x = _smooth_patches(rng, n[0], n[1], value)
+    x = x.astype(np.float32)
+    x = np.ascontiguousarray((x + x.T) / np.float32(2))
+    got, _, _, info = _invert(x, np.eye(4, dtype=np.float32), 0.0)
+    assert info == [0, 0]
+    d = x.astype(np.float64)
+    s = 1 / np.sqrt(np.diag(d))
+    kappa = np.linalg.cond(d * s[:, None] * s[None, :])
+    scaled = (1 / s)[:, None] * (1 / s)[None, :]
+    ref = np.linalg.inv(d) * scaled
+    # An elimination in fp32 that takes the pivots one after the other stays below 1.1 kappa 2^-24 of the largest element on
+    # one tile (30 draws of every rho), and below 2.1 on these larger ones, whose products carry 2^-23 each: twice the latter.
+    assert np.abs(got * scaled - ref).max() <= 4 * kappa * 2.0 ** -24 * np.abs(ref).max()
+
+
 def test_leaves_of_all_sizes_in_one_call():
     """One launch takes the leaves of all sizes: the same bits as a call per size."""
     X = {}
