@@ -515,7 +515,9 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
         const size_t fit = std::stable_partition(by_fit.begin(), by_fit.end(), [](const Shape &q) { return 4.0 * q.tiles[0] <= 1.5 * q.tiles[1]; }) - by_fit.begin();
         if (fit > 0 && fit < by_fit.size()) consider(by_fit.data(), by_fit.data() + fit, by_fit.data() + by_fit.size());
     }
+    const size_t mark = arena.used;
     for (int q = 0; q < 2; ++q) {
+        arena.release_to(mark);   // the second launch starts when the reduction of the first one is done
         std::vector<GemmProblem> sel;
         long long n = 0;
         for (const Shape *t = q ? cut : first; t != (q ? last : cut); ++t) {
@@ -541,7 +543,7 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
     }
 }
 
-// Upper bound of the scratch of one such phase on matrices with n rows each.
+// Upper bound of the scratch of one such phase on matrices with n rows each (its launches share it).
 size_t max_tail_bytes(const std::vector<int> &n)
 {
     double tiles = 0, parts = 1;

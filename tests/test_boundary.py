@@ -55,6 +55,17 @@ def test_workspace_bytes():
     assert kfac.kfac_workspace_bytes(wl.config_layers(2), kfac.KFAC_BF16) >= 576 * 100352 * 2
 
 
+def test_scratch_of_two_launches_with_split_tails():
+    """Products of two contraction lengths go out as two launches, each with a tail that is split into at most 1024 parts of
+    128 x 128 sums: the second launch takes the scratch of the first one, as the bound in kfac_workspace_bytes counts."""
+    layers = [wl.fc_layer(1, 8608, 354, 0)] + [wl.fc_layer(1, 8464, 926, 0)] * 6
+    intermediate = sum(4 * L.dA * (-(-L.dG // 4) * 4) for L in layers)
+    need = kfac.kfac_step_workspace_bytes(layers, kfac.KFAC_F32, [0] * len(layers))
+    assert need - intermediate <= 1024 * 128 * 128 * 4 + (64 << 10)      # tables and alignment: a few KB
+    assert need - intermediate > 512 * 128 * 128 * 4                     # there are tails
+
+
+
 def _fake_ctx(nbytes=1 << 20):
     """A context on a made-up (aligned, never dereferenced) workspace address: enough to
     exercise validation, which must fail before any GPU call."""
