@@ -421,7 +421,11 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
 //   64-tile, staged / direct: latency of one workgroup (the direct one halves it: its wavefronts split K), then
 //     100 to 120 TFLOP/s.
 //   32-tile, direct: a quarter of the latency again and half the rate.
-struct PhaseCost { double us; int cfg, tail_parts; };
+struct PhaseCost {
+    double us;
+    int cfg;
+    int round, parts;                               // the last (tiles % round) tiles of the launch are split into `parts` (1: none; round 0: all)
+};
 struct Shape {                                      // what the estimate knows of a product
     double tiles[4], K, steps;                      // tiles per configuration, contraction length, K steps of 32
     const GemmProblem *P;
@@ -451,34 +455,78 @@ PhaseCost cost_128(const Shape *first, const Shape *last)
         return (3.0 * full + slope) * steps;
     };
     const double head = 11.0 + 3.0 * (work - tail_work) / kSlots128;
-    PhaseCost best{head + (r > 0 ? round(r, tail_work / r) : 0.0), 0, 1};
+    PhaseCost best{head + (r > 0 ? round(r, tail_work / r) : 0.0), 0, kSlots128, 1};
     for (int s = 2; s <= kMaxTailParts && r > 0 && r * s <= kMaxTailWgs && (last - 1)->steps >= 4.0 * s; ++s) {
         const double us = head + round(r * s, tail_work / r / s + 1.5) + 9.0 + 0.03 * r * s;
-        if (us < best.us) best = {us, 0, s};
+        if (us < best.us) best = {us, 0, kSlots128, s};
+    }
+    return best;
+}
+
+// Parts of a contraction of `steps` K steps where a launch asks for s.
+int parts_of(double steps, int s) { return std::max(1, std::min(s, (int)steps / 4)); }
+
+// With the fp32 matrix instruction two 128-tile workgroups on a compute unit take as long as one after the other (2.05 us a
+// step each: 256, 512 and 768 equal tiles of 32 steps take 75, 142 and 206 us), so a round is 256 workgroups; 64-tiles take
+// 0.6 us a step each and 0.77 alone.  There is no direct kernel for it: long products of few tiles are split instead
+// (1501 x 77 x 1501: 16 + 6 us in four parts of 64-tiles, 42 whole; 4096 x 10 x 4096: 23 + 8, 99 whole).
+PhaseCost best_kernel_fp32(const Tunables &tun, const Shape *first, const Shape *last)
+{
+    constexpr int kRound = 256;
+    double n[2] = {0, 0}, work[2] = {0, 0};
+    for (const Shape *q = first; q != last; ++q)
+        for (int c = 0; c < 2; ++c) { n[c] += q->tiles[c]; work[c] += q->tiles[c] * q->steps; }
+    PhaseCost best{1e300, 0, 0, 1};
+    auto take = [&](const PhaseCost &x) { if (x.us < best.us) best = x; };
+    for (int s = 1; s <= kMaxTailParts && tun.force_tile != 128; ++s) {
+        double parts = 0, longest = 0;
+        for (const Shape *q = first; q != last; ++q) {
+            const int p = parts_of(q->steps, s);
+            parts += q->tiles[1] * p;
+            longest = std::max(longest, q->steps / p);
+        }
+        if (s > 1 && (parts == n[1] || parts > 4 * kMaxTailWgs)) break;
+        take({6.0 + std::max(0.77 * longest, 0.6 * std::ceil(parts / kRound) * (work[1] / parts + 1.5)) + (s > 1 ? 6.0 + 0.0045 * parts : 0.0), 1, 0, s});
+    }
+    if (tun.force_tile == 64) return best;
+    // whole tiles, then either those beyond whole rounds or all of them in parts
+    for (int round : {kRound, 0}) {
+        const double r = round ? n[0] - kRound * std::floor(n[0] / kRound) : n[0];
+        double tail_work = 0, left = r, longest = 0;
+        for (const Shape *q = last; q != first && left > 0;) {
+            --q;
+            const double c = std::min(left, q->tiles[0]);
+            tail_work += c * q->steps;
+            longest = q->steps;
+            left -= c;
+        }
+        const double head = 11.0 + 2.05 * (r < n[0] ? std::max((work[0] - tail_work) / kRound, first->steps) : 0.0);
+        if (round) take({head + 2.05 * longest, 0, round, 1});
+        for (int s = 2; s <= kMaxTailParts && r > 0 && r * s <= kMaxTailWgs && (last - 1)->steps >= 4.0 * s; ++s)
+            take({head + 2.05 * std::max(longest / s + 1.5, std::ceil(r * s / kRound) * (tail_work / r / s + 1.5)) + 6.0 + 0.02 * r * s, 0, round, s});
     }
     return best;
 }
 
 PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last)
 {
+    if (!tun.split) return best_kernel_fp32(tun, first, last);
     double nk[4] = {0, 0, 0, 0}, n64 = 0;
     for (const Shape *q = first; q != last; ++q) {
         for (int c = 1; c < 4; ++c) nk[c] += q->tiles[c] * q->K;
         n64 += q->tiles[1];
     }
     const double kmax = first->K;
-    const PhaseCost c64{6.0 + std::max(0.0265 * kmax, 0.0065 * kmax + 6.45e-5 * nk[1]), 1, 1};
+    const PhaseCost c64{6.0 + std::max(0.0265 * kmax, 0.0065 * kmax + 6.45e-5 * nk[1]), 1, 0, 1};
     if (tun.force_tile == 64) return c64;
     PhaseCost best = cost_128(first, last);
     if (tun.force_tile == 128) return best;
     if (c64.us < best.us) best = c64;
-    if (tun.split) {
-        const PhaseCost d32{5.0 + std::max(0.0066 * kmax, 3.65e-5 * nk[2]), 2, 1};
-        const double per_cu = n64 / 256;
-        const PhaseCost d64{8.0 + std::max((per_cu <= 1 ? 0.013 + 0.006 * per_cu : 0.034) * kmax, 0.0035 * kmax + 6.45e-5 * nk[3]), 3, 1};
-        if (d32.us < best.us) best = d32;
-        if (d64.us < best.us) best = d64;
-    }
+    const PhaseCost d32{5.0 + std::max(0.0066 * kmax, 3.65e-5 * nk[2]), 2, 0, 1};
+    const double per_cu = n64 / 256;
+    const PhaseCost d64{8.0 + std::max((per_cu <= 1 ? 0.013 + 0.006 * per_cu : 0.034) * kmax, 0.0035 * kmax + 6.45e-5 * nk[3]), 3, 0, 1};
+    if (d32.us < best.us) best = d32;
+    if (d64.us < best.us) best = d64;
     return best;
 }
 
@@ -499,7 +547,7 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
     }
     std::stable_sort(all.begin(), all.end(), [](const Shape &x, const Shape &y) { return x.K > y.K; });
     const Shape *first = all.data(), *last = first + all.size(), *cut = last;
-    PhaseCost cost[2] = {best_kernel(tun, first, last), {0, 0, 1}};
+    PhaseCost cost[2] = {best_kernel(tun, first, last), {0, 0, 0, 1}};
     auto consider = [&](const Shape *a, const Shape *b, const Shape *c) {   // [a, b) in one launch, [b, c) in another
         const PhaseCost x = best_kernel(tun, a, b), y = best_kernel(tun, b, c);
         if (x.us + y.us >= cost[0].us + cost[1].us) return;
@@ -526,24 +574,26 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
             finish_problem(sel.back());
             n += sel.back().n_tiles;
         }
-        const int s = cost[q].tail_parts;
-        long long left = s > 1 ? n % kSlots128 : 0;   // the last tiles of the launch, those beyond whole rounds
+        const int s = cost[q].parts, B = tile_edge(cost[q].cfg);
+        long long left = s == 1 ? 0 : cost[q].round ? n % cost[q].round : n;   // the last tiles of the launch, those beyond whole rounds
         for (size_t i = sel.size(); i-- > 0 && left > 0;) {
             GemmProblem &P = sel[i];
             const int split_tiles = (int)std::min<long long>(left, P.n_tiles);
             left -= split_tiles;
-            P.k_per_split = ((P.K + s - 1) / s + 31) / 32 * 32;
+            const int parts = parts_of((P.K + 31) / 32, s);
+            P.k_per_split = ((P.K + parts - 1) / parts + 31) / 32 * 32;
             P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
             if (P.splits == 1) continue;
             P.split_from = P.n_tiles - split_tiles;
             if (!tun.worst_case_splits)               // (the workspace bound adds max_tail_bytes instead)
-                P.partial = (float *)arena.take((size_t)split_tiles * P.splits * 128 * 128 * sizeof(float));
+                P.partial = (float *)arena.take((size_t)split_tiles * P.splits * B * B * sizeof(float));
         }
         push_gemm_launch(plan, tun, sel, cost[q].cfg, 0, 1);
     }
 }
 
-// Upper bound of the scratch of one such phase on matrices with n rows each (its launches share it).
+// Upper bound of the scratch of one such phase on matrices with n rows each (its launches share it): tiles of 128 rows, or four
+// of 64 rows in the place of each.
 size_t max_tail_bytes(const std::vector<int> &n)
 {
     double tiles = 0, parts = 1;
