@@ -100,6 +100,10 @@ typedef struct {
     int32_t correlation_form;     /* A factor of 3x3 / stride 1 / pad 1 layers from displaced image correlations; 1 */
     int32_t pipeline_phases;      /* kfac_step: factor phases spread over the streams; 1 */
     int32_t early_n;              /* kfac_step: layers with a factor at least this large are built and inverted first; 2048 */
+    /* The split rule of the products.  While the three limits and force_tile have their defaults it is the factor
+     * contractions' only, and the products of the inversion and the preconditioning are priced launch by launch (kernel,
+     * tile, parts); with other values it holds for all of them.  Not for bn_full_precondition, whose workspace is sized
+     * without options: there only force_tile acts, and without splits beyond the default's. */
     int32_t target_workgroups;    /* split along K until a product has this many workgroups; 128 */
     int32_t min_k_per_split;      /* ... but no part shorter than this; 512 */
     int32_t max_k_per_workgroup;  /* ... and none longer than this; 4096 */

@@ -25,6 +25,8 @@ constexpr size_t kAlign = 256;
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+constexpr int kTargetWgs = 128, kMinKPerSplit = 512, kMaxKPerWg = 4096;   // defaults of the split rule
+
 struct Tunables {
     int target_wgs;      // split-K gives a problem at least this many workgroups (if K allows)
     int min_k_per_split; // never split below this contraction length
@@ -45,6 +47,8 @@ struct Tunables {
                          // (fp32 accuracy at the bf16 unit's rate); 0: the fp32 matrix instruction
     int force_tile;      // 0: the planner chooses; 64 / 128: every product with that tile
     bool worst_case_splits = false;   // set for the workspace bound: every product split as if it were alone in its launch
+    bool chosen_rule;    // a limit of the split rule or the tile was chosen by the caller: the rule holds for every product, the
+                         // inversion's and the preconditioning's, too, which are priced phase by phase otherwise
     int by_depth;        // kfac_invert: layers grouped onto streams by the length of their chains (1) or by total n^3 (0)
     explicit Tunables(const kfac_options &o)
     {
@@ -60,6 +64,7 @@ struct Tunables {
         chunk_gf = std::max(0.0f, o.chunk_gflop);
         split = o.fp32_products == KFAC_PRODUCTS_FP32_MFMA ? 0 : 1;
         force_tile = (o.force_tile == 64 || o.force_tile == 128) ? o.force_tile : 0;
+        chosen_rule = force_tile != 0 || o.target_workgroups != kTargetWgs || o.min_k_per_split != kMinKPerSplit || o.max_k_per_workgroup != kMaxKPerWg;
         by_depth = o.group_by_depth != 0;
     }
 };
@@ -75,9 +80,9 @@ kfac_options default_options()
     o.correlation_form = 1;
     o.pipeline_phases = 1;
     o.early_n = 2048;
-    o.target_workgroups = 128;
-    o.min_k_per_split = 512;
-    o.max_k_per_workgroup = 4096;
+    o.target_workgroups = kTargetWgs;
+    o.min_k_per_split = kMinKPerSplit;
+    o.max_k_per_workgroup = kMaxKPerWg;
     o.recursion_leaf = 288;
     o.chunk_gflop = 48.0f;
     o.force_tile = 0;
@@ -338,7 +343,8 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
     }
 }
 
-// Emits the launches of one phase of factor products: per tile configuration one GEMM launch and its reduction.
+// Emits the launches of one phase by the split rule (factor products; all products where a caller chose the rule): per tile
+// configuration one GEMM launch and its reduction.
 void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<GemmProblem> &probs,
                      int dtype, std::vector<Launch> *deferred)
 {
@@ -367,7 +373,7 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
         }
         finish_problem(P);
     }
-    if (dtype == 0 && tun.split && !tun.force_tile && !tun.worst_case_splits) {   // (no scratch: the workspace bound leaves it out)
+    if (dtype == 0 && tun.split && !tun.chosen_rule && !tun.worst_case_splits) {   // (no scratch: the workspace bound leaves it out)
         const int cfg = choose_direct(probs, tun);
         if (cfg >= 0)
             for (auto &P : probs) { P.tile_cfg = cfg; finish_problem(P); }
@@ -536,6 +542,10 @@ PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last
 void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::vector<GemmProblem> &probs)
 {
     if (probs.empty()) return;
+    if (tun.chosen_rule) {
+        std::vector<GemmProblem> by_rule = probs;
+        return emit_gemm_phase(plan, arena, tun, by_rule, 0, nullptr);
+    }
     std::vector<Shape> all;
     for (auto &P : probs) {
         Shape q{{0, 0, 0, 0}, (double)P.K, std::ceil(P.K / 32.0), &P};
@@ -1864,8 +1874,10 @@ size_t kfac_workspace_bytes_opt(const kfac_layer *L, int32_t n_layers, kfac_dtyp
         // fused step, all layers inverted.  A partial mask moves layers between the factor phases
         // and the inversion groups, which changes tile choices and split-K scratch by a few percent
         // (searching over masks found 10 % above the full mask's plan at most): the sum of the
-        // separate peaks plus a quarter covers that with room; kfac_step_workspace_bytes gives the
-        // exact figure for one mask, and every call checks its own plan before it launches anything
+        // separate peaks plus a quarter covers that with room.  Where the caller chose the split rule, the partial
+        // sums of the step's concurrent launches can outweigh it: the step's own peak plus a quarter then (masks took
+        // up to 6 % more than that peak).  kfac_step_workspace_bytes gives the exact figure for one mask, and every
+        // call checks its own plan before it launches anything
         for (int nhwc = 0; nhwc < 2; ++nhwc) {
             Plan plan; Arena arena(nullptr);
             StatsArgs st{n_layers, L, in, nullptr, nullptr, 0.5f, 0, nullptr, nullptr};
@@ -1874,7 +1886,7 @@ size_t kfac_workspace_bytes_opt(const kfac_layer *L, int32_t n_layers, kfac_dtyp
             PrecondArgs pc{n_layers, L, nullptr, nullptr, nullptr, nullptr};
             plan_step(plan, arena, tun, st, iv, nullptr, pc, true);
             arena.take_tail(plan.tab.buf.size() + 16);
-            best = std::max(best, std::max(arena.peak, sum_peaks + sum_peaks / 4));
+            best = std::max(best, std::max(arena.peak + (tun.chosen_rule ? arena.peak / 4 : 0), sum_peaks + sum_peaks / 4));
         }
     }
     // the split tails of the plain products: up to four chains and the preconditioning have one phase each under way
@@ -2315,8 +2327,10 @@ kfac_status bn_full_precondition(kfac_ctx *ctx, int32_t n_layers, int32_t N, con
         if (F_ema[l] == F_inv[l]) return KFAC_ERR_INVALID;
     }
     BnFullArgs a{n_layers, N, C, g_gamma, g_beta, decay, lambda, F_ema, invert_mask, F_inv, info, out_gamma, out_beta};
+    Tunables tun = ctx->tun;
+    tun.chosen_rule = false;   // bn_full_workspace_bytes knows no options: no more scratch than by default
     Plan plan; Arena arena(ctx->ws);
-    plan_bn_full(plan, arena, ctx->tun, a, false);
+    plan_bn_full(plan, arena, tun, a, false);
     return run_plan(ctx, plan, arena);
 }
 

@@ -64,6 +64,15 @@ def test_scratch_of_two_launches_with_split_tails():
     assert need - intermediate <= 1024 * 128 * 128 * 4 + (64 << 10)      # tables and alignment: a few KB
     assert need - intermediate > 512 * 128 * 128 * 4                     # there are tails
 
+def test_scratch_of_chosen_split_limits():
+    """Limits of the split rule hold for the products of the inversion, too: their partial sums are in the bound."""
+    layers = [wl.fc_layer(1, 1200, 1200, 0)]
+    limits = kfac.options(min_k_per_split=32, max_k_per_workgroup=64, target_workgroups=4096)
+    need = kfac.kfac_step_workspace_bytes(layers, kfac.KFAC_F32, [1], limits)
+    # the last product of the recursion: 600 x 600 x 600 in ten parts, of either factor
+    assert need > 2 * 10 * 600 * 600 * 4
+    assert need > kfac.kfac_step_workspace_bytes(layers, kfac.KFAC_F32, [1]) + (8 << 20)
+    assert need <= kfac.kfac_workspace_bytes(layers, kfac.KFAC_F32, limits)
 
 
 def _fake_ctx(nbytes=1 << 20):

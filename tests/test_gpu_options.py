@@ -66,6 +66,41 @@ def reference():
     return acts, grads, gws, ref
 
 
+def _plain_products(ctx):
+    """(variants of the products, number of reductions) of an inversion and a preconditioning of LAYERS."""
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    spd = [[torch.eye(d, device="cuda") for d in (L.dA, L.dG)] for L in LAYERS]
+    A, G = [x[0] for x in spd], [x[1] for x in spd]
+    Ai, Gi = [torch.zeros_like(x) for x in A], [torch.zeros_like(x) for x in G]
+    W = [torch.randn(L.dG, L.dA, device="cuda", generator=gen) for L in LAYERS]
+    U = [torch.zeros_like(w) for w in W]
+    pi, info = torch.zeros(len(LAYERS), device="cuda"), torch.zeros(2 * len(LAYERS), dtype=torch.int32, device="cuda")
+    kfac.kfac_profile_enable(ctx, True)
+    kfac.kfac_invert(ctx, LAYERS, A, G, GAMMA, Ai, Gi, pi, info)
+    inv = kfac.kfac_profile_read(ctx)
+    kfac.kfac_precondition(ctx, LAYERS, Gi, Ai, W, U)
+    pre = kfac.kfac_profile_read(ctx)
+    return [({e["variant"] for e in es if e["kernel"] == "gemm_f32_split"}, sum(e["kernel"] == "gemm_reduce" for e in es)) for es in (inv, pre)]
+
+
+@pytest.mark.parametrize("fields,variants,split", [
+    ({}, None, (False, False)),                                                    # nothing of this size is split by default
+    ({"min_k_per_split": 32, "max_k_per_workgroup": 64, "target_workgroups": 4096}, {0, 1}, (True, True)),
+    ({"target_workgroups": 1, "max_k_per_workgroup": 1 << 20}, {0, 1}, (False, False)),
+    ({"force_tile": 64}, {1}, (False, False)),                                     # (contractions too short for two parts of 512)
+    ({"force_tile": 64, "min_k_per_split": 128}, {1}, (True, True)),
+    ({"force_tile": 128, "min_k_per_split": 128}, {0}, (True, True)),
+    ({"max_k_per_workgroup": 128}, {0, 1}, (True, True)),
+], ids=lambda v: ",".join("%s=%s" % kv for kv in v.items()) or "defaults" if isinstance(v, dict) else "")
+def test_split_rule_holds_for_plain_products(gpu, fields, variants, split):
+    """The limits of the split rule and the tile, where they are set, hold for the inversion's and the preconditioning's products."""
+    ctx = kfac.Context(LAYERS, opts=kfac.options(**fields))
+    for (seen, reductions), expected in zip(_plain_products(ctx), split):
+        assert (reductions > 0) == expected
+        assert variants is None or seen <= variants
+    ctx.close()
+
+
 @pytest.mark.parametrize("fields", OPTIONS, ids=lambda f: ",".join("%s=%s" % kv for kv in f.items()))
 def test_results_do_not_depend_on_the_options(gpu, reference, fields):
     acts, grads, gws, ref = reference
