@@ -258,14 +258,13 @@ void finish_problem(GemmProblem &P)
     if (P.mirror_band == 0) P.mirror_band = INT_MAX;
 }
 
-// Whether a phase of plain fp32 products (three-plane mode) runs through the direct kernel of gemm_direct.hip, and with
-// which tile: 2 (32 x 32), 3 (64 x 64), or -1: the staged kernels of gemm_nt.hip with the configurations already chosen.
-// All problems of the phase go into one launch then.  Microseconds, fitted to launches of 1 to 30 products of
-// 33 ... 2304 rows (gfx950): a fixed part, then either the contraction of one workgroup (latency) or all tile steps
-// spread over the chip (throughput).  The 32-tile moves twice the operand bytes per flop and ends at 55 TFLOP/s, but
-// 288 x 288 x 288 takes 6.5 us instead of 13 (symmetric, with beta: 8 instead of 16) and 576 x 576 x 576 13.7 instead
-// of 21.5; the 64-tile without LDS staging has a shorter fixed part and K loop than the staged one at the same rate
-// (1152 x 1152 x 1152 symmetric: 28 us instead of 40).
+// Whether a phase of factor products (three-plane mode) runs through a direct kernel (gemm_direct.hip), and which: 2 (32 x 32),
+// 3 (64 x 64) or -1.  Plain matrices only: fully-connected layers without bias.  All problems go into one launch then, against
+// up to two staged launches and a reduction: both factors of 512 -> 100 units take 17 us (8 to 64 samples) to 21 us (512)
+// instead of 20 to 30; from 1024 units on the staged kernels are as fast.  Microseconds: a fixed part, then either the
+// contraction of one workgroup (latency) or all tile steps spread over the chip (throughput).  The figures are those of
+// contractions as short as a batch against large results; with the ones of best_kernel below, which are fitted to the
+// products of the inversion, 31 of 56 random lists on which the two disagree were slower (by up to a quarter), 21 faster.
 int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun)
 {
     double wgk[4] = {0, 0, 0, 0}, kmax[4] = {0, 0, 0, 0}, kall = 0;
