@@ -1,6 +1,6 @@
 """Launches of 128-row tiles with a few tiles more than the chip holds at once: the contractions of those last tiles are split
-and added up by a second kernel.  U = G^-1 dW A^-1 of several layers against float64 products.  With the fp32 instruction
-also long products of few 64-row tiles."""
+and added up by a second kernel.  U = G^-1 dW A^-1 of several layers against float64 products, and inverses by their residual.
+With the fp32 instruction also long products of few 64-row tiles."""
 import pytest
 import torch
 
@@ -48,3 +48,37 @@ def test_long_products_of_few_tiles_with_the_fp32_instruction(sizes):
     assert (first["kernel"], first["variant"], second["kernel"]) == ("gemm_f32", 1, "gemm_reduce")
     tiles = -(-sizes[0][0] // 64) * -(-sizes[0][1] // 64)
     assert first["workgroups"] >= 2 * tiles
+
+
+# 12 matrices of 2323 = 1152 + 1171 rows: every product of the first partition (rectangular with a transposed copy, symmetric
+# with the old values and with the part above the diagonal left out) has a split tail.  8 of 1361 = 672 + 689: the 64-row tiles
+# of the direct kernel take all four, contractions of 672 and 689.
+@pytest.mark.parametrize("n,d,variant,reductions", [(6, 2323, 0, 4), (4, 1361, 3, 0)])
+def test_inversion_of_ragged_matrices(n, d, variant, reductions):
+    layers = [wl.fc_layer(4, d, d, 0)] * n
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X = []
+    for _ in range(2 * n):   # 2 I + E, the norm of E about 1/2
+        e = torch.randn(d, d, device="cuda", generator=gen) * (0.18 / d ** 0.5)
+        X.append(e + e.t() + 2 * torch.eye(d, device="cuda"))
+    out = [torch.full((d * d + 64,), float("nan"), device="cuda") for _ in X]
+    pi, info = torch.zeros(n, device="cuda"), torch.zeros(2 * n, dtype=torch.int32, device="cuda")
+    ctx = kfac.Context(layers)
+    kfac.kfac_profile_enable(ctx, True)
+    kfac.kfac_invert(ctx, layers, X[:n], X[n:], 0.0, out[:n], out[n:], pi, info)
+    torch.cuda.synchronize()
+    entries = kfac.kfac_profile_read(ctx)
+    ctx.close()
+    assert not info.any()
+    assert variant in {e["variant"] for e in entries if e["kernel"] == "gemm_f32_split"}
+    assert sum(e["kernel"] == "gemm_reduce" for e in entries) == reductions
+    for x, y in zip(X, out):
+        assert bool(y[d * d:].isnan().all())
+        y = y[:d * d].view(d, d)
+        assert bool((y == y.t()).all())
+        x, y = x.double(), y.double()
+        # The residual of a block inverse is at most the rounding of its products, as above, times |X| |X^-1| once for
+        # the product and once for the inverse it was made with.
+        p = x.abs() @ y.abs()
+        r = (x @ y - torch.eye(d, device="cuda", dtype=torch.float64)).abs()
+        assert bool((r <= (d + 8) * 2.0 ** -23 * (p @ p)).all())
