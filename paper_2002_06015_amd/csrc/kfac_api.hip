@@ -494,7 +494,12 @@ PhaseCost best_kernel_fp32(const Tunables &tun, const Shape *first, const Shape 
         take({6.0 + std::max(0.77 * longest, 0.6 * std::ceil(parts / kRound) * (work[1] / parts + 1.5)) + (s > 1 ? 6.0 + 0.0045 * parts : 0.0), 1, 0, s});
     }
     if (tun.force_tile == 64) return best;
-    // whole tiles, then either those beyond whole rounds or all of them in parts
+    // Whole tiles, then either those beyond whole rounds or all of them in parts.  The parts of symmetric products cost more
+    // (their reduction also reads the old values and writes the mirror image), and the 64-tiles they compete with less (a
+    // diagonal tile stages one operand): 1152 rows six times, 14 tiles beyond a round, 110 + 13 us in eight parts, 111 as
+    // 64-tiles; inversion of ResNet-50's factors 5720 us without the factor, 5670 with it.  (The longest product speaks for
+    // the launch.)
+    const double sym_parts = (first->P->flags & GEMM_SYM) ? 1.15 : 1.0;
     for (int round : {kRound, 0}) {
         const double r = round ? n[0] - kRound * std::floor(n[0] / kRound) : n[0];
         double tail_work = 0, left = r, longest = 0;
@@ -508,7 +513,7 @@ PhaseCost best_kernel_fp32(const Tunables &tun, const Shape *first, const Shape 
         const double head = 11.0 + 2.05 * (r < n[0] ? std::max((work[0] - tail_work) / kRound, first->steps) : 0.0);
         if (round) take({head + 2.05 * longest, 0, round, 1});
         for (int s = 2; s <= kMaxTailParts && r > 0 && r * s <= kMaxTailWgs && (last - 1)->steps >= 4.0 * s; ++s)
-            take({head + 2.05 * std::max(longest / s + 1.5, std::ceil(r * s / kRound) * (tail_work / r / s + 1.5)) + 6.0 + 0.02 * r * s, 0, round, s});
+            take({sym_parts * (head + 2.05 * std::max(longest / s + 1.5, std::ceil(r * s / kRound) * (tail_work / r / s + 1.5)) + 6.0 + 0.02 * r * s), 0, round, s});
     }
     return best;
 }
