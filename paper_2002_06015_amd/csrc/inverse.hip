@@ -51,7 +51,7 @@ hipError_t launch_trace(const TraceJob *jobs_dev, int n_layers, float gamma, flo
 
 // ------------------------------------------------------------------ dst = src + damp I
 // Bandwidth bound.  The recursion reads the lower triangle of a source only, except inside the diagonal blocks that are
-// inverted as leaves: a row is copied up to kLeafMax columns past the diagonal (ResNet-50's factors: 232 -> 130 us).
+// inverted as leaves: a row is copied up to kLeafMax columns past the diagonal (ResNet-50's factors: 232 -> 153 us).
 constexpr int COPY_ROWS = 8;
 
 __global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restrict__ jobs, int n_jobs,
@@ -692,7 +692,7 @@ hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, int size_class, cons
                        int32_t *info, hipStream_t s)
 {
     if (n_jobs <= 0) return hipSuccess;
-    switch (kLeafClasses[size_class]) {   // class value = n_max / 32: 16, 32 or 48 tile slots
+    switch (kLeafClasses[size_class]) {   // class value = n_max / 32: one, two or three tiles for each of fifteen wavefronts
         case 5: return launch_leaf_block<1>(jobs_dev, n_jobs, damp_dev, info, s);
         case 7: return launch_leaf_block<2>(jobs_dev, n_jobs, damp_dev, info, s);
         case 9: return launch_leaf_block<3>(jobs_dev, n_jobs, damp_dev, info, s);
