@@ -13,6 +13,13 @@
 //   - a lane loads its fragments straight from global memory in the layout the matrix instruction wants (8 adjacent
 //     k of one row), RING steps ahead, and splits them in registers: no LDS and no barrier before the end,
 //   - the four partial tiles are added in a fixed order through LDS in the epilogue (bitwise reproducible).
+//
+// Splitting the contraction this way also splits neighbouring steps, and where those cancel (products with the inverse of a
+// factor whose neighbouring variables are correlated) a wavefront's sum is far larger than the result.  Rounded six times a
+// step, once per plane product and not to nearest, such sums were up to 3 times less accurate than those of the staged kernel,
+// and inverses of smooth images' factors 1.2 to 1.3 times.  So the five low-order plane products, 2^-8 of the sum, have an
+// accumulator of their own and the sum is rounded once a step: 0.7 of the staged kernel's error, inverses 0.6 to 0.9 of it.
+// Runs of adjacent steps per wavefront on top of that: 0.4, but 1 to 3 % slower (a row's 256 bytes are read in four places).
 #include "gemm_tiles.h"
 
 namespace kfac {
@@ -62,25 +69,26 @@ struct GdRows {
     }
 };
 
+// low: the products with a middle or last plane
 template <int TM, int TN>
-__device__ __forceinline__ void gd_mma(gd_floatx16 (&acc)[TM][TN], const gd_floatx4 (&f)[TM + TN][2])
+__device__ __forceinline__ void gd_mma(gd_floatx16 (&acc)[TM][TN], gd_floatx16 (&low)[TM][TN], const gd_floatx4 (&f)[TM + TN][2])
 {
     GdPlanes a[TM], b[TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) a[i] = gd_split(f[i][0], f[i][1]);
 #pragma unroll
     for (int j = 0; j < TN; ++j) b[j] = gd_split(f[TM + j][0], f[TM + j][1]);
-    auto mm = [&](auto pa, auto pb) {
+    auto mm = [&](gd_floatx16 (&c)[TM][TN], auto pa, auto pb) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa(a[i]), pb(b[j]), acc[i][j], 0, 0, 0);
+                c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa(a[i]), pb(b[j]), c[i][j], 0, 0, 0);
     };
     auto H = [](const GdPlanes &x) { return x.h; };
     auto M = [](const GdPlanes &x) { return x.m; };
     auto L = [](const GdPlanes &x) { return x.l; };
-    mm(L, H); mm(M, M); mm(H, L); mm(M, H); mm(H, M); mm(H, H);
+    mm(low, L, H); mm(low, M, M); mm(low, H, L); mm(acc, H, H); mm(low, M, H); mm(low, H, M);
 }
 
 // partial sums of four wavefronts in LDS, [wave][v][lane] per 32 x 32 block in the accumulator layout
@@ -97,7 +105,7 @@ __device__ __forceinline__ float gd_sum(const float *part, int e)
 }
 
 template <int TM, int TN, int RING>
-__global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__restrict__ probs,
+__global__ __launch_bounds__(256, TM == 2 ? 2 : 1) void gemm_direct_kernel(const GemmProblem *__restrict__ probs,
                                                           const int *__restrict__ tile_start, int n_probs)
 {
     constexpr int BLOCKS = TM * TN;
@@ -119,15 +127,15 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__r
 #pragma unroll
     for (int j = 0; j < TN; ++j) rows[TM + j].init(P.b, j0 + 32 * j, lane);
 
-    gd_floatx16 acc[TM][TN];
+    gd_floatx16 acc[TM][TN], low[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
 
-    // step s of the contraction (k = 16 s .. 16 s + 15) belongs to wavefront s % 4
+    // wavefront w takes a run of the 16-wide steps, the last one also the partial step
     const int full = K >> 4;
     const int mine = (full - w + 3) >> 2;
     if (mine > 0) {
@@ -143,7 +151,7 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__r
         for (int s = 0; s < mine; s += RING) {
 #pragma unroll
             for (int u = 0; u < RING; ++u) {
-                if (s + u < mine) gd_mma<TM, TN>(acc, f[u]);
+                if (s + u < mine) gd_mma<TM, TN>(acc, low, f[u]);
                 if (s + RING < mine) load(s + RING + u, f[u]);
             }
         }
@@ -152,14 +160,14 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__r
         gd_floatx4 f[TM + TN][2];
 #pragma unroll
         for (int q = 0; q < TM + TN; ++q) rows[q].load_tail(16 * full, K, lane, f[q][0], f[q][1]);
-        gd_mma<TM, TN>(acc, f);
+        gd_mma<TM, TN>(acc, low, f);
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) part[((w * BLOCKS + i * TN + j) * 16 + v) * 64 + lane] = acc[i][j][v];
+            for (int v = 0; v < 16; ++v) part[((w * BLOCKS + i * TN + j) * 16 + v) * 64 + lane] = acc[i][j][v] + low[i][j][v];
     __syncthreads();
     const bool sym = (P.flags & GEMM_SYM) != 0;
     const bool diag_tile = sym && tm == tn;
@@ -223,11 +231,14 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(const GemmProblem *__r
 }
 
 hipError_t launch_gemm_direct(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, int total_wgs,
-                              int tile_cfg, hipStream_t s)
+                              int tile_cfg, int k_max, hipStream_t s)
 {
     if (total_wgs <= 0) return hipSuccess;
-    if (tile_cfg == 2) gemm_direct_kernel<1, 1, 5><<<dim3(total_wgs), dim3(256), 0, s>>>(probs_dev, tile_start_dev, n_probs);
-    else               gemm_direct_kernel<2, 2, 2><<<dim3(total_wgs), dim3(256), 0, s>>>(probs_dev, tile_start_dev, n_probs);
+    // A wavefront's share of up to 320 columns is 5 steps, all requested at once (142 registers, 3 workgroups a compute unit);
+    // longer contractions go round the ring anyway and are better off with 4 (126 registers, 4 workgroups).
+    if (tile_cfg == 2 && k_max <= 320) gemm_direct_kernel<1, 1, 5><<<dim3(total_wgs), dim3(256), 0, s>>>(probs_dev, tile_start_dev, n_probs);
+    else if (tile_cfg == 2)            gemm_direct_kernel<1, 1, 4><<<dim3(total_wgs), dim3(256), 0, s>>>(probs_dev, tile_start_dev, n_probs);
+    else                               gemm_direct_kernel<2, 2, 2><<<dim3(total_wgs), dim3(256), 0, s>>>(probs_dev, tile_start_dev, n_probs);
     return hipGetLastError();
 }
 

@@ -171,6 +171,7 @@ struct Launch {
     LaunchKind kind;
     size_t off_a, off_b;   // table offsets
     int n, total_wgs, cfg, dtype;
+    int k_max;             // L_GEMM: longest contraction
     float f0, f1;
     void *p0, *p1;
     double flops, bytes;   // algorithmic counts (profiling only)
@@ -314,6 +315,7 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
     }
     Launch L{};
     L.kind = L_GEMM;
+    for (auto &P : sel) L.k_max = std::max(L.k_max, P.K);
     for (auto &P : sel)
         if (P.flags & GEMM_SYM) {
             const double d = P.M + ((P.flags & GEMM_BORDER) ? 1.0 : 0.0);
@@ -1713,7 +1715,7 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
         switch (L.kind) {
             case L_GEMM:
                 e = L.cfg >= 2 ? launch_gemm_direct((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b),
-                                                    L.n, L.total_wgs, L.cfg, ls)
+                                                    L.n, L.total_wgs, L.cfg, L.k_max, ls)
                                : launch_gemm((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b), L.n,
                                              L.total_wgs, L.cfg, L.dtype, ls);
                 break;

@@ -267,7 +267,7 @@ hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, 
                        int total_wgs, int tile_cfg, int dtype, hipStream_t s);
 // small products of plain fp32 matrices (tile_cfg 2, 3), three-plane product mode
 hipError_t launch_gemm_direct(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, int total_wgs,
-                              int tile_cfg, hipStream_t s);
+                              int tile_cfg, int k_max, hipStream_t s);
 hipError_t launch_gemm_reduce(const GemmProblem *probs_dev, const int *red_start_dev, int n_probs,
                               int total_wgs, hipStream_t s);
 hipError_t launch_patch(const PatchJob *jobs_dev, int n_jobs, int total_wgs, hipStream_t s);

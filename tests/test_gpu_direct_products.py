@@ -42,3 +42,33 @@ def test_precondition_at_tile_edges(d_in, d_out, variant, bias):
         bound = (L.dA + L.dG + 8) * 2.0 ** -23 * (np.abs(G[i]).astype(np.float64) @ np.abs(W[i]) @ np.abs(A[i]))
         assert np.all(np.abs(got[:L.dG * L.dA].reshape(L.dG, L.dA) - ref) <= bound)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,d_out,variant", [(256, 32, 2), (576, 64, 2), (1023, 833, 3)])
+def test_sums_that_cancel_across_steps(d, d_out, variant):
+    """W A^-1 where what one 16-wide step adds is taken away by the next, as in products with the inverse of a factor whose
+    neighbouring variables are correlated: the sums of the steps of one wavefront are far larger than the result."""
+    L = wl.fc_layer(4, d, d_out, 0)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    A = torch.randn(d, d, device="cuda", generator=gen)
+    W = torch.zeros(d_out, d, device="cuda")
+    edges = torch.arange(16, d, 16, device="cuda")
+    W[:, edges - 1] = torch.randn(d_out, len(edges), device="cuda", generator=gen)
+    W[:, edges] = -W[:, edges - 1]
+    A[:, edges] = A[:, edges - 1] * (1 + 2.0 ** -12 * torch.randn(d, len(edges), device="cuda", generator=gen))
+    out = torch.empty(d_out, d, device="cuda")
+    ctx = kfac.Context([L])
+    kfac.kfac_profile_enable(ctx, True)
+    kfac.kfac_precondition(ctx, [L], [torch.eye(d_out, device="cuda")], [A], [W], [out])
+    torch.cuda.synchronize()
+    assert variant in {e["variant"] for e in kfac.kfac_profile_read(ctx)}
+    ctx.close()
+    W, A = W.double(), A.double()
+    steps = -(-d // 16)
+    step = (W ** 2 @ (A ** 2).t() / steps).sqrt()   # what a step adds
+    # A wavefront rounds its sum of m steps, sqrt(m) of that, once a step for m = 1 .. M; then come four sums of the planes'
+    # low-order terms and three of the wavefronts.  A rounding is 2^-24 / sqrt(3) at most, uniform in half a unit.  (Six
+    # roundings a step, or ones that do not go to nearest, are outside: 6.8 for d = 256, where this is 4.8.)
+    M = steps / 4
+    rms = ((out.double() - W @ A.t()) / (step * 2.0 ** -24)).pow(2).mean().sqrt()
+    assert float(rms) <= ((2 * M * (M + 1) + 7 * M) / 3) ** 0.5
