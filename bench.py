@@ -284,8 +284,8 @@ def main():
     gemm_dt = "bf16" if dom_name.startswith("gemm_bf16") else "f32"
     split_mode = "split" in dom_name
     # the peak of the pipe the kernel issues on: the fp32 matrix instruction, the bf16 one, or -- fp32 products
-    # formed by six bf16 instructions each -- a sixth of the bf16 peak in fp32-equivalent flops
-    pipe_peak = PEAK_TFLOPS["bf16"] / 6.0 if split_mode else PEAK_TFLOPS[gemm_dt]
+    # formed by three fp16 instructions each -- a third of the fp16 (bf16) peak in fp32-equivalent flops
+    pipe_peak = PEAK_TFLOPS["bf16"] / 3.0 if split_mode else PEAK_TFLOPS[gemm_dt]
     if dom["flops"] > 0:
         achieved = dom["flops"] / (dom["ms"] * 1e-3) / 1e12
         roofline = {"kernel": dom_name, "bound": "mfma", "achieved": round(achieved, 3), "peak": round(pipe_peak, 1),
@@ -294,13 +294,13 @@ def main():
                     "launches_per_step": dom["launches"], "avg_launch_ms": round(dom["ms"] / dom["launches"], 4)}
         if split_mode:
             roofline["frac_of_fp32_mfma_peak"] = round(achieved / PEAK_TFLOPS["f32"], 4)
-            roofline["executed_bf16_tflops"] = round(6.0 * achieved, 1)
-            roofline["note"] = ("fp32 contraction computed by six bf16 matrix instructions per product block (operands split "
-                                "exactly into three bf16 planes, fp32 accumulation, fp32-level accuracy): achieved = fp32 flops "
-                                "of the contraction, peak = the dense bf16 peak / 6 (the pipe the kernel issues on); a loop of "
-                                "nothing but these matrix instructions on operands with random sign, exponent and mantissa "
-                                "reaches about 0.7 of that peak on this GPU (the clock settles at 1.7-1.8 GHz instead of 2.4; "
-                                "profiles/mfma_bf16_peak_loop.txt)")
+            roofline["executed_fp16_tflops"] = round(3.0 * achieved, 1)
+            roofline["note"] = ("fp32 contraction computed by three fp16 matrix instructions per product block (operands split "
+                                "into two fp16 planes under a scale per row, fp32 accumulation, fp32-level accuracy): achieved = "
+                                "fp32 flops of the contraction, peak = the dense fp16 peak / 3 (the pipe the kernel issues on); a "
+                                "loop of nothing but such matrix instructions (measured with bf16) on operands with random sign, "
+                                "exponent and mantissa reaches about 0.7 of that peak on this GPU (the clock settles at 1.7-1.8 "
+                                "GHz instead of 2.4; profiles/mfma_bf16_peak_loop.txt)")
     else:
         achieved = dom["bytes"] / (dom["ms"] * 1e-3) / 1e9
         roofline = {"kernel": dom_name, "bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
@@ -320,7 +320,7 @@ def main():
     # which roofline bounds each stage (stages one after the other): the three dense stages against the matrix
     # pipe they issue on (algorithmic flops = the definitions, executed = what the launches multiply out),
     # the unit-wise BatchNorm call against HBM
-    mat_peak = PEAK_TFLOPS["bf16"] / 6.0 if (args.dtype == "f32" and split_mode) else PEAK_TFLOPS["f32"]
+    mat_peak = PEAK_TFLOPS["bf16"] / 3.0 if (args.dtype == "f32" and split_mode) else PEAK_TFLOPS["f32"]
     roofline_by_stage = {}
     for name, alg in (("stats", fl["stats_A"] + fl["stats_G"]), ("invert", fl["inv"]), ("precondition", fl["precond"])):
         ms = stage_ms[name]
@@ -410,8 +410,8 @@ def main():
 
 
         # ------------------------------------------------------------ beside the step: the fp32 matrix instruction
-        # (options.fp32_products = KFAC_PRODUCTS_FP32_MFMA: every product by v_mfma_f32_32x32x2_f32 instead of six bf16
-        # instructions on split operands; the same step on a context of its own, its results compared with those of
+        # (options.fp32_products = KFAC_PRODUCTS_FP32_MFMA: every product by v_mfma_f32_32x32x2_f32 instead of fp16
+        # (bf16) instructions on split operands; the same step on a context of its own, its results compared with those of
         # the default mode)
         split_obj = None
         if args.dtype == "f32":
@@ -707,8 +707,8 @@ def main():
             5: "full ResNet-50 layer set, batch 128, inverses refreshed for a seeded 25% subset"}[cfg]),
             "layers": n, "bn_layers": len(Cs), "batch": N, "inverted_layers": len(subset),
             "g_spatial_mean": bool(spatial_mean), "schedule": args.schedule,
-            "fp32_products": ("six bf16 matrix instructions on operands split exactly into three bf16 planes, fp32 "
-                              "accumulation (fp32-level accuracy; the library's default; object fp32_instruction: the same "
+            "fp32_products": ("three fp16 matrix instructions on operands split into two fp16 planes (small products: six on "
+                              "three bf16 planes), fp32 accumulation (fp32-level accuracy; the library's default; object fp32_instruction: the same "
                               "step with the fp32 matrix instruction)")},
         "algorithmic_gflop": {k: round(v / 1e9, 2) for k, v in fl.items()},
         "step_tflops": round(total_flops / (ms_per_step * 1e-3) / 1e12, 3),

@@ -27,6 +27,26 @@ typedef unsigned short ushortx4 __attribute__((ext_vector_type(4)));
 constexpr int KT = 32;      // contraction tile
 constexpr int LDF = 36;     // LDS row length in floats (32 + 4 pad: conflict-free 16-byte reads)
 
+// operand stages, then the output tile
+template <int TM, int TN>
+constexpr size_t gemm_lds_bytes()
+{
+    const size_t stages = 2 * (64 * TM + 64 * TN) * LDF * sizeof(float);   // same size for LDH bf16 rows
+    const size_t tile = (size_t)(64 * TM) * (64 * TN + 1) * sizeof(float);
+    return stages > tile ? stages : tile;
+}
+
+// the same for the kernel of the products through planes: two stages of two fp16 planes or one of three bf16 planes; the scales
+// of the rows and two flags lie behind
+template <int TM, int TN>
+constexpr size_t split_lds_bytes()
+{
+    constexpr size_t rows = 64 * TM + 64 * TN;
+    const size_t two = 2 * 2 * rows * 32 * 2, three = 3 * rows * 40 * 2, tile = 64 * TM * (64 * TN + 1) * sizeof(float);
+    const size_t most = two > three ? (two > tile ? two : tile) : (three > tile ? three : tile);
+    return (most + 15) / 16 * 16 + (rows + 2) * sizeof(float);
+}
+
 // Final write of a ROWS x COLS slab of accumulated sums held in LDS (T[r][c] at
 // T[r * (COLS + 1) + c], global position (gi0 + r, gj0 + c)):
 //     C[i][j] = alpha * T + beta * C[i][j]
@@ -154,7 +174,8 @@ struct LoaderF32 {
     unsigned dead;             // bit s: slot row is outside the operand
     long long batch_stride;
     long long col;             // offset of the thread's chunk within a row: n * batch_stride + t
-    int hw, kq, r0, m, n, t;
+    int hw, kq, r0, t;
+    int m;                     // first k of the chunk, as of the last seek
     bool zero_all;             // the tile held in registers is to be stored as zeros
 
     __device__ __forceinline__ void init(const Operand &op, int tile_row0, int tid)
@@ -170,26 +191,26 @@ struct LoaderF32 {
             if (row >= op.rows) dead |= 1u << s;
             rowoff[s] = (long long)min(row, op.rows - 1) * op.row_stride;
         }
-        m = n = t = 0;
+        m = t = 0;
         col = 0;
         zero_all = false;
     }
     __device__ __forceinline__ void seek(int tile_k0)   // position on the tile starting at tile_k0
     {
         m = tile_k0 + kq;
-        n = m / hw;
+        const int n = m < hw ? 0 : m / hw;   // (plain matrices: one run)
         t = m - n * hw;
         col = (long long)n * batch_stride + t;
     }
     __device__ __forceinline__ void advance()
     {
-        m += KT; t += KT; col += KT;
+        t += KT; col += KT;
         while (t >= hw) { t -= hw; col += batch_stride - hw; }
     }
     // the same for runs of at least one tile (hw >= KT): at most one wrap, no branch
     __device__ __forceinline__ void advance_once()
     {
-        m += KT; t += KT; col += KT;
+        t += KT; col += KT;
         const bool wrap = t >= hw;
         t -= wrap ? hw : 0;
         col += wrap ? batch_stride - hw : 0;
@@ -481,8 +502,8 @@ __device__ __forceinline__ void gemm_f32_mainloop(const GemmProblem &P, int tm, 
 // with fp32 accumulation inside the matrix unit: six bf16 instructions give the product to
 // fp32 accuracy in 6 x 32 cycles per 32x32x16 block instead of 8 x 64.  The operands stay fp32 in
 // HBM; the loader of the fp32 kernel brings a K tile of 32 into registers and the split happens
-// on the way into LDS, which holds one stage of three planes (two barriers per tile; the second
-// workgroup of the compute unit computes while this one stores).
+// on the way into LDS, which holds one stage of three planes.  What the loop of two fp16 planes below
+// leaves (and operands stored transposed).
 constexpr int LDQ = 40;     // LDS row length in bf16 (32 + 8 pad: 80-byte rows, conflict-free 16-byte reads)
 // Rows of a group of 8 are stored in the order 0 4 1 5 2 6 3 7: the 8-byte stores of 16 lanes cover two
 // rows, and rows 80 bytes apart share 4 of their 16 banks while rows 4 apart (320 bytes) share none.  The
@@ -536,12 +557,11 @@ __device__ __forceinline__ float fill_remainder_split(const Operand &op, int til
     return x[0] + x[1] + x[2];
 }
 
-// SAME: a and b are the same operand tile (a diagonal tile of a Gram matrix): it is loaded, split and stored
-// once, and the fragments of b are read from the rows of a.
-template <int TM, int TN, bool LIVE, bool RS, bool SAME>
+template <int TM, int TN, bool LIVE, bool RS>
 __device__ __forceinline__ void gemm_split_mainloop(const GemmProblem &P, int tm, int tn, int tid,
-                                                    LoaderF32<64 * TM> &la, LoaderF32<64 * TN> &lb, unsigned short *lds,
-                                                    int k0, int k1, int wave_m, int wave_n, int l32, int half,
+                                                    LoaderF32<64 * TM> &la,
+                                                    LoaderF32<64 * TN> &lb, unsigned short *lds, int k0,
+                                                    int k1, int wave_m, int wave_n, int l32, int half,
                                                     floatx16 (&acc)[TM][TN], float (&rs)[2 * TM], float &rs_rem)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
@@ -554,51 +574,33 @@ __device__ __forceinline__ void gemm_split_mainloop(const GemmProblem &P, int tm
     const int nvec = nfull + ((shifted || careful) ? 1 : 0);
     const int nk = nvec + (klen4 < klen ? 1 : 0);
     if (nk == 0) return;
-    // two tiles in flight in registers: the loads of tile it + 2 are issued when tile it has gone
-    // into LDS, and have two tile times to arrive
-    floatx4 ra0[BM / 32], rb0[BN / 32], ra1[BM / 32], rb1[BN / 32];
-    bool za0 = false, zb0 = false, za1 = false, zb1 = false;   // the loaders' zero_all of the tile held
-
-    auto load_tile = [&](int it, auto &ra, auto &rb, bool &za, bool &zb) {
-        if (it < nfull) {
-            if constexpr (SAME) {
-                if (it > 0) la.advance();
-                la.load_full(ra);
-            } else {
-                if (it > 0) { la.advance(); lb.advance(); }
-                la.load_full(ra); lb.load_full(rb);
-            }
-        } else if (it < nvec) {
-            if (careful) {
-                la.load_careful(ra, k0 + klen4);
-                if constexpr (!SAME) lb.load_careful(rb, k0 + klen4);
-            } else if constexpr (SAME) {
-                la.seek(k0 + klen4 - KT);
-                la.load_full(ra);
-                la.zero_below(k0 + nfull * KT);
-            } else {
-                la.seek(k0 + klen4 - KT); lb.seek(k0 + klen4 - KT);
-                la.load_full(ra); lb.load_full(rb);
-                la.zero_below(k0 + nfull * KT);
-            }
-        }
-        za = la.zero_all; zb = lb.zero_all;
-    };
-    auto store_tile = [&](int it, const auto &ra, const auto &rb, bool za, bool zb) {
-        if (it < nvec) {
-            float unused[BN / 32];
-            la.zero_all = za; lb.zero_all = zb;
-            store_split<BM, RS>(la, ra, lds, PLANE, rs);
-            if constexpr (!SAME) store_split<BN, false>(lb, rb, lds + BM * LDQ, PLANE, unused);
-        } else {
+    floatx4 ra[BM / 32], rb[BN / 32];
+    la.zero_all = false; lb.zero_all = false;
+    la.seek(k0); lb.seek(k0);
+    auto stage_tile = [&](int it) {
+        if (it == nvec) {
             rs_rem = fill_remainder_split<BM>(P.a, tm * BM, k0 + klen4, k1, tid, lds, PLANE);
-            if constexpr (!SAME) fill_remainder_split<BN>(P.b, tn * BN, k0 + klen4, k1, tid, lds + BM * LDQ, PLANE);
+            fill_remainder_split<BN>(P.b, tn * BN, k0 + klen4, k1, tid, lds + BM * LDQ, PLANE);
+            return;
         }
+        if (careful) {
+            la.load_careful(ra, k0 + klen4); lb.load_careful(rb, k0 + klen4);
+        } else if (it < nfull) {
+            if (it > 0) { la.advance(); lb.advance(); }
+            la.load_full(ra); lb.load_full(rb);
+        } else {
+            la.seek(k0 + klen4 - KT); lb.seek(k0 + klen4 - KT);
+            la.load_full(ra); lb.load_full(rb);
+            la.zero_below(k0 + nfull * KT);
+        }
+        float unused[BN / 32];
+        store_split<BM, RS>(la, ra, lds, PLANE, rs);
+        store_split<BN, false>(lb, rb, lds + BM * LDQ, PLANE, unused);
     };
     // v_mfma_f32_32x32x16_bf16: a lane supplies 8 consecutive k of row lane % 32, the half-waves
     // two different groups of 8; step u of a tile uses k = 16u + 8*half + 0..7 for both operands
     const int off_a = (wave_m * 32 * TM + lds_row(l32)) * LDQ + 8 * half;
-    const int off_b = (SAME ? 0 : BM * LDQ) + (wave_n * 32 * TN + lds_row(l32)) * LDQ + 8 * half;
+    const int off_b = BM * LDQ + (wave_n * 32 * TN + lds_row(l32)) * LDQ + 8 * half;
     // One step: the fragments of the h and m planes and of l' are requested up front, the l
     // fragments of the a operand take over the registers of h once its products are issued (their
     // latency lies under the m products).  Fixed order (the scheduling barriers keep the compiler
@@ -645,24 +647,425 @@ __device__ __forceinline__ void gemm_split_mainloop(const GemmProblem &P, int tm
         }
     };
 
-    if constexpr (SAME) la.seek(k0);
-    else { la.seek(k0); lb.seek(k0); }
-    load_tile(0, ra0, rb0, za0, zb0);
-    load_tile(1, ra1, rb1, za1, zb1);
-    for (int it = 0; it < nk; it += 2) {
+    for (int it = 0; it < nk; ++it) {
         if (it > 0) __syncthreads();   // every wavefront has read the tile before
-        store_tile(it, ra0, rb0, za0, zb0);
-        load_tile(it + 2, ra0, rb0, za0, zb0);
+        stage_tile(it);
         __syncthreads();
         compute();
-        if (it + 1 < nk) {
-            __syncthreads();
-            store_tile(it + 1, ra1, rb1, za1, zb1);
-            load_tile(it + 3, ra1, rb1, za1, zb1);
-            __syncthreads();
-            compute();
+    }
+}
+
+// ------------------------------------------------------------------ fp32 through two fp16 planes
+// The main loop of the product mode (the one above is its fallback).  x s = h + l with s a power of two per operand row, h the
+// fp16 value nearest to x s and l the one nearest to x s - h: 11 + 11 significant bits and the sign of l, so h + l is x s
+// itself for three values of four and one unit of the 24th bit off for the fourth; with
+//     x y  =  (h h' + h l' + l h') / (s s')  +  terms below 2^-22 |x y| of random sign
+// three fp16 instructions do what took six bf16 ones.  What bounds the product is power: at the clock the chip holds under it
+// (1.75 GHz) the six-instruction loop kept the matrix unit busy 0.54 of the time and did no more work at a higher share.  Half
+// the matrix work, 2.5 instead of 5.5 vector instructions and 4 instead of 6 bytes of LDS a staged element:
+// see the figures at gemm_nt_f32_split_kernel.  It is also the more accurate one, because the accumulator is rounded three
+// times per 16 k instead of six.
+//
+// The range of fp16 is what the scale is for.  A workgroup takes it from its own rows, before its main loop: the largest of up
+// to 128 elements of the row, spread over the workgroup's part of the contraction, goes to [2^10, 2^11) (rows that sample as
+// zero are read in full, rows of an inverse also sample their diagonal element).  Above, there is a factor of 32 to the largest
+// fp16 value; a row that goes beyond it leaves infinities or NaN in the accumulator, which costs nothing to provide for: the
+// workgroup finds them after its loop and repeats it in the three-plane mode, which has the range of fp32.  Below, elements
+// down to 2^-12 of the sampled maximum are exact as above, smaller ones to an absolute 2^-35 of it: in all, 2^-24 of the row's
+// norm or less even where almost every element is that small.  For a Gram matrix that is the scale of its element, sqrt(C_ii C_jj).  Where an operand is an inverse (or is multiplied with one before), the terms of a sum
+// can be of one size although one factor grows along the row as the other falls: variables of different scale.  Their
+// scales are the diagonal of the inverse (P.kdiag); where its square roots spread over more than 2^11, so that an element with
+// weight may lie in the absolute range, the workgroup takes the three-plane mode from the start.
+constexpr int kHalfTop = 10;         // exponent the largest sampled element of a row is brought to
+constexpr int kHalfSpread = kHalfTop + 1;   // see above: spread of a well-scaled contraction, in exponents of the variables
+constexpr int LDP = 32;              // LDS row length in fp16; 16-byte chunks of a row are permuted instead of padded (half_swz)
+__device__ __forceinline__ int half_swz(int row) { return ((row >> 1) & 3) ^ ((row >> 3) & 1); }
+
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+
+// two fp32 values, scaled -> their packed (h, l) fp16 pairs, low half = first value
+__device__ __forceinline__ void split_half_pair(float x0, float x1, float s, unsigned &h, unsigned &l)
+{
+    const float y0 = x0 * s, y1 = x1 * s;
+    half2_t hh = {(_Float16)y0, (_Float16)y1};
+    asm("" : "+v"(hh));   // (keeps the compiler from converting each half a second time)
+    const half2_t ll = {(_Float16)(y0 - (float)hh[0]), (_Float16)(y1 - (float)hh[1])};
+    h = __builtin_bit_cast(unsigned, hh);
+    l = __builtin_bit_cast(unsigned, ll);
+}
+// power of two that brings |x| in [2^e, 2^(e+1)) to [2^kHalfTop, 2^(kHalfTop+1)); 1 for x == 0.  (2^118 at most: its reciprocal
+// and the scaled row stay finite.)
+__device__ __forceinline__ float half_scale(float x)
+{
+    const int e = (int)(__float_as_uint(x) >> 23);
+    return x == 0.f ? 1.f : __uint_as_float((unsigned)min(254 + kHalfTop - e, 127 + 118) << 23);
+}
+__device__ __forceinline__ float half_unscale(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }   // 1 / s
+__device__ __forceinline__ float max_abs(float m, const floatx4 &v)
+{
+    return fmaxf(fmaxf(m, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
+}
+
+// Largest sampled magnitudes of the thread's rows over [k0, k0 + klen): request() issues the loads of up to four chunks per row,
+// finish() waits for them, so that both operands' loads are in flight together.
+template <int BR>
+struct RowSample {
+    static constexpr int SLOTS = BR / 32;
+    floatx4 v[4][SLOTS];
+
+    __device__ __forceinline__ void request(LoaderF32<BR> &ld, int k0, int klen)
+    {
+        const int span = (klen & ~3) - KT;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            ld.seek(k0 + (q == 3 ? span : (span / 3 * q) & ~3));
+            ld.load_full(v[q]);
         }
     }
+    __device__ __forceinline__ void finish(const LoaderF32<BR> &ld, const Operand &op, int tile_row0, int k0, int klen, float (&mx)[SLOTS]) const
+    {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            mx[s] = max_abs(max_abs(0.f, v[0][s]), v[1][s]);
+            mx[s] = max_abs(max_abs(mx[s], v[2][s]), v[3][s]);
+            const int row = tile_row0 + ld.r0 + 32 * s;
+            if (op.diag && row >= k0 && row < k0 + klen && row < op.rows) mx[s] = fmaxf(mx[s], fabsf(ld.base[ld.rowoff[s] + row]));
+            for (int k = klen & ~3; k < klen; ++k) mx[s] = fmaxf(mx[s], fabsf(ld.base[ld.rowoff[s] + k0 + k]));   // (plain matrices only)
+        }
+    }
+};
+// the same over every element (rows that sampled as zero)
+template <int BR>
+__device__ __forceinline__ void scan_rows(LoaderF32<BR> &ld, int k0, int klen, float (&mx)[BR / 32])
+{
+    constexpr int SLOTS = BR / 32;
+    const int nfull = (klen & ~3) / KT;
+    ld.seek(k0);
+    for (int it = 0; it < nfull; ++it) {   // (the remainder was sampled: the last chunk ends at the range end)
+        if (it > 0) ld.advance();
+        floatx4 v[SLOTS];
+        ld.load_full(v);
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) mx[s] = max_abs(mx[s], v[s]);
+    }
+}
+template <int SLOTS>
+__device__ __forceinline__ bool reduce_rows(float (&mx)[SLOTS], unsigned dead)   // over the 8 lanes of a row; true: a row of zeros
+{
+    bool zero = false;
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        mx[s] = fmaxf(mx[s], __shfl_xor(mx[s], 1));
+        mx[s] = fmaxf(mx[s], __shfl_xor(mx[s], 2));
+        mx[s] = fmaxf(mx[s], __shfl_xor(mx[s], 4));
+        zero |= mx[s] == 0.f && !((dead >> s) & 1);
+    }
+    return zero;
+}
+
+// Scales of the rows of both operand tiles into registers and into sc[0 .. BM) and sc[BM .. BM + BN); false: the variables of
+// the contraction are too differently scaled for them (see above).
+template <int BM, int BN, bool SAME>
+__device__ __forceinline__ bool half_scales(const GemmProblem &P, int tm, int tn, LoaderF32<BM> &la, LoaderF32<BN> &lb,
+                                            int k0, int klen, float *sc, int tid, float (&sa)[BM / 32],
+                                            float (&sb)[BN / 32])
+{
+    int *range = (int *)(sc + BM + BN);   // largest exponent of kdiag, and 255 minus the smallest
+    if (P.kdiag) {
+        if (tid < 2) range[tid] = 0;
+        __syncthreads();
+    }
+    {
+        RowSample<BM> va;
+        RowSample<BN> vb;
+        va.request(la, k0, klen);
+        if constexpr (!SAME) vb.request(lb, k0, klen);
+        if (P.kdiag) {
+            int hi = 0, lo = 0;
+            for (int k = k0 + tid; k < k0 + klen; k += 256) {
+                const int e = (int)((__float_as_uint(P.kdiag[(long long)k * P.kdiag_step]) >> 23) & 255);
+                hi = max(hi, e);
+                lo = max(lo, 255 - e);
+            }
+            for (int d = 32; d > 4; d >>= 1) { hi = max(hi, __shfl_xor(hi, d)); lo = max(lo, __shfl_xor(lo, d)); }
+            if ((tid & 63) < 8) { atomicMax(range, hi); atomicMax(range + 1, lo); }
+        }
+        va.finish(la, P.a, tm * BM, k0, klen, sa);
+        if constexpr (!SAME) vb.finish(lb, P.b, tn * BN, k0, klen, sb);
+    }
+    bool zero = reduce_rows(sa, la.dead);
+    if constexpr (!SAME) zero |= reduce_rows(sb, lb.dead);
+    zero = __syncthreads_or(zero);
+    if (P.kdiag && range[0] + range[1] - 255 > 2 * kHalfSpread) return false;
+    if (zero) {
+        scan_rows<BM>(la, k0, klen, sa);
+        reduce_rows(sa, la.dead);
+        if constexpr (!SAME) {
+            scan_rows<BN>(lb, k0, klen, sb);
+            reduce_rows(sb, lb.dead);
+        }
+    }
+    const bool first = (tid & 7) == 0;
+#pragma unroll
+    for (int s = 0; s < BM / 32; ++s) {
+        sa[s] = half_scale(sa[s]);
+        if (first) sc[la.r0 + 32 * s] = sa[s];
+    }
+#pragma unroll
+    for (int s = 0; s < BN / 32; ++s) {
+        if constexpr (SAME) sb[s] = sa[s];
+        else sb[s] = half_scale(sb[s]);
+        if (first) sc[BM + lb.r0 + 32 * s] = sb[s];
+    }
+    return true;
+}
+
+// One slot of a staged tile into its rows of the two planes (plane stride in fp16 units).  Rows outside the operand repeat its
+// last row: what they contribute to is not stored.  MASK: the tile may hold k positions that count as zero.
+template <int BR, bool RS, bool MASK>
+__device__ __forceinline__ void store_half_slot(const LoaderF32<BR> &ld, const floatx4 &x, unsigned short *rows, int plane, float scale,
+                                                float &rs, int s)
+{
+    floatx4 v = x;
+    if constexpr (MASK) {
+        if (ld.zero_all) { v[0] = 0.f; v[1] = 0.f; v[2] = 0.f; v[3] = 0.f; }
+    }
+    if constexpr (RS) rs += (v[0] + v[1]) + (v[2] + v[3]);
+    uint2 h, l;
+    split_half_pair(v[0], v[1], scale, h.x, l.x);
+    split_half_pair(v[2], v[3], scale, h.y, l.y);
+    unsigned short *dst = rows + (ld.r0 + 32 * s) * LDP + (((ld.kq >> 3) ^ half_swz(ld.r0)) << 3) + (ld.kq & 4);
+    *(uint2 *)dst = h;
+    *(uint2 *)(dst + plane) = l;
+}
+
+// K % 4 remainder tile: thread tid < BR fills row tid of the planes with the elements k4 .. kend-1 of its operand row followed
+// by zeros; returns their sum
+template <int BR>
+__device__ __forceinline__ float fill_remainder_half(const Operand &op, int tile_row0, int k4, int kend, int tid,
+                                                     unsigned short *rows, int plane, const float *sc)
+{
+    if (tid >= BR) return 0.f;
+    const int row = tile_row0 + tid;
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
+    if (row < op.rows) {
+        gfloat_ptr p = (gfloat_ptr)op.base + (long long)row * op.row_stride + k4;
+        for (int e = 0; e < 3; ++e)
+            if (k4 + e < kend) x[e] = p[e];
+    }
+    uint2 v[2];
+    split_half_pair(x[0], x[1], sc[tid], v[0].x, v[1].x);
+    split_half_pair(x[2], x[3], sc[tid], v[0].y, v[1].y);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            *(uint4 *)(rows + q * plane + tid * LDP + ((c ^ half_swz(tid)) << 3)) = c == 0 ? uint4{v[q].x, v[q].y, 0u, 0u} : uint4{0u, 0u, 0u, 0u};
+    return x[0] + x[1] + x[2];
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void zero_acc(floatx16 (&acc)[TM][TN])
+{
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+}
+
+// Software pipeline over K tiles of 32 with two stages in LDS and one barrier per tile.  While the matrix instructions of tile
+// `it` run, the wavefront converts tile it + 1, which its registers hold, stores it into the other stage and issues the loads
+// of tile it + 2.  The six phases of a tile (h h', h l', l h' of its first and of its second 16 k) need 2 TM + 2 TN fragments
+// between them: each is requested one phase ahead, into the registers of one whose last product has been issued (the two sets
+// of b fragments change roles at the second half).
+// SAME: a and b are the same operand tile (a diagonal tile of a Gram matrix): staged once.
+template <int TM, int TN, bool LIVE, bool RS, bool SAME>
+__device__ __forceinline__ bool gemm_half_mainloop(const GemmProblem &P, int tm, int tn, int tid,
+                                                   LoaderF32<64 * TM> &la,
+                                                   LoaderF32<64 * TN> &lb, unsigned short *lds, float *sc,
+                                                   int k0, int k1, int wave_m, int wave_n, int l32, int half,
+                                                   floatx16 (&acc)[TM][TN], float (&rs)[2 * TM], float &rs_rem)
+{
+    constexpr int BM = 64 * TM, BN = 64 * TN;
+    constexpr int PLANE = (BM + BN) * LDP, STAGE = 2 * PLANE;
+    constexpr int SA = BM / 32, SB = SAME ? 0 : BN / 32;
+    const int klen = k1 - k0;                            // more than one K tile
+    const int klen4 = klen & ~3;
+    const int nfull = klen4 / KT;
+    const int nvec = nfull + (klen4 > nfull * KT ? 1 : 0);   // one more full tile ending at k0 + klen4
+    const int nk = nvec + (klen4 < klen ? 1 : 0);
+    float sa[BM / 32], sb[BN / 32];
+    floatx4 ra[BM / 32], rb[BN / 32];
+
+    auto load_tile = [&](int it) {
+        if (it < nfull) {
+            if (it > 0) {
+                la.advance();
+                if constexpr (!SAME) lb.advance();
+            }
+            la.load_full(ra);
+            if constexpr (!SAME) lb.load_full(rb);
+        } else if (it < nvec) {
+            la.seek(k0 + klen4 - KT);
+            la.load_full(ra);
+            if constexpr (!SAME) {
+                lb.seek(k0 + klen4 - KT);
+                lb.load_full(rb);
+            }
+            la.zero_below(k0 + nfull * KT);
+        }
+    };
+    auto store_tile = [&](int it) {
+        unsigned short *st = lds + (it & 1) * STAGE;
+        if (it < nvec) {
+            float unused = 0.f;
+#pragma unroll
+            for (int s = 0; s < SA; ++s) store_half_slot<BM, RS, true>(la, ra[s], st, PLANE, sa[s], rs[s], s);
+#pragma unroll
+            for (int s = 0; s < SB; ++s) store_half_slot<BN, false, true>(lb, rb[s], st + BM * LDP, PLANE, sb[s], unused, s);
+        } else {
+            rs_rem = fill_remainder_half<BM>(P.a, tm * BM, k0 + klen4, k1, tid, st, PLANE, sc);
+            if constexpr (!SAME) fill_remainder_half<BN>(P.b, tn * BN, k0 + klen4, k1, tid, st + BM * LDP, PLANE, sc + BM);
+        }
+    };
+    // v_mfma_f32_32x32x16_f16: a lane supplies 8 consecutive k of row lane % 32, the half-waves two different groups of 8;
+    // half u of a tile uses k = 16u + 8*half + 0..7 (chunk 2u + half of the row) for both operands
+    const int off_a = (wave_m * 32 * TM + l32) * LDP + ((half ^ half_swz(l32)) << 3);
+    const int off_b = ((SAME ? 0 : BM) + wave_n * 32 * TN + l32) * LDP + ((half ^ half_swz(l32)) << 3);
+    halfx8 ah[TM], al[TM], b0[TN], b1[TN];
+    auto read_a = [&](halfx8 (&f)[TM], const unsigned short *st, int plane, int u) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) f[i] = __builtin_bit_cast(halfx8, *(const ushortx8 *)(st + (off_a ^ (u << 4)) + i * 32 * LDP + plane * PLANE));
+    };
+    auto read_b = [&](halfx8 (&f)[TN], const unsigned short *st, int plane, int u) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) f[j] = __builtin_bit_cast(halfx8, *(const ushortx8 *)(st + (off_b ^ (u << 4)) + j * 32 * LDP + plane * PLANE));
+    };
+    // one phase; side(0) behind its first matrix instruction, side(1) behind the middle one.  Fixed order: the scheduling
+    // barriers keep the compiler from drawing loads and conversions together, for which there are no registers.
+    auto mma = [&](const halfx8 (&x)[TM], const halfx8 (&y)[TN], auto side) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < TM * TN; ++n) {
+            const int i = n / TN, j = n % TN;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[i], y[j], acc[i][j], 0, 0, 0);
+            if (n == 0 || 2 * n == TM * TN) {
+                __builtin_amdgcn_sched_barrier(0);
+                side(n != 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto nothing = [](int) {};
+    // the phases of one tile; side(q), q = 0 .. 7, is dealt out over the first four, which lie before the barrier
+    auto phases = [&](const unsigned short *cur, const unsigned short *nxt, bool more, auto side) {
+        if constexpr (LIVE) {
+            read_b(b1, cur, 1, 0);
+            read_a(al, cur, 1, 0);
+            mma(ah, b0, [&](int q) { side(q); });
+            mma(ah, b1, [&](int q) { side(2 + q); });
+            read_b(b1, cur, 0, 1);
+            read_a(ah, cur, 0, 1);
+            mma(al, b0, [&](int q) { side(4 + q); });
+            read_b(b0, cur, 1, 1);
+            read_a(al, cur, 1, 1);
+            mma(ah, b1, [&](int q) { side(6 + q); });
+            __syncthreads();
+            mma(ah, b0, nothing);
+            if (more) {
+                read_b(b0, nxt, 0, 0);
+                read_a(ah, nxt, 0, 0);
+            }
+            mma(al, b1, nothing);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) side(q);
+            __syncthreads();
+        }
+    };
+
+    // the loads of the first tile are on their way while the rows are sampled
+    la.seek(k0);
+    if constexpr (!SAME) lb.seek(k0);
+    load_tile(0);
+    if (!half_scales<BM, BN, SAME>(P, tm, tn, la, lb, k0, klen, sc, tid, sa, sb)) return false;
+    la.seek(k0);
+    if constexpr (!SAME) lb.seek(k0);
+    zero_acc(acc);
+    store_tile(0);
+    load_tile(1);
+    __syncthreads();
+    if constexpr (LIVE) {
+        read_b(b0, lds, 0, 0);
+        read_a(ah, lds, 0, 0);
+    }
+    int it = 0;
+    // The steady state: tile it + 2 is a full one reached by a single wrap of the position.
+    if (la.hw >= KT && lb.hw >= KT)
+        for (; it + 2 < nfull; ++it) {
+            const unsigned short *cur = lds + (it & 1) * STAGE;
+            unsigned short *nxt = lds + ((it + 1) & 1) * STAGE;
+            la.advance_once();
+            if constexpr (!SAME) lb.advance_once();
+            phases(cur, nxt, true, [&](int q) {
+                constexpr int EVERY = 8 / (SA + SB);   // 8, 4 or (one operand) 2 slots
+                if (q % EVERY == 0) {
+                    const int k = q / EVERY;
+                    float unused = 0.f;
+                    if (k < SA) {
+                        store_half_slot<BM, RS, false>(la, ra[k], nxt, PLANE, sa[k], rs[k], k);
+                        la.load_slot(ra, k);
+                    } else if (k < SA + SB) {
+                        store_half_slot<BN, false, false>(lb, rb[k - SA], nxt + BM * LDP, PLANE, sb[k - SA], unused, k - SA);
+                        lb.load_slot(rb, k - SA);
+                    }
+                }
+            });
+        }
+    for (; it < nk; ++it)
+        phases(lds + (it & 1) * STAGE, lds + ((it + 1) & 1) * STAGE, it + 1 < nk, [&](int q) {
+            if (q != 0) return;
+            if (it + 1 < nk) store_tile(it + 1);
+            load_tile(it + 2);
+        });
+    return true;
+}
+
+// Undoes the scales of the rows: acc[i][j][v] is element (row, column) = (8 (v / 4) + 4 half + v % 4, l32) of block (i, j).
+template <int TM, int TN>
+__device__ __forceinline__ void half_unscale_tile(floatx16 (&acc)[TM][TN], const float *sc, int wave_m, int wave_n, int l32, int half)
+{
+    float ub[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) ub[j] = half_unscale(sc[64 * TM + wave_n * 32 * TN + j * 32 + l32]);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const floatx4 s = *(const floatx4 *)(sc + wave_m * 32 * TM + i * 32 + 8 * g + 4 * half);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float ua = half_unscale(s[e]);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j][4 * g + e] = acc[i][j][4 * g + e] * ua * ub[j];
+            }
+        }
+}
+template <int TM, int TN>
+__device__ __forceinline__ bool any_nonfinite(const floatx16 (&acc)[TM][TN])
+{
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) z = fmaf(acc[i][j][v], 0.f, z);
+    return z != 0.f;   // (0 * inf and 0 * NaN are NaN, which differs from 0)
 }
 
 // ------------------------------------------------------------------ transposed operands (NHWC in place)
@@ -837,7 +1240,8 @@ __device__ __forceinline__ void finish_row_sums_trans(const GemmProblem &P, floa
     __syncthreads();
 }
 
-template <int TM, int TN, bool SPLIT, bool TRANS = false>
+// TRANS: the product mode of three bf16 planes on operands stored with the rows contiguous; otherwise the fp32 instruction.
+template <int TM, int TN, bool TRANS>
 __device__ __forceinline__ void gemm_nt_f32_body(const GemmProblem *__restrict__ probs,
                                                  const int *__restrict__ tile_start, int n_probs)
 {
@@ -862,12 +1266,7 @@ __device__ __forceinline__ void gemm_nt_f32_body(const GemmProblem *__restrict__
     lb.init(P.b, tn * BN, tid);
 
     floatx16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    zero_acc(acc);
 
     const int lane = tid & 63, wid = tid >> 6;
     const int wave_m = wid >> 1, wave_n = wid & 1;
@@ -884,26 +1283,11 @@ __device__ __forceinline__ void gemm_nt_f32_body(const GemmProblem *__restrict__
     float rs[BM / 32], rs_rem = 0.f;
 #pragma unroll
     for (int s = 0; s < BM / 32; ++s) rs[s] = 0.f;
-    // a diagonal tile of a Gram matrix (a and b the same operand) stages its operand tile once (64 x 64 tiles
-    // only: the large tile has no registers to spare for one more copy of the main loop)
-    constexpr bool CAN_SHARE = SPLIT && TM == 1 && TN == 1;
-    const bool same = CAN_SHARE && tm == tn && P.a.base == P.b.base && P.a.row_stride == P.b.row_stride &&
-                      P.a.batch_stride == P.b.batch_stride && P.a.hw == P.b.hw && P.a.rows == P.b.rows;
     auto mainloop = [&](auto live_c, auto rs_c) {
-        constexpr bool LV = decltype(live_c)::value, RSUM = decltype(rs_c)::value;
-        if constexpr (SPLIT) {
-            if (CAN_SHARE && same)
-                gemm_split_mainloop<TM, TN, LV, RSUM, CAN_SHARE>(P, tm, tn, tid, la, lb, (unsigned short *)lds, k0, k1,
-                                                                 wave_m, wave_n, l32, half, acc, rs, rs_rem);
-            else
-                gemm_split_mainloop<TM, TN, LV, RSUM, false>(P, tm, tn, tid, la, lb, (unsigned short *)lds, k0, k1, wave_m,
-                                                             wave_n, l32, half, acc, rs, rs_rem);
-        } else
-            gemm_f32_mainloop<TM, TN, LV, RSUM>(P, tm, tn, tid, la, lb, lds, k0, k1, wave_m, wave_n, l32, half, acc, rs,
-                                                rs_rem);
+        gemm_f32_mainloop<TM, TN, decltype(live_c)::value, decltype(rs_c)::value>(P, tm, tn, tid, la, lb, lds, k0, k1, wave_m,
+                                                                                 wave_n, l32, half, acc, rs, rs_rem);
     };
     if constexpr (TRANS) {   // both operands stored with the rows contiguous (a launch of its own)
-        static_assert(SPLIT, "transposed operands: product mode of three bf16 planes only");
         float rst[4] = {0.f, 0.f, 0.f, 0.f};
         unsigned short *l16 = (unsigned short *)lds;
         if (border) {
@@ -969,15 +1353,124 @@ template <int TM, int TN>
 __global__ __launch_bounds__(256, 2) void gemm_nt_f32_split_trans_kernel(const GemmProblem *__restrict__ probs,
                                                                          const int *__restrict__ tile_start, int n_probs)
 {
-    gemm_nt_f32_body<TM, TN, true, true>(probs, tile_start, n_probs);
+    gemm_nt_f32_body<TM, TN, true>(probs, tile_start, n_probs);
 }
 
-// (two wavefronts per SIMD: the register allocation is held to 256)
+// fp32 products through planes: two of fp16, or three of bf16 where the scales do not serve.
+// What bounds it: of its energy, which the clock pays for (1.65 GHz under it), the matrix instructions and fragment reads take
+// about half, the conversion on the way into LDS a third and the loads the rest; without the staging it would run at 540
+// TFLOP/s, without the matrix instructions at 490.  Random operands, 128-tile (64-tile): 4096^3 265 to 290 TFLOP/s against 167
+// to 185 with three planes, ResNet-50's statistics at batch 128 264 (117) against 169 (107), 512 channels at 7x7 (64-tile) 179
+// against 143.  Tiles of 256 x 128 by eight wavefronts were 5 % faster on 4096^3 and too coarse for the rest; 256 x 256 spills.
+// (Two wavefronts per SIMD, four of the small tile: the register allocation is held to 256 and 128.)
 template <int TM, int TN>
-__global__ __launch_bounds__(256, 2) void gemm_nt_f32_split_kernel(const GemmProblem *__restrict__ probs,
-                                                                   const int *__restrict__ tile_start, int n_probs)
+__global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_kernel(const GemmProblem *__restrict__ probs,
+                                                                            const int *__restrict__ tile_start, int n_probs)
 {
-    gemm_nt_f32_body<TM, TN, true>(probs, tile_start, n_probs);
+    constexpr int BM = 64 * TM, BN = 64 * TN;
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // operand stages, then slabs of the output tile; scales behind
+    float *sc = lds + split_lds_bytes<TM, TN>() / sizeof(float) - (BM + BN + 2);
+    unsigned short *l16 = (unsigned short *)lds;
+
+    const int wg = blockIdx.x;
+    const int pi = find_problem(tile_start, n_probs, wg);
+    const GemmProblem &P = probs[pi];
+    const int local = wg - tile_start[pi];
+    if (local >= n_workgroups(P)) return;   // padding up to the next problem
+    int tile, split, tm, tn;
+    const bool part_of_k = locate_tile(P, local, tile, split);   // neighbours: neighbouring tiles of the same K range
+    decode_tile(P, tile, tm, tn);
+    const int k0 = split * P.k_per_split;
+    const int k1 = part_of_k ? min(P.K, k0 + P.k_per_split) : P.K;
+    const int tid = threadIdx.x;
+    LoaderF32<BM> la;
+    LoaderF32<BN> lb;
+    la.init(P.a, tm * BM, tid);
+    lb.init(P.b, tn * BN, tid);
+    const int lane = tid & 63, wid = tid >> 6;
+    const int wave_m = wid >> 1, wave_n = wid & 1;
+    const int l32 = lane & 31, half = lane >> 5;
+
+    // A wavefront whose whole sub-tile lies outside the matrix, or above the diagonal of a
+    // symmetric product, stores nothing: it only helps with the loads and skips the math.
+    const bool diag_tile = (P.flags & GEMM_SYM) && tm == tn;
+    const int wave_r0 = tm * BM + wave_m * 32 * TM, wave_c0 = tn * BN + wave_n * 32 * TN;
+    const bool live = wave_r0 < P.M && wave_c0 < P.N && !(diag_tile && wave_c0 >= wave_r0 + 32 * TM);
+
+    // The diagonal tiles of a bordered problem also take the row sums of their operand rows.
+    const bool border = diag_tile && (P.flags & GEMM_BORDER);
+    floatx16 acc[TM][TN];
+    float rs[BM / 32], rs_rem = 0.f;
+#pragma unroll
+    for (int s = 0; s < BM / 32; ++s) rs[s] = 0.f;
+    // a diagonal tile of a Gram matrix (a and b the same operand) stages its operand tile once (64 x 64 tiles only: the others
+    // have no registers to spare for one more copy of the main loop)
+    constexpr bool CAN_SHARE = TM == 1 && TN == 1;
+    const bool same = CAN_SHARE && tm == tn && P.a.base == P.b.base && P.a.row_stride == P.b.row_stride &&
+                      P.a.batch_stride == P.b.batch_stride && P.a.hw == P.b.hw && P.a.rows == P.b.rows;
+    auto mainloop = [&](auto live_c, auto rs_c) {
+        constexpr bool LV = decltype(live_c)::value, RSUM = decltype(rs_c)::value;
+        // (a single K tile is not worth the scales, which take a memory latency: 64 -> 32 units, 32 samples, as a step 52 us against 51)
+        bool half_ok = k1 - k0 > KT;
+        if (!half_ok)
+            ;
+        else if (CAN_SHARE && same)
+            half_ok = gemm_half_mainloop<TM, TN, LV, RSUM, CAN_SHARE>(P, tm, tn, tid, la, lb, l16, sc, k0, k1, wave_m, wave_n, l32,
+                                                                      half, acc, rs, rs_rem);
+        else
+            half_ok = gemm_half_mainloop<TM, TN, LV, RSUM, false>(P, tm, tn, tid, la, lb, l16, sc, k0, k1, wave_m, wave_n, l32,
+                                                                  half, acc, rs, rs_rem);
+        const bool wide = __syncthreads_or(!half_ok || (LV && any_nonfinite(acc)));
+        if (LV && !wide) half_unscale_tile(acc, sc, wave_m, wave_n, l32, half);
+        if (wide) {
+            zero_acc(acc);
+#pragma unroll
+            for (int s = 0; s < BM / 32; ++s) rs[s] = 0.f;
+            gemm_split_mainloop<TM, TN, LV, RSUM>(P, tm, tn, tid, la, lb, l16, k0, k1, wave_m, wave_n, l32, half, acc, rs,
+                                                          rs_rem);
+        }
+    };
+    if (border) {
+        if (live) mainloop(std::true_type{}, std::true_type{});
+        else      mainloop(std::false_type{}, std::true_type{});
+        finish_row_sums<BM>(P, lds, tm, tile, split, tid, rs, rs_rem);
+    } else {
+        if (live) mainloop(std::true_type{}, std::false_type{});
+        else      mainloop(std::false_type{}, std::false_type{});
+    }
+
+    // accumulator layout of the 32x32 block: column = lane % 32,
+    // row = 8 * (v / 4) + 4 * (lane / 32) + v % 4 for register v = 0..15
+    if (part_of_k) {
+        float *part = P.partial + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = wave_m * 32 * TM + i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+                    const int c = wave_n * 32 * TN + j * 32 + l32;
+                    part[r * BN + c] = acc[i][j][v];
+                }
+    } else {
+        // stage the tile in LDS (the operand stages are dead by now), then store whole rows
+        __syncthreads();
+        if (live) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int r = wave_m * 32 * TM + i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+                        const int c = wave_n * 32 * TN + j * 32 + l32;
+                        lds[r * (BN + 1) + c] = acc[i][j][v];
+                    }
+        }
+        __syncthreads();
+        store_slab<BM, BN>(P, lds, tm * BM, tn * BN, diag_tile, tid);
+    }
 }
 
 // ------------------------------------------------------------------ bf16 operand loader
@@ -1626,10 +2119,10 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmProblem *__r
     if (tm * B + slab * rows >= P.M) return;
     if (rows == 32) {
         if (B == 128) reduce_slab<128, 32>(P, tile, slab, tm, tn, T, sums);
-        else          reduce_slab<64, 32>(P, tile, slab, tm, tn, T, sums);
+        else               reduce_slab<64, 32>(P, tile, slab, tm, tn, T, sums);
     } else {
         if (B == 128) reduce_slab<128, 8>(P, tile, slab, tm, tn, T, sums);
-        else          reduce_slab<64, 8>(P, tile, slab, tm, tn, T, sums);
+        else               reduce_slab<64, 8>(P, tile, slab, tm, tn, T, sums);
     }
 }
 
@@ -1660,29 +2153,12 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_trans_kernel(const GemmProbl
     gemm_nt_bf16_body<TM, TN, false, true>(P, local, lds);
 }
 
-template <int TM, int TN>
-constexpr size_t gemm_lds_bytes()
+template <typename Kernel>
+static hipError_t launch_one(Kernel kernel, bool &configured, size_t lds_bytes, const GemmProblem *probs_dev,
+                             const int *tile_start_dev, int n_probs, int total_wgs, hipStream_t s)
 {
-    const size_t stages = 2 * (64 * TM + 64 * TN) * LDF * sizeof(float);   // same size for LDH bf16 rows
-    const size_t tile = (size_t)(64 * TM) * (64 * TN + 1) * sizeof(float);
-    return stages > tile ? stages : tile;
-}
-
-template <int TM, int TN, int DT>
-static hipError_t launch_one(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, int total_wgs,
-                             hipStream_t s)
-{
-    static_assert(2 * LDH == 4 * LDF, "bf16 and fp32 stages have the same size");
-    constexpr size_t lds_bytes = gemm_lds_bytes<TM, TN>();
-    static_assert(3 * (64 * TM + 64 * TN) * LDQ * sizeof(unsigned short) <= gemm_lds_bytes<TM, TN>(), "the three planes fit");
-    static_assert(3 * KT * (64 * TM + 16 + 64 * TN + 16) * sizeof(unsigned short) <= gemm_lds_bytes<TM, TN>(), "and so do the transposed ones");
-    auto kernel = DT == 0 ? gemm_nt_f32_kernel<TM, TN> : DT == 2 ? gemm_nt_f32_split_kernel<TM, TN>
-                  : DT == 3 ? gemm_nt_f32_split_trans_kernel<TM, TN> : DT == 4 ? gemm_nt_bf16_trans_kernel<TM, TN>
-                  : gemm_nt_bf16_kernel<TM, TN>;
-    static bool configured = false;   // the attribute is per function, set once per process
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds_bytes);
+    if (!configured) {   // the attribute is per function, set once per process
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
@@ -1690,28 +2166,27 @@ static hipError_t launch_one(const GemmProblem *probs_dev, const int *tile_start
     return hipGetLastError();
 }
 
+// dtype 0: fp32 instruction, 1: bf16, 2: fp32 through planes, 3 / 4: 2 / 1 on operands stored transposed
 hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs,
                        int total_wgs, int tile_cfg, int dtype, hipStream_t s)
 {
+    static_assert(2 * LDH == 4 * LDF, "bf16 and fp32 stages have the same size");
+    static_assert(3 * KT * (128 + 16 + 128 + 16) * sizeof(unsigned short) <= gemm_lds_bytes<2, 2>() &&
+                  3 * KT * (64 + 16 + 64 + 16) * sizeof(unsigned short) <= gemm_lds_bytes<1, 1>(), "three transposed planes fit");
     if (total_wgs <= 0) return hipSuccess;
-    if (dtype == 0) {
-        if (tile_cfg == 0) return launch_one<2, 2, 0>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-        return launch_one<1, 1, 0>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
+    static bool configured[5][2];
+    auto go = [&](auto kernel, size_t lds_bytes) {
+        return launch_one(kernel, configured[dtype][tile_cfg == 0], lds_bytes, probs_dev, tile_start_dev, n_probs, total_wgs, s);
+    };
+    constexpr size_t big = gemm_lds_bytes<2, 2>(), small = gemm_lds_bytes<1, 1>();
+    switch (dtype) {
+        case 0: return tile_cfg == 0 ? go(gemm_nt_f32_kernel<2, 2>, big) : go(gemm_nt_f32_kernel<1, 1>, small);
+        case 1: return tile_cfg == 0 ? go(gemm_nt_bf16_kernel<2, 2>, big) : go(gemm_nt_bf16_kernel<1, 1>, small);
+        case 3: return tile_cfg == 0 ? go(gemm_nt_f32_split_trans_kernel<2, 2>, big) : go(gemm_nt_f32_split_trans_kernel<1, 1>, small);
+        case 4: return tile_cfg == 0 ? go(gemm_nt_bf16_trans_kernel<2, 2>, big) : go(gemm_nt_bf16_trans_kernel<1, 1>, small);
     }
-    if (dtype == 4) {   // bf16 operands stored transposed
-        if (tile_cfg == 0) return launch_one<2, 2, 4>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-        return launch_one<1, 1, 4>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-    }
-    if (dtype == 3) {   // the same on operands stored transposed
-        if (tile_cfg == 0) return launch_one<2, 2, 3>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-        return launch_one<1, 1, 3>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-    }
-    if (dtype == 2) {   // fp32 operands, products through three bf16 planes
-        if (tile_cfg == 0) return launch_one<2, 2, 2>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-        return launch_one<1, 1, 2>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-    }
-    if (tile_cfg == 0) return launch_one<2, 2, 1>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
-    return launch_one<1, 1, 1>(probs_dev, tile_start_dev, n_probs, total_wgs, s);
+    if (tile_cfg == 0) return go(gemm_nt_f32_split_kernel<2, 2>, split_lds_bytes<2, 2>());
+    return go(gemm_nt_f32_split_kernel<1, 1>, split_lds_bytes<1, 1>());
 }
 
 hipError_t launch_gemm_reduce(const GemmProblem *probs_dev, const int *red_start_dev, int n_probs,

@@ -43,7 +43,7 @@ struct Tunables {
                          // reductions of the previous one under the matrix launches of the current one)
     double chunk_gf;     // fused step: matrix launches of the later factor phases in parts of about this many
                          // GFLOP (0: whole)
-    int split;           // 1 (default): fp32 products through three bf16 planes and six bf16 matrix instructions
+    int split;           // 1 (default): fp32 products through two fp16 or three bf16 planes and their matrix instructions
                          // (fp32 accuracy at the bf16 unit's rate); 0: the fp32 matrix instruction
     int force_tile;      // 0: the planner chooses; 64 / 128: every product with that tile
     bool worst_case_splits = false;   // set for the workspace bound: every product split as if it were alone in its launch
@@ -287,8 +287,8 @@ int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun)
         kall = std::max(kall, (double)P.K);
     }
     double staged = split ? 6.0 : 0.0;   // the reduction launch
-    if (kmax[0] > 0) staged += 12.0 + std::max(0.050 * kmax[0], 2.0e-4 * wgk[0]);
-    if (kmax[1] > 0) staged += 5.0 + std::max(0.0265 * kmax[1], 8.3e-5 * wgk[1]);
+    if (kmax[0] > 0) staged += 14.0 + std::max(0.026 * kmax[0], 1.1e-4 * wgk[0]);
+    if (kmax[1] > 0) staged += 9.0 + std::max(0.0143 * kmax[1], 5.0e-5 * wgk[1]);
     const double d32 = 5.0 + std::max(0.0066 * kall, 3.65e-5 * wgk[2]);
     const double d64 = 8.0 + std::max(0.013 * kall, 8.0e-5 * wgk[3]);
     if (staged <= std::min(d32, d64)) return -1;
@@ -423,10 +423,11 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
 // ---- products of plain fp32 matrices (the inversion's and the preconditioning's): which kernel takes a phase
 // Estimated microseconds of one launch of `ps` per kernel, fitted to launches of 1 to 30 products of 33 ... 4096 rows on
 // gfx950.  They are measured shapes, not a theory: what they have to get right is which kernel is faster.
-//   128-tile, staged: a compute unit holds two workgroups.  One alone takes 1.7 us a K step of 32 (it waits for its own loads
-//     and barriers), two together 3.0 us a step for both, where the matrix cores' power limit lies (171 TFLOP/s).
-//   64-tile, staged / direct: latency of one workgroup (the direct one halves it: its wavefronts split K), then
-//     100 to 120 TFLOP/s.
+//   128-tile, staged: a compute unit holds two workgroups.  One alone takes 0.82 us a K step of 32 (it waits for its own loads
+//     and barriers), two together 1.77 us a step for both, near the power limit (260 to 290 TFLOP/s); 14 us around that (the
+//     scales of the rows, the first loads, the epilogue).
+//   64-tile, staged: 11 us and the latency of one workgroup, 0.0143 us a column, then 190 to 230 TFLOP/s.
+//   64-tile, direct: half that latency (its wavefronts split K), then 100 to 120 TFLOP/s.
 //   32-tile, direct: a quarter of the latency again and half the rate.
 struct PhaseCost {
     double us;
@@ -458,11 +459,12 @@ PhaseCost cost_128(const Shape *first, const Shape *last)
     }
     auto round = [](double q, double steps) {       // q workgroups of `steps` each
         const double full = std::floor(q / kSlots128), rest = q - kSlots128 * full;
-        const double slope = rest == 0 ? 0.0 : rest <= 256 ? 1.7 + 0.5 * rest / 256 : 2.6 + 0.4 * (rest - 256) / 256;
-        return (3.0 * full + slope) * steps;
+        const double slope = rest == 0 ? 0.0 : rest <= 256 ? 0.82 + 0.17 * rest / 256 : 1.25 + 0.55 * (rest - 256) / 256;
+        return (1.77 * full + slope) * steps;
     };
-    const double head = 11.0 + 3.0 * (work - tail_work) / kSlots128;
-    PhaseCost best{head + (r > 0 ? round(r, tail_work / r) : 0.0), 0, kSlots128, 1};
+    const double head = 14.0 + 1.77 * (work - tail_work) / kSlots128;
+    // (behind a whole round the workgroups of the tail start one by one: 136 tiles of 34 steps add 44 us to 512, not 31)
+    PhaseCost best{head + (r > 0 ? (n > r ? 1.35 : 1.0) * round(r, tail_work / r) : 0.0), 0, kSlots128, 1};
     for (int s = 2; s <= kMaxTailParts && r > 0 && r * s <= kMaxTailWgs && (last - 1)->steps >= 4.0 * s; ++s) {
         const double us = head + round(r * s, tail_work / r / s + 1.5) + 9.0 + 0.03 * r * s;
         if (us < best.us) best = {us, 0, kSlots128, s};
@@ -529,7 +531,7 @@ PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last
         n64 += q->tiles[1];
     }
     const double kmax = first->K;
-    const PhaseCost c64{6.0 + std::max(0.0265 * kmax, 0.0065 * kmax + 6.45e-5 * nk[1]), 1, 0, 1};
+    const PhaseCost c64{11.0 + std::max(0.0143 * kmax, 0.0075 * kmax + 4.2e-5 * nk[1]), 1, 0, 1};
     if (tun.force_tile == 64) return c64;
     PhaseCost best = cost_128(first, last);
     if (tun.force_tile == 128) return best;
@@ -1110,8 +1112,10 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         GemmProblem &P = op.gemm;
         P.a = plain_operand(X21, ld, n2, n1);
         P.b = plain_operand(X11, ld, n1, n1);
+        P.b.diag = 1;
         P.C = Y; P.ldc = ldy; P.Ct = W; P.ldct = ldw;
         P.M = n2; P.N = n1; P.K = n1; P.flags = 0;
+        P.kdiag = X11; P.kdiag_step = ld + 1;
         P.alpha = 1.f; P.beta = 0.f;
         ops.push_back(op);
     }
@@ -1123,6 +1127,7 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         P.b = plain_operand(X21, ld, n2, n1);
         P.C = X22; P.ldc = ld; P.Ct = nullptr;
         P.M = n2; P.N = n2; P.K = n1; P.flags = GEMM_SYM;
+        P.kdiag = X11; P.kdiag_step = ld + 1;
         P.mirror_band = rec_leaf;   // above the diagonal only the leaf inversion reads its source
         P.alpha = -1.f; P.beta = 1.f;
         ops.push_back(op);
@@ -1134,8 +1139,10 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         GemmProblem &P = op.gemm;
         P.a = plain_operand(W, ldw, n1, n2);
         P.b = plain_operand(X22, ld, n2, n2);
+        P.b.diag = 1;
         P.C = X12; P.ldc = ld; P.Ct = X21; P.ldct = ld;
         P.M = n1; P.N = n2; P.K = n2; P.flags = 0;
+        P.kdiag = X22; P.kdiag_step = ld + 1;
         P.alpha = -1.f; P.beta = 0.f;
         ops.push_back(op);
     }
@@ -1147,6 +1154,7 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         P.b = plain_operand(W, ldw, n1, n2);
         P.C = X11; P.ldc = ld; P.Ct = nullptr;
         P.M = n1; P.N = n1; P.K = n2; P.flags = GEMM_SYM;
+        P.kdiag = X22; P.kdiag_step = ld + 1;
         P.alpha = -1.f; P.beta = 1.f;
         ops.push_back(op);
     }
@@ -1419,16 +1427,20 @@ void plan_precondition(Plan &plan, Arena &arena, const Tunables &tun, const Prec
         float *Vt = (float *)arena.take((size_t)dA * ldv * sizeof(float));
         GemmProblem P{};
         P.a = plain_operand(dry ? nullptr : a.A_inv[l], dA, dA, dA);
+        P.a.diag = 1;
         P.b = plain_operand(dry ? nullptr : a.grad_W[l], dA, dG, dA);
         P.C = Vt; P.ldc = ldv; P.Ct = nullptr;
         P.M = dA; P.N = dG; P.K = dA; P.flags = 0;
+        P.kdiag = (const float *)P.a.base; P.kdiag_step = dA + 1;
         P.alpha = 1.f; P.beta = 0.f;
         p1.push_back(P);
         GemmProblem Q{};
         Q.a = plain_operand(dry ? nullptr : a.G_inv[l], dG, dG, dG);
+        Q.a.diag = 1;
         Q.b = plain_operand(Vt, ldv, dA, dG);
         Q.C = dry ? nullptr : a.out[l]; Q.ldc = dA; Q.Ct = nullptr;
         Q.M = dG; Q.N = dA; Q.K = dG; Q.flags = 0;
+        Q.kdiag = (const float *)Q.a.base; Q.kdiag_step = dG + 1;
         Q.alpha = 1.f; Q.beta = 0.f;
         p2.push_back(Q);
     }

@@ -30,6 +30,7 @@ struct Operand {
     int trans;  // 1 (fp32 in the product mode of three bf16 planes, or bf16): the operand is stored with its rows as
                 // the contiguous direction, element (r, m) at base + m * row_stride + r (an NHWC tensor [N*hw, rows]
                 // contracted in place); a chunk is 16 bytes of adjacent rows at one m, rows a whole number of chunks
+    int diag;   // 1: a symmetric matrix whose diagonal may be far larger than the rest (an inverse): element (r, r) at m = r
 };
 
 // GEMM_SYM:    M == N and the product is symmetric (a == b, or a b^T symmetric by construction as in the Schur
@@ -59,6 +60,8 @@ struct GemmProblem {
     int flags;
     int tile_cfg;             // 0: 128x128 tiles, 1: 64x64 tiles; direct kernel: 2: 32x32, 3: 64x64
     float alpha, beta;        // C = alpha * acc + beta * C   (beta == 0: C is not read)
+    const float *kdiag;       // null, or where the contraction runs over the variables of an inverse: its diagonal, element k at
+    long long kdiag_step;     // kdiag[k * kdiag_step] (what scales the variables have; see the two-plane product mode)
 };
 
 // Rows of a partial tile that one workgroup of the reduction sums up.

@@ -1,0 +1,104 @@
+"""fp32 products through two fp16 planes with a scale per operand row (the staged kernels): edges of tiles and K tiles, and what
+happens where the range of fp16 does not cover a row.  Every product stays within the bound of an fp32 sum of fp32 products."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2002_06015_amd import kfac, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _precondition(G, A, W, tile):
+    L = wl.fc_layer(4, A.shape[0], G.shape[0], 0)
+    with kfac.default_options(force_tile=tile):
+        ctx = kfac.Context([L])
+    dev = [[torch.from_numpy(x).cuda()] for x in (G, A, W)]
+    out = torch.full((L.dG * L.dA + 64,), 7.25, device="cuda")
+    kfac.kfac_profile_enable(ctx, True)
+    kfac.kfac_precondition(ctx, [L], *dev, [out])
+    torch.cuda.synchronize()
+    assert {e["variant"] for e in kfac.kfac_profile_read(ctx) if e["kernel"] == "gemm_f32_split"} == {0 if tile == 128 else 1}
+    ctx.close()
+    got = out.cpu().numpy()
+    assert np.all(got[L.dG * L.dA:] == 7.25)
+    return got[:L.dG * L.dA].reshape(L.dG, L.dA).astype(np.float64)
+
+
+def _check(G, A, W, tile):
+    got = _precondition(G, A, W, tile)
+    G, A, W = (x.astype(np.float64) for x in (G, A, W))
+    ref = G @ W @ A.T
+    # products to 2^-22, a sum of K terms K 2^-24 of the sum of magnitudes at most; two contractions follow each other
+    bound = (len(A) + len(G) + 16) * 2.0 ** -23 * (np.abs(G) @ np.abs(W) @ np.abs(A).T)
+    assert np.all(np.abs(got - ref) <= bound)
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+def _sym(rng, n):
+    x = rng.standard_normal((n, n)).astype(np.float32)
+    return np.ascontiguousarray((x + x.T) * np.float32(0.5))
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("d_in,d_out", [(1, 1), (3, 2), (31, 33), (32, 64), (63, 65), (64, 96), (66, 127), (97, 128), (129, 31),
+                                        (161, 130), (255, 257), (391, 100)])
+def test_products_at_tile_edges(d_in, d_out, tile):
+    rng = np.random.default_rng(1000 * d_in + d_out)
+    err = _check(_sym(rng, d_out), _sym(rng, d_in), rng.standard_normal((d_out, d_in)).astype(np.float32), tile)
+    assert err < 1e-6
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+def test_rows_outside_the_range_of_fp16(tile):
+    """Elements the scale was not taken from and that are too large for it (the workgroup repeats the tile), rows that are zero
+    where they are sampled, rows of zeros, subnormal elements; the ends of the fp32 range."""
+    rng = np.random.default_rng(tile)
+    d_in, d_out = 520, 200
+    G, A = _sym(rng, d_out), _sym(rng, d_in)
+    W = rng.standard_normal((d_out, d_in)).astype(np.float32)
+    W[3, 77] = 3e5                      # between the sampled chunks
+    W[5, :] = 0.0
+    W[5, 101] = 2.5                     # likewise, alone in its row
+    W[9] = 0.0
+    W[20, 40:44] = 1e-41
+    _check(G, A, W, tile)
+    for scale in (2.0 ** 100, 2.0 ** -90):
+        _check(G, A, W * np.float32(scale), tile)
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+def test_badly_scaled_variables(tile):
+    """An inverse whose variables differ by up to 2^15 in scale, with gradients of the inverse scales: all terms of a sum are of
+    one size although its factors are not."""
+    rng = np.random.default_rng(7 + tile)
+    d_in, d_out = 300, 70
+    s = np.exp2(rng.integers(-15, 16, d_in)).astype(np.float32)
+    A = _sym(rng, d_in) + 4 * np.eye(d_in, dtype=np.float32)
+    A = np.ascontiguousarray(A * s[:, None] * s[None, :])
+    W = np.ascontiguousarray(rng.standard_normal((d_out, d_in)).astype(np.float32) / s[None, :])
+    _check(np.eye(d_out, dtype=np.float32), A, W, tile)
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("hw", [4, 6, 7, 8])
+def test_statistics_of_channels_of_different_scale(hw, tile):
+    """Factors of a pointwise layer: short runs (the tail path of the main loop), channels from 2^-40 to 2^40, a channel of
+    zeros and one with a single element; bias border."""
+    N, C = 37, 130
+    rng = np.random.default_rng(hw)
+    x = rng.standard_normal((N, C, hw, hw)).astype(np.float32) * np.exp2(rng.integers(-40, 41, (1, C, 1, 1))).astype(np.float32)
+    x[:, 11] = 0.0
+    x[:, 12] = 0.0
+    x[20, 12, 1, 2] = 1.5
+    L = wl.Layer(N, C, 8, 1, 1, 0, hw, hw, 1)
+    with kfac.default_options(force_tile=tile):
+        ctx = kfac.Context([L])
+    A = torch.empty(C + 1, C + 1, device="cuda")
+    kfac.kfac_stats(ctx, [L], kfac.KFAC_F32, [torch.from_numpy(x).cuda()], None, 0.0, True, [A], [torch.empty(8, 8, device="cuda")])
+    torch.cuda.synchronize()
+    ctx.close()
+    m = np.concatenate([x.astype(np.float64).transpose(1, 0, 2, 3).reshape(C, -1), np.ones((1, N * hw * hw))])
+    ref = m @ m.T / m.shape[1]
+    bound = (m.shape[1] + 16) * 2.0 ** -23 * (np.abs(m) @ np.abs(m).T) / m.shape[1]
+    assert np.all(np.abs(A.cpu().numpy() - ref) <= bound)
