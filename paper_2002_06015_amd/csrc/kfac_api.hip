@@ -1321,6 +1321,17 @@ double chain_load(const kfac_layer &L)
     return cube(dA) + cube(dG);
 }
 
+// Whether the inversions of the layers `ids` are spread over streams at all.  Below 10 GFLOP nothing is won by running chains
+// beside each other, since no launch fills the chip, and the launches of one level are merged on one stream but not across two:
+// lists of random layers 3 % faster on one stream on average, up to 15 % (885, 385, 256 rows: 302 us against 348; 7 layers, 826
+// rows and less, bf16: 515 against 592), above 10 GFLOP 3 % slower, up to 20 %.
+bool spread_chains(const kfac_layer *L, const std::vector<int> &ids)
+{
+    double sum = 0;
+    for (int l : ids) sum += chain_load(L[l]);
+    return sum >= 1e10;
+}
+
 // Deals layers (largest chains first) into n_groups groups of similar total n^3.
 std::vector<std::vector<int>> deal_layers(const kfac_layer *L, std::vector<int> ids, int n_groups, int first_group)
 {
@@ -1380,9 +1391,9 @@ void plan_invert(Plan &plan, Arena &arena, const Tunables &tun, const InvertArgs
         Z.n = 2 * a.n_layers;
         plan.launches.push_back(Z);
     }
-    const int n_groups = std::max(1, std::min(tun.inv_streams, 4));
     std::vector<int> all(a.n_layers);
     for (int l = 0; l < a.n_layers; ++l) all[l] = l;
+    const int n_groups = spread_chains(a.L, all) ? std::max(1, std::min(tun.inv_streams, 4)) : 1;
     std::vector<std::vector<int>> groups = tun.by_depth ? deal_by_depth(a.L, all, n_groups, 0) : deal_layers(a.L, all, n_groups, 0);
     bool forked = false;
     // auxiliary groups first, so that their launches are enqueued before the main chain's
@@ -1478,7 +1489,10 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
         Z.n = 2 * n;
         plan.launches.push_back(Z);
     }
-    const int n_aux = std::max(0, std::min(tun.inv_streams, 4) - 1);
+    std::vector<int> inverted_ids;
+    for (int l = 0; l < n; ++l)
+        if (!mask || mask[l]) inverted_ids.push_back(l);
+    const int n_aux = spread_chains(st.L, inverted_ids) ? std::max(0, std::min(tun.inv_streams, 4) - 1) : 0;
     std::vector<int> cls[2], late, late_inv;
     for (int l = 0; l < n; ++l) {
         int dA, dG;
@@ -1512,10 +1526,10 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
     if (pipe) plan.sync(L_RECORD, 6, 0);
     // Beside running chains, the matrix launches of the later phases are cut into successive parts
     // of about chunk_gf GFLOP (at most 8): a chain's workgroups mostly get compute units where a
-    // large launch drains, so more such points let the chains advance (configuration 4: -2 % on
-    // the step, although the parts cost the factor contractions themselves 5-10 %).  Only when
-    // the early chains are long against the contractions they run beside (n^3 per inverse against
-    // K d^2 per factor); with few or short chains the parts only cost (configuration 5: +2.7 %).
+    // large launch drains, so more such points let the chains advance.  Only when the early chains are
+    // long against the contractions they run beside (n^3 per inverse against K d^2 per factor): with
+    // equal work the parts cost more than that gives (the ResNet-50 layer set, ratio 1.6 at batch 32:
+    // 7.7 ms a step in parts, 7.4 whole; bf16 6.6 against 6.35; batch 128, 6.4: +2.7 %).
     auto factor_gf = [&](int l) {
         int dA, dG, h, w;
         layer_ok(st.L[l], &dA, &dG, &h, &w);
@@ -1532,7 +1546,7 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
             }
         for (int l : cls[1]) gf_later += factor_gf(l);
         for (int l : late) gf_later += factor_gf(l);
-        chunked = gf_later <= 2.0 * inv_early;
+        chunked = gf_later <= 0.5 * inv_early;
     }
     bool pre_waited = false;
     int n_phase = 0;
