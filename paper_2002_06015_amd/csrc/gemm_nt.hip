@@ -2031,8 +2031,8 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmProblem &P, int loca
 // One workgroup per slab of rows of a partial tile: sums the partial tiles in a fixed order (reproducible bit for bit) into
 // LDS and applies the same row-wise epilogue.  red_start counts slabs.  A chain of load latencies where the splits are many
 // and the tiles few (13 tiles of 147 parts for the 64-channel correlations): slabs of 8 rows then (red_rows), the splits dealt
-// to the thread groups a slab leaves, 8 loads in flight a thread: 13 tiles 54 -> 33 us, ResNet-50's 64-row
-// tiles (bf16) 77 -> 42 us.
+// to the thread groups a slab leaves, 8 loads in flight a thread, the border's row sums likewise: those 13 tiles 13 us,
+// ResNet-50's 64-row tiles (bf16) 17 us.
 // Few splits stream at the memory's rate and keep slabs of 32 rows, whose mirror image is written in 128-byte pieces.
 template <int B, int ROWS>
 __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int slab, int tm, int tn, float *T, floatx4 *sums)
@@ -2086,15 +2086,22 @@ __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int 
     __syncthreads();
     store_slab<ROWS, B>(P, T, tm * B + slab * ROWS, tn * B, diag_tile, threadIdx.x);
     if (diag_tile && (P.flags & GEMM_BORDER)) {
+        // the row sums: the splits dealt to groups of ROWS threads, whose sums are added in order (one thread after all the
+        // splits of its row is a chain of memory latencies: 79 of them cost 15 us)
+        constexpr int RG = 256 / ROWS;
+        const int r = threadIdx.x % ROWS, g = threadIdx.x / ROWS;
+        const float *prs = P.partial_rs + (long long)tm * P.splits * B + slab * ROWS + r;
+        float sum = 0.f;
+        for (int q = g; q < P.splits; q += RG) sum += prs[(long long)q * B];
+        float *part_sums = (float *)sums;
+        __syncthreads();
+        part_sums[threadIdx.x] = sum;
+        __syncthreads();
         const int row = tm * B + slab * ROWS + threadIdx.x;
         if (threadIdx.x < ROWS && row < P.M) {
-            const float *prs = P.partial_rs + (long long)tm * P.splits * B + slab * ROWS + threadIdx.x;
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int q = 0; q < P.splits; q += 4)
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (q + k < P.splits) sum[k] += prs[(long long)(q + k) * B];
-            store_border(P, row, (sum[0] + sum[1]) + (sum[2] + sum[3]));
+            float total = 0.f;
+            for (int q = 0; q < RG; ++q) total += part_sums[q * ROWS + threadIdx.x];
+            store_border(P, row, total);
         }
         if (tile == 0 && slab == 0 && threadIdx.x == 0) store_corner(P);
     }
