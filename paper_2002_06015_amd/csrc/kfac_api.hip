@@ -818,8 +818,10 @@ void plan_stats(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &
                 J.cols = (float *)arena.take(((size_t)2 * C * N * Lh + 4) * sizeof(float));
                 J.corners = (float *)arena.take(((size_t)4 * C * N + 4) * sizeof(float));
                 J.N = N; J.C = C; J.H = h; J.W = w; J.Hp = Hp; J.Wp = Wp; J.Lw = Lw; J.Lh = Lh;
+                J.magic_pp = PP < 65536 && (long long)N * C * PP < (1LL << 31) ? ~0ULL / (unsigned)PP + 1ULL : 0ULL;
+                J.magic_w = (unsigned)((1ULL << 32) / (unsigned)Wp + 1ULL);
                 J.wg_start = pad_wgs;
-                const long long threads = J.padded_floats / 4 + (2LL * C * N * Lw + 4) + (2LL * C * N * Lh + 4) + 4LL * C * N;
+                const long long threads = J.padded_floats / 4 + (2LL * C * N * (Lw / 4) + 1) + (2LL * C * N * (Lh / 4) + 1) + 4LL * C * N;   // (behind the first term 32 bits are enough: 2^30 planes, 5 x 5 at least, do not fit the memory)
                 pad_wgs += (int)((threads + 255) / 256);
                 pad_bytes += 4.0 * ((double)N * C * hw + (double)J.padded_floats);
                 padjobs.push_back(J);

@@ -90,6 +90,8 @@ struct PadJob {
     float *corners;          // [4][C][N]: (top,left), (top,right), (bottom,left), (bottom,right)
     int N, C, H, W, Lw, Lh;
     int Hp, Wp;              // padded plane: Hp - H >= 2 zero rows on top, Wp - W >= 2 zero columns on the left
+    unsigned long long magic_pp; // floor(2^64 / (Hp Wp)) + 1, or 0: g / (Hp Wp) == mulhi64(g, magic_pp) for g < 2^31 (all positions)
+    unsigned magic_w;            // floor(2^32 / Wp) + 1: r / Wp == mulhi(r, magic_w) for r < Hp Wp < 2^16
     int wg_start;
 };
 
