@@ -352,7 +352,7 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
     if (probs.empty()) return;
     // Tile configuration per problem.  When the phase as a whole keeps the GPU busy with 128x128
     // tiles, each problem takes the big tile unless that is more than 1.5x the work (it moves half the operand
-    // bytes per flop and runs at 183 TFLOP/s against 113, bf16 at 490 to 620 against 200 to 310; 256 x 256, symmetric, is
+    // bytes per flop and runs at 264 TFLOP/s against 117, bf16 at 490 to 620 against 200 to 310; 256 x 256, symmetric, is
     // 3 big tiles or 10 small ones, 1.2x; a 64-row problem 4x); otherwise the latency model decides.
     double tile_steps128 = 0;   // 128x128 tiles times 32-wide K steps: the work of the phase
     for (auto &P : probs) {
