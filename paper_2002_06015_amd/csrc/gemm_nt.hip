@@ -694,14 +694,14 @@ __device__ __forceinline__ void split_half_pair(float x0, float x1, float s, uns
     h = __builtin_bit_cast(unsigned, hh);
     l = __builtin_bit_cast(unsigned, ll);
 }
-// power of two that brings |x| in [2^e, 2^(e+1)) to [2^kHalfTop, 2^(kHalfTop+1)); 1 for x == 0.  (2^118 at most: its reciprocal
-// and the scaled row stay finite.)
+// power of two that brings |x| in [2^e, 2^(e+1)) to [2^kHalfTop, 2^(kHalfTop+1)); 1 for x == 0.  (2^118 at most:
+// the scaled row stays finite.)
 __device__ __forceinline__ float half_scale(float x)
 {
     const int e = (int)(__float_as_uint(x) >> 23);
     return x == 0.f ? 1.f : __uint_as_float((unsigned)min(254 + kHalfTop - e, 127 + 118) << 23);
 }
-__device__ __forceinline__ float half_unscale(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }   // 1 / s
+__device__ __forceinline__ int half_exponent(float s) { return (int)(__float_as_uint(s) >> 23) - 127; }   // log2 of a scale
 __device__ __forceinline__ float max_abs(float m, const floatx4 &v)
 {
     return fmaxf(fmaxf(m, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
@@ -1036,12 +1036,13 @@ __device__ __forceinline__ bool gemm_half_mainloop(const GemmProblem &P, int tm,
 }
 
 // Undoes the scales of the rows: acc[i][j][v] is element (row, column) = (8 (v / 4) + 4 half + v % 4, l32) of block (i, j).
+// Both exponents at once: one after the other, a row near 2^110 against one near 2^-100 leaves the range in between.
 template <int TM, int TN>
 __device__ __forceinline__ void half_unscale_tile(floatx16 (&acc)[TM][TN], const float *sc, int wave_m, int wave_n, int l32, int half)
 {
-    float ub[TN];
+    int eb[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) ub[j] = half_unscale(sc[64 * TM + wave_n * 32 * TN + j * 32 + l32]);
+    for (int j = 0; j < TN; ++j) eb[j] = half_exponent(sc[64 * TM + wave_n * 32 * TN + j * 32 + l32]);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1049,9 +1050,9 @@ __device__ __forceinline__ void half_unscale_tile(floatx16 (&acc)[TM][TN], const
             const floatx4 s = *(const floatx4 *)(sc + wave_m * 32 * TM + i * 32 + 8 * g + 4 * half);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float ua = half_unscale(s[e]);
+                const int ea = half_exponent(s[e]);
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j][4 * g + e] = acc[i][j][4 * g + e] * ua * ub[j];
+                for (int j = 0; j < TN; ++j) acc[i][j][4 * g + e] = __builtin_amdgcn_ldexpf(acc[i][j][4 * g + e], -(ea + eb[j]));
             }
         }
 }

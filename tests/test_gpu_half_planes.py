@@ -68,6 +68,17 @@ def test_rows_outside_the_range_of_fp16(tile):
 
 
 @pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("ea,ew,eg", [(116, -60, 0), (-60, 116, 0), (0, -60, 116), (120, -110, 0), (110, -110, 100)])
+def test_large_against_small(ea, ew, eg, tile):
+    """Either operand near the top of the fp32 range against one near the bottom: the products are of ordinary size."""
+    rng = np.random.default_rng(ea + 2 * ew + 4 * eg + 2000 + tile)
+    d_in, d_out = 260, 190
+    G, A = _sym(rng, d_out) * np.float32(2.0 ** eg), _sym(rng, d_in) * np.float32(2.0 ** ea)
+    err = _check(G, A, (rng.standard_normal((d_out, d_in)) * 2.0 ** ew).astype(np.float32), tile)
+    assert err < 1e-6
+
+
+@pytest.mark.parametrize("tile", [64, 128])
 def test_badly_scaled_variables(tile):
     """An inverse whose variables differ by up to 2^15 in scale, with gradients of the inverse scales: all terms of a sum are of
     one size although its factors are not."""
