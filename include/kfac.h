@@ -99,6 +99,10 @@ typedef enum {
 typedef struct {
     int32_t struct_size;          /* sizeof(kfac_options); any other value is rejected */
     int32_t fp32_products;        /* kfac_products */
+    /* The schedule: streams, pipeline_phases, early_n, group_by_depth, chunk_gflop.  While all five have their defaults,
+     * kfac_step and kfac_invert use the context's stream alone where that is the faster one (inversions below about 10 GFLOP in
+     * all), and no factor launch is cut into parts.  A value other
+     * than the default in any of them makes all five hold for every list. */
     int32_t streams;              /* 1..4: HIP streams a call may use at once (the context's + internal ones); 4 */
     int32_t staging_slots;        /* 2..8: calls the host may run ahead of the device; 2 */
     int32_t correlation_form;     /* A factor of 3x3 / stride 1 / pad 1 layers from displaced image correlations; 1 */
@@ -115,7 +119,8 @@ typedef struct {
     int32_t force_tile;           /* 0: chosen per product; 64 / 128: every product with that tile */
     int32_t group_by_depth;       /* kfac_invert: layers share a stream with layers whose chains are as long (1) or
                                      the streams get equal sums of n^3 (0); 1 */
-    float chunk_gflop;            /* kfac_step: factor launches beside long inversion chains in parts of this size; 48 */
+    float chunk_gflop;            /* kfac_step: factor launches beside long inversion chains in parts of this size (0, and
+                                     the default: whole); 48 */
 } kfac_options;
 
 void kfac_options_default(kfac_options *opt);

@@ -26,6 +26,8 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 constexpr int kTargetWgs = 128, kMinKPerSplit = 512, kMaxKPerWg = 4096;   // defaults of the split rule
+constexpr int kStreams = 4, kEarlyN = 2048;                                // defaults of the schedule
+constexpr float kChunkGflop = 48.0f;
 
 struct Tunables {
     int target_wgs;      // split-K gives a problem at least this many workgroups (if K allows)
@@ -50,6 +52,8 @@ struct Tunables {
     bool chosen_rule;    // a limit of the split rule or the tile was chosen by the caller: the rule holds for every product, the
                          // inversion's and the preconditioning's, too, which are priced phase by phase otherwise
     int by_depth;        // kfac_invert: layers grouped onto streams by the length of their chains (1) or by total n^3 (0)
+    bool chosen_schedule;// a field of the schedule was chosen by the caller: it holds for every list, also where the rules of
+                         // spread_chains and of the parts of factor launches would leave the streams or the parts out
     explicit Tunables(const kfac_options &o)
     {
         target_wgs = std::max(1, o.target_workgroups);
@@ -66,6 +70,7 @@ struct Tunables {
         force_tile = (o.force_tile == 64 || o.force_tile == 128) ? o.force_tile : 0;
         chosen_rule = force_tile != 0 || o.target_workgroups != kTargetWgs || o.min_k_per_split != kMinKPerSplit || o.max_k_per_workgroup != kMaxKPerWg;
         by_depth = o.group_by_depth != 0;
+        chosen_schedule = inv_streams != kStreams || early_n != kEarlyN || !pipe || !by_depth || o.chunk_gflop != kChunkGflop;
     }
 };
 
@@ -75,16 +80,16 @@ kfac_options default_options()
     memset(&o, 0, sizeof(o));
     o.struct_size = (int32_t)sizeof(kfac_options);
     o.fp32_products = KFAC_PRODUCTS_SPLIT_BF16;
-    o.streams = 4;
+    o.streams = kStreams;
     o.staging_slots = 2;
     o.correlation_form = 1;
     o.pipeline_phases = 1;
-    o.early_n = 2048;
+    o.early_n = kEarlyN;
     o.target_workgroups = kTargetWgs;
     o.min_k_per_split = kMinKPerSplit;
     o.max_k_per_workgroup = kMaxKPerWg;
     o.recursion_leaf = 288;
-    o.chunk_gflop = 48.0f;
+    o.chunk_gflop = kChunkGflop;
     o.force_tile = 0;
     o.group_by_depth = 1;
     return o;
@@ -1327,8 +1332,9 @@ double chain_load(const kfac_layer &L)
 // beside each other, since no launch fills the chip, and the launches of one level are merged on one stream but not across two:
 // lists of random layers 3 % faster on one stream on average, up to 15 % (885, 385, 256 rows: 302 us against 348; 7 layers, 826
 // rows and less, bf16: 515 against 592), above 10 GFLOP 3 % slower, up to 20 %.
-bool spread_chains(const kfac_layer *L, const std::vector<int> &ids)
+bool spread_chains(const Tunables &tun, const kfac_layer *L, const std::vector<int> &ids)
 {
+    if (tun.chosen_schedule) return true;
     double sum = 0;
     for (int l : ids) sum += chain_load(L[l]);
     return sum >= 1e10;
@@ -1395,7 +1401,7 @@ void plan_invert(Plan &plan, Arena &arena, const Tunables &tun, const InvertArgs
     }
     std::vector<int> all(a.n_layers);
     for (int l = 0; l < a.n_layers; ++l) all[l] = l;
-    const int n_groups = spread_chains(a.L, all) ? std::max(1, std::min(tun.inv_streams, 4)) : 1;
+    const int n_groups = spread_chains(tun, a.L, all) ? std::max(1, std::min(tun.inv_streams, 4)) : 1;
     std::vector<std::vector<int>> groups = tun.by_depth ? deal_by_depth(a.L, all, n_groups, 0) : deal_layers(a.L, all, n_groups, 0);
     bool forked = false;
     // auxiliary groups first, so that their launches are enqueued before the main chain's
@@ -1491,10 +1497,15 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
         Z.n = 2 * n;
         plan.launches.push_back(Z);
     }
+    auto factor_gf = [&](int l) {
+        int dA, dG, h, w;
+        layer_ok(st.L[l], &dA, &dG, &h, &w);
+        return 1e-9 * (double)st.L[l].N * h * w * ((double)dA * dA + (double)dG * dG);
+    };
     std::vector<int> inverted_ids;
     for (int l = 0; l < n; ++l)
         if (!mask || mask[l]) inverted_ids.push_back(l);
-    const int n_aux = spread_chains(st.L, inverted_ids) ? std::max(0, std::min(tun.inv_streams, 4) - 1) : 0;
+    const int n_aux = spread_chains(tun, st.L, inverted_ids) ? std::max(0, std::min(tun.inv_streams, 4) - 1) : 0;
     std::vector<int> cls[2], late, late_inv;
     for (int l = 0; l < n; ++l) {
         int dA, dG;
@@ -1526,19 +1537,14 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
     const std::vector<int> *phases[3] = {&cls[0], &cls[1], &late};
     const bool pipe = n_aux > 0 && tun.pipe;
     if (pipe) plan.sync(L_RECORD, 6, 0);
-    // Beside running chains, the matrix launches of the later phases are cut into successive parts
-    // of about chunk_gf GFLOP (at most 8): a chain's workgroups mostly get compute units where a
-    // large launch drains, so more such points let the chains advance.  Only when the early chains are
-    // long against the contractions they run beside (n^3 per inverse against K d^2 per factor): with
-    // equal work the parts cost more than that gives (the ResNet-50 layer set, ratio 1.6 at batch 32:
-    // 7.7 ms a step in parts, 7.4 whole; bf16 6.6 against 6.35; batch 128, 6.4: +2.7 %).
-    auto factor_gf = [&](int l) {
-        int dA, dG, h, w;
-        layer_ok(st.L[l], &dA, &dG, &h, &w);
-        return 1e-9 * (double)st.L[l].N * h * w * ((double)dA * dA + (double)dG * dG);
-    };
+    // Where the caller asks for it (a chunk_gflop other than the default), the matrix launches of the later phases are cut into
+    // successive parts of that many GFLOP, at most 8, beside chains that are long against the contractions (n^3 per inverse against
+    // K d^2 per factor): a chain's workgroups mostly get compute units where a large launch drains.  Not by default: with the
+    // contractions as fast as they are the parts cost as much as that gives or more (three to eight factors of 4609 rows beside two
+    // to twelve 128-channel layers at 28 x 28, 48 GFLOP a part: ratio 0.23 6363 us in parts, 6212 whole; 0.46 4263, 4258; 0.69 5895,
+    // 5989 at batch 128 and 7440, 7174 at 64; 1.4 4337, 4015).
     bool chunked = false;
-    if (tun.chunk_gf > 0) {
+    if (tun.chunk_gf > 0 && tun.chunk_gf != kChunkGflop) {
         double inv_early = 0, gf_later = 0;
         for (int c = 0; c < 2; ++c)
             for (int l : cls[c]) {
@@ -1548,7 +1554,7 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
             }
         for (int l : cls[1]) gf_later += factor_gf(l);
         for (int l : late) gf_later += factor_gf(l);
-        chunked = gf_later <= 0.5 * inv_early;
+        chunked = gf_later <= 2.0 * inv_early;
     }
     bool pre_waited = false;
     int n_phase = 0;

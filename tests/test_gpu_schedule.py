@@ -1,0 +1,60 @@
+"""Which schedule a call takes: one stream for little inversion work, several for much of it or where a field of
+the schedule is set; and factor launches in parts where they are asked for.  Seen in the profile of the call."""
+import pytest
+import torch
+
+from paper_2002_06015_amd import kfac, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+SMALL = [wl.conv_layer(2, 40, 130, 3, 1, 1, 10), wl.fc_layer(32, 64, 32), wl.conv_layer(4, 16, 70, 3, 1, 1, 12),
+         wl.conv_layer(2, 8, 5, 1, 1, 0, 6), wl.fc_layer(16, 300, 310), wl.fc_layer(8, 600, 300)]   # chains of two and three leaves
+
+
+def _profile(layers, mask=None, **fields):
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    act = [torch.randn(L.N * L.c_in * L.h_in * L.w_in, device="cuda", generator=gen) for L in layers]
+    grad = [torch.randn(L.M * L.c_out, device="cuda", generator=gen) for L in layers]
+    A, Ai = ([torch.zeros(L.dA, L.dA, device="cuda") for L in layers] for _ in range(2))
+    G, Gi = ([torch.zeros(L.dG, L.dG, device="cuda") for L in layers] for _ in range(2))
+    W, U = ([torch.randn(L.dG, L.dA, device="cuda", generator=gen) for L in layers] for _ in range(2))
+    info = torch.zeros(2 * len(layers), dtype=torch.int32, device="cuda")
+    ctx = kfac.Context(layers, opts=kfac.options(**fields))
+    kfac.kfac_profile_enable(ctx, True)
+    kfac.kfac_step(ctx, layers, kfac.KFAC_F32, act, grad, 0.0, True, A, G, mask, 0.1, Ai, Gi, None, info, W, U)
+    step = kfac.kfac_profile_read(ctx)
+    kfac.kfac_invert(ctx, layers, A, G, 0.1, Ai, Gi, None, info)
+    invert = kfac.kfac_profile_read(ctx)
+    ctx.close()
+    assert not info.cpu().numpy().any()
+    return step, invert
+
+
+def _streams(entries):
+    return {e["stream"] for e in entries}
+
+
+@pytest.mark.parametrize("fields,step,invert", [
+    ({}, {0}, {0}),
+    ({"early_n": 100}, {0, 1, 2, 3}, {0, 1}),
+    ({"early_n": 100, "streams": 2}, {0, 1}, {0, 1}),
+    ({"early_n": 100, "streams": 3, "pipeline_phases": 0}, {0, 1, 2}, {0, 1}),
+    ({"early_n": 100, "streams": 1}, {0}, {0}),
+    ({"group_by_depth": 0}, {0, 1}, {0, 1, 2}),
+])
+def test_fields_of_the_schedule_hold_for_small_lists(fields, step, invert):
+    got = _profile(SMALL, **fields)
+    assert (_streams(got[0]), _streams(got[1])) == (step, invert)
+
+
+def test_default_schedule():
+    """2200 rows are more than 10 GFLOP."""
+    assert len(_streams(_profile([wl.fc_layer(64, 2199, 64)] + SMALL)[0])) > 1
+    assert _streams(_profile([wl.fc_layer(64, 1500, 64)] + SMALL)[0]) == {0}
+
+
+def test_factor_launches_in_parts():
+    def factor_launches(**fields):
+        return sum(e["kernel"] == "gemm_f32_split" and e["stream"] == 0 for e in _profile(SMALL, early_n=100, **fields)[0])
+    whole = factor_launches()
+    assert whole == factor_launches(chunk_gflop=0.0) < factor_launches(chunk_gflop=0.002) < factor_launches(chunk_gflop=0.0001)
