@@ -101,7 +101,7 @@ typedef struct {
     int32_t fp32_products;        /* kfac_products */
     /* The schedule: streams, pipeline_phases, early_n, group_by_depth, chunk_gflop.  While all five have their defaults,
      * kfac_step and kfac_invert use the context's stream alone where that is the faster one (inversions below about 10 GFLOP in
-     * all), and no factor launch is cut into parts.  A value other
+     * all, unless a long chain runs under contractions that take longer), and no factor launch is cut into parts.  A value other
      * than the default in any of them makes all five hold for every list. */
     int32_t streams;              /* 1..4: HIP streams a call may use at once (the context's + internal ones); 4 */
     int32_t staging_slots;        /* 2..8: calls the host may run ahead of the device; 2 */

@@ -1503,9 +1503,23 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
         return 1e-9 * (double)st.L[l].N * h * w * ((double)dA * dA + (double)dG * dG);
     };
     std::vector<int> inverted_ids;
-    for (int l = 0; l < n; ++l)
-        if (!mask || mask[l]) inverted_ids.push_back(l);
-    const int n_aux = spread_chains(tun, st.L, inverted_ids) ? std::max(0, std::min(tun.inv_streams, 4) - 1) : 0;
+    double later_gf = 0, all_n3 = 0;
+    bool early = false;
+    for (int l = 0; l < n; ++l) {
+        const bool inverted = !mask || mask[l];
+        int dA, dG;
+        layer_ok(st.L[l], &dA, &dG, nullptr, nullptr);
+        if (inverted) inverted_ids.push_back(l);
+        if (std::max(dA, dG) < tun.early_n) later_gf += factor_gf(l);
+        else early |= inverted;
+        all_n3 += 1e-9 * chain_load(st.L[l]);
+    }
+    // ... also below 10 GFLOP where one long chain runs under contractions that take longer than it: 2048 -> 500 units (8.7
+    // GFLOP) beside one, four 64-channel 3x3 layers at 56 x 56, 64 samples 930, 1500 us against 980, 1625 on one stream; beside 0.3 GFLOP
+    // of contractions 805 against 747.  (Of the whole list, whatever is inverted: a mask never takes streams, and scratch,
+    // that the whole list would not.)
+    const bool under_contractions = early && later_gf >= 4.0 * all_n3;
+    const int n_aux = under_contractions || spread_chains(tun, st.L, inverted_ids) ? std::max(0, std::min(tun.inv_streams, 4) - 1) : 0;
     std::vector<int> cls[2], late, late_inv;
     for (int l = 0; l < n; ++l) {
         int dA, dG;

@@ -1,5 +1,5 @@
-"""Which schedule a call takes: one stream for little inversion work, several for much of it or where a field of
-the schedule is set; and factor launches in parts where they are asked for.  Seen in the profile of the call."""
+"""Which schedule a call takes: one stream for little inversion work, several for much of it, under long contractions or where a
+field of the schedule is set; and factor launches in parts where they are asked for.  Seen in the profile of the call."""
 import pytest
 import torch
 
@@ -9,6 +9,8 @@ pytestmark = pytest.mark.gpu
 
 SMALL = [wl.conv_layer(2, 40, 130, 3, 1, 1, 10), wl.fc_layer(32, 64, 32), wl.conv_layer(4, 16, 70, 3, 1, 1, 12),
          wl.conv_layer(2, 8, 5, 1, 1, 0, 6), wl.fc_layer(16, 300, 310), wl.fc_layer(8, 600, 300)]   # chains of two and three leaves
+LONG_CHAIN = [wl.fc_layer(64, 2047, 500)]                              # one factor of 2048 rows: 8.6 GFLOP
+CONTRACTIONS = [wl.conv_layer(16, 64, 64, 3, 1, 1, 56, bias=0)] * 4    # 0.2 GFLOP of inversions each, 17 of contractions
 
 
 def _profile(layers, mask=None, **fields):
@@ -48,9 +50,12 @@ def test_fields_of_the_schedule_hold_for_small_lists(fields, step, invert):
 
 
 def test_default_schedule():
-    """2200 rows are more than 10 GFLOP."""
+    """2200 rows are more than 10 GFLOP; 2048 are not, and take streams where their chain runs under contractions."""
     assert len(_streams(_profile([wl.fc_layer(64, 2199, 64)] + SMALL)[0])) > 1
-    assert _streams(_profile([wl.fc_layer(64, 1500, 64)] + SMALL)[0]) == {0}
+    assert _streams(_profile(LONG_CHAIN)[0]) == {0}
+    step, invert = _profile(LONG_CHAIN + CONTRACTIONS)
+    assert len(_streams(step)) > 1 and _streams(invert) == {0}
+    assert _streams(_profile(LONG_CHAIN + CONTRACTIONS, [False] + [True] * 4)[0]) == {0}
 
 
 def test_factor_launches_in_parts():
