@@ -30,17 +30,18 @@
  *     products of the inversion, preconditioning): fp32 accumulation of products
  *     that are exact to fp32 rounding.  By default an fp32 operand is split into
  *     two fp16 planes under a power-of-two scale of its row (three matrix
- *     instructions a block product; rounded to 2^-23 of the element where that is
- *     above 2^-12 of the largest one sampled in its row, to 2^-35 of that largest
- *     one below), or exactly into three bf16 planes (six instructions, every term
- *     above 2^-23 of the product kept) where a row exceeds the range of fp16, the
- *     variables of an inverse differ too much in scale, or the product is small.
+ *     instructions a block product, operands rounded to 2^-23 of the element), or
+ *     exactly into three bf16 planes (six instructions, every term above 2^-23 of
+ *     the product kept) where a row exceeds the range of fp16, its small elements
+ *     decide a sum, the variables of an inverse differ too much in scale, or the
+ *     product is small.  Single sums of that kind are formed in fp32 from the
+ *     operands.
  *     A context created with kfac_options.fp32_products = KFAC_PRODUCTS_FP32_MFMA
  *     uses the fp32 matrix instruction instead.  Range of the default mode: operands
  *     of magnitude 2^-110 and above; smaller ones lose low bits step by step (2^-120:
  *     about 4e-5 relative) and fp32 subnormals are lost; an infinite operand gives
  *     NaN where the fp32 instruction gives infinity.  Results of the two agree to
- *     fp32 rounding of the accumulation.  bf16 operands (kfac_dtype KFAC_BF16) are
+ *     the rounding of fp32 sums.  bf16 operands (kfac_dtype KFAC_BF16) are
  *     multiplied as they are.
  */
 #ifndef KFAC_H

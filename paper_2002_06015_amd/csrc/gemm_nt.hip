@@ -37,14 +37,15 @@ constexpr size_t gemm_lds_bytes()
 }
 
 // the same for the kernel of the products through planes: two stages of two fp16 planes or one of three bf16 planes; the scales
-// of the rows and two flags lie behind
+// and floors of the rows, two flags and the list of sums in doubt lie behind
+constexpr int kMaxDoubts = 128;      // sums of a tile formed again one by one (see the two fp16 planes)
 template <int TM, int TN>
 constexpr size_t split_lds_bytes()
 {
     constexpr size_t rows = 64 * TM + 64 * TN;
     const size_t two = 2 * 2 * rows * 32 * 2, three = 3 * rows * 40 * 2, tile = 64 * TM * (64 * TN + 1) * sizeof(float);
     const size_t most = two > three ? (two > tile ? two : tile) : (three > tile ? three : tile);
-    return (most + 15) / 16 * 16 + (rows + 2) * sizeof(float);
+    return (most + 15) / 16 * 16 + (2 * rows + 2 + 1 + kMaxDoubts) * sizeof(float);
 }
 
 // Final write of a ROWS x COLS slab of accumulated sums held in LDS (T[r][c] at
@@ -667,17 +668,28 @@ __device__ __forceinline__ void gemm_split_mainloop(const GemmProblem &P, int tm
 // times per 16 k instead of six.
 //
 // The range of fp16 is what the scale is for.  A workgroup takes it from its own rows, before its main loop: the largest of up
-// to 128 elements of the row, spread over the workgroup's part of the contraction, goes to [2^10, 2^11) (rows that sample as
-// zero are read in full, rows of an inverse also sample their diagonal element).  Above, there is a factor of 32 to the largest
-// fp16 value; a row that goes beyond it leaves infinities or NaN in the accumulator, which costs nothing to provide for: the
-// workgroup finds them after its loop and repeats it in the three-plane mode, which has the range of fp32.  Below, elements
-// down to 2^-12 of the sampled maximum are exact as above, smaller ones to an absolute 2^-35 of it: in all, 2^-24 of the row's
-// norm or less even where almost every element is that small.  For a Gram matrix that is the scale of its element, sqrt(C_ii C_jj).  Where an operand is an inverse (or is multiplied with one before), the terms of a sum
-// can be of one size although one factor grows along the row as the other falls: variables of different scale.  Their
-// scales are the diagonal of the inverse (P.kdiag); where its square roots spread over more than 2^11, so that an element with
-// weight may lie in the absolute range, the workgroup takes the three-plane mode from the start.
-constexpr int kHalfTop = 10;         // exponent the largest sampled element of a row is brought to
-constexpr int kHalfSpread = kHalfTop + 1;   // see above: spread of a well-scaled contraction, in exponents of the variables
+// to 128 elements of the row, 32 at each of four places, goes to [2^t, 2^(t+1)), t = 10.  (Rows that sample as zero are read on until
+// an element is not; rows of an inverse also sample their diagonal.)
+//   - Above, there is a factor of 32 to the largest fp16 value.  A row that goes beyond it leaves infinities or NaN in the
+//     accumulator, which costs nothing to provide for: the workgroup finds them after its loop and repeats it in the three-plane mode.
+//   - Below, elements down to 2^-2 (scaled) are exact as above, smaller ones to an absolute 2^-25, 2^-(t+25) of the largest.  That
+//     is lost in the sum unless the large elements of a row meet zeros or tiny ones of the other, or one operand falls along k as
+//     the other grows.  The result shows it: K terms off by at most 2^-25 2^t are within 2^-23 K of a sum of 2^(t-2), the bound of
+//     a sum in fp32, and if only one term in q is off, within that of a sum of 2^(t-2) / q.  That is the floor of a row, with q from
+//     32 of the sampled elements (RowSample::floor_of), 128 at most.  Sums below the floors of their rows are formed again one by
+//     one, in fp32 from the operands (statistics of independent rows of random sign have sums of about sqrt(K) 2^18 and floors of
+//     4 together: one tile in a hundred has such a sum; of the products of an inversion one in six).  Where there are many of
+//     them the rows are read: if no element is below 2^-2, or all these sums are zero and no element has become zero, they are
+//     right as they are; otherwise the tile is repeated in the three-plane mode.
+// Where an operand is an inverse (or is multiplied with one before), the scales of the contraction's variables are its diagonal
+// (P.kdiag): where its square roots spread over more than 2^11, so that the sums come out below the floors, the three-plane mode is
+// taken from the start.
+constexpr int kHalfTop = 10;         // t
+constexpr float kHalfFloor = 0x1p8f;
+constexpr float kHalfExact = 0x1p-2f, kHalfNonzero = 0x1p-24f;   // smaller elements are exact in part; become zero
+constexpr int kHalfSpread = kHalfTop + 1;   // spread of a well-scaled contraction, in exponents of the variables
+constexpr int kHalfFew = 8;          // a row with fewer elements of 32 above kHalfExact is dominated by them
+constexpr float kNoFloor = -0x1p100f;   // of rows of zeros, and of rows outside the operand
 constexpr int LDP = 32;              // LDS row length in fp16; 16-byte chunks of a row are permuted instead of padded (half_swz)
 __device__ __forceinline__ int half_swz(int row) { return ((row >> 1) & 3) ^ ((row >> 3) & 1); }
 
@@ -694,12 +706,11 @@ __device__ __forceinline__ void split_half_pair(float x0, float x1, float s, uns
     h = __builtin_bit_cast(unsigned, hh);
     l = __builtin_bit_cast(unsigned, ll);
 }
-// power of two that brings |x| in [2^e, 2^(e+1)) to [2^kHalfTop, 2^(kHalfTop+1)); 1 for x == 0.  (2^118 at most:
-// the scaled row stays finite.)
-__device__ __forceinline__ float half_scale(float x)
+// power of two that brings |x| in [2^e, 2^(e+1)) to [2^top, 2^(top+1)); 1 for x == 0.  (2^118 at most: the scaled row stays finite.)
+__device__ __forceinline__ float half_scale(float x, int top)
 {
     const int e = (int)(__float_as_uint(x) >> 23);
-    return x == 0.f ? 1.f : __uint_as_float((unsigned)min(254 + kHalfTop - e, 127 + 118) << 23);
+    return x == 0.f ? 1.f : __uint_as_float((unsigned)min(254 + top - e, 127 + 118) << 23);
 }
 __device__ __forceinline__ int half_exponent(float s) { return (int)(__float_as_uint(s) >> 23) - 127; }   // log2 of a scale
 __device__ __forceinline__ float max_abs(float m, const floatx4 &v)
@@ -707,7 +718,7 @@ __device__ __forceinline__ float max_abs(float m, const floatx4 &v)
     return fmaxf(fmaxf(m, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
 }
 
-// Largest sampled magnitudes of the thread's rows over [k0, k0 + klen): request() issues the loads of up to four chunks per row,
+// Largest sampled magnitudes of the thread's rows over [k0, k0 + klen): request() issues the loads of four chunks per row and lane,
 // finish() waits for them, so that both operands' loads are in flight together.
 template <int BR>
 struct RowSample {
@@ -734,91 +745,162 @@ struct RowSample {
             for (int k = klen & ~3; k < klen; ++k) mx[s] = fmaxf(mx[s], fabsf(ld.base[ld.rowoff[s] + k0 + k]));   // (plain matrices only)
         }
     }
+    // The floor of the thread's row of slot s under its scale, from one element of each chunk: `most` for a row that a few elements
+    // dominate (whether a small element of the other row meets one of these, no share tells; twice that where hardly any is left),
+    // otherwise by the share of small ones and the mean (of what is above 16, 16), which their errors are measured against.
+    __device__ __forceinline__ float floor_of(float scale, int s, float most) const
+    {
+        float f = 0.f;   // sum of up to 512 + 2^10 times the larger elements + 2^16 times the small ones, to 2^-2
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float y = fabsf(v[e][s][0]) * scale;
+            f += fminf(y, 16.f) + (y >= kHalfExact ? 0x1p10f : y != 0.f ? 0x1p16f : 0.f);
+        }
+        f += __shfl_xor(f, 1);
+        f += __shfl_xor(f, 2);
+        f += __shfl_xor(f, 4);
+        const float n_small = floorf(f * 0x1p-16f);
+        f -= n_small * 0x1p16f;
+        const float n_larger = floorf(f * 0x1p-10f);
+        f -= n_larger * 0x1p10f;
+        return most * (n_larger <= 1.f ? 2.f : n_larger < kHalfFew ? 1.f : fminf(fmaxf(1.f / 128, n_small / (4.f * f)), 1.f));
+    }
 };
-// the same over every element (rows that sampled as zero)
-template <int BR>
-__device__ __forceinline__ void scan_rows(LoaderF32<BR> &ld, int k0, int klen, float (&mx)[BR / 32])
+// over the 8 lanes of a row
+__device__ __forceinline__ float row_max(float x)
 {
-    constexpr int SLOTS = BR / 32;
-    const int nfull = (klen & ~3) / KT;
-    ld.seek(k0);
-    for (int it = 0; it < nfull; ++it) {   // (the remainder was sampled: the last chunk ends at the range end)
-        if (it > 0) ld.advance();
-        floatx4 v[SLOTS];
-        ld.load_full(v);
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) mx[s] = max_abs(mx[s], v[s]);
-    }
-}
-template <int SLOTS>
-__device__ __forceinline__ bool reduce_rows(float (&mx)[SLOTS], unsigned dead)   // over the 8 lanes of a row; true: a row of zeros
-{
-    bool zero = false;
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) {
-        mx[s] = fmaxf(mx[s], __shfl_xor(mx[s], 1));
-        mx[s] = fmaxf(mx[s], __shfl_xor(mx[s], 2));
-        mx[s] = fmaxf(mx[s], __shfl_xor(mx[s], 4));
-        zero |= mx[s] == 0.f && !((dead >> s) & 1);
-    }
-    return zero;
+    x = fmaxf(x, __shfl_xor(x, 1));
+    x = fmaxf(x, __shfl_xor(x, 2));
+    return fmaxf(x, __shfl_xor(x, 4));
 }
 
-// Scales of the rows of both operand tiles into registers and into sc[0 .. BM) and sc[BM .. BM + BN); false: the variables of
-// the contraction are too differently scaled for them (see above).
+// A row [k0, k0 + klen) for a wavefront, 2048 elements at a time, until f(thread's part) says that it is enough.
+template <typename F>
+__device__ __forceinline__ void walk_row(const Operand &op, int row, int k0, int klen, int lane, F f)
+{
+    constexpr int U = 8;
+    gfloat_ptr p = (gfloat_ptr)op.base + (long long)min(row, op.rows - 1) * op.row_stride;
+    const int last = (klen & ~3) - 4;
+    bool enough = false;
+    for (int k = 0; k <= last && !enough; k += 256 * U) {
+        floatx4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {   // (beyond the end: the last four again)
+            const int m = k0 + min(k + 256 * u + 4 * lane, last), n = m < op.hw ? 0 : m / op.hw;
+            v[u] = *(gfloat4_ptr)(p + n * op.batch_stride + (m - n * op.hw));
+        }
+        enough = f(v);
+    }
+    if (!enough && (klen & 3)) {        // (plain matrices only)
+        floatx4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (lane < (klen & 3)) v[0][0] = p[k0 + (klen & ~3) + lane];
+        f(v);
+    }
+}
+
+// Scales of the rows of both operand tiles into registers and into sc[0 .. BM) and sc[BM .. BM + BN), their floors into the BM + BN
+// places behind; false: the two planes do not serve (see above).
 template <int BM, int BN, bool SAME>
 __device__ __forceinline__ bool half_scales(const GemmProblem &P, int tm, int tn, LoaderF32<BM> &la, LoaderF32<BN> &lb,
                                             int k0, int klen, float *sc, int tid, float (&sa)[BM / 32],
                                             float (&sb)[BN / 32])
 {
-    int *range = (int *)(sc + BM + BN);   // largest exponent of kdiag, and 255 minus the smallest
+    int *range = (int *)(sc + 2 * (BM + BN));   // largest exponent of kdiag, and 255 minus the smallest
     if (P.kdiag) {
         if (tid < 2) range[tid] = 0;
         __syncthreads();
     }
-    {
-        RowSample<BM> va;
-        RowSample<BN> vb;
-        va.request(la, k0, klen);
-        if constexpr (!SAME) vb.request(lb, k0, klen);
-        if (P.kdiag) {
-            int hi = 0, lo = 0;
-            for (int k = k0 + tid; k < k0 + klen; k += 256) {
-                const int e = (int)((__float_as_uint(P.kdiag[(long long)k * P.kdiag_step]) >> 23) & 255);
-                hi = max(hi, e);
-                lo = max(lo, 255 - e);
-            }
-            for (int d = 32; d > 4; d >>= 1) { hi = max(hi, __shfl_xor(hi, d)); lo = max(lo, __shfl_xor(lo, d)); }
-            if ((tid & 63) < 8) { atomicMax(range, hi); atomicMax(range + 1, lo); }
+    RowSample<BM> va;
+    RowSample<BN> vb;
+    va.request(la, k0, klen);
+    if constexpr (!SAME) vb.request(lb, k0, klen);
+    if (P.kdiag) {
+        int hi = 0, lo = 0;
+        for (int k = k0 + tid; k < k0 + klen; k += 256) {
+            const int e = (int)((__float_as_uint(P.kdiag[(long long)k * P.kdiag_step]) >> 23) & 255);
+            hi = max(hi, e);
+            lo = max(lo, 255 - e);
         }
-        va.finish(la, P.a, tm * BM, k0, klen, sa);
-        if constexpr (!SAME) vb.finish(lb, P.b, tn * BN, k0, klen, sb);
-    }
-    bool zero = reduce_rows(sa, la.dead);
-    if constexpr (!SAME) zero |= reduce_rows(sb, lb.dead);
-    zero = __syncthreads_or(zero);
-    if (P.kdiag && range[0] + range[1] - 255 > 2 * kHalfSpread) return false;
-    if (zero) {
-        scan_rows<BM>(la, k0, klen, sa);
-        reduce_rows(sa, la.dead);
-        if constexpr (!SAME) {
-            scan_rows<BN>(lb, k0, klen, sb);
-            reduce_rows(sb, lb.dead);
-        }
+        for (int d = 32; d > 4; d >>= 1) { hi = max(hi, __shfl_xor(hi, d)); lo = max(lo, __shfl_xor(lo, d)); }
+        if ((tid & 63) < 8) { atomicMax(range, hi); atomicMax(range + 1, lo); }
     }
     const bool first = (tid & 7) == 0;
+    const int top = kHalfTop;
+    const float most_floor = kHalfFloor;
+    bool odd = false;   // a row of the thread sampled as zero or nearly so
+    auto scales = [&](auto &ld, const auto &v, const Operand &op, int row0, float *out, auto &scale) {
+        constexpr int SLOTS = std::remove_reference_t<decltype(ld)>::SLOTS;
+        v.finish(ld, op, row0, k0, klen, scale);
 #pragma unroll
-    for (int s = 0; s < BM / 32; ++s) {
-        sa[s] = half_scale(sa[s]);
-        if (first) sc[la.r0 + 32 * s] = sa[s];
-    }
+        for (int s = 0; s < SLOTS; ++s) {
+            const float most = row_max(scale[s]);
+            scale[s] = half_scale(most, top);
+            const float floor = v.floor_of(scale[s], s, most_floor);
+            if (most == 0.f) scale[s] = 0.f;
+            odd |= floor > most_floor;
+            if (first) {
+                out[ld.r0 + 32 * s] = scale[s];
+                out[BM + BN + ld.r0 + 32 * s] = (ld.dead >> s) & 1 ? kNoFloor : floor;
+            }
+        }
+    };
+    scales(la, va, P.a, tm * BM, sc, sa);
+    if constexpr (!SAME) scales(lb, vb, P.b, tn * BN, sc + BM, sb);
+    if (__syncthreads_or(odd)) {
+        // rows that sampled as zero are dealt to the wavefronts, which read on until an element is not
+        for (int r = tid >> 6; r < (SAME ? BM : BM + BN); r += 4) {
+            if (sc[r] != 0.f) continue;
+            float mx = 0.f;
+            walk_row(r < BM ? P.a : P.b, r < BM ? tm * BM + r : tn * BN + r - BM, k0, klen, tid & 63, [&](const auto &v) {
 #pragma unroll
-    for (int s = 0; s < BN / 32; ++s) {
-        if constexpr (SAME) sb[s] = sa[s];
-        else sb[s] = half_scale(sb[s]);
-        if (first) sc[BM + lb.r0 + 32 * s] = sb[s];
+                for (const floatx4 &x : v) mx = max_abs(mx, x);
+                for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+                return mx != 0.f;
+            });
+            if ((tid & 63) == 0) {
+                sc[r] = half_scale(mx, top);
+                if (mx == 0.f) sc[BM + BN + r] = kNoFloor;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < BM / 32; ++s) sa[s] = sc[la.r0 + 32 * s];
+        if constexpr (!SAME)
+#pragma unroll
+            for (int s = 0; s < BN / 32; ++s) sb[s] = sc[BM + lb.r0 + 32 * s];
     }
-    return true;
+    if constexpr (SAME) {
+#pragma unroll
+        for (int s = 0; s < BM / 32; ++s) {
+            sb[s] = sa[s];
+            if (first) {
+                sc[BM + la.r0 + 32 * s] = sa[s];
+                sc[BM + BN + BM + la.r0 + 32 * s] = sc[BM + BN + la.r0 + 32 * s];
+            }
+        }
+    }
+    return !(P.kdiag && range[0] + range[1] - 255 > 2 * kHalfSpread);
+}
+
+// Whether an element of the rows of a tile, scaled, is below `least` and not zero (the rows are dealt to the wavefronts).
+template <int BR>
+__device__ __forceinline__ bool any_below(const Operand &op, int tile_row0, int k0, int klen, const float *scales, float least, int tid)
+{
+    bool found = false;
+    for (int r = tid >> 6; r < BR && tile_row0 + r < op.rows && !found; r += 4) {
+        const float limit = __builtin_amdgcn_ldexpf(least, -half_exponent(scales[r]));
+        walk_row(op, tile_row0 + r, k0, klen, tid & 63, [&](const auto &v) {
+#pragma unroll
+            for (const floatx4 &x : v)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) found |= x[e] != 0.f && fabsf(x[e]) < limit;
+            found = __any(found);
+            return found;
+        });
+    }
+    return found;
 }
 
 // One slot of a staged tile into its rows of the two planes (plane stride in fp16 units).  Rows outside the operand repeat its
@@ -855,8 +937,9 @@ __device__ __forceinline__ float fill_remainder_half(const Operand &op, int tile
             if (k4 + e < kend) x[e] = p[e];
     }
     uint2 v[2];
-    split_half_pair(x[0], x[1], sc[tid], v[0].x, v[1].x);
-    split_half_pair(x[2], x[3], sc[tid], v[0].y, v[1].y);
+    const float scale = sc[tid];
+    split_half_pair(x[0], x[1], scale, v[0].x, v[1].x);
+    split_half_pair(x[2], x[3], scale, v[0].y, v[1].y);
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -1035,8 +1118,83 @@ __device__ __forceinline__ bool gemm_half_mainloop(const GemmProblem &P, int tm,
     return true;
 }
 
-// Undoes the scales of the rows: acc[i][j][v] is element (row, column) = (8 (v / 4) + 4 half + v % 4, l32) of block (i, j).
-// Both exponents at once: one after the other, a row near 2^110 against one near 2^-100 leaves the range in between.
+// acc[i][j][v] is element (row, column) = (8 (v / 4) + 4 half + v % 4, l32) of block (i, j).  Returns bit 0 if a sum is below
+// the floors of its rows, bit 1 if one is not finite, bit 2 if one of the former is not zero either.  The
+// former are counted in doubts[0] and the first kMaxDoubts listed behind it (row * 256 + column).
+template <int TM, int TN>
+__device__ __forceinline__ int half_doubts(const floatx16 (&acc)[TM][TN], const float *sc, int *doubts, int wave_m, int wave_n, int l32, int half)
+{
+    const float *floors = sc + 64 * TM + 64 * TN;
+    float fb[TN], z = 0.f, least = 0.f;   // z: (0 * inf and 0 * NaN are NaN, which differs from 0)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fb[j] = floors[64 * TM + wave_n * 32 * TN + j * 32 + l32];
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int row = wave_m * 32 * TM + i * 32 + 8 * g + 4 * half;
+                const floatx4 fa = *(const floatx4 *)(floors + row);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) f(fabsf(acc[i][j][4 * g + e]), fa[e] + fb[j], row + e, wave_n * 32 * TN + j * 32 + l32);
+            }
+    };
+    each([&](float v, float floor, int, int) {
+        z = fmaf(v, 0.f, z);
+        least = fminf(least, v - floor);
+    });
+    int bits = z != 0.f ? 2 : 0;
+    if (least < 0.f)
+        each([&](float v, float floor, int row, int column) {
+            if (v < floor) {
+                bits |= v == 0.f ? 1 : 5;
+                const int n = atomicAdd(doubts, 1);
+                if (n < kMaxDoubts) doubts[1 + n] = row * 256 + column;
+            }
+        });
+    return bits;
+}
+
+// The listed sums in fp32, four per wavefront at a time, into their places in `out` (rows of ld elements).
+template <int BM, int BN>
+__device__ __forceinline__ void half_settle(const GemmProblem &P, const int *doubts, int n, int tm, int tn, int k0, int k1, int tid, float *out, int ld)
+{
+    constexpr int U = 4;
+    const int lane = tid & 63, end4 = k0 + ((k1 - k0) & ~3);
+    for (int q = U * (tid >> 6); q < n; q += 4 * U) {
+        gfloat_ptr a[U], b[U];
+        float sum[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int d = doubts[1 + min(q + u, n - 1)];
+            a[u] = (gfloat_ptr)P.a.base + (long long)(tm * BM + (d >> 8)) * P.a.row_stride;
+            b[u] = (gfloat_ptr)P.b.base + (long long)(tn * BN + (d & 255)) * P.b.row_stride;
+            sum[u] = 0.f;
+        }
+        for (int k = k0 + 4 * lane; k < end4; k += 256) {
+            const int na = k / P.a.hw, nb = k / P.b.hw;
+            const long long ka = na * P.a.batch_stride + (k - na * P.a.hw), kb = nb * P.b.batch_stride + (k - nb * P.b.hw);
+            floatx4 x[U], y[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) { x[u] = *(gfloat4_ptr)(a[u] + ka); y[u] = *(gfloat4_ptr)(b[u] + kb); }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[u] = fmaf(x[u][e], y[u][e], sum[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (end4 + lane < k1) sum[u] = fmaf(a[u][end4 + lane], b[u][end4 + lane], sum[u]);   // (plain matrices only)
+            for (int d = 32; d > 0; d >>= 1) sum[u] += __shfl_xor(sum[u], d);
+            if (lane == 0 && q + u < n) out[(doubts[1 + q + u] >> 8) * ld + (doubts[1 + q + u] & 255)] = sum[u];
+        }
+    }
+}
+
+// Undoes the scales of the rows.  Both exponents at once: one after the other, a row near 2^110 against one near 2^-100 leaves the
+// range in between.
 template <int TM, int TN>
 __device__ __forceinline__ void half_unscale_tile(floatx16 (&acc)[TM][TN], const float *sc, int wave_m, int wave_n, int l32, int half)
 {
@@ -1055,18 +1213,6 @@ __device__ __forceinline__ void half_unscale_tile(floatx16 (&acc)[TM][TN], const
                 for (int j = 0; j < TN; ++j) acc[i][j][4 * g + e] = __builtin_amdgcn_ldexpf(acc[i][j][4 * g + e], -(ea + eb[j]));
             }
         }
-}
-template <int TM, int TN>
-__device__ __forceinline__ bool any_nonfinite(const floatx16 (&acc)[TM][TN])
-{
-    float z = 0.f;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) z = fmaf(acc[i][j][v], 0.f, z);
-    return z != 0.f;   // (0 * inf and 0 * NaN are NaN, which differs from 0)
 }
 
 // ------------------------------------------------------------------ transposed operands (NHWC in place)
@@ -1370,7 +1516,8 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_k
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
     extern __shared__ __attribute__((aligned(16))) float lds[];   // operand stages, then slabs of the output tile; scales behind
-    float *sc = lds + split_lds_bytes<TM, TN>() / sizeof(float) - (BM + BN + 2);
+    float *sc = lds + split_lds_bytes<TM, TN>() / sizeof(float) - (2 * (BM + BN) + 2 + 1 + kMaxDoubts);
+    int *doubts = (int *)(sc + 2 * (BM + BN) + 2);
     unsigned short *l16 = (unsigned short *)lds;
 
     const int wg = blockIdx.x;
@@ -1384,10 +1531,6 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_k
     const int k0 = split * P.k_per_split;
     const int k1 = part_of_k ? min(P.K, k0 + P.k_per_split) : P.K;
     const int tid = threadIdx.x;
-    LoaderF32<BM> la;
-    LoaderF32<BN> lb;
-    la.init(P.a, tm * BM, tid);
-    lb.init(P.b, tn * BN, tid);
     const int lane = tid & 63, wid = tid >> 6;
     const int wave_m = wid >> 1, wave_n = wid & 1;
     const int l32 = lane & 31, half = lane >> 5;
@@ -1402,43 +1545,75 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_k
     const bool border = diag_tile && (P.flags & GEMM_BORDER);
     floatx16 acc[TM][TN];
     float rs[BM / 32], rs_rem = 0.f;
-#pragma unroll
-    for (int s = 0; s < BM / 32; ++s) rs[s] = 0.f;
     // a diagonal tile of a Gram matrix (a and b the same operand) stages its operand tile once (64 x 64 tiles only: the others
     // have no registers to spare for one more copy of the main loop)
     constexpr bool CAN_SHARE = TM == 1 && TN == 1;
     const bool same = CAN_SHARE && tm == tn && P.a.base == P.b.base && P.a.row_stride == P.b.row_stride &&
                       P.a.batch_stride == P.b.batch_stride && P.a.hw == P.b.hw && P.a.rows == P.b.rows;
-    auto mainloop = [&](auto live_c, auto rs_c) {
-        constexpr bool LV = decltype(live_c)::value, RSUM = decltype(rs_c)::value;
-        // (a single K tile is not worth the scales, which take a memory latency: 64 -> 32 units, 32 samples, as a step 52 us against 51)
-        bool half_ok = k1 - k0 > KT;
-        if (!half_ok)
-            ;
-        else if (CAN_SHARE && same)
-            half_ok = gemm_half_mainloop<TM, TN, LV, RSUM, CAN_SHARE>(P, tm, tn, tid, la, lb, l16, sc, k0, k1, wave_m, wave_n, l32,
-                                                                      half, acc, rs, rs_rem);
-        else
-            half_ok = gemm_half_mainloop<TM, TN, LV, RSUM, false>(P, tm, tn, tid, la, lb, l16, sc, k0, k1, wave_m, wave_n, l32,
-                                                                  half, acc, rs, rs_rem);
-        const bool wide = __syncthreads_or(!half_ok || (LV && any_nonfinite(acc)));
-        if (LV && !wide) half_unscale_tile(acc, sc, wave_m, wave_n, l32, half);
-        if (wide) {
-            zero_acc(acc);
-#pragma unroll
-            for (int s = 0; s < BM / 32; ++s) rs[s] = 0.f;
-            gemm_split_mainloop<TM, TN, LV, RSUM>(P, tm, tn, tid, la, lb, l16, k0, k1, wave_m, wave_n, l32, half, acc, rs,
-                                                          rs_rem);
+    auto dispatch = [&](auto f) {
+        if (border) {
+            if (live) f(std::true_type{}, std::true_type{});
+            else      f(std::false_type{}, std::true_type{});
+        } else {
+            if (live) f(std::true_type{}, std::false_type{});
+            else      f(std::false_type{}, std::false_type{});
         }
     };
-    if (border) {
-        if (live) mainloop(std::true_type{}, std::true_type{});
-        else      mainloop(std::false_type{}, std::true_type{});
-        finish_row_sums<BM>(P, lds, tm, tile, split, tid, rs, rs_rem);
-    } else {
-        if (live) mainloop(std::true_type{}, std::false_type{});
-        else      mainloop(std::false_type{}, std::false_type{});
+    auto no_sums = [&]() {
+#pragma unroll
+        for (int s = 0; s < BM / 32; ++s) rs[s] = 0.f;
+    };
+    // (a single K tile is not worth the scales, which take a memory latency: 64 -> 32 units, 32 samples, as a step 52 us against 51)
+    bool wide = k1 - k0 <= KT;
+    int n_doubts = 0;
+    if (!wide) {
+        if (tid == 0) doubts[0] = 0;
+        no_sums();
+        dispatch([&](auto live_c, auto rs_c) {
+            constexpr bool LV = decltype(live_c)::value, RSUM = decltype(rs_c)::value;
+            LoaderF32<BM> la;
+            LoaderF32<BN> lb;
+            la.init(P.a, tm * BM, tid);
+            lb.init(P.b, tn * BN, tid);
+            if (CAN_SHARE && same)
+                wide = !gemm_half_mainloop<TM, TN, LV, RSUM, CAN_SHARE>(P, tm, tn, tid, la, lb, l16, sc, k0, k1, wave_m, wave_n, l32, half, acc,
+                                                                        rs, rs_rem);
+            else
+                wide = !gemm_half_mainloop<TM, TN, LV, RSUM, false>(P, tm, tn, tid, la, lb, l16, sc, k0, k1, wave_m, wave_n, l32, half, acc,
+                                                                    rs, rs_rem);
+        });
     }
+    if (!wide) {
+        const int bits = live ? half_doubts(acc, sc, doubts, wave_m, wave_n, l32, half) : 0;
+        if (__syncthreads_or(bits)) {
+            wide = __syncthreads_or(bits & 2);
+            n_doubts = doubts[0];
+            // (sixteen sums at a time take about 2 us, most of it latency: no more of them than take a part of the tile's time)
+            if (wide || n_doubts > min(kMaxDoubts, 24 + (k1 - k0) / 32)) {
+                n_doubts = 0;
+                if (!wide) {
+                    const float least = __syncthreads_or(bits & 4) ? kHalfExact : kHalfNonzero;
+                    wide = __syncthreads_or(any_below<BM>(P.a, tm * BM, k0, k1 - k0, sc, least, tid) ||
+                                            any_below<BN>(P.b, tn * BN, k0, k1 - k0, sc + BM, least, tid));
+                }
+            }
+        }
+    }
+    if (!wide) {
+        if (live) half_unscale_tile(acc, sc, wave_m, wave_n, l32, half);
+    } else {
+        zero_acc(acc);
+        no_sums();
+        LoaderF32<BM> la;
+        LoaderF32<BN> lb;
+        la.init(P.a, tm * BM, tid);
+        lb.init(P.b, tn * BN, tid);
+        dispatch([&](auto live_c, auto rs_c) {
+            gemm_split_mainloop<TM, TN, decltype(live_c)::value, decltype(rs_c)::value>(P, tm, tn, tid, la, lb, l16, k0, k1, wave_m, wave_n,
+                                                                                        l32, half, acc, rs, rs_rem);
+        });
+    }
+    if (border) finish_row_sums<BM>(P, lds, tm, tile, split, tid, rs, rs_rem);
 
     // accumulator layout of the 32x32 block: column = lane % 32,
     // row = 8 * (v / 4) + 4 * (lane / 32) + v % 4 for register v = 0..15
@@ -1454,6 +1629,10 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_k
                     const int c = wave_n * 32 * TN + j * 32 + l32;
                     part[r * BN + c] = acc[i][j][v];
                 }
+        if (n_doubts) {
+            __syncthreads();
+            half_settle<BM, BN>(P, doubts, n_doubts, tm, tn, k0, k1, tid, part, BN);
+        }
     } else {
         // stage the tile in LDS (the operand stages are dead by now), then store whole rows
         __syncthreads();
@@ -1470,6 +1649,10 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_k
                     }
         }
         __syncthreads();
+        if (n_doubts) {
+            half_settle<BM, BN>(P, doubts, n_doubts, tm, tn, k0, k1, tid, lds, BN + 1);
+            __syncthreads();
+        }
         store_slab<BM, BN>(P, lds, tm * BM, tn * BN, diag_tile, tid);
     }
 }

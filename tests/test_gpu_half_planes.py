@@ -92,6 +92,79 @@ def test_badly_scaled_variables(tile):
 
 
 @pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("place", [0, 37])
+@pytest.mark.parametrize("outlier", [2.0 ** 6, 2.0 ** 14, 2.0 ** 20, 2.0 ** 30, 2.0 ** 60])
+def test_outliers_keep_the_rest_of_their_row(outlier, place, tile):
+    """One element far above the rest of its row, where the row is sampled (0) and where it is not (37 of 391): with identity
+    matrices every result is an element of W, rounded to 2^-23 at most.  What is far enough below its row's largest is formed
+    again from the operand, so it comes out as it is."""
+    rng = np.random.default_rng(place + tile)
+    d_in, d_out = 391, 200
+    W = rng.standard_normal((d_out, d_in)).astype(np.float32)
+    W[::3, place] = outlier
+    got = _precondition(np.eye(d_out, dtype=np.float32), np.eye(d_in, dtype=np.float32), W, tile)
+    # two roundings of 2^-23, one in each product
+    assert np.all(np.abs(got - W) <= 2.0 ** -22 * np.abs(W))
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+def test_ordinary_rows_take_the_two_planes(tile):
+    """With identity matrices a result differs from W where h + l does, one value of four; the three planes are exact, and take the
+    variables of too different scale, here in powers of two.  (The second contraction, of 32 terms, takes them in any case.)"""
+    rng = np.random.default_rng(tile)
+    d_in, d_out = 391, 32
+    W = rng.standard_normal((d_out, d_in)).astype(np.float32)
+    eye = np.eye(d_out, dtype=np.float32)
+    assert 0.2 < np.mean(_precondition(eye, np.eye(d_in, dtype=np.float32), W, tile) != W) < 0.3
+    s = np.exp2(np.arange(d_in) % 41 - 20).astype(np.float32)
+    assert np.array_equal(_precondition(eye, np.diag(s), W / s, tile), W)
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("spread", [8, 10, 12, 20])
+def test_spread_of_an_inverse_around_the_limit(spread, tile):
+    """Variables of scales 2^0 and 2^spread (squares on the diagonal: the limit lies at 2^11), gradients of the inverse scales."""
+    rng = np.random.default_rng(spread + tile)
+    d_in, d_out = 300, 70
+    s = np.exp2(spread * (np.arange(d_in) % 2)).astype(np.float32)
+    A = (_sym(rng, d_in) + 4 * np.eye(d_in, dtype=np.float32)) * s[:, None] * s[None, :]
+    W = (rng.standard_normal((d_out, d_in)) / s[None, :]).astype(np.float32)
+    got = _precondition(np.eye(d_out, dtype=np.float32), np.ascontiguousarray(A), np.ascontiguousarray(W), tile)
+    terms = np.abs(W.astype(np.float64)) @ np.abs(A.astype(np.float64)).T
+    err = np.abs(got - W.astype(np.float64) @ A.astype(np.float64).T) / terms
+    # roundings of random sign: sqrt(300) 2^-24 of the sum of magnitudes, the largest of 21000 at 5 times that
+    assert err.max() <= 5 * np.sqrt(d_in) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+def test_gram_rows_of_disjoint_support(tile):
+    """Channels that are never active together, channels whose large values meet zeros of the others, channels with one image far
+    above the rest and dead ones: every element of the factor to the bound of an fp32 sum of its own terms."""
+    N, C, hw = 48, 140, 8
+    rng = np.random.default_rng(tile)
+    x = rng.standard_normal((N, C, hw, hw)).astype(np.float32)
+    x[: N // 2, 0:20] = 0.0
+    x[N // 2:, 20:40] = 0.0
+    x[:, 40:44] = 0.0
+    x[0, 44:50] = 0.0
+    x[0, 50:56] *= np.float32(2.0 ** 24)
+    x[0, 50:53, 3, 5] = 2.0 ** 30
+    x[17, 60:70] *= np.float32(2.0 ** 9)
+    L = wl.Layer(N, C, 8, 1, 1, 0, hw, hw, 1)
+    with kfac.default_options(force_tile=tile):
+        ctx = kfac.Context([L])
+    A = torch.empty(C + 1, C + 1, device="cuda")
+    kfac.kfac_stats(ctx, [L], kfac.KFAC_F32, [torch.from_numpy(x).cuda()], None, 0.0, True, [A], [torch.empty(8, 8, device="cuda")])
+    torch.cuda.synchronize()
+    ctx.close()
+    m = np.concatenate([x.astype(np.float64).transpose(1, 0, 2, 3).reshape(C, -1), np.ones((1, N * hw * hw))])
+    terms = np.abs(m) @ np.abs(m).T / m.shape[1]
+    err = np.abs(A.cpu().numpy() - m @ m.T / m.shape[1])
+    # roundings of random sign, as above (3072 terms)
+    assert np.all(err <= 5 * np.sqrt(m.shape[1]) * 2.0 ** -24 * terms)
+
+
+@pytest.mark.parametrize("tile", [64, 128])
 @pytest.mark.parametrize("hw", [4, 6, 7, 8])
 def test_statistics_of_channels_of_different_scale(hw, tile):
     """Factors of a pointwise layer: short runs (the tail path of the main loop), channels from 2^-40 to 2^40, a channel of
