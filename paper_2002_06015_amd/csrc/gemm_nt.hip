@@ -576,23 +576,24 @@ __device__ __forceinline__ void gemm_split_mainloop(const GemmProblem &P, int tm
     const int nk = nvec + (klen4 < klen ? 1 : 0);
     if (nk == 0) return;
     floatx4 ra[BM / 32], rb[BN / 32];
-    la.zero_all = false; lb.zero_all = false;
     la.seek(k0); lb.seek(k0);
-    auto stage_tile = [&](int it) {
+    auto load_tile = [&](int it) {   // into registers, a tile ahead
+        if (it < nfull) {
+            if (it > 0) { la.advance(); lb.advance(); }
+            la.load_full(ra); lb.load_full(rb);
+        } else if (it < nvec && careful) {
+            la.load_careful(ra, k0 + klen4); lb.load_careful(rb, k0 + klen4);
+        } else if (it < nvec) {
+            la.seek(k0 + klen4 - KT); lb.seek(k0 + klen4 - KT);
+            la.load_full(ra); lb.load_full(rb);
+            la.zero_below(k0 + nfull * KT);
+        }
+    };
+    auto store_tile = [&](int it) {
         if (it == nvec) {
             rs_rem = fill_remainder_split<BM>(P.a, tm * BM, k0 + klen4, k1, tid, lds, PLANE);
             fill_remainder_split<BN>(P.b, tn * BN, k0 + klen4, k1, tid, lds + BM * LDQ, PLANE);
             return;
-        }
-        if (careful) {
-            la.load_careful(ra, k0 + klen4); lb.load_careful(rb, k0 + klen4);
-        } else if (it < nfull) {
-            if (it > 0) { la.advance(); lb.advance(); }
-            la.load_full(ra); lb.load_full(rb);
-        } else {
-            la.seek(k0 + klen4 - KT); lb.seek(k0 + klen4 - KT);
-            la.load_full(ra); lb.load_full(rb);
-            la.zero_below(k0 + nfull * KT);
         }
         float unused[BN / 32];
         store_split<BM, RS>(la, ra, lds, PLANE, rs);
@@ -648,9 +649,11 @@ __device__ __forceinline__ void gemm_split_mainloop(const GemmProblem &P, int tm
         }
     };
 
+    load_tile(0);
     for (int it = 0; it < nk; ++it) {
         if (it > 0) __syncthreads();   // every wavefront has read the tile before
-        stage_tile(it);
+        store_tile(it);
+        load_tile(it + 1);
         __syncthreads();
         compute();
     }
@@ -668,26 +671,32 @@ __device__ __forceinline__ void gemm_split_mainloop(const GemmProblem &P, int tm
 // times per 16 k instead of six.
 //
 // The range of fp16 is what the scale is for.  A workgroup takes it from its own rows, before its main loop: the largest of up
-// to 128 elements of the row, 32 at each of four places, goes to [2^t, 2^(t+1)), t = 10.  (Rows that sample as zero are read on until
-// an element is not; rows of an inverse also sample their diagonal.)
-//   - Above, there is a factor of 32 to the largest fp16 value.  A row that goes beyond it leaves infinities or NaN in the
-//     accumulator, which costs nothing to provide for: the workgroup finds them after its loop and repeats it in the three-plane mode.
+// to 128 elements of the row, 16 at each of eight places spread over the workgroup's part of the contraction (products with an
+// inverse: 32 at each of four), goes to [2^t, 2^(t+1)).  (Rows that sample as zero are read on until an element is not; rows of
+// an inverse also sample their diagonal.)
+//   - Above, there is room to 2^16.  A row that goes beyond it leaves infinities or NaN in the accumulator, which costs nothing to
+//     provide for: the workgroup finds them after its loop and repeats it in the three-plane mode, which has the range of fp32.
+//     t = 6 leaves statistics a factor of 512 to 1024 (images and pixels differ), t = 10 the products with an inverse 32 to 64
+//     (their largest element is mostly the diagonal one, and the others lie far below it).
 //   - Below, elements down to 2^-2 (scaled) are exact as above, smaller ones to an absolute 2^-25, 2^-(t+25) of the largest.  That
 //     is lost in the sum unless the large elements of a row meet zeros or tiny ones of the other, or one operand falls along k as
 //     the other grows.  The result shows it: K terms off by at most 2^-25 2^t are within 2^-23 K of a sum of 2^(t-2), the bound of
 //     a sum in fp32, and if only one term in q is off, within that of a sum of 2^(t-2) / q.  That is the floor of a row, with q from
 //     32 of the sampled elements (RowSample::floor_of), 128 at most.  Sums below the floors of their rows are formed again one by
-//     one, in fp32 from the operands (statistics of independent rows of random sign have sums of about sqrt(K) 2^18 and floors of
-//     4 together: one tile in a hundred has such a sum; of the products of an inversion one in six).  Where there are many of
+//     one, in fp32 from the operands (statistics of independent rows of random sign have sums of about sqrt(K) 2^10 and floors of
+//     1/4 together: one tile in a hundred has such a sum; of the products of an inversion one in six).  Where there are many of
 //     them the rows are read: if no element is below 2^-2, or all these sums are zero and no element has become zero, they are
 //     right as they are; otherwise the tile is repeated in the three-plane mode.
 // Where an operand is an inverse (or is multiplied with one before), the scales of the contraction's variables are its diagonal
 // (P.kdiag): where its square roots spread over more than 2^11, so that the sums come out below the floors, the three-plane mode is
 // taken from the start.
-constexpr int kHalfTop = 10;         // t
-constexpr float kHalfFloor = 0x1p8f;
+// What the input costs: statistics of 64 to 1024 channels (56 x 56 to 7 x 7, 32 to 128 samples) take the same time, to 7 %, for
+// normal values, images scaled by exp(2 N(0,1)) and fifth powers; 5 % of dead channels cost 14 to 19 %; half of them, or 95 % of
+// zeros, lead to the three-plane mode, whose time that is (541 us against 405 for 512 channels at 7 x 7, 128 samples).
+constexpr int kHalfTop = 6, kHalfTopInverse = 10;   // t
+constexpr float kHalfFloor = 0x1p4f, kHalfFloorInverse = 0x1p8f;
 constexpr float kHalfExact = 0x1p-2f, kHalfNonzero = 0x1p-24f;   // smaller elements are exact in part; become zero
-constexpr int kHalfSpread = kHalfTop + 1;   // spread of a well-scaled contraction, in exponents of the variables
+constexpr int kHalfSpread = kHalfTopInverse + 1;    // spread of a well-scaled contraction, in exponents of the variables
 constexpr int kHalfFew = 8;          // a row with fewer elements of 32 above kHalfExact is dominated by them
 constexpr float kNoFloor = -0x1p100f;   // of rows of zeros, and of rows outside the operand
 constexpr int LDP = 32;              // LDS row length in fp16; 16-byte chunks of a row are permuted instead of padded (half_swz)
@@ -725,12 +734,14 @@ struct RowSample {
     static constexpr int SLOTS = BR / 32;
     floatx4 v[4][SLOTS];
 
-    __device__ __forceinline__ void request(LoaderF32<BR> &ld, int k0, int klen)
+    // four places of 32 elements instead of eight of 16: fewer lines of memory, where the rows are not made of many images
+    __device__ __forceinline__ void request(LoaderF32<BR> &ld, int k0, int klen, bool four)
     {
-        const int span = (klen & ~3) - KT;
+        const int span = (klen & ~3) - (four ? 32 : 16), last = four ? 3 : 7;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            ld.seek(k0 + (q == 3 ? span : (span / 3 * q) & ~3));
+            const int c = four ? q : 2 * q + ld.kq / 16;
+            ld.seek(k0 - (four ? 0 : ld.kq & 16) + (c == last ? span : (span / last * c) & ~3));
             ld.load_full(v[q]);
         }
     }
@@ -814,8 +825,8 @@ __device__ __forceinline__ bool half_scales(const GemmProblem &P, int tm, int tn
     }
     RowSample<BM> va;
     RowSample<BN> vb;
-    va.request(la, k0, klen);
-    if constexpr (!SAME) vb.request(lb, k0, klen);
+    va.request(la, k0, klen, P.kdiag != nullptr);
+    if constexpr (!SAME) vb.request(lb, k0, klen, P.kdiag != nullptr);
     if (P.kdiag) {
         int hi = 0, lo = 0;
         for (int k = k0 + tid; k < k0 + klen; k += 256) {
@@ -827,8 +838,8 @@ __device__ __forceinline__ bool half_scales(const GemmProblem &P, int tm, int tn
         if ((tid & 63) < 8) { atomicMax(range, hi); atomicMax(range + 1, lo); }
     }
     const bool first = (tid & 7) == 0;
-    const int top = kHalfTop;
-    const float most_floor = kHalfFloor;
+    const int top = P.kdiag ? kHalfTopInverse : kHalfTop;
+    const float most_floor = P.kdiag ? kHalfFloorInverse : kHalfFloor;
     bool odd = false;   // a row of the thread sampled as zero or nearly so
     auto scales = [&](auto &ld, const auto &v, const Operand &op, int row0, float *out, auto &scale) {
         constexpr int SLOTS = std::remove_reference_t<decltype(ld)>::SLOTS;
@@ -849,6 +860,11 @@ __device__ __forceinline__ bool half_scales(const GemmProblem &P, int tm, int tn
     scales(la, va, P.a, tm * BM, sc, sa);
     if constexpr (!SAME) scales(lb, vb, P.b, tn * BN, sc + BM, sb);
     if (__syncthreads_or(odd)) {
+        // Where a quarter of the rows on both sides has hardly any elements, too many sums would come out in doubt; and where they have
+        // none that were sampled, reading on costs more than the two planes give.
+        const bool few = tid < (SAME ? BM : BM + BN) && sc[BM + BN + tid] > most_floor;
+        const int n_a = __syncthreads_count(few && tid < BM), n_b = SAME ? n_a : __syncthreads_count(few && tid >= BM);
+        if (4 * n_a > BM && 4 * n_b > BN) return false;
         // rows that sampled as zero are dealt to the wavefronts, which read on until an element is not
         for (int r = tid >> 6; r < (SAME ? BM : BM + BN); r += 4) {
             if (sc[r] != 0.f) continue;
