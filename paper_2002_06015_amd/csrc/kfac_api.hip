@@ -527,23 +527,33 @@ PhaseCost best_kernel_fp32(const Tunables &tun, const Shape *first, const Shape 
     return best;
 }
 
-PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last)
+// The direct kernels are priced at 1 / margin of their time: they add up four partial sums and hold the low-order products apart,
+// where a staged one rounds one sum three times per 16 k.  Preconditioned gradients (512 x 2048, 1000 x 2049): errors of 2.0e-7
+// and 2.1e-7 against 2.9e-7 and 4.7e-7, and up to three times as large staged for one to six layers of 100 to 3000 units; more
+// than a round of 128-tiles pays less for them (eight layers of 1085 units: 174 us against 115), and the large launches of the
+// ResNet-50 set stay staged, and as fast.  Inverses, whose products are not all of the error: residual of 3073 rows of neighbours
+// correlated at 0.95 9.1e-4 against 1.06e-3, 2305 and 4609 rows alike; a step with a 4609-row inverse 2636 us against 2592, and
+// 2803 with 1.75 in the place of 1.3.
+constexpr double kDirectMarginGradients = 1.7, kDirectMarginInverse = 1.3, kDirectMarginFull = 1.4;
+PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last, double margin)
 {
     if (!tun.split) return best_kernel_fp32(tun, first, last);
-    double nk[4] = {0, 0, 0, 0}, n64 = 0;
+    double nk[4] = {0, 0, 0, 0}, n64 = 0, n128 = 0;
     for (const Shape *q = first; q != last; ++q) {
         for (int c = 1; c < 4; ++c) nk[c] += q->tiles[c] * q->K;
         n64 += q->tiles[1];
+        n128 += q->tiles[0];
     }
+    if (n128 > kSlots128) margin = std::min(margin, kDirectMarginFull);
     const double kmax = first->K;
     const PhaseCost c64{11.0 + std::max(0.0143 * kmax, 0.0075 * kmax + 4.2e-5 * nk[1]), 1, 0, 1};
     if (tun.force_tile == 64) return c64;
     PhaseCost best = cost_128(first, last);
     if (tun.force_tile == 128) return best;
     if (c64.us < best.us) best = c64;
-    const PhaseCost d32{5.0 + std::max(0.0066 * kmax, 3.65e-5 * nk[2]), 2, 0, 1};
+    const PhaseCost d32{(5.0 + std::max(0.0066 * kmax, 3.65e-5 * nk[2])) / margin, 2, 0, 1};
     const double per_cu = n64 / 256;
-    const PhaseCost d64{8.0 + std::max((per_cu <= 1 ? 0.013 + 0.006 * per_cu : 0.034) * kmax, 0.0035 * kmax + 6.45e-5 * nk[3]), 3, 0, 1};
+    const PhaseCost d64{(8.0 + std::max((per_cu <= 1 ? 0.013 + 0.006 * per_cu : 0.034) * kmax, 0.0035 * kmax + 6.45e-5 * nk[3])) / margin, 3, 0, 1};
     if (d32.us < best.us) best = d32;
     if (d64.us < best.us) best = d64;
     return best;
@@ -552,7 +562,7 @@ PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last
 // Emits a phase of independent plain products: through one kernel, or through two launches, where the products with the
 // longer contractions take one kernel and the others another, or where 128-tiles take those they fit and another kernel
 // the rest, whichever the estimate prefers.
-void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::vector<GemmProblem> &probs)
+void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::vector<GemmProblem> &probs, double margin)
 {
     if (probs.empty()) return;
     if (tun.chosen_rule) {
@@ -570,9 +580,9 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
     }
     std::stable_sort(all.begin(), all.end(), [](const Shape &x, const Shape &y) { return x.K > y.K; });
     const Shape *first = all.data(), *last = first + all.size(), *cut = last;
-    PhaseCost cost[2] = {best_kernel(tun, first, last), {0, 0, 0, 1}};
+    PhaseCost cost[2] = {best_kernel(tun, first, last, margin), {0, 0, 0, 1}};
     auto consider = [&](const Shape *a, const Shape *b, const Shape *c) {   // [a, b) in one launch, [b, c) in another
-        const PhaseCost x = best_kernel(tun, a, b), y = best_kernel(tun, b, c);
+        const PhaseCost x = best_kernel(tun, a, b, margin), y = best_kernel(tun, b, c, margin);
         if (x.us + y.us >= cost[0].us + cost[1].us) return;
         cost[0] = x; cost[1] = y;
         first = a; cut = b; last = c;
@@ -1263,7 +1273,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             if (op.level == lv && op.kind == OP_GEMM) gp.push_back(op.gemm);
         // split-K scratch of one level is dead once the level's launches are enqueued (in order)
         const size_t mark = arena.used;
-        emit_plain_phase(plan, arena, tun, gp);
+        emit_plain_phase(plan, arena, tun, gp, kDirectMarginInverse);
         arena.release_to(mark);
     }
     if (!bjobs.empty()) {
@@ -1464,9 +1474,9 @@ void plan_precondition(Plan &plan, Arena &arena, const Tunables &tun, const Prec
         p2.push_back(Q);
     }
     const size_t mark = arena.used;
-    emit_plain_phase(plan, arena, tun, p1);
+    emit_plain_phase(plan, arena, tun, p1, kDirectMarginGradients);
     arena.release_to(mark);
-    emit_plain_phase(plan, arena, tun, p2);
+    emit_plain_phase(plan, arena, tun, p2, kDirectMarginGradients);
     arena.release_to(mark);
 }
 

@@ -72,3 +72,28 @@ def test_sums_that_cancel_across_steps(d, d_out, variant):
     M = steps / 4
     rms = ((out.double() - W @ A.t()) / (step * 2.0 ** -24)).pow(2).mean().sqrt()
     assert float(rms) <= ((2 * M * (M + 1) + 7 * M) / 3) ** 0.5
+
+
+@pytest.mark.parametrize("sizes", [[(1879, 1382)], [(2574, 1056), (427, 1047), (134, 214)], [(1000, 512)] * 6])
+def test_error_of_middle_sizes(sizes):
+    """Gradients of middle size keep the direct kernels' error, though a staged one would be the faster by up to 1.7."""
+    layers = [wl.fc_layer(4, d_in, d_out, 0) for d_in, d_out in sizes]
+    gen = torch.Generator(device="cuda").manual_seed(len(sizes))
+
+    def inverse(d):
+        x = torch.randn(d, d, device="cuda", generator=gen) * (0.6 / d ** 0.5)
+        return (x + x.t() + 1.5 * torch.eye(d, device="cuda")).contiguous()
+
+    A, G = [inverse(L.dA) for L in layers], [inverse(L.dG) for L in layers]
+    W = [torch.randn(L.dG, L.dA, device="cuda", generator=gen) for L in layers]
+    U = [torch.empty_like(w) for w in W]
+    ctx = kfac.Context(layers)
+    kfac.kfac_precondition(ctx, layers, G, A, W, U)
+    torch.cuda.synchronize()
+    ctx.close()
+    for L, a, g, w, u in zip(layers, A, G, W, U):
+        ref = g.double() @ w.double() @ a.double()
+        # a wavefront rounds its sum of m = 1 .. K / 64 steps once each, 2^-24 / sqrt(3) of it at most: sqrt(K / 64 / 6) 2^-24 of the
+        # result, and two sums of partial ones per contraction; half as much again for what is not random
+        bound = 1.5 * 2.0 ** -24 * ((L.dA + L.dG) / 64 / 6 + 2) ** 0.5
+        assert float((u.double() - ref).norm() / ref.norm()) <= bound
