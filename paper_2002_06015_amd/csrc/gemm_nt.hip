@@ -2237,6 +2237,8 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmProblem &P, int loca
 template <int B, int ROWS>
 __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int slab, int tm, int tn, float *T, floatx4 *sums)
 {
+    static_assert(B % ROWS == 0 && ROWS % 4 == 0 && ROWS <= kRedRows && B <= 128, "slabs of a tile, in T");
+    static_assert((ROWS * B / 4) % 256 == 0 || 256 % (ROWS * B / 4) == 0, "whole passes, or whole groups of threads");
     const bool diag_tile = (P.flags & GEMM_SYM) && tm == tn;
     const float *part = P.partial + (long long)(tile - P.split_from) * P.splits * (B * B) + slab * ROWS * B;
     // ROWS * B elements, 4 per thread per pass; where they are fewer than 4 per thread, `groups` groups of threads take every
@@ -2310,7 +2312,7 @@ __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int 
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmProblem *__restrict__ probs,
                                                           const int *__restrict__ red_start, int n_probs)
 {
-    __shared__ float T[32 * 129];
+    __shared__ float T[kRedRows * 129];
     __shared__ floatx4 sums[256];
     const int wg = blockIdx.x;
     const int pi = find_problem(red_start, n_probs, wg);
@@ -2324,12 +2326,12 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmProblem *__r
     int tm, tn;
     decode_tile(P, tile, tm, tn);
     if (tm * B + slab * rows >= P.M) return;
-    if (rows == 32) {
-        if (B == 128) reduce_slab<128, 32>(P, tile, slab, tm, tn, T, sums);
-        else               reduce_slab<64, 32>(P, tile, slab, tm, tn, T, sums);
+    if (rows == kRedRows) {
+        if (B == 128) reduce_slab<128, kRedRows>(P, tile, slab, tm, tn, T, sums);
+        else               reduce_slab<64, kRedRows>(P, tile, slab, tm, tn, T, sums);
     } else {
-        if (B == 128) reduce_slab<128, 8>(P, tile, slab, tm, tn, T, sums);
-        else               reduce_slab<64, 8>(P, tile, slab, tm, tn, T, sums);
+        if (B == 128) reduce_slab<128, kRedRowsMany>(P, tile, slab, tm, tn, T, sums);
+        else               reduce_slab<64, kRedRowsMany>(P, tile, slab, tm, tn, T, sums);
     }
 }
 

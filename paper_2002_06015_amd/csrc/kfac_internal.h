@@ -64,8 +64,10 @@ struct GemmProblem {
     long long kdiag_step;     // kdiag[k * kdiag_step] (what scales the variables have; see the two-plane product mode)
 };
 
-// Rows of a partial tile that one workgroup of the reduction sums up.
-__host__ __device__ inline int red_rows(int splits) { return splits > 8 ? 8 : 32; }
+// Rows of a partial tile that one workgroup of the reduction sums up: the launches count slabs of that many, and the kernel
+// has an instance for either.
+constexpr int kRedRows = 32, kRedRowsMany = 8;
+__host__ __device__ inline int red_rows(int splits) { return splits > 8 ? kRedRowsMany : kRedRows; }
 
 // ---- patch extraction ------------------------------------------------------------
 struct PatchJob {
