@@ -9,10 +9,12 @@
 //   - the Schur-complement products of the blocked inverse (Eq. 12);
 //   - the two products of the preconditioned gradient G^-1 dW A^-1 (Eq. 6).
 //
-// Tiling: a 256-thread workgroup (2x2 wavefronts of 64) owns a BM x BN tile; each
-// wavefront owns TM x TN blocks of 32x32 computed with v_mfma_f32_32x32x2_f32 (fp32)
-// or v_mfma_f32_32x32x16_bf16.  The contraction runs in tiles of 32 staged through LDS
-// (two stages in LDS, a third tile in flight in registers).
+// Tiling: a 256-thread workgroup (2x2 wavefronts of 64) owns a BM x BN tile; each wavefront owns TM x TN blocks of 32x32.  The
+// contraction runs in tiles staged through LDS.  The matrix instructions of a block product:
+//   - bf16 operands: v_mfma_f32_32x32x16_bf16;
+//   - fp32 operands by default: v_mfma_f32_32x32x16_f16 on two fp16 planes of each (three per 16 k), or the bf16 one on three bf16
+//     planes (six) where those do not serve and for operands stored transposed;
+//   - fp32 operands on request: v_mfma_f32_32x32x2_f32.
 #include "gemm_tiles.h"
 #include <type_traits>
 

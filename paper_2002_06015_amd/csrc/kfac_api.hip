@@ -264,7 +264,7 @@ void finish_problem(GemmProblem &P)
     if (P.mirror_band == 0) P.mirror_band = INT_MAX;
 }
 
-// Whether a phase of factor products (three-plane mode) runs through a direct kernel (gemm_direct.hip), and which: 2 (32 x 32),
+// Whether a phase of fp32 factor products (through planes) runs through a direct kernel (gemm_direct.hip), and which: 2 (32 x 32),
 // 3 (64 x 64) or -1.  Plain matrices only: fully-connected layers without bias.  All problems go into one launch then, against
 // up to two staged launches and a reduction: both factors of 512 -> 100 units take 17 us (8 to 64 samples) to 21 us (512)
 // instead of 20 to 30; from 1024 units on the staged kernels are as fast.  Microseconds: a fixed part, then either the
@@ -356,9 +356,10 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
 {
     if (probs.empty()) return;
     // Tile configuration per problem.  When the phase as a whole keeps the GPU busy with 128x128
-    // tiles, each problem takes the big tile unless that is more than 1.5x the work (it moves half the operand
-    // bytes per flop and runs at 264 TFLOP/s against 117, bf16 at 490 to 620 against 200 to 310; 256 x 256, symmetric, is
-    // 3 big tiles or 10 small ones, 1.2x; a 64-row problem 4x); otherwise the latency model decides.
+    // tiles, each problem takes the big tile unless that is more than 1.5x the work (it moves half the operand bytes per flop;
+    // 256 x 256, symmetric, is 3 big tiles or 10 small ones, 1.2x; a 64-row problem 4x); otherwise the latency model decides.
+    // Eight pointwise layers at 28 x 28, 64 samples, small tile against big: 160 channels (2.0x) 238 us against 291, 192 (2.0x)
+    // 269 against 313; 320 (1.6x) 579 against 493, so that the line could lie higher for these (bf16: 116, 157; 141, 167; 299, 269).
     double tile_steps128 = 0;   // 128x128 tiles times 32-wide K steps: the work of the phase
     for (auto &P : probs) {
         const double tm = (P.M + 127) / 128, tn = (P.N + 127) / 128;
