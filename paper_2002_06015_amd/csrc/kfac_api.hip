@@ -433,6 +433,7 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
 //     and barriers), two together 1.77 us a step for both, near the power limit (260 to 290 TFLOP/s); 14 us around that (the
 //     scales of the rows, the first loads, the epilogue).
 //   64-tile, staged: 11 us and the latency of one workgroup, 0.0143 us a column, then 190 to 230 TFLOP/s.
+//   Both with three planes: 1.7 us a step alone, 3.0 for two (171 TFLOP/s), 0.0265 us a column (100 to 120 TFLOP/s).
 //   64-tile, direct: half that latency (its wavefronts split K), then 100 to 120 TFLOP/s.
 //   32-tile, direct: a quarter of the latency again and half the rate.
 struct PhaseCost {
@@ -445,13 +446,22 @@ struct Shape {                                      // what the estimate knows o
     const GemmProblem *P;
 };
 
+struct StagedPrices {
+    double head128, pair, alone, alone_rise, two, two_rise;   // 128-tile: fixed part; us a step of a full round, of 1 .. 256 and of 257 .. 511 workgroups
+    double behind;                                            // the workgroups of a tail behind a whole round start one by one: 136 tiles
+                                                              // of 34 steps add 44 us to 512, not 31
+    double head64, column64, share64, rate64;
+};
+constexpr StagedPrices kTwoPlanes{14.0, 1.77, 0.82, 0.17, 1.25, 0.55, 1.35, 11.0, 0.0143, 0.0075, 4.2e-5};
+constexpr StagedPrices kThreePlanes{11.0, 3.0, 1.7, 0.5, 2.6, 0.4, 1.0, 6.0, 0.0265, 0.0065, 6.45e-5};
+
 constexpr int kSlots128 = 512;                      // workgroups of the 128-tile kernel resident at once
 constexpr int kMaxTailParts = 8, kMaxTailWgs = 1024;
 
 // (Shapes in falling order of K.)  The workgroups of a 128-tile launch beyond a whole number of rounds (512) leave most of
 // the chip idle: 513 equal tiles take as long as 768.  Their contractions are cut into `tail_parts`, and a reduction adds
 // the parts up (9 us and 128 KB of traffic per part).
-PhaseCost cost_128(const Shape *first, const Shape *last)
+PhaseCost cost_128(const Shape *first, const Shape *last, const StagedPrices &c)
 {
     double n = 0, work = 0;
     for (const Shape *q = first; q != last; ++q) { n += q->tiles[0]; work += q->tiles[0] * q->steps; }
@@ -459,18 +469,17 @@ PhaseCost cost_128(const Shape *first, const Shape *last)
     double tail_work = 0, left = r;
     for (const Shape *q = last; q != first && left > 0;) {
         --q;
-        const double c = std::min(left, q->tiles[0]);
-        tail_work += c * q->steps;
-        left -= c;
+        const double t = std::min(left, q->tiles[0]);
+        tail_work += t * q->steps;
+        left -= t;
     }
-    auto round = [](double q, double steps) {       // q workgroups of `steps` each
+    auto round = [&](double q, double steps) {      // q workgroups of `steps` each
         const double full = std::floor(q / kSlots128), rest = q - kSlots128 * full;
-        const double slope = rest == 0 ? 0.0 : rest <= 256 ? 0.82 + 0.17 * rest / 256 : 1.25 + 0.55 * (rest - 256) / 256;
-        return (1.77 * full + slope) * steps;
+        const double slope = rest == 0 ? 0.0 : rest <= 256 ? c.alone + c.alone_rise * rest / 256 : c.two + c.two_rise * (rest - 256) / 256;
+        return (c.pair * full + slope) * steps;
     };
-    const double head = 14.0 + 1.77 * (work - tail_work) / kSlots128;
-    // (behind a whole round the workgroups of the tail start one by one: 136 tiles of 34 steps add 44 us to 512, not 31)
-    PhaseCost best{head + (r > 0 ? (n > r ? 1.35 : 1.0) * round(r, tail_work / r) : 0.0), 0, kSlots128, 1};
+    const double head = c.head128 + c.pair * (work - tail_work) / kSlots128;
+    PhaseCost best{head + (r > 0 ? (n > r ? c.behind : 1.0) * round(r, tail_work / r) : 0.0), 0, kSlots128, 1};
     for (int s = 2; s <= kMaxTailParts && r > 0 && r * s <= kMaxTailWgs && (last - 1)->steps >= 4.0 * s; ++s) {
         const double us = head + round(r * s, tail_work / r / s + 1.5) + 9.0 + 0.03 * r * s;
         if (us < best.us) best = {us, 0, kSlots128, s};
@@ -528,30 +537,38 @@ PhaseCost best_kernel_fp32(const Tunables &tun, const Shape *first, const Shape 
     return best;
 }
 
-// The direct kernels are priced at 1 / margin of their time: they add up four partial sums and hold the low-order products apart,
-// where a staged one rounds one sum three times per 16 k.  Preconditioned gradients (512 x 2048, 1000 x 2049): errors of 2.0e-7
-// and 2.1e-7 against 2.9e-7 and 4.7e-7, and up to three times as large staged for one to six layers of 100 to 3000 units; more
-// than a round of 128-tiles pays less for them (eight layers of 1085 units: 174 us against 115), and the large launches of the
-// ResNet-50 set stay staged, and as fast.  Inverses, whose products are not all of the error: residual of 3073 rows of neighbours
-// correlated at 0.95 9.1e-4 against 1.06e-3, 2305 and 4609 rows alike; a step with a 4609-row inverse 2636 us against 2592, and
-// 2803 with 1.75 in the place of 1.3.
-constexpr double kDirectMarginGradients = 1.7, kDirectMarginInverse = 1.3, kDirectMarginFull = 1.4;
-PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last, double margin)
+PhaseCost best_staged(const Tunables &tun, const Shape *first, const Shape *last, const StagedPrices &c)
+{
+    double nk = 0;
+    for (const Shape *q = first; q != last; ++q) nk += q->tiles[1] * q->K;
+    const PhaseCost c64{c.head64 + std::max(c.column64 * first->K, c.share64 * first->K + c.rate64 * nk), 1, 0, 1};
+    if (tun.force_tile == 64) return c64;
+    const PhaseCost c128 = cost_128(first, last, c);
+    return tun.force_tile != 128 && c64.us < c128.us ? c64 : c128;
+}
+
+// The direct kernels err less than the staged ones: they add up four partial sums and hold the low-order products apart, where a
+// staged one rounds one sum three times per 16 k.  With three planes a staged kernel rounds it six times, and is slower.
+//   - Preconditioned gradients, whose products are all of the error (2574 x 1056: 2.2e-7 direct, 6.8e-7 staged), take a direct kernel
+//     where it is the faster one against three planes; the others as the inversion does.  Of 394 gradients in random lists of 1 to 8
+//     layers of 45 to 4600 units none has a larger error than where the faster kernel forms it (mean 2.6e-7 against 3.6e-7), two
+//     a larger one than with three planes throughout (1.2 times; mean 3.5e-7), in the time of the former to 1 % on average (up to 1.4
+//     times: 2049 x 1000 160 us against 111).
+//   - Inverses: the direct kernels at 1 / 1.3 of their time.  Residual of 3073 rows of neighbours correlated at 0.95 9.1e-4 against
+//     1.06e-3, 2305 and 4609 rows alike; a step with a 4609-row inverse 2636 us against 2592, and 2803 with 1.75 in the place of 1.3.
+constexpr double kDirectMarginInverse = 1.3;
+PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last, bool gradients)
 {
     if (!tun.split) return best_kernel_fp32(tun, first, last);
-    double nk[4] = {0, 0, 0, 0}, n64 = 0, n128 = 0;
+    PhaseCost best = best_staged(tun, first, last, gradients ? kThreePlanes : kTwoPlanes);
+    if (tun.force_tile) return best;
+    const double margin = gradients ? 1.0 : kDirectMarginInverse;
+    double nk[4] = {0, 0, 0, 0}, n64 = 0;
     for (const Shape *q = first; q != last; ++q) {
-        for (int c = 1; c < 4; ++c) nk[c] += q->tiles[c] * q->K;
+        for (int c = 2; c < 4; ++c) nk[c] += q->tiles[c] * q->K;
         n64 += q->tiles[1];
-        n128 += q->tiles[0];
     }
-    if (n128 > kSlots128) margin = std::min(margin, kDirectMarginFull);
     const double kmax = first->K;
-    const PhaseCost c64{11.0 + std::max(0.0143 * kmax, 0.0075 * kmax + 4.2e-5 * nk[1]), 1, 0, 1};
-    if (tun.force_tile == 64) return c64;
-    PhaseCost best = cost_128(first, last);
-    if (tun.force_tile == 128) return best;
-    if (c64.us < best.us) best = c64;
     const PhaseCost d32{(5.0 + std::max(0.0066 * kmax, 3.65e-5 * nk[2])) / margin, 2, 0, 1};
     const double per_cu = n64 / 256;
     const PhaseCost d64{(8.0 + std::max((per_cu <= 1 ? 0.013 + 0.006 * per_cu : 0.034) * kmax, 0.0035 * kmax + 6.45e-5 * nk[3])) / margin, 3, 0, 1};
@@ -563,7 +580,7 @@ PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last
 // Emits a phase of independent plain products: through one kernel, or through two launches, where the products with the
 // longer contractions take one kernel and the others another, or where 128-tiles take those they fit and another kernel
 // the rest, whichever the estimate prefers.
-void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::vector<GemmProblem> &probs, double margin)
+void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::vector<GemmProblem> &probs, bool gradients)
 {
     if (probs.empty()) return;
     if (tun.chosen_rule) {
@@ -581,9 +598,9 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
     }
     std::stable_sort(all.begin(), all.end(), [](const Shape &x, const Shape &y) { return x.K > y.K; });
     const Shape *first = all.data(), *last = first + all.size(), *cut = last;
-    PhaseCost cost[2] = {best_kernel(tun, first, last, margin), {0, 0, 0, 1}};
+    PhaseCost cost[2] = {best_kernel(tun, first, last, gradients), {0, 0, 0, 1}};
     auto consider = [&](const Shape *a, const Shape *b, const Shape *c) {   // [a, b) in one launch, [b, c) in another
-        const PhaseCost x = best_kernel(tun, a, b, margin), y = best_kernel(tun, b, c, margin);
+        const PhaseCost x = best_kernel(tun, a, b, gradients), y = best_kernel(tun, b, c, gradients);
         if (x.us + y.us >= cost[0].us + cost[1].us) return;
         cost[0] = x; cost[1] = y;
         first = a; cut = b; last = c;
@@ -597,6 +614,11 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
         const size_t fit = std::stable_partition(by_fit.begin(), by_fit.end(), [](const Shape &q) { return 4.0 * q.tiles[0] <= 1.5 * q.tiles[1]; }) - by_fit.begin();
         if (fit > 0 && fit < by_fit.size()) consider(by_fit.data(), by_fit.data() + fit, by_fit.data() + by_fit.size());
     }
+    if (tun.split && gradients)
+        for (int q = 0; q < 2; ++q) {
+            const Shape *a = q ? cut : first, *b = q ? last : cut;
+            if (a != b && cost[q].cfg < 2) cost[q] = best_kernel(tun, a, b, false);
+        }
     const size_t mark = arena.used;
     for (int q = 0; q < 2; ++q) {
         arena.release_to(mark);   // the second launch starts when the reduction of the first one is done
@@ -1274,7 +1296,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             if (op.level == lv && op.kind == OP_GEMM) gp.push_back(op.gemm);
         // split-K scratch of one level is dead once the level's launches are enqueued (in order)
         const size_t mark = arena.used;
-        emit_plain_phase(plan, arena, tun, gp, kDirectMarginInverse);
+        emit_plain_phase(plan, arena, tun, gp, false);
         arena.release_to(mark);
     }
     if (!bjobs.empty()) {
@@ -1475,9 +1497,9 @@ void plan_precondition(Plan &plan, Arena &arena, const Tunables &tun, const Prec
         p2.push_back(Q);
     }
     const size_t mark = arena.used;
-    emit_plain_phase(plan, arena, tun, p1, kDirectMarginGradients);
+    emit_plain_phase(plan, arena, tun, p1, true);
     arena.release_to(mark);
-    emit_plain_phase(plan, arena, tun, p2, kDirectMarginGradients);
+    emit_plain_phase(plan, arena, tun, p2, true);
     arena.release_to(mark);
 }
 

@@ -76,7 +76,7 @@ def test_sums_that_cancel_across_steps(d, d_out, variant):
 
 @pytest.mark.parametrize("sizes", [[(1879, 1382)], [(2574, 1056), (427, 1047), (134, 214)], [(1000, 512)] * 6])
 def test_error_of_middle_sizes(sizes):
-    """Gradients of middle size keep the direct kernels' error, though a staged one would be the faster by up to 1.7."""
+    """Gradients of middle size keep the direct kernels' error, though a staged one would be the faster by up to 1.5."""
     layers = [wl.fc_layer(4, d_in, d_out, 0) for d_in, d_out in sizes]
     gen = torch.Generator(device="cuda").manual_seed(len(sizes))
 
