@@ -552,17 +552,17 @@ PhaseCost best_staged(const Tunables &tun, const Shape *first, const Shape *last
 //   - Preconditioned gradients, whose products are all of the error (2574 x 1056: 2.2e-7 direct, 6.8e-7 staged), take a direct kernel
 //     where it is the faster one against three planes; the others as the inversion does.  Of 394 gradients in random lists of 1 to 8
 //     layers of 45 to 4600 units none has a larger error than where the faster kernel forms it (mean 2.6e-7 against 3.6e-7), two
-//     a larger one than with three planes throughout (1.2 times; mean 3.5e-7), in the time of the former to 1 % on average (up to 1.4
-//     times: 2049 x 1000 160 us against 111).
+//     a larger one than with three planes throughout (1.2 times; mean 3.5e-7).  All lists take 12.1 ms, 11.6 with the faster kernel,
+//     14.3 with three planes (the most given away: 2049 x 1000, 155 us against 111).
 //   - Inverses: the direct kernels at 1 / 1.3 of their time.  Residual of 3073 rows of neighbours correlated at 0.95 9.1e-4 against
 //     1.06e-3, 2305 and 4609 rows alike; a step with a 4609-row inverse 2636 us against 2592, and 2803 with 1.75 in the place of 1.3.
 constexpr double kDirectMarginInverse = 1.3;
-PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last, bool gradients)
+PhaseCost best_kernel(const Tunables &tun, const Shape *first, const Shape *last, bool three_planes)
 {
     if (!tun.split) return best_kernel_fp32(tun, first, last);
-    PhaseCost best = best_staged(tun, first, last, gradients ? kThreePlanes : kTwoPlanes);
+    PhaseCost best = best_staged(tun, first, last, three_planes ? kThreePlanes : kTwoPlanes);
     if (tun.force_tile) return best;
-    const double margin = gradients ? 1.0 : kDirectMarginInverse;
+    const double margin = three_planes ? 1.0 : kDirectMarginInverse;
     double nk[4] = {0, 0, 0, 0}, n64 = 0;
     for (const Shape *q = first; q != last; ++q) {
         for (int c = 2; c < 4; ++c) nk[c] += q->tiles[c] * q->K;
@@ -597,28 +597,33 @@ void emit_plain_phase(Plan &plan, Arena &arena, const Tunables &tun, const std::
         all.push_back(q);
     }
     std::stable_sort(all.begin(), all.end(), [](const Shape &x, const Shape &y) { return x.K > y.K; });
-    const Shape *first = all.data(), *last = first + all.size(), *cut = last;
-    PhaseCost cost[2] = {best_kernel(tun, first, last, gradients), {0, 0, 0, 1}};
-    auto consider = [&](const Shape *a, const Shape *b, const Shape *c) {   // [a, b) in one launch, [b, c) in another
-        const PhaseCost x = best_kernel(tun, a, b, gradients), y = best_kernel(tun, b, c, gradients);
-        if (x.us + y.us >= cost[0].us + cost[1].us) return;
-        cost[0] = x; cost[1] = y;
-        first = a; cut = b; last = c;
-    };
-    std::vector<Shape> by_fit;
-    if (!tun.force_tile) {
-        const Shape *end = last;
-        for (const Shape *q = all.data() + 1; q < end; ++q)
+    std::vector<Shape> by_fit = all;
+    const size_t fit = std::stable_partition(by_fit.begin(), by_fit.end(), [](const Shape &q) { return 4.0 * q.tiles[0] <= 1.5 * q.tiles[1]; }) - by_fit.begin();
+    const Shape *first, *cut, *last;
+    PhaseCost cost[2];
+    auto choose = [&](bool three_planes) {
+        first = all.data();
+        cut = last = first + all.size();
+        cost[0] = best_kernel(tun, first, last, three_planes);
+        cost[1] = {0, 0, 0, 1};
+        auto consider = [&](const Shape *a, const Shape *b, const Shape *c) {   // [a, b) in one launch, [b, c) in another
+            const PhaseCost x = best_kernel(tun, a, b, three_planes), y = best_kernel(tun, b, c, three_planes);
+            if (x.us + y.us >= cost[0].us + cost[1].us) return;
+            cost[0] = x; cost[1] = y;
+            first = a; cut = b; last = c;
+        };
+        if (tun.force_tile) return;
+        for (const Shape *q = all.data() + 1, *end = all.data() + all.size(); q < end; ++q)
             if (q->K != q[-1].K) consider(all.data(), q, end);
-        by_fit = all;
-        const size_t fit = std::stable_partition(by_fit.begin(), by_fit.end(), [](const Shape &q) { return 4.0 * q.tiles[0] <= 1.5 * q.tiles[1]; }) - by_fit.begin();
         if (fit > 0 && fit < by_fit.size()) consider(by_fit.data(), by_fit.data() + fit, by_fit.data() + by_fit.size());
+    };
+    choose(gradients);
+    if (tun.split && gradients) {
+        if (cost[0].cfg < 2 && cost[1].cfg < 2) choose(false);
+        else if (cut != last)
+            for (int q = 0; q < 2; ++q)
+                if (cost[q].cfg < 2) cost[q] = best_kernel(tun, q ? cut : first, q ? last : cut, false);
     }
-    if (tun.split && gradients)
-        for (int q = 0; q < 2; ++q) {
-            const Shape *a = q ? cut : first, *b = q ? last : cut;
-            if (a != b && cost[q].cfg < 2) cost[q] = best_kernel(tun, a, b, false);
-        }
     const size_t mark = arena.used;
     for (int q = 0; q < 2; ++q) {
         arena.release_to(mark);   // the second launch starts when the reduction of the first one is done
