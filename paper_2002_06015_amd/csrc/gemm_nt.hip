@@ -1524,9 +1524,9 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_f32_split_trans_kernel(const G
 // fp32 products through planes: two of fp16, or three of bf16 where the scales do not serve.
 // What bounds it: of its energy, which the clock pays for (1.65 GHz under it), the matrix instructions and fragment reads take
 // about half, the conversion on the way into LDS a third and the loads the rest; without the staging it would run at 540
-// TFLOP/s, without the matrix instructions at 490.  Random operands, 128-tile (64-tile): 4096^3 265 to 290 TFLOP/s against 167
-// to 185 with three planes, ResNet-50's statistics at batch 128 264 (117) against 169 (107), 512 channels at 7x7 (64-tile) 179
-// against 143.  Tiles of 256 x 128 by eight wavefronts were 5 % faster on 4096^3 and too coarse for the rest; 256 x 256 spills.
+// TFLOP/s, without the matrix instructions at 490.  Random operands, 128-tile (64-tile): 4096^3 260 (200) TFLOP/s against 167
+// to 185 with three planes, ResNet-50's statistics at batch 128 268 (123) against 169 (107), 512 channels at 7x7 301 (200; with
+// three planes 143).  Eight places of a row and the floors of the rows take 2 to 5 % (without them 268, 274 and 318).  Tiles of 256 x 128 by eight wavefronts were 5 % faster on 4096^3 and too coarse for the rest; 256 x 256 spills.
 // (Two wavefronts per SIMD, four of the small tile: the register allocation is held to 256 and 128.)
 template <int TM, int TN>
 __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_kernel(const GemmProblem *__restrict__ probs,
