@@ -704,25 +704,6 @@ constexpr float kNoFloor = -0x1p100f;   // of rows of zeros, and of rows outside
 constexpr int LDP = 32;              // LDS row length in fp16; 16-byte chunks of a row are permuted instead of padded (half_swz)
 __device__ __forceinline__ int half_swz(int row) { return ((row >> 1) & 3) ^ ((row >> 3) & 1); }
 
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-
-// two fp32 values, scaled -> their packed (h, l) fp16 pairs, low half = first value
-__device__ __forceinline__ void split_half_pair(float x0, float x1, float s, unsigned &h, unsigned &l)
-{
-    const float y0 = x0 * s, y1 = x1 * s;
-    half2_t hh = {(_Float16)y0, (_Float16)y1};
-    asm("" : "+v"(hh));   // (keeps the compiler from converting each half a second time)
-    const half2_t ll = {(_Float16)(y0 - (float)hh[0]), (_Float16)(y1 - (float)hh[1])};
-    h = __builtin_bit_cast(unsigned, hh);
-    l = __builtin_bit_cast(unsigned, ll);
-}
-// power of two that brings |x| in [2^e, 2^(e+1)) to [2^top, 2^(top+1)); 1 for x == 0.  (2^118 at most: the scaled row stays finite.)
-__device__ __forceinline__ float half_scale(float x, int top)
-{
-    const int e = (int)(__float_as_uint(x) >> 23);
-    return x == 0.f ? 1.f : __uint_as_float((unsigned)min(254 + top - e, 127 + 118) << 23);
-}
 __device__ __forceinline__ int half_exponent(float s) { return (int)(__float_as_uint(s) >> 23) - 127; }   // log2 of a scale
 __device__ __forceinline__ float max_abs(float m, const floatx4 &v)
 {

@@ -17,9 +17,10 @@ __global__ __launch_bounds__(256) void trace_kernel(const TraceJob *__restrict__
 {
     __shared__ double red[2][256];
     const TraceJob J = jobs[blockIdx.x];
+    const Global<const float> A = global(J.A), G = global(J.G);
     double sa = 0.0, sg = 0.0;
-    for (int i = threadIdx.x; i < J.dA; i += 256) sa += (double)J.A[(long long)i * J.dA + i];
-    for (int i = threadIdx.x; i < J.dG; i += 256) sg += (double)J.G[(long long)i * J.dG + i];
+    for (int i = threadIdx.x; i < J.dA; i += 256) sa += (double)A[(long long)i * J.dA + i];
+    for (int i = threadIdx.x; i < J.dG; i += 256) sg += (double)G[(long long)i * J.dG + i];
     red[0][threadIdx.x] = sa;
     red[1][threadIdx.x] = sg;
     __syncthreads();
@@ -66,7 +67,9 @@ __global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restric
     const CopyJob J = jobs[lo];
     const float d = (J.damp_idx >= 0) ? damp[J.damp_idx] : 0.f;
     const int r0 = (wg - J.wg_start) * COPY_ROWS;
-    const float *last = J.src + (long long)J.n * J.lds;   // the border row u^T, c (if any)
+    const Global<const float> src = global(J.src);
+    const Global<float> dst = global(J.dst);
+    const Global<const float> last = src + (long long)J.n * J.lds;   // the border row u^T, c (if any)
     const float ic = J.border ? 1.f / (last[J.n] + d) : 0.f;
     const int r1 = min(J.n, r0 + COPY_ROWS);
     // four adjacent columns per thread (16-byte accesses that only need element alignment: the
@@ -77,9 +80,9 @@ __global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restric
         vec4 v[COPY_ROWS];
 #pragma unroll
         for (int q = 0; q < COPY_ROWS; ++q)
-            if (r0 + q < r1) v[q] = *(const vec4 *)(J.src + (long long)(r0 + q) * J.lds + c);
+            if (r0 + q < r1) v[q] = *(Global<const vec4>)(src + (long long)(r0 + q) * J.lds + c);
         vec4 u = {0.f, 0.f, 0.f, 0.f};
-        if (J.border) u = *(const vec4 *)(last + c);
+        if (J.border) u = *(Global<const vec4>)(last + c);
 #pragma unroll
         for (int q = 0; q < COPY_ROWS; ++q) {
             const int r = r0 + q;
@@ -91,16 +94,16 @@ __global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restric
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[e] = fmaf(-ur, u[e], x[e]);
             }
-            *(vec4 *)(J.dst + (long long)r * J.ldd + c) = x;
+            *(Global<vec4>)(dst + (long long)r * J.ldd + c) = x;
         }
     }
     for (int r = r0; r < r1; ++r) {
         const float ur = J.border ? last[r] * ic : 0.f;
         for (int c = n4 + (int)threadIdx.x; c < min(J.n, n4 + 4); c += 256) {
-            float v = J.src[(long long)r * J.lds + c];
+            float v = src[(long long)r * J.lds + c];
             if (r == c) v += d;
             if (J.border) v = fmaf(-ur, last[c], v);
-            J.dst[(long long)r * J.ldd + c] = v;
+            dst[(long long)r * J.ldd + c] = v;
         }
     }
 }
@@ -129,14 +132,14 @@ __global__ __launch_bounds__(256) void border_kernel(const BorderJob *__restrict
         const BorderJob J = jobs[lo];
         const int i = (wg - J.wg_start) * 4 + wave;
         if (i >= J.n) return;
-        const float *u = J.src + (long long)J.n * J.lds;
-        const float *x = J.X + (long long)i * J.ldx;
+        const Global<const float> u = global(J.src) + (long long)J.n * J.lds;
+        const Global<float> X = global(J.X), x = X + (long long)i * J.ldx;
         // 16-byte accesses that only need element alignment (the leading dimensions are odd)
         typedef float vec4 __attribute__((ext_vector_type(4), aligned(4)));
         float a4[4] = {0.f, 0.f, 0.f, 0.f};
         const int n4 = J.n & ~3;
         for (int j = 4 * lane; j < n4; j += 256) {
-            const vec4 xv = *(const vec4 *)(x + j), uv = *(const vec4 *)(u + j);
+            const vec4 xv = *(Global<const vec4>)(x + j), uv = *(Global<const vec4>)(u + j);
 #pragma unroll
             for (int e = 0; e < 4; ++e) a4[e] = fmaf(xv[e], uv[e], a4[e]);
         }
@@ -147,16 +150,16 @@ __global__ __launch_bounds__(256) void border_kernel(const BorderJob *__restrict
         if (lane == 0) {
             const float c = u[J.n] + ((J.damp_idx >= 0) ? damp[J.damp_idx] : 0.f);
             const float v = -acc / c;
-            J.X[(long long)i * J.ldx + J.n] = v;
-            J.X[(long long)J.n * J.ldx + i] = v;
+            X[(long long)i * J.ldx + J.n] = v;
+            X[(long long)J.n * J.ldx + i] = v;
         }
         return;
     }
     // corner: X[n][n] = (1 - sum_i u_i X[n][i]) / c   (X[n][i] = -w_i / c from pass 0)
     __shared__ float red[4];
     const BorderJob J = jobs[blockIdx.x];
-    const float *u = J.src + (long long)J.n * J.lds;
-    const float *xr = J.X + (long long)J.n * J.ldx;
+    const Global<const float> u = global(J.src) + (long long)J.n * J.lds;
+    const Global<float> xr = global(J.X) + (long long)J.n * J.ldx;
     float acc = 0.f;
     for (int i = threadIdx.x; i < J.n; i += 256) acc = fmaf(u[i], xr[i], acc);
 #pragma unroll
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(256) void border_kernel(const BorderJob *__restrict
     if (threadIdx.x == 0) {
         const float c = u[J.n] + ((J.damp_idx >= 0) ? damp[J.damp_idx] : 0.f);
         const float q = (red[0] + red[1]) + (red[2] + red[3]);
-        J.X[(long long)J.n * J.ldx + J.n] = (1.f - q) / c;
+        xr[J.n] = (1.f - q) / c;
         if (!(c > 0.f) && info && J.info_idx >= 0) atomicCAS(&info[J.info_idx], 0, J.n + 1);
     }
 }
@@ -193,7 +196,7 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ blocked leaf inverse on the matrix cores
-// (X + damp I)^-1 for n <= 288 by one 1024-thread workgroup, as a symmetric block sweep with 32x32 blocks.  The matrix
+// (X + damp I)^-1 for n <= 288 by one 768-thread workgroup, as a symmetric block sweep with 32x32 blocks.  The matrix
 // is first scaled to unit diagonal (s_i = 1/sqrt(x_ii), undone at the end), which makes every pivot of the elimination
 // lie in (0, 1].  The workgroup holds N = -(scaled matrix), one 32x32 tile per unordered pair of block indices, in the
 // accumulator layout of the 32x32 matrix instructions in the registers of one wavefront.  Sweeping block k
@@ -206,127 +209,177 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s)
 // The kernel is a latency chain on one compute unit: 9 dependent blocks for n = 288.  What it does about that:
 //   - One wavefront (the chain wavefront) holds no tile.  In step k it takes R_{k+1} and the diagonal tile of block
 //     k + 1 as the previous step left them, forms P_{k+1}, brings that tile up to date and sweeps it, all out of its own
-//     registers, while the other fifteen do the rest of step k.  D of the next block is ready when they are.
-//   - The tiles are dealt out as stars: a wavefront's tiles (at most three) share one block index v, so it needs one
-//     P_v only and forms it itself.  It forms the transpose, D R_v^T: its accumulator layout (lane: row of block v,
-//     registers: k) is, split into planes, the operand layout of the update R_j P_v^T, with the contraction index in the
-//     order the registers have.  Every operand uses that order; P never goes through LDS and one barrier per step is left.
+//     registers, while the others do the rest of step k.  D of the next block is ready when they are.  It has a SIMD for
+//     itself: beside it, the tiles' wavefronts waited for its issue slots and finished last.
+//   - The tiles are dealt to nine wavefronts, three on each other SIMD, as stars: the five tiles of wavefront v share the
+//     block index v, so it needs one P_v only and forms it itself.  It forms the transpose, D R_v^T: its accumulator layout
+//     (lane: row of block v, registers: k) is, split into planes, the operand layout of the update R_j P_v^T, with the
+//     contraction index in the order the registers have.  Every operand uses that order; P never goes through LDS and one
+//     barrier per step is left.  (Twelve wavefronts with four tiles: more P's, and registers that spill.)
 //   - A tile is (registers: row of block j, lanes: row of block v).  For the panel of step k a tile with j = k is stored
-//     as the fragments its readers load (three planes, 16 bytes a lane: form F), a tile with v = k as [k][row] rows that
-//     are read with the transposing LDS read (form T); no 2-byte stores.  The panels of two steps alternate.
-// n = 288: 49 us (77 us with two barriers per step, P and R through LDS and the sweep between the products of its
-// wavefront); 224: 33 (51), 160: 20.5 (31), 64: 8.5 (15).  In-kernel times at n = 288, cycles a block: the chain 8800 to 9700
-// (sweep 3500 alone on its SIMD, 6000 to 7300 beside the others; D into planes 900, operand reads 300, P and update 1300), the
-// other wavefronts up to 10900, most of it the 192 matrix instructions of a SIMD (6100) and the conversions around them.
-// Loads and stores: 6 us.
+//     as the fragments its readers load (two planes, 16 bytes a lane: form F), a tile with v = k as [k][row] rows that
+//     are read with the transposing LDS read (form T); no 2-byte stores.  The panels of two steps alternate.  The wavefront
+//     that stores most of the next panel goes first in its SIMD.
 //
-// Products are in the three-plane mode (x = h + m + l exactly, see split_pair; six bf16 matrix instructions per
-// 16-wide step, fp32 accumulation).
+// Products are through two fp16 planes (x s = h + l, three instructions per 16-wide step instead of six; see gemm_nt.hip), with
+// scales that are exact: a panel block and D take the power of two that brings their largest element to [2^14, 2^15), P_v one per
+// row (a lane).  Nothing overflows, and elements down to 2^-16 of the largest of their block lose nothing.  The sum of a product
+// is scaled back into the tile with one fma, so a tile is rounded once per step (six times as the accumulator of bf16 planes):
+// inverses of 10 to 288 rows err 0.66 of what they did, those of 289 to 4609 rows 0.52 (128 and 87 factors of random layers);
+// rows that are nearly parallel lose: pairs correlated by 0.9995 2.9e-3 against 1.2e-3 at 288 rows, 0.95^|i-j| 0.9 of before.
+//
+// n = 288: 40.9 us (51.8 with fifteen wavefronts, three bf16 planes and an address per element), 224: 29.6 (35.9), 160: 20.0
+// (23.4), 64: 11.2 (11.2).  In-kernel cycles at n = 288: loads and scales 8400, a step 7650, stores 9000.  Of a step, the chain
+// needs 5600 (sweep 3640, D into planes 850, operand reads 260, P and update 900); a SIMD with three stars 3460 for its matrix
+// instructions and 5800 for the vector ones.
 typedef float lb_floatx16 __attribute__((ext_vector_type(16)));
 typedef float lb_floatx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 lb_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float lb_floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
 typedef short lb_shortx4 __attribute__((ext_vector_type(4)));
 typedef short lb_shortx8 __attribute__((ext_vector_type(8)));
 typedef lb_shortx4 __attribute__((address_space(3))) *lb_lds_shortx4_ptr;
 constexpr int LB_MAXT = 9;
-constexpr int LB_CHAIN = 15;                            // the chain wavefront
+constexpr int LB_THREADS = 768;                         // three wavefronts a SIMD
+constexpr int LB_CHAIN = 11;                            // the chain wavefront
 constexpr int LB_TROW = 72;                             // bytes per k row of form T (32 bf16 + 8 bytes: spreads the banks)
 constexpr int LB_BLK = 32 * LB_TROW;                    // bytes of one plane of one panel block (form F needs 2048)
 constexpr int LB_IDENT = LB_MAXT;                       // a panel block that always holds the identity, form F
 constexpr int LB_PLANE = (LB_MAXT + 1) * LB_BLK;        // bytes of one plane of a panel
-constexpr int LB_PANEL = 3 * LB_PLANE;                  // one panel: [plane][block]
-constexpr int LB_DP = 3 * 2048;                         // planes of D, form F
+constexpr int LB_PANEL = 2 * LB_PLANE;                  // one panel: [plane][block]
+constexpr int LB_DP = 2 * 2048;                         // planes of D, form F
+constexpr int LB_TOP = 14;                              // a scaled block has its largest element in [2^14, 2^15)
 constexpr int LB_LDS_D = 2 * LB_PANEL, LB_LDS_DIAG = LB_LDS_D + 2 * LB_DP,
-              LB_LDS_SC = LB_LDS_DIAG + 2 * 4096, LB_LDS_BYTES = LB_LDS_SC + 32 * LB_MAXT * 4;
+              LB_LDS_SC = LB_LDS_DIAG + 2 * 4096, LB_LDS_UN = LB_LDS_SC + 32 * LB_MAXT * 4,
+              LB_LDS_BYTES = LB_LDS_UN + 2 * 16 * 4;   // UN: reciprocal scales of two panels' blocks, of I and (LB_UN_D) of D
+constexpr int LB_UN_D = LB_IDENT + 1;
 static_assert(LB_LDS_BYTES <= 160 * 1024 - 64, "one compute unit's LDS");
-static_assert(LB_LDS_D >= 15 * 32 * 33 * 4, "the staging tiles of the final store fit into the panels");
+constexpr int LB_STAGE = 36;                            // row length of the staging tiles (16-byte accesses spread over the banks)
+static_assert(LB_LDS_D >= LB_MAXT * 2 * 32 * LB_STAGE * 4, "the staging tiles of the final store fit into the panels");
 
-// Tiles of 6 .. 9 blocks dealt to the wavefronts as stars {v; j, j, j} (-1: none), found by a search that minimises the
-// matrix instructions of the busiest SIMD (wavefront % 4, the chain's included) summed over the steps, with v = k + 1 for
-// the tile of blocks k + 1 and k (the chain reads form F only).  Up to 5 blocks: one tile per wavefront, v the larger index.
-__constant__ signed char kLeafStar[4][15][4] = {
-    {{2, 1, 4, -1}, {3, 5, 1, -1}, {1, 1, 0, -1}, {5, 4, -1, -1}, {5, 5, 0, -1}, {4, 4, 3, -1}, {2, 2, 0, -1},
-     {4, 0, -1, -1}, {3, 3, 2, -1}, {0, 0, 3, -1}, {1, 5, 4, -1}, {2, 5, -1, -1}, {-1, -1, -1, -1}, {-1, -1, -1,
-     -1}, {-1, -1, -1, -1}},
-    {{5, 2, 3, -1}, {0, 0, 6, -1}, {4, 0, 1, -1}, {3, 0, 1, -1}, {6, 1, 4, -1}, {3, 3, 2, -1}, {6, 5, 3, -1},
-     {4, 4, 3, -1}, {2, 0, 1, -1}, {5, 5, 4, -1}, {1, 1, 5, -1}, {2, 2, 4, -1}, {5, 0, -1, -1}, {1, 0, -1, -1},
-     {6, 6, 2, -1}},
-    {{4, 4, 0, 6}, {6, 0, 1, -1}, {7, 3, 0, -1}, {3, 6, 2, -1}, {0, 0, 5, 2}, {5, 5, 7, 2}, {1, 7, 0, -1}, {2,
-     2, 6, 7}, {6, 6, 5, -1}, {1, 1, 5, -1}, {5, 4, 3, -1}, {7, 7, 6, -1}, {2, 4, 1, -1}, {4, 3, 7, 1}, {3, 3,
-     1, 0}},
-    {{4, 4, 3, 0}, {1, 1, 0, 3}, {6, 6, 0, 4}, {2, 4, 0, 7}, {1, 6, 7, 4}, {8, 0, 7, 2}, {7, 0, 3, 4}, {0, 0, 3,
-     5}, {8, 8, 6, 1}, {2, 2, 5, 1}, {7, 7, 6, 5}, {8, 5, 3, 4}, {5, 5, 4, 1}, {6, 5, 2, 3}, {3, 3, 2, 5}},
-};
-// bit i of [blocks - 6][k]: the tile of blocks i and k is held with v = i (panel form F in step k), else with v = k (T)
-__constant__ unsigned short kLeafForm[4][9] = {
-    {0x36, 0xc, 0x8, 0x11, 0x26, 0xe, 0x0, 0x0, 0x0},
-    {0x3e, 0x5c, 0x68, 0x70, 0x64, 0x42, 0x1, 0x0, 0x0},
-    {0xda, 0x5c, 0x29, 0xb0, 0x24, 0x43, 0x9c, 0x36, 0x0},
-    {0x1d6, 0x124, 0x148, 0x1d3, 0x1e6, 0x1cd, 0x182, 0x106, 0x0},
-};
+// Of T blocks in a circle, the tile of blocks v and j is held as (v, j) where v is at most half a circle ahead of j (exactly
+// half of it: where v > j): star v is {v; v, v - 1, ..., v - T / 2}, the same number of tiles for every wavefront.
+constexpr int LB_SLOTS = LB_MAXT / 2 + 1;
+__device__ __forceinline__ int lb_star(int T, int v, int s)   // tile s of star v: its j, or -1
+{
+    return 2 * s < T || (2 * s == T && 2 * v >= T) ? (v >= s ? v - s : v - s + T) : -1;
+}
+__device__ __forceinline__ bool lb_form_f(int T, int i, int k)   // in step k: block i of the panel comes from star i
+{
+    const int d = i >= k ? i - k : i - k + T;
+    return 2 * d < T || (2 * d == T && i > k);
+}
 
 __device__ __forceinline__ float lb_readlane(float x, int lane)
 {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
-struct LbFrag { lb_bf16x8 h, m, l; };
+struct LbFrag { halfx8 h, l; };
 
-// eight accumulator registers (8 u .. 8 u + 7) of a tile as an operand fragment of step u
-__device__ __forceinline__ LbFrag lb_split8(const lb_floatx16 &t, int u)
+// eight accumulator registers (8 u .. 8 u + 7) of a tile, scaled, as an operand fragment of step u
+__device__ __forceinline__ LbFrag lb_split8(const lb_floatx16 &t, int u, float scale)
 {
-    uint4 h, m, l;
-    split_pair(t[8 * u + 0], t[8 * u + 1], h.x, m.x, l.x);
-    split_pair(t[8 * u + 2], t[8 * u + 3], h.y, m.y, l.y);
-    split_pair(t[8 * u + 4], t[8 * u + 5], h.z, m.z, l.z);
-    split_pair(t[8 * u + 6], t[8 * u + 7], h.w, m.w, l.w);
-    return {__builtin_bit_cast(lb_bf16x8, h), __builtin_bit_cast(lb_bf16x8, m), __builtin_bit_cast(lb_bf16x8, l)};
+    uint4 h, l;
+    split_half_pair(t[8 * u + 0], t[8 * u + 1], scale, h.x, l.x);
+    split_half_pair(t[8 * u + 2], t[8 * u + 3], scale, h.y, l.y);
+    split_half_pair(t[8 * u + 4], t[8 * u + 5], scale, h.z, l.z);
+    split_half_pair(t[8 * u + 6], t[8 * u + 7], scale, h.w, l.w);
+    return {__builtin_bit_cast(halfx8, h), __builtin_bit_cast(halfx8, l)};
 }
-__device__ __forceinline__ void lb_mma(lb_floatx16 &acc, const LbFrag &a, const LbFrag &b)
+// product of two blocks (fragments of both 16-wide steps), the small terms first
+__device__ __forceinline__ lb_floatx16 lb_mma(const LbFrag (&a)[2], const LbFrag (&b)[2])
 {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc, 0, 0, 0);
+    lb_floatx16 c;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) c[q] = 0.f;
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0].l, b[0].h, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0].h, b[0].l, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1].l, b[1].h, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1].h, b[1].l, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0].h, b[0].h, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1].h, b[1].h, c, 0, 0, 0);
+    return c;
 }
+__device__ __forceinline__ float lb_max_abs(const lb_floatx16 &t)
+{
+    float m = fmaxf(fabsf(t[0]), fabsf(t[1]));
+#pragma unroll
+    for (int q = 2; q < 16; q += 2) m = fmaxf(fmaxf(m, fabsf(t[q])), fabsf(t[q + 1]));
+    return m;
+}
+// (magnitudes compare as unsigned numbers, which have no quiet form to be brought into)
+template <int CTRL>
+__device__ __forceinline__ unsigned lb_max_dpp(unsigned x)
+{
+    return max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ unsigned lb_max_halves(unsigned x)   // of lanes l and l + 32
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return max(s[0], s[1]);
+}
+// the largest magnitudes of the lanes' parts of N tiles -> the scales of the tiles (uniform)
+template <int N>
+__device__ __forceinline__ void lb_tile_scales(float (&most)[N])
+{
+    unsigned m[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) m[n] = lb_max_dpp<0xB1>(__float_as_uint(most[n]));   // quad_perm 1 0 3 2
+#pragma unroll
+    for (int n = 0; n < N; ++n) m[n] = lb_max_dpp<0x4E>(m[n]);                       // quad_perm 2 3 0 1
+#pragma unroll
+    for (int n = 0; n < N; ++n) m[n] = lb_max_dpp<0x141>(m[n]);                      // row_half_mirror
+#pragma unroll
+    for (int n = 0; n < N; ++n) m[n] = lb_max_dpp<0x140>(m[n]);                      // row_mirror
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        const auto s = __builtin_amdgcn_permlane16_swap(m[n], m[n], false, false);
+        m[n] = max(s[0], s[1]);
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) most[n] = half_scale(__uint_as_float(__builtin_amdgcn_readfirstlane(lb_max_halves(m[n]))), LB_TOP);
+}
+__device__ __forceinline__ float lb_tile_scale(const lb_floatx16 &t)
+{
+    float m[1] = {lb_max_abs(t)};
+    lb_tile_scales(m);
+    return m[0];
+}
+__device__ __forceinline__ float lb_reciprocal(float s) { return __uint_as_float((254u << 23) - __float_as_uint(s)); }   // of a power of two
 // form F: fragments as they are read, plane stride given; [u][lane] 16 bytes each
 __device__ __forceinline__ LbFrag lb_read_f(const char *blk, int plane, int u, int lane)
 {
-    auto rd = [&](int q) { return __builtin_bit_cast(lb_bf16x8, *(const lb_shortx8 *)(blk + q * plane + u * 1024 + lane * 16)); };
-    return {rd(0), rd(1), rd(2)};
+    auto rd = [&](int q) { return __builtin_bit_cast(halfx8, *(const lb_shortx8 *)(blk + q * plane + u * 1024 + lane * 16)); };
+    return {rd(0), rd(1)};
 }
 __device__ __forceinline__ void lb_store_f(char *blk, int plane, int u, const LbFrag &f, int lane)
 {
     *(lb_shortx8 *)(blk + u * 1024 + lane * 16) = __builtin_bit_cast(lb_shortx8, f.h);
-    *(lb_shortx8 *)(blk + plane + u * 1024 + lane * 16) = __builtin_bit_cast(lb_shortx8, f.m);
-    *(lb_shortx8 *)(blk + 2 * plane + u * 1024 + lane * 16) = __builtin_bit_cast(lb_shortx8, f.l);
+    *(lb_shortx8 *)(blk + plane + u * 1024 + lane * 16) = __builtin_bit_cast(lb_shortx8, f.l);
 }
 // form T: [k][row]; the tile's lanes are k and its registers rows.  The transposing read gives lane i of 16 element i % 4
 // of the 8-byte groups addressed by lanes i / 4, i / 4 + 4, i / 4 + 8, i / 4 + 12: four adjacent k of row i.
 __device__ __forceinline__ LbFrag lb_read_t(const char *blk, int u, int lane)
 {
     const int i = lane & 15, row0 = lane & 16, half = lane >> 5;
-    const char *p = blk + (16 * u + 4 * half + (i >> 2)) * LB_TROW + 2 * (row0 + 4 * (i & 3));
+    const char *p = blk + __umul24(16 * u + 4 * half + (i >> 2), LB_TROW) + 2 * (row0 + 4 * (i & 3));
     auto rd = [&](int q) {
         const lb_shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lb_lds_shortx4_ptr)(p + q * LB_PLANE));
         const lb_shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lb_lds_shortx4_ptr)(p + q * LB_PLANE + 8 * LB_TROW));
-        return __builtin_bit_cast(lb_bf16x8, lb_shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+        return __builtin_bit_cast(halfx8, lb_shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
     };
-    return {rd(0), rd(1), rd(2)};
+    return {rd(0), rd(1)};
 }
-__device__ __forceinline__ void lb_store_t(char *blk, const lb_floatx16 &t, int lane)
+__device__ __forceinline__ void lb_store_t(char *blk, const lb_floatx16 &t, float scale, int lane)
 {
     char *d = blk + (lane & 31) * LB_TROW + 8 * (lane >> 5);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {   // rows 8 g + 4 half .. + 3
-        uint2 h, m, l;
-        split_pair(t[4 * g], t[4 * g + 1], h.x, m.x, l.x);
-        split_pair(t[4 * g + 2], t[4 * g + 3], h.y, m.y, l.y);
+        uint2 h, l;
+        split_half_pair(t[4 * g], t[4 * g + 1], scale, h.x, l.x);
+        split_half_pair(t[4 * g + 2], t[4 * g + 3], scale, h.y, l.y);
         *(uint2 *)(d + 16 * g) = h;
-        *(uint2 *)(d + LB_PLANE + 16 * g) = m;
-        *(uint2 *)(d + 2 * LB_PLANE + 16 * g) = l;
+        *(uint2 *)(d + LB_PLANE + 16 * g) = l;
     }
 }
 // both fragments of panel block i
@@ -425,13 +478,13 @@ __device__ __forceinline__ int leaf_chain_sweep(lb_floatx16 &t, int lane)
     return first;
 }
 
-template <int NSLOT>
-__global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restrict__ jobs,
+__global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *__restrict__ jobs,
                                                           const float *__restrict__ damp,
                                                           int32_t *__restrict__ info)
 {
     extern __shared__ __attribute__((aligned(16))) char lb_lds[];
     float *sc = (float *)(lb_lds + LB_LDS_SC);       // [32 T] diagonal scaling
+    float *unscale = (float *)(lb_lds + LB_LDS_UN);  // [2][16]
 
     const LeafJob J = jobs[blockIdx.x];
     const int n = J.n;
@@ -441,29 +494,32 @@ __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restr
     const int l32_ = lane & 31, h_ = lane >> 5;
     const float d = (J.damp_idx >= 0) ? damp[J.damp_idx] : 0.f;
     const unsigned lds = (unsigned)J.lds, ldd = (unsigned)J.ldd;
+    const Global<const float> src = global(J.src);
+    const Global<float> dst = global(J.dst);
 
     // my tiles: (rows of block j[s]: registers, rows of block v: lanes)
-    int v_ = -1, j_[NSLOT];
+    const int worker = (w & 3) == 3 ? LB_MAXT : w - (w >> 2);   // (the chain's SIMD has no other)
+    const int v_ = worker < T ? worker : -1;
+    int j_[LB_SLOTS];
 #pragma unroll
-    for (int s = 0; s < NSLOT; ++s) j_[s] = -1;
-    if (NSLOT == 1 || T < 6) {
-        int r = 0;
-        while ((r + 1) * (r + 2) / 2 <= w) ++r;
-        if (w < T * (T + 1) / 2 && w != LB_CHAIN) { v_ = r; j_[0] = w - r * (r + 1) / 2; }
-    } else if (w != LB_CHAIN) {
-        v_ = kLeafStar[T - 6][w][0];
-#pragma unroll
-        for (int s = 0; s < NSLOT; ++s) j_[s] = kLeafStar[T - 6][w][1 + s];
-    }
-    // bit i: the panel block i of step k is in form F
-    auto form_mask = [&](int k) { return (NSLOT == 1 || T < 6) ? ~((2u << k) - 1u) : (unsigned)kLeafForm[T - 6][k]; };
+    for (int s = 0; s < LB_SLOTS; ++s) j_[s] = v_ >= 0 ? lb_star(T, v_, s) : -1;
 
     // the chain wavefront loads the first diagonal tile, the others their tiles; the scaling needs the diagonal
+    // (row pointers of whole tiles are uniform, with one offset per lane: as an address per element, the vector instructions for
+    // them took most of the loads' time, and of the stores')
+    auto whole = [&](int bi, int bj) { return 32 * (max(bi, bj) + 1) <= n; };
     auto load_tile = [&](lb_floatx16 &t, int bi, int bj, bool chain) {
+        if (whole(bi, bj)) {
+            const Global<const char> row = (Global<const char>)(src + (long long)(32 * bi) * lds + 32 * bj);
+            const unsigned at = 4u * (chain ? h_ * lds + lb_row_of(l32_) : 4 * h_ * lds + l32_);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) t[q] = *(Global<const float>)(row + (long long)(chain ? lb_row(q, 0) : 8 * (q >> 2) + (q & 3)) * lds * 4 + at);
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int i = 32 * bi + (chain ? lb_row(q, h_) : 8 * (q >> 2) + 4 * h_ + (q & 3)), j = 32 * bj + (chain ? lb_row_of(l32_) : l32_);
-            t[q] = J.src[(unsigned)min(i, n - 1) * lds + (unsigned)min(j, n - 1)];   // (outside: replaced when it is scaled)
+            t[q] = src[(unsigned)min(i, n - 1) * lds + (unsigned)min(j, n - 1)];   // (outside: replaced when it is scaled)
         }
     };
     // scales of the tile's rows (by register) and of its lane's column
@@ -481,14 +537,15 @@ __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restr
         }
         sj = sc[32 * bj + (chain ? lb_row_of(l32_) : l32_)];
     };
-    auto whole = [&](int bi, int bj) { return 32 * (max(bi, bj) + 1) <= n; };
-    auto scale_tile = [&](lb_floatx16 &t, int bi, int bj, bool chain) {
+    auto scale_tile = [&](lb_floatx16 &t, int bi, int bj, bool chain, bool diagonal) {
         float si[16], sj;
         tile_scales(si, sj, bi, bj, chain);
-        const float dd = bi == bj ? d : 0.f;
-        // (the diagonal lies at the same registers and lanes in either order)
+        if (diagonal) {   // (at the same registers and lanes in either order)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) t[q] = -(t[q] + (8 * (q >> 2) + 4 * h_ + (q & 3) == l32_ ? dd : 0.f)) * si[q] * sj;
+            for (int q = 0; q < 16; ++q) t[q] += 8 * (q >> 2) + 4 * h_ + (q & 3) == l32_ ? d : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) t[q] = t[q] * si[q] * -sj;
         if (!whole(bi, bj)) {
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
@@ -501,7 +558,7 @@ __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restr
         if (tid < 32 * T) {
             float v = 1.f;
             if (tid < n) {
-                const float a = J.src[(unsigned)tid * lds + (unsigned)tid] + d;
+                const float a = src[(unsigned)tid * lds + (unsigned)tid] + d;
                 v = a > 0.f ? rsqrtf(a) : 1.f;   // a non-positive diagonal shows up as a non-positive pivot
             }
             sc[tid] = v;
@@ -513,7 +570,7 @@ __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restr
         lb_floatx16 t;
         load_tile(t, 0, 0, true);
         __syncthreads();
-        scale_tile(t, 0, 0, true);
+        scale_tile(t, 0, 0, true, true);
         __builtin_amdgcn_s_setprio(3);
         int bad = 0;
         for (int k = 0; k < T; ++k) {
@@ -524,10 +581,12 @@ __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restr
             if (bad == 0 && b != 0) bad = 32 * k + b;
             char *Dq = lb_lds + LB_LDS_D + (k & 1) * LB_DP;
             {
+                const float scale = lb_tile_scale(t);
                 const lb_floatx16 dt = lb_plain_rows(t);       // lanes (D is symmetric: its rows) in the chain's order yet
                 const int at = (l64 & 32) | lb_row_of(l64 & 31);
-                lb_store_f(Dq, 2048, 0, lb_split8(dt, 0), at);
-                lb_store_f(Dq, 2048, 1, lb_split8(dt, 1), at);
+                lb_store_f(Dq, 2048, 0, lb_split8(dt, 0, scale), at);
+                lb_store_f(Dq, 2048, 1, lb_split8(dt, 1, scale), at);
+                if (l64 == 0) unscale[16 * (k & 1) + LB_UN_D] = lb_reciprocal(scale);
             }
             __syncthreads();   // D and panel of step k, diagonal tile of block k + 1
             if (k + 1 == T) break;
@@ -535,7 +594,8 @@ __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restr
             const char *blk = lb_lds + (k & 1) * LB_PANEL + (k + 1) * LB_BLK;
             const int from = (l64 & 32) | lb_row_of(l64 & 31);
             const LbFrag r[2] = {lb_read_f(blk, LB_PLANE, 0, from), lb_read_f(blk, LB_PLANE, 1, from)};
-            const LbFrag d0 = lb_read_f(Dq, 2048, 0, l64), d1 = lb_read_f(Dq, 2048, 1, l64);
+            const LbFrag d[2] = {lb_read_f(Dq, 2048, 0, l64), lb_read_f(Dq, 2048, 1, l64)};
+            const float un_r = unscale[16 * (k & 1) + k + 1], un_d = unscale[16 * (k & 1) + LB_UN_D];
             const lb_floatx4 *o = (const lb_floatx4 *)(lb_lds + LB_LDS_DIAG + ((k + 1) & 1) * 4096);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -543,161 +603,200 @@ __global__ __launch_bounds__(1024) void leaf_block_kernel(const LeafJob *__restr
 #pragma unroll
                 for (int e = 0; e < 4; ++e) t[4 * g + e] = x[e];
             }
-            lb_floatx16 p;
+            const lb_floatx16 p = lb_mma(d, r);      // P^T = D R^T
+            const float scale = half_scale(__uint_as_float(lb_max_halves(__float_as_uint(lb_max_abs(p)))), LB_TOP), un = lb_reciprocal(scale) * un_d * un_r * un_r;
+            const LbFrag pf[2] = {lb_split8(p, 0, scale), lb_split8(p, 1, scale)};
+            const lb_floatx16 c = lb_mma(r, pf);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) p[q] = 0.f;
-            lb_mma(p, d0, r[0]);      // P^T = D R^T
-            lb_mma(p, d1, r[1]);
-            lb_mma(t, r[0], lb_split8(p, 0));
-            lb_mma(t, r[1], lb_split8(p, 1));
+            for (int q = 0; q < 16; ++q) t[q] = fmaf(c[q], un, t[q]);
         }
         if (bad != 0 && lane == 0 && info && J.info_idx >= 0) atomicCAS(&info[J.info_idx], 0, J.pivot_base + bad);
         __syncthreads();
         return;
     }
 
-    lb_floatx16 acc[NSLOT];
+    lb_floatx16 acc[LB_SLOTS];
 #pragma unroll
-    for (int s = 0; s < NSLOT; ++s)
+    for (int s = 0; s < LB_SLOTS; ++s) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[s][q] = 0.f;
         if (j_[s] >= 0) load_tile(acc[s], j_[s], v_, false);
+    }
     scales();
-    if (w < 12) {   // the identity: wavefront w writes step fragments w % 2 of plane (w / 2) % 3 of panel w / 6
-        const int u = w & 1, q = (w >> 1) % 3;
+    if (w < 8) {   // the identity: wavefront w writes step fragments w % 2 of plane (w / 2) % 2 of panel w / 4
+        const int u = w & 1, q = (w >> 1) & 1;
         lb_shortx8 e;
 #pragma unroll
-        for (int x = 0; x < 8; ++x) e[x] = (q == 0 && 16 * u + 8 * (x >> 2) + 4 * h_ + (x & 3) == l32_) ? (short)0x3F80 : (short)0;
-        *(lb_shortx8 *)(lb_lds + (w / 6) * LB_PANEL + q * LB_PLANE + LB_IDENT * LB_BLK + u * 1024 + lane * 16) = e;
+        for (int x = 0; x < 8; ++x) e[x] = (q == 0 && 16 * u + 8 * (x >> 2) + 4 * h_ + (x & 3) == l32_) ? (short)0x3C00 : (short)0;
+        *(lb_shortx8 *)(lb_lds + (w >> 2) * LB_PANEL + q * LB_PLANE + LB_IDENT * LB_BLK + u * 1024 + lane * 16) = e;
+        if (lane == 0) unscale[16 * (w >> 2) + LB_IDENT] = 1.f;
     }
     __syncthreads();
     // panel of step kk from the tiles that have an index kk, and the diagonal tile of block kk + 1 for the chain
     auto publish = [&](int kk, int l64) {
         char *panel = lb_lds + (kk & 1) * LB_PANEL;
+        float *un = unscale + 16 * (kk & 1);
+        if (v_ == kk) {
+            // all tiles but the diagonal one, their scales side by side (a lone reduction over the lanes is latency)
+            float scale[LB_SLOTS - 1];
 #pragma unroll
-        for (int s = 0; s < NSLOT; ++s) {
-            const int j = j_[s];
-            if (j < 0) continue;
-            if (v_ == kk && j != kk) lb_store_t(panel + j * LB_BLK, acc[s], l64);
-            else if (j == kk && v_ != kk) {
-                lb_store_f(panel + v_ * LB_BLK, LB_PLANE, 0, lb_split8(acc[s], 0), l64);
-                lb_store_f(panel + v_ * LB_BLK, LB_PLANE, 1, lb_split8(acc[s], 1), l64);
-            }
-            if (j == v_ && v_ == kk + 1) {
-                // in the chain's order: row 8 g + 4 half + e is its register 4 g + 2 half + e / 2 of half-wave e % 2
-                float *o = (float *)(lb_lds + LB_LDS_DIAG + ((kk + 1) & 1) * 4096) + 4 * lb_tile_row(l64 & 31) + 2 * (l64 >> 5);
+            for (int s = 1; s < LB_SLOTS; ++s) scale[s - 1] = lb_max_abs(acc[s]);
+            lb_tile_scales(scale);
 #pragma unroll
-                for (int q = 0; q < 16; ++q) o[(q >> 2) * 256 + 128 * (q & 1) + ((q >> 1) & 1)] = acc[s][q];
+            for (int s = 1; s < LB_SLOTS; ++s) {
+                if (j_[s] < 0) break;
+                lb_store_t(panel + j_[s] * LB_BLK, acc[s], scale[s - 1], l64);
+                if (l64 == 0) un[j_[s]] = lb_reciprocal(scale[s - 1]);
             }
+            return;
+        }
+#pragma unroll
+        for (int s = 1; s < LB_SLOTS; ++s) {
+            if (j_[s] != kk) continue;
+            const float scale = lb_tile_scale(acc[s]);
+            lb_store_f(panel + v_ * LB_BLK, LB_PLANE, 0, lb_split8(acc[s], 0, scale), l64);
+            lb_store_f(panel + v_ * LB_BLK, LB_PLANE, 1, lb_split8(acc[s], 1, scale), l64);
+            if (l64 == 0) un[v_] = lb_reciprocal(scale);
+        }
+        if (v_ == kk + 1) {
+            // in the chain's order: row 8 g + 4 half + e is its register 4 g + 2 half + e / 2 of half-wave e % 2
+            float *o = (float *)(lb_lds + LB_LDS_DIAG + ((kk + 1) & 1) * 4096) + 4 * lb_tile_row(l64 & 31) + 2 * (l64 >> 5);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) o[(q >> 2) * 256 + 128 * (q & 1) + ((q >> 1) & 1)] = acc[0][q];
         }
     };
 #pragma unroll
-    for (int s = 0; s < NSLOT; ++s)
-        if (j_[s] >= 0) scale_tile(acc[s], j_[s], v_, false);
+    for (int s = 0; s < LB_SLOTS; ++s)
+        if (j_[s] >= 0) scale_tile(acc[s], j_[s], v_, false, s == 0);
     publish(0, lane);
 
     for (int k = 0; k < T; ++k) {
         // (per-step copy of the lane index: as loop invariants, LDS addresses would be kept live throughout)
         int l64 = lane;
         asm volatile("" : "+v"(l64));
-        const unsigned fm = form_mask(k);
         const char *panel = lb_lds + (k & 1) * LB_PANEL, *Dq = lb_lds + LB_LDS_D + (k & 1) * LB_DP;
         __syncthreads();   // D and panel of step k
         __builtin_amdgcn_s_sleep(2);   // the chain's reads first
+        // the star whose whole panel is published at the end of the step goes first, then those that publish one tile
+        if (v_ == k + 1) __builtin_amdgcn_s_setprio(3);
+        else if (k + 1 < T && lb_form_f(T, v_, k + 1)) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
         if (v_ >= 0) {
-            // One path for all tiles: N_jv (+)= R_j P_v^T with the identity for R_v where v = k (P = D) and for R_j where
-            // j = k, and a zero start for the tiles of block k (I P = P_v^T, R_j D, I D: exact, h + m + l).  The diagonal
-            // tile of block k + 1 is the chain's: what is left in it here is replaced in the next step.
-            LbFrag f[2], dq[2];
-            lb_read_panel(f, panel, v_ == k ? LB_IDENT : v_, v_ == k || ((fm >> v_) & 1), l64);
+            // N_jv += R_j P_v^T with the identity for R_v where v = k (P = D); of the tiles of block k, N_kv = P_v^T (j = k) and
+            // N_jk = R_j D (v = k).  The diagonal tile of block k + 1 is the chain's: what is left in it here is replaced in the
+            // next step.
+            LbFrag f[2][2], dq[2];
+            const float *un = unscale + 16 * (k & 1);
+            const int iv = v_ == k ? LB_IDENT : v_;
+            lb_read_panel(f[1], panel, iv, v_ == k || lb_form_f(T, v_, k), l64);
             dq[0] = lb_read_f(Dq, 2048, 0, l64);
             dq[1] = lb_read_f(Dq, 2048, 1, l64);
-            lb_floatx16 p;
+            const float un_p = un[LB_UN_D] * un[iv];
+            float un_j[LB_SLOTS];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) p[q] = 0.f;
-            lb_mma(p, dq[0], f[0]);
-            lb_mma(p, dq[1], f[1]);
-            const LbFrag p0 = lb_split8(p, 0), p1 = lb_split8(p, 1);
+            for (int s = 0; s < LB_SLOTS; ++s) un_j[s] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(un[max(j_[s], 0)])));
+            // the fragments of a tile are requested ahead of the products of the one before (those of tile (v, v) are at hand)
+            auto read_tile = [&](int s) {
+                if (j_[s] >= 0 && j_[s] != k) lb_read_panel(f[(s + 1) & 1], panel, j_[s], lb_form_f(T, j_[s], k), l64);
+            };
+            read_tile(1);
+            const lb_floatx16 p = lb_mma(dq, f[1]);
+            const float scale = half_scale(__uint_as_float(lb_max_halves(__float_as_uint(lb_max_abs(p)))), LB_TOP), un_v = lb_reciprocal(scale) * un_p;
+            dq[0] = lb_split8(p, 0, scale);
+            dq[1] = lb_split8(p, 1, scale);
 #pragma unroll
-            for (int s = 0; s < NSLOT; ++s) {
+            for (int s = 0; s < LB_SLOTS; ++s)
+                if (j_[s] == k) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) acc[s][q] = p[q] * un_p;
+                }
+#pragma unroll
+            for (int s = 0; s < LB_SLOTS; ++s) {
                 const int j = j_[s];
                 if (j < 0) break;                       // (the slots of a star are filled from the front)
-                lb_read_panel(f, panel, j == k ? LB_IDENT : j, j == k || ((fm >> j) & 1), l64);
-                if (v_ == k || j == k) {
+                if (s > 0 && s + 1 < LB_SLOTS) read_tile(s + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (j == k) continue;
+                const float u = un_v * un_j[s];
+                const lb_floatx16 c = lb_mma(f[(s + 1) & 1], dq);
+                __builtin_amdgcn_sched_barrier(0);
+                if (v_ == k) {
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) acc[s][q] = 0.f;
+                    for (int q = 0; q < 16; ++q) acc[s][q] = c[q] * u;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) acc[s][q] = fmaf(c[q], u, acc[s][q]);
                 }
-                lb_mma(acc[s], f[0], p0);
-                lb_mma(acc[s], f[1], p1);
             }
         }
         if (k + 1 < T) publish(k + 1, l64);
     }
     __syncthreads();   // the panels are dead: staging tiles
 
-    // undo the scaling; every off-diagonal tile is written twice, as it is and (through a per-wavefront 32x33 LDS tile, so
-    // that it goes along rows as well) transposed; of a diagonal tile the lower half is written and mirrored: exactly symmetric
+    // undo the scaling; every off-diagonal tile is written twice, as it is and transposed, both through LDS tiles of the wavefront,
+    // so that a store is 16 bytes a lane along rows; of a diagonal tile the lower half is written and mirrored: exactly symmetric
     if (v_ < 0) return;
-    float *stage = (float *)lb_lds + w * (32 * 33);
+    float *st = (float *)lb_lds + worker * (2 * 32 * LB_STAGE), *stt = st + 32 * LB_STAGE;
 #pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
+    for (int s = 0; s < LB_SLOTS; ++s) {
         const int bi = j_[s], bj = v_;
-        if (bi < 0) continue;
+        if (bi < 0) break;
         float si[16], sj;
         tile_scales(si, sj, bi, bj, false);
-        lb_floatx16 x, y;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            x[q] = acc[s][q] * si[q] * sj;
-            stage[l32_ * 33 + 8 * (q >> 2) + 4 * h_ + (q & 3)] = x[q];          // transposed
-        }
+        for (int g = 0; g < 4; ++g) {
+            lb_floatx4 x;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) y[q] = stage[(8 * (q >> 2) + 4 * h_ + (q & 3)) * 33 + l32_];
-        float *dx = J.dst + (unsigned)(32 * bi) * ldd + (unsigned)(32 * bj + l32_);   // rows of block bi
-        float *dy = J.dst + (unsigned)(32 * bj) * ldd + (unsigned)(32 * bi + l32_);   // the mirror image
-        if (bi != bj && whole(bi, bj)) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) dx[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = x[q];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) dy[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = y[q];
-        } else {
-            const int room_i = n - 32 * bi, room_j = n - 32 * bj;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int r = 8 * (q >> 2) + 4 * h_ + (q & 3);
-                // of a diagonal tile the elements below and on the diagonal, and those above from their mirror image
-                const float z = (bi != bj || l32_ <= r) ? x[q] : y[q];
-                if (r < room_i && l32_ < room_j) dx[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = z;
-                if (bi != bj && r < room_j && l32_ < room_i) dy[(unsigned)(8 * (q >> 2) + 4 * h_ + (q & 3)) * ldd] = y[q];
+            for (int e = 0; e < 4; ++e) {
+                x[e] = acc[s][4 * g + e] * si[4 * g + e] * sj;
+                st[(8 * g + 4 * h_ + e) * LB_STAGE + l32_] = x[e];
             }
+            *(lb_floatx4 *)(stt + l32_ * LB_STAGE + 8 * g + 4 * h_) = x;
         }
+        const int c4 = 4 * (lane & 7), r8 = lane >> 3;
+        const bool inside = whole(bi, bj);
+        auto store = [&](const float *from, int br, int bc) {   // rows of block br
+            const Global<char> to = (Global<char>)(dst + (long long)(32 * br) * ldd + 32 * bc);
+            const unsigned at = 4u * (r8 * ldd + c4);
+            lb_floatx4 x[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                x[g] = *(const lb_floatx4 *)(from + (8 * g + r8) * LB_STAGE + c4);
+                if (s == 0) {   // above the diagonal: from the mirror image
+                    const lb_floatx4 y = *(const lb_floatx4 *)(stt + (8 * g + r8) * LB_STAGE + c4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[g][e] = c4 + e <= 8 * g + r8 ? x[g][e] : y[e];
+                }
+            }
+            if (inside) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) *(Global<lb_floatx4_u>)(to + (long long)(8 * g) * ldd * 4 + at) = x[g];
+            } else {
+                const int cols = n - 32 * bc, rows = n - 32 * br;
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (8 * g + r8 < rows && c4 + e < cols) *(Global<float>)(to + (long long)(8 * g) * ldd * 4 + at + 4 * e) = x[g][e];
+            }
+        };
+        store(st, bi, bj);
+        if (s > 0) store(stt, bj, bi);
     }
 }
 
-template <int NSLOT>
-static hipError_t launch_leaf_block(const LeafJob *jobs_dev, int n_jobs, const float *damp_dev, int32_t *info,
-                                    hipStream_t s)
+hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, const float *damp_dev, int32_t *info, hipStream_t s)
 {
+    if (n_jobs <= 0) return hipSuccess;
     constexpr size_t lds_bytes = LB_LDS_BYTES;
     static bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void *)leaf_block_kernel<NSLOT>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        hipError_t e = hipFuncSetAttribute((const void *)leaf_block_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    leaf_block_kernel<NSLOT><<<dim3(n_jobs), dim3(1024), lds_bytes, s>>>(jobs_dev, damp_dev, info);
+    leaf_block_kernel<<<dim3(n_jobs), dim3(LB_THREADS), lds_bytes, s>>>(jobs_dev, damp_dev, info);
     return hipGetLastError();
-}
-
-hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, int size_class, const float *damp_dev,
-                       int32_t *info, hipStream_t s)
-{
-    if (n_jobs <= 0) return hipSuccess;
-    switch (kLeafClasses[size_class]) {   // class value = n_max / 32: one, two or three tiles for each of fifteen wavefronts
-        case 5: return launch_leaf_block<1>(jobs_dev, n_jobs, damp_dev, info, s);
-        case 7: return launch_leaf_block<2>(jobs_dev, n_jobs, damp_dev, info, s);
-        case 9: return launch_leaf_block<3>(jobs_dev, n_jobs, damp_dev, info, s);
-        default: return hipErrorInvalidValue;
-    }
 }
 
 }  // namespace kfac

@@ -1101,13 +1101,6 @@ struct InvOp {
     GemmProblem gemm;
 };
 
-int leaf_class(int n)
-{
-    for (int c = 0; c < kNumLeafClasses; ++c)
-        if (n <= 32 * kLeafClasses[c]) return c;
-    return -1;
-}
-
 int split_point(int n)
 {
     int n1 = ((n / 2) + 16) / 32 * 32;
@@ -1291,7 +1284,6 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             Lf.kind = L_LEAF;
             Lf.off_a = plan.tab.add(lj.data(), lj.size() * sizeof(LeafJob));
             Lf.n = (int)lj.size();
-            Lf.cfg = leaf_class(lj.front().n);
             Lf.p0 = damp;
             Lf.p1 = info;
             plan.launches.push_back(Lf);
@@ -1830,8 +1822,7 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
                 e = launch_copy_damp((const CopyJob *)(tab_dev + L.off_a), L.n, L.total_wgs, (const float *)L.p0, ls);
                 break;
             case L_LEAF:
-                e = launch_leaf((const LeafJob *)(tab_dev + L.off_a), L.n, L.cfg, (const float *)L.p0,
-                                (int32_t *)L.p1, ls);
+                e = launch_leaf((const LeafJob *)(tab_dev + L.off_a), L.n, (const float *)L.p0, (int32_t *)L.p1, ls);
                 break;
             case L_ZERO:
                 e = launch_zero_i32((int32_t *)L.p0, L.n, ls);

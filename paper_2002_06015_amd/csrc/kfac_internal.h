@@ -254,6 +254,14 @@ struct PackJob {
 constexpr int kPackChunk = 4096;
 
 #ifdef __HIPCC__
+// A pointer that comes out of a device table is a generic one to the compiler.  Accesses through it are flat instructions, which
+// count as LDS accesses too and return in no order: every wait for one, or for LDS beside one, is a wait for all of them.  Kernels
+// take the pointers of their tables through global().
+template <typename T>
+using Global = T __attribute__((address_space(1))) *;
+template <typename T>
+__device__ __forceinline__ Global<T> global(T *p) { return (Global<T>)p; }
+
 // ---- fp32 as the exact sum of three bf16 values (8 + 8 + 8 significant bits) -------------------------
 // two fp32 values -> their packed (h, m, l) bf16 pairs, low half = first value
 __device__ __forceinline__ void split_pair(float x0, float x1, unsigned &h, unsigned &m, unsigned &l)
@@ -265,6 +273,27 @@ __device__ __forceinline__ void split_pair(float x0, float x1, unsigned &h, unsi
     h = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
     m = __builtin_amdgcn_perm(c1, c0, 0x07060302u);
     l = __builtin_amdgcn_perm(__float_as_uint(q1), __float_as_uint(q0), 0x07060302u);
+}
+
+// ---- fp32, scaled, as the sum of two fp16 values (11 + 11 significant bits and the sign of the second) ----
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+
+// two fp32 values, scaled -> their packed (h, l) fp16 pairs, low half = first value
+__device__ __forceinline__ void split_half_pair(float x0, float x1, float s, unsigned &h, unsigned &l)
+{
+    const float y0 = x0 * s, y1 = x1 * s;
+    half2_t hh = {(_Float16)y0, (_Float16)y1};
+    asm("" : "+v"(hh));   // (keeps the compiler from converting each half a second time)
+    const half2_t ll = {(_Float16)(y0 - (float)hh[0]), (_Float16)(y1 - (float)hh[1])};
+    h = __builtin_bit_cast(unsigned, hh);
+    l = __builtin_bit_cast(unsigned, ll);
+}
+// power of two that brings |x| in [2^e, 2^(e+1)) to [2^top, 2^(top+1)); 1 for x == 0.  (2^118 at most: the scaled row stays finite.)
+__device__ __forceinline__ float half_scale(float x, int top)
+{
+    const int e = (int)(__float_as_uint(x) >> 23);
+    return x == 0.f ? 1.f : __uint_as_float((unsigned)min(254 + top - e, 127 + 118) << 23);
 }
 
 #endif
@@ -288,8 +317,7 @@ hipError_t launch_copy_damp(const CopyJob *jobs_dev, int n_jobs, int total_wgs, 
 // pass 0: the border row/column (total_wgs workgroups); pass 1: the corner (one workgroup per job)
 hipError_t launch_border(const BorderJob *jobs_dev, int n_jobs, int total_wgs, int pass, const float *damp_dev,
                          int32_t *info, hipStream_t s);
-hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, int size_class, const float *damp_dev,
-                       int32_t *info, hipStream_t s);
+hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, const float *damp_dev, int32_t *info, hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s);
 hipError_t launch_bn(const BnJob *jobs_dev, int n_jobs, int total_wgs, int N, float decay, float lambda,
                      hipStream_t s);
@@ -306,9 +334,6 @@ hipError_t launch_update(const UpdateJob *jobs_dev, int n_jobs, int total_wgs, i
                          float eps, hipStream_t s);
 hipError_t launch_staleness(const StaleJob *jobs_dev, int n_jobs, int total_wgs, int pass, hipStream_t s);
 
-// leaf size classes: the kernel of class value B serves n <= 32*B
-static const int kLeafClasses[] = {5, 7, 9};
-static const int kNumLeafClasses = 3;
-static const int kLeafMax = 288;
+static const int kLeafMax = 288;   // largest n of a leaf inversion
 
 }  // namespace kfac

@@ -107,6 +107,45 @@ def test_correlated_neighbours(kind, n, value):
     assert np.abs(got * scaled - ref).max() <= 4 * kappa * 2.0 ** -24 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("n", [64, 65, 96, 128, 160, 200, 256, 288])
+@pytest.mark.parametrize("kind", ["diagonal", "steep", "far"])
+def test_blocks_of_different_magnitude(n, kind):
+    """Panel blocks are scaled one by one: zero blocks, blocks whose elements grow large once their rows are swept beside others
+    that stay small, and couplings far below the diagonal."""
+    rng = np.random.default_rng(n)
+    b = rng.standard_normal((2 * n + 8, n))
+    x = b.T @ b / len(b)
+    block = np.arange(n) // 32
+    if kind == "diagonal":
+        x = np.where(block[:, None] == block[None, :], x, 0.0)
+    elif kind == "steep":      # the first block nearly singular, the others tied to it
+        first = block == 0
+        q, _ = np.linalg.qr(rng.standard_normal((32, 32)))
+        x[np.ix_(first, first)] = q @ np.diag(np.geomspace(1, 1e-3, 32)) @ q.T
+        x[np.ix_(first, ~first)] *= 1e-3
+        x[np.ix_(~first, first)] *= 1e-3
+    else:
+        x = np.where(block[:, None] == block[None, :], x, x * 2.0 ** -18)
+    x = x.astype(np.float32)
+    x = np.ascontiguousarray((x + x.T) / np.float32(2))
+    got, _, _, info = _invert(x, np.eye(4, dtype=np.float32), 0.0)
+    assert info == [0, 0]
+    d = x.astype(np.float64)
+    s = 1 / np.sqrt(np.diag(d))
+    kappa = np.linalg.cond(d * s[:, None] * s[None, :])
+    scaled = (1 / s)[:, None] * (1 / s)[None, :]
+    ref = np.linalg.inv(d) * scaled
+    # the bound of test_correlated_neighbours; where blocks do not touch, each is as accurate as if it were alone, to what its
+    # scale keeps of elements 2^-18 of the largest (2^-22 of them)
+    err = np.abs(got * scaled - ref)
+    assert err.max() <= 4 * kappa * 2.0 ** -24 * np.abs(ref).max()
+    if kind == "diagonal":
+        assert not err[block[:, None] != block[None, :]].any()
+    if kind == "far":
+        off = block[:, None] != block[None, :]
+        assert err[off].max() <= 4 * n * kappa * 2.0 ** -22 * np.abs(ref[off]).max()
+
+
 def test_leaves_of_all_sizes_in_one_call():
     """One launch takes the leaves of all sizes: the same bits as a call per size."""
     X = {}
