@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(const BnReduceJob *__res
     const int here = (int)(rows - row0 < R ? rows - row0 : R);        // rows of this workgroup
     const bn_vec4 zero = {0.f, 0.f, 0.f, 0.f};
     if (HW <= 128) {
-        const float *dy = J.dy + row0 * HW, *xh = J.xhat + row0 * HW;
+        const Global<const float> dy = global(J.dy) + row0 * HW, xh = global(J.xhat) + row0 * HW;
         const int total = here * HW;                                  // <= 4096
         bn_vec4 a[4], b[4];
 #pragma unroll
@@ -57,8 +57,8 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(const BnReduceJob *__res
             const int e = 4 * (tid + 256 * g);
             a[g] = b[g] = zero;
             if (e + 4 <= total) {
-                a[g] = __builtin_nontemporal_load((const bn_vec4 *)(dy + e));
-                b[g] = __builtin_nontemporal_load((const bn_vec4 *)(xh + e));
+                a[g] = __builtin_nontemporal_load((Global<const bn_vec4>)(dy + e));
+                b[g] = __builtin_nontemporal_load((Global<const bn_vec4>)(xh + e));
             } else {
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
@@ -85,8 +85,8 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(const BnReduceJob *__res
         }
         for (int o = T >> 1; o > 0; o >>= 1) { sg += __shfl_xor(sg, o, 64); sb += __shfl_xor(sb, o, 64); }
         if (r < here && j == 0) {
-            J.g_gamma[row0 + r] = sg;
-            J.g_beta[row0 + r] = sb;
+            global(J.g_gamma)[row0 + r] = sg;
+            global(J.g_beta)[row0 + r] = sb;
         }
         return;
     }
@@ -95,14 +95,14 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(const BnReduceJob *__res
     if (first >= here) return;
     const int n4 = HW & ~3;
     if (per_wave == 4) {
-        const float *dy = J.dy + (row0 + first) * HW, *xh = J.xhat + (row0 + first) * HW;
+        const Global<const float> dy = global(J.dy) + (row0 + first) * HW, xh = global(J.xhat) + (row0 + first) * HW;
         bn_vec4 a[4], b[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             a[q] = b[q] = zero;
             if (first + q < here && 4 * lane < n4) {
-                a[q] = __builtin_nontemporal_load((const bn_vec4 *)(dy + q * HW + 4 * lane));
-                b[q] = __builtin_nontemporal_load((const bn_vec4 *)(xh + q * HW + 4 * lane));
+                a[q] = __builtin_nontemporal_load((Global<const bn_vec4>)(dy + q * HW + 4 * lane));
+                b[q] = __builtin_nontemporal_load((Global<const bn_vec4>)(xh + q * HW + 4 * lane));
             }
         }
         float sg[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
@@ -121,13 +121,13 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(const BnReduceJob *__res
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             if (lane == 0 && first + q < here) {
-                J.g_gamma[row0 + first + q] = sg[q];
-                J.g_beta[row0 + first + q] = sb[q];
+                global(J.g_gamma)[row0 + first + q] = sg[q];
+                global(J.g_beta)[row0 + first + q] = sb[q];
             }
         return;
     }
     const long long row = row0 + first;
-    const float *dy = J.dy + row * HW, *xh = J.xhat + row * HW;
+    const Global<const float> dy = global(J.dy) + row * HW, xh = global(J.xhat) + row * HW;
     float sg = 0.f, sb = 0.f;
     for (int t = 4 * lane; t < n4; t += 1024) {
         bn_vec4 a[4], b[4];
@@ -135,8 +135,8 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(const BnReduceJob *__res
         for (int q = 0; q < 4; ++q) {
             a[q] = b[q] = zero;
             if (t + 256 * q < n4) {
-                a[q] = __builtin_nontemporal_load((const bn_vec4 *)(dy + t + 256 * q));
-                b[q] = __builtin_nontemporal_load((const bn_vec4 *)(xh + t + 256 * q));
+                a[q] = __builtin_nontemporal_load((Global<const bn_vec4>)(dy + t + 256 * q));
+                b[q] = __builtin_nontemporal_load((Global<const bn_vec4>)(xh + t + 256 * q));
             }
         }
 #pragma unroll
@@ -150,8 +150,8 @@ __global__ __launch_bounds__(256) void bn_reduce_kernel(const BnReduceJob *__res
     sg = wave_sum(sg);
     sb = wave_sum(sb);
     if (lane == 0) {
-        J.g_gamma[row] = sg;
-        J.g_beta[row] = sb;
+        global(J.g_gamma)[row] = sg;
+        global(J.g_beta)[row] = sb;
     }
 }
 
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc_kernel(const BnReduceJob *
     const int chunks = (J.C + 63) / 64;
     const int local = wg - J.wg_start;
     const int n = local / chunks, c0 = (local - n * chunks) * 64;
-    const float *dy = J.dy + (long long)n * J.HW * J.C;
-    const float *xh = J.xhat + (long long)n * J.HW * J.C;
+    const Global<const float> dy = global(J.dy) + (long long)n * J.HW * J.C;
+    const Global<const float> xh = global(J.xhat) + (long long)n * J.HW * J.C;
     const bool vec = ((J.C & 3) == 0) && ((((uintptr_t)J.dy | (uintptr_t)J.xhat) & 15) == 0);
     const int tid = threadIdx.x;
     if (vec) {
@@ -180,8 +180,8 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc_kernel(const BnReduceJob *
         floatx4 sg = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
         if (c < J.C)
             for (int t = part; t < J.HW; t += 16) {
-                const floatx4 a = *(const floatx4 *)(dy + (long long)t * J.C + c);
-                const floatx4 b = *(const floatx4 *)(xh + (long long)t * J.C + c);
+                const floatx4 a = *(Global<const floatx4>)(dy + (long long)t * J.C + c);
+                const floatx4 b = *(Global<const floatx4>)(xh + (long long)t * J.C + c);
                 sg += a * b;
                 sb += a;
             }
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc_kernel(const BnReduceJob *
         const int parts = vec ? 16 : 4;
         float sum = 0.f;
         for (int q = 0; q < parts; ++q) sum += red[which][q][cl];
-        if (c0 + cl < J.C) (which ? J.g_beta : J.g_gamma)[(long long)n * J.C + c0 + cl] = sum;
+        if (c0 + cl < J.C) global(which ? J.g_beta : J.g_gamma)[(long long)n * J.C + c0 + cl] = sum;
     }
 }
 
@@ -228,8 +228,8 @@ __global__ __launch_bounds__(256) void bn_unit_kernel(const BnJob *__restrict__ 
     if (i < J.C) {
 #pragma unroll 8
         for (int n = part; n < N; n += 4) {
-            const float gg = J.g_gamma[(long long)n * J.C + i];
-            const float gb = J.g_beta[(long long)n * J.C + i];
+            const float gg = global(J.g_gamma)[(long long)n * J.C + i];
+            const float gb = global(J.g_beta)[(long long)n * J.C + i];
             a = fmaf(gg, gg, a); b = fmaf(gg, gb, b); d = fmaf(gb, gb, d);
             mg += gg; mb += gb;
         }
@@ -241,15 +241,15 @@ __global__ __launch_bounds__(256) void bn_unit_kernel(const BnJob *__restrict__ 
     a = sum(0); b = sum(1); d = sum(2); mg = sum(3); mb = sum(4);
     const float inv_n = 1.0f / (float)N;
     a *= inv_n; b *= inv_n; d *= inv_n; mg *= inv_n; mb *= inv_n;
-    float *F = J.F_ema + (long long)3 * i;
+    const Global<float> F = global(J.F_ema) + (long long)3 * i;
     float f0 = (1.0f - decay) * a, f1 = (1.0f - decay) * b, f2 = (1.0f - decay) * d;
     if (decay != 0.0f) { f0 += decay * F[0]; f1 += decay * F[1]; f2 += decay * F[2]; }
     F[0] = f0; F[1] = f1; F[2] = f2;
     // (F + lambda I)^-1 [mg, mb]^T with [[a,b],[c,d]]^-1 = 1/(ad - bc) [[d,-b],[-c,a]]
     const float fa = f0 + lambda, fd = f2 + lambda;
     const float det = fa * fd - f1 * f1;
-    J.out_gamma[i] = (fd * mg - f1 * mb) / det;
-    J.out_beta[i] = (fa * mb - f1 * mg) / det;
+    global(J.out_gamma)[i] = (fd * mg - f1 * mb) / det;
+    global(J.out_beta)[i] = (fa * mb - f1 * mg) / det;
 }
 
 hipError_t launch_bn(const BnJob *jobs_dev, int n_jobs, int total_wgs, int N, float decay, float lambda,

@@ -20,9 +20,9 @@ __device__ __forceinline__ const BnFullJob *bnf_find(const BnFullJob *jobs, int 
 }
 
 // element k of the interleaved per-sample gradient of sample n
-__device__ __forceinline__ float bnf_elem(const float *g_gamma, const float *g_beta, int C, int n, int k)
+__device__ __forceinline__ float bnf_elem(Global<const float> g_gamma, Global<const float> g_beta, int C, int n, int k)
 {
-    const float *src = (k & 1) ? g_beta : g_gamma;
+    const Global<const float> src = (k & 1) ? g_beta : g_gamma;
     return src[(long long)n * C + (k >> 1)];
 }
 
@@ -35,8 +35,8 @@ __global__ __launch_bounds__(256) void bn_full_factor_kernel(const BnFullJob *__
     __shared__ float rows[32][64];
     __shared__ float cols[32][64];
     const BnFullJob *Jp = bnf_find(jobs, n_jobs, blockIdx.x, 0);
-    const float *g_gamma = Jp->g_gamma, *g_beta = Jp->g_beta;
-    float *F = Jp->F_ema;
+    const Global<const float> g_gamma = global(Jp->g_gamma), g_beta = global(Jp->g_beta);
+    const Global<float> F = global(Jp->F_ema);
     const int C = Jp->C;
     const int local = blockIdx.x - Jp->wg_start[0];
     const int d = 2 * C;
@@ -47,11 +47,11 @@ __global__ __launch_bounds__(256) void bn_full_factor_kernel(const BnFullJob *__
     // whole tile (every tile when C is a multiple of 32): 16-byte accesses, and the old values are
     // requested before the products are formed
     const bool whole = r0 + 64 <= d && c0 + 64 <= d;
-    float *base = F + (long long)(r0 + 4 * ty) * d + c0 + 4 * tx;
+    const Global<float> base = F + (long long)(r0 + 4 * ty) * d + c0 + 4 * tx;
     v4 old[4];
     if (whole && decay != 0.f) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) old[i] = *(const v4 *)(base + (long long)i * d);
+        for (int i = 0; i < 4; ++i) old[i] = *(Global<const v4>)(base + (long long)i * d);
     }
     float acc[4][4];
 #pragma unroll
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void bn_full_factor_kernel(const BnFullJob *__
             v4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] = decay == 0.f ? w * acc[i][j] : fmaf(decay, old[i][j], w * acc[i][j]);
-            *(v4 *)(base + (long long)i * d) = o;
+            *(Global<v4>)(base + (long long)i * d) = o;
         }
         return;
     }
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void bn_full_factor_kernel(const BnFullJob *__
         for (int j = 0; j < 4; ++j) {
             const int c = c0 + 4 * tx + j;
             if (c >= d) continue;
-            float *p = F + (long long)r * d + c;
+            const Global<float> p = F + (long long)r * d + c;
             // decay == 0 must not read F (it may hold anything, NaN included, before the first step)
             *p = decay == 0.f ? w * acc[i][j] : fmaf(decay, *p, w * acc[i][j]);
         }
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void bn_full_mean_kernel(const BnFullJob *__re
                                                            float lambda, float *__restrict__ damp)
 {
     const BnFullJob *Jp = bnf_find(jobs, n_jobs, blockIdx.x, 1);
-    const float *g_gamma = Jp->g_gamma, *g_beta = Jp->g_beta;
+    const Global<const float> g_gamma = global(Jp->g_gamma), g_beta = global(Jp->g_beta);
     const int C = Jp->C, damp_idx = Jp->damp_idx;
     const int local = blockIdx.x - Jp->wg_start[1];
     const int k = local * 256 + threadIdx.x;
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void bn_full_mean_kernel(const BnFullJob *__re
     if (k >= 2 * C) return;
     float s = 0.f;
     for (int n = 0; n < N; ++n) s += bnf_elem(g_gamma, g_beta, C, n, k);
-    Jp->gbar[k] = s / (float)N;
+    global(Jp->gbar)[k] = s / (float)N;
 }
 
 // Pass 2: u = F_inv gbar, one wavefront per row, four rows per workgroup.
@@ -128,17 +128,17 @@ __global__ __launch_bounds__(256) void bn_full_apply_kernel(const BnFullJob *__r
     typedef float v4 __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte access, element alignment
     const BnFullJob *Jp = bnf_find(jobs, n_jobs, blockIdx.x, 2);
     const int local = blockIdx.x - Jp->wg_start[2];
-    const float *gbar = Jp->gbar;
+    const Global<const float> gbar = global((const float *)Jp->gbar);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int d = 2 * Jp->C;
     const int r = local * 4 + wave;
     if (r >= d) return;
-    const float *row = Jp->F_inv + (long long)r * d;
+    const Global<const float> row = global(Jp->F_inv) + (long long)r * d;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
     if ((d & 3) == 0) {
         for (int k = 4 * lane; k < d; k += 256) {
-            const v4 f = *(const v4 *)(row + k);
-            const v4 g = *(const v4 *)(gbar + k);
+            const v4 f = *(Global<const v4>)(row + k);
+            const v4 g = *(Global<const v4>)(gbar + k);
             s0 = fmaf(f.x, g.x, s0); s1 = fmaf(f.y, g.y, s1); s2 = fmaf(f.z, g.z, s2); s3 = fmaf(f.w, g.w, s3);
         }
     } else {
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void bn_full_apply_kernel(const BnFullJob *__r
     float s = (s0 + s1) + (s2 + s3);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) ((r & 1) ? Jp->out_beta : Jp->out_gamma)[r >> 1] = s;
+    if (lane == 0) global((r & 1) ? Jp->out_beta : Jp->out_gamma)[r >> 1] = s;
 }
 
 hipError_t launch_bn_full(const BnFullJob *jobs_dev, int n_jobs, int total_wgs, int pass, int N, float decay,

@@ -43,6 +43,7 @@ __global__ __launch_bounds__(256) void pad_kernel(const PadJob *__restrict__ job
     // group that starts in the last column where there are only two of them.  ResNet-50, batch 128 (32): 452 us (105), 528 (127)
     // with divisions and single loads here and in part 2.
     const long long n4 = J.padded_floats / 4;
+    const Global<const float> src = global(J.src);
     if (idx < n4) {
         typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
         // (total and the front slack are multiples of 4: a group lies inside the planes or outside as a whole)
@@ -62,12 +63,12 @@ __global__ __launch_bounds__(256) void pad_kernel(const PadJob *__restrict__ job
                 yp = r / Wp;
             }
             const int xp = r - yp * Wp;
-            const float *sp = J.src + plane * H * W;
+            const Global<const float> sp = src + plane * H * W;
             if (yp >= y0) {
                 const int c0 = xp - x0;                                     // source column of the first element
                 const int o = (yp - y0) * W + c0;
                 if ((plane > 0 || o >= 0) && (plane + 1 < planes || o + 4 <= H * W)) {
-                    const floatx4_u x = *(const floatx4_u *)(sp + o);
+                    const floatx4_u x = *(Global<const floatx4_u>)(sp + o);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = c0 + e >= 0 && c0 + e < W ? x[e] : 0.f;
                 } else {                                                    // first and last groups of the tensor
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256) void pad_kernel(const PadJob *__restrict__ job
             }
             if (xp == Wp - 1 && x0 == 2 && yp + 1 >= y0 && yp + 1 < J.Hp) v[3] = sp[(yp + 1 - y0) * W];
         }
-        *(corr_floatx4 *)(J.padded + idx * 4) = v;
+        *(Global<corr_floatx4>)(global(J.padded) + idx * 4) = v;
         return;
     }
     // Part 2: border rows (top, bottom) [2][C][N][Lw], border columns (left, right) [2][C][N][Lh], 4 elements of a line per thread
@@ -90,21 +91,21 @@ __global__ __launch_bounds__(256) void pad_kernel(const PadJob *__restrict__ job
         corr_floatx4 v = {0.f, 0.f, 0.f, 0.f};
         if (l < 2 * CN) {
             const unsigned which = l >= CN ? 1 : 0, cn = l - which * CN, c = cn / (unsigned)J.N, n = cn - c * (unsigned)J.N;
-            const float *sp = J.src + ((long long)n * J.C + c) * H * W;
+            const Global<const float> sp = src + ((long long)n * J.C + c) * H * W;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if ((int)q0 + e < len) v[e] = source(sp, which, (int)q0 + e);
         }
-        *(corr_floatx4 *)(out + 4LL * k) = v;
+        *(Global<corr_floatx4>)(global(out) + 4LL * k) = v;
     };
     const unsigned rows4 = 2 * CN * (J.Lw / 4) + 1, cols4 = 2 * CN * (J.Lh / 4) + 1;
     if (k0 < rows4) {
-        line(k0, J.Lw / 4, J.rows, W, [&](const float *sp, unsigned which, int q) { return sp[(which ? H - 1 : 0) * W + q]; });
+        line(k0, J.Lw / 4, J.rows, W, [&](Global<const float> sp, unsigned which, int q) { return sp[(which ? H - 1 : 0) * W + q]; });
     } else if (k0 - rows4 < cols4) {
-        line(k0 - rows4, J.Lh / 4, J.cols, H, [&](const float *sp, unsigned which, int q) { return sp[q * W + (which ? W - 1 : 0)]; });
+        line(k0 - rows4, J.Lh / 4, J.cols, H, [&](Global<const float> sp, unsigned which, int q) { return sp[q * W + (which ? W - 1 : 0)]; });
     } else if (k0 - rows4 - cols4 < 4 * CN) {
         const unsigned k = k0 - rows4 - cols4, which = k / CN, cn = k - which * CN, c = cn / (unsigned)J.N, n = cn - c * (unsigned)J.N;
-        J.corners[k] = J.src[((long long)n * J.C + c) * H * W + (which & 2 ? H - 1 : 0) * W + (which & 1 ? W - 1 : 0)];
+        global(J.corners)[k] = src[((long long)n * J.C + c) * H * W + (which & 2 ? H - 1 : 0) * W + (which & 1 ? W - 1 : 0)];
     }
 }
 
@@ -139,6 +140,7 @@ __global__ __launch_bounds__(256) void pad_bf16_kernel(const PadJobBF16 *__restr
     // in the source, too): the window is a run of 12 source elements with the columns outside the image zeroed by value,
     // two loads instead of twelve (ResNet-50, batch 32: 173 us, 200 with twelve).  Element-aligned 16-byte accesses.
     const long long per_copy = J.copy_elems / 8;
+    const Global<const unsigned short> src = global(J.src);
     if (idx < per_copy) {
         const long long g = idx * 8 - J.front_slack, total = planes * PP;
         unsigned short win[12];
@@ -161,8 +163,8 @@ __global__ __launch_bounds__(256) void pad_bf16_kernel(const PadJobBF16 *__restr
                 const int c0 = xp - x0 - 2;                                      // source column of win[0]
                 const long long o = row + c0;
                 if (o >= 0 && o + 12 <= planes * H * W) {
-                    const corr_ushortx8_u lo8 = *(const corr_ushortx8_u *)(J.src + o);
-                    const corr_ushortx4_u hi4 = *(const corr_ushortx4_u *)(J.src + o + 8);
+                    const corr_ushortx8_u lo8 = *(Global<const corr_ushortx8_u>)(src + o);
+                    const corr_ushortx4_u hi4 = *(Global<const corr_ushortx4_u>)(src + o + 8);
 #pragma unroll
                     for (int e = 0; e < 12; ++e) {
                         const unsigned short x = e < 8 ? lo8[e & 7] : hi4[e & 3];
@@ -171,13 +173,13 @@ __global__ __launch_bounds__(256) void pad_bf16_kernel(const PadJobBF16 *__restr
                 } else {                                                         // first and last groups of the tensor
 #pragma unroll
                     for (int e = 0; e < 12; ++e)
-                        if (c0 + e >= 0 && c0 + e < W) win[e] = J.src[o + e];
+                        if (c0 + e >= 0 && c0 + e < W) win[e] = src[o + e];
                 }
             }
             // (yp == 0: the row before is the last one of the plane before; rows 1 .. y0 follow zero rows)
             if (xp == 0 && (yp > y0 || (yp == 0 && plane > 0))) {
-                win[0] = J.src[row - 2];
-                win[1] = J.src[row - 1];
+                win[0] = src[row - 2];
+                win[1] = src[row - 1];
             }
         }
 #pragma unroll
@@ -185,7 +187,7 @@ __global__ __launch_bounds__(256) void pad_bf16_kernel(const PadJobBF16 *__restr
             corr_ushortx8 v;
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = win[q + e];
-            *(corr_ushortx8 *)(J.padded + (long long)q * J.copy_elems + idx * 8) = v;
+            *(Global<corr_ushortx8>)(global(J.padded) + (long long)q * J.copy_elems + idx * 8) = v;
         }
         return;
     }
@@ -202,9 +204,9 @@ __global__ __launch_bounds__(256) void pad_bf16_kernel(const PadJobBF16 *__restr
             const int qx = (int)(r % J.Lw);
             const long long cn = r / J.Lw;
             const int n = (int)(cn % J.N), c = (int)(cn / J.N);
-            if (qx < W) x = J.src[((long long)n * J.C + c) * H * W + (long long)(which ? H - 1 : 0) * W + qx];
+            if (qx < W) x = src[((long long)n * J.C + c) * H * W + (long long)(which ? H - 1 : 0) * W + qx];
         }
-        J.rows[idx] = x;
+        global(J.rows)[idx] = x;
         return;
     }
     idx -= 3 * J.rows_elems;
@@ -219,9 +221,9 @@ __global__ __launch_bounds__(256) void pad_bf16_kernel(const PadJobBF16 *__restr
             const int py = (int)(r % J.Lh);
             const long long cn = r / J.Lh;
             const int n = (int)(cn % J.N), c = (int)(cn / J.N);
-            if (py < H) x = J.src[((long long)n * J.C + c) * H * W + (long long)py * W + (which ? W - 1 : 0)];
+            if (py < H) x = src[((long long)n * J.C + c) * H * W + (long long)py * W + (which ? W - 1 : 0)];
         }
-        J.cols[idx] = x;
+        global(J.cols)[idx] = x;
         return;
     }
     idx -= 3 * J.cols_elems;
@@ -230,7 +232,7 @@ __global__ __launch_bounds__(256) void pad_bf16_kernel(const PadJobBF16 *__restr
         const long long r = idx - (long long)which * J.C * J.Ln;
         const int n = (int)(r % J.Ln), c = (int)(r / J.Ln);
         const int py = (which & 2) ? H - 1 : 0, qx = (which & 1) ? W - 1 : 0;
-        J.corners[idx] = n < J.N ? J.src[((long long)n * J.C + c) * H * W + (long long)py * W + qx] : (unsigned short)0;
+        global(J.corners)[idx] = n < J.N ? src[((long long)n * J.C + c) * H * W + (long long)py * W + qx] : (unsigned short)0;
     }
 }
 
@@ -248,7 +250,7 @@ hipError_t launch_pad_bf16(const PadJobBF16 *jobs_dev, int n_jobs, int total_wgs
 // row of a Gram matrix and every write along the row of A (the interleaving of the nine k'
 // goes through LDS).
 struct CorrSource {
-    const float *full, *row, *col, *corner;   // row / col / corner: null if no such correction
+    Global<const float> full, row, col, corner;   // row / col / corner: null if no such correction
     int ld_full, ld_row, ld_col;
 };
 
@@ -259,21 +261,21 @@ __device__ __forceinline__ CorrSource corr_source(const AssembleJob &J, int ky, 
     const bool fwd = dy > 0 || (dy == 0 && dx >= 0);
     const int ey = fwd ? dy : -dy, ex = fwd ? dx : -dx;
     const int slot = ey == 0 ? ex : 3 + (ey - 1) * 5 + (ex + 2);
-    S.full = fwd ? J.full[slot] : J.full_t[slot];
+    S.full = global(fwd ? J.full[slot] : J.full_t[slot]);
     S.ld_full = J.ld_full[slot];
     const int row_out = (ky == kyp) ? (ky == 2 ? 0 : (ky == 0 ? 1 : -1)) : -1;   // 0: top row left out, 1: bottom
     const int col_out = (kx == kxp) ? (kx == 2 ? 0 : (kx == 0 ? 1 : -1)) : -1;   // 0: left column, 1: right
     if (row_out >= 0) {
         const int d = dx >= 0 ? dx : -dx;
-        S.row = dx >= 0 ? J.rows[row_out][d] : J.rows_t[row_out][d];
+        S.row = global(dx >= 0 ? J.rows[row_out][d] : J.rows_t[row_out][d]);
         S.ld_row = J.ld_rows[row_out][d];
     }
     if (col_out >= 0) {
         const int d = dy >= 0 ? dy : -dy;
-        S.col = dy >= 0 ? J.cols[col_out][d] : J.cols_t[col_out][d];
+        S.col = global(dy >= 0 ? J.cols[col_out][d] : J.cols_t[col_out][d]);
         S.ld_col = J.ld_cols[col_out][d];
     }
-    if (row_out >= 0 && col_out >= 0) S.corner = J.corners[2 * row_out + col_out];
+    if (row_out >= 0 && col_out >= 0) S.corner = global(J.corners[2 * row_out + col_out]);
     return S;
 }
 
@@ -281,14 +283,14 @@ __device__ __forceinline__ CorrSource corr_source(const AssembleJob &J, int ky, 
 __device__ __forceinline__ float corr_row_sum(const AssembleJob &J, int c, int ky, int kx)
 {
     const int row_out = ky == 2 ? 0 : (ky == 0 ? 1 : -1), col_out = kx == 2 ? 0 : (kx == 0 ? 1 : -1);
-    float v = J.full[0][(long long)c * J.ld_full[0] + J.C];
-    if (row_out >= 0) v -= J.rows[row_out][0][(long long)c * J.ld_rows[row_out][0] + J.C];
-    if (col_out >= 0) v -= J.cols[col_out][0][(long long)c * J.ld_cols[col_out][0] + J.C];
-    if (row_out >= 0 && col_out >= 0) v += J.corners[2 * row_out + col_out][(long long)c * J.ld_corner + J.C];
+    float v = global(J.full[0])[(long long)c * J.ld_full[0] + J.C];
+    if (row_out >= 0) v -= global(J.rows[row_out][0])[(long long)c * J.ld_rows[row_out][0] + J.C];
+    if (col_out >= 0) v -= global(J.cols[col_out][0])[(long long)c * J.ld_cols[col_out][0] + J.C];
+    if (row_out >= 0 && col_out >= 0) v += global(J.corners[2 * row_out + col_out])[(long long)c * J.ld_corner + J.C];
     return v;
 }
 
-__device__ __forceinline__ void corr_store(const AssembleJob &J, float *out, float v)
+__device__ __forceinline__ void corr_store(const AssembleJob &J, Global<float> out, float v)
 {
     float r = J.alpha * v;
     if (J.beta != 0.f) r = fmaf(J.beta, *out, r);
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(256) void assemble_kernel(const AssembleJob *__rest
     const AssembleJob &J = jobs[lo];
     const int d0 = 9 * J.C;
     const int i = wg - J.wg_start;          // row of A
-    float *out_row = J.A + (long long)i * J.ldA;
+    const Global<float> out_row = global(J.A) + (long long)i * J.ldA;
     if (i < d0) {
         const int c = i / 9, k = i - 9 * c, ky = k / 3, kx = k - 3 * ky;
         typedef float v4 __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte access, element alignment
@@ -331,18 +333,18 @@ __global__ __launch_bounds__(256) void assemble_kernel(const AssembleJob *__rest
             }
             __syncthreads();
             const int nout = 9 * min(256, J.C - cp0);
-            float *dst = out_row + 9 * cp0;
+            const Global<float> dst = out_row + 9 * cp0;
             for (int e = 4 * threadIdx.x; e < nout; e += 1024) {
                 if (e + 3 < nout) {
                     v4 r;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) r[q] = J.alpha * vals[(e + q) % 9][(e + q) / 9];
                     if (J.beta != 0.f) {
-                        const v4 o = *(const v4 *)(dst + e);
+                        const v4 o = *(Global<const v4>)(dst + e);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) r[q] = fmaf(J.beta, o[q], r[q]);
                     }
-                    *(v4 *)(dst + e) = r;
+                    *(Global<v4>)(dst + e) = r;
                 } else {
                     for (int q = 0; e + q < nout; ++q) corr_store(J, dst + e + q, vals[(e + q) % 9][(e + q) / 9]);
                 }

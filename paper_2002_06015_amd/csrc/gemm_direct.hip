@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 2 : 1) void gemm_direct_kernel(const
     const float alpha = P.alpha, beta = P.beta;
     // direct pass: a thread owns 4 adjacent columns of one row of every block; old values of all blocks requested first
     const int q8 = 4 * (tid & 7), r32 = tid >> 3;
-    float *mbase = !sym ? P.Ct : i0 - j0 - (32 * TN - 1) < P.mirror_band ? P.C : nullptr;
+    const Global<float> C = global(P.C), mbase = global(!sym ? P.Ct : i0 - j0 - (32 * TN - 1) < P.mirror_band ? P.C : nullptr);
     const long long ldm = sym ? P.ldc : P.ldct;
     gd_floatx4 old[BLOCKS];
 #pragma unroll
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 2 : 1) void gemm_direct_kernel(const
 #pragma unroll
         for (int b = 0; b < BLOCKS; ++b) {
             const int i = i0 + 32 * (b / TN) + r32, j = j0 + 32 * (b % TN) + q8;
-            if (i < P.M && j + 3 <= min(diag_tile ? i : P.N - 1, P.N - 1)) old[b] = *(const gd_floatx4_u *)(P.C + (long long)i * P.ldc + j);
+            if (i < P.M && j + 3 <= min(diag_tile ? i : P.N - 1, P.N - 1)) old[b] = *(Global<const gd_floatx4_u>)(C + (long long)i * P.ldc + j);
         }
     }
 #pragma unroll
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 2 : 1) void gemm_direct_kernel(const
         const int i = i0 + 32 * (b / TN) + r32, j = j0 + 32 * (b % TN) + q8;
         const int jmax = min(diag_tile ? i : P.N - 1, P.N - 1);   // last column this row may write
         if (i >= P.M || j > jmax) continue;
-        float *dst = P.C + (long long)i * P.ldc + j;
+        const Global<float> dst = C + (long long)i * P.ldc + j;
         gd_floatx4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = alpha * gd_sum<BLOCKS>(part, gd_place(b, r32, q8 + e));
@@ -201,8 +201,8 @@ __global__ __launch_bounds__(256, TM == 2 ? 2 : 1) void gemm_direct_kernel(const
             else
                 for (int e = 0; e < 4 && j + e <= jmax; ++e) v[e] = fmaf(beta, dst[e], v[e]);
         }
-        if (P.C) {
-            if (j + 3 <= jmax) *(gd_floatx4_u *)dst = v;
+        if (C) {
+            if (j + 3 <= jmax) *(Global<gd_floatx4_u>)dst = v;
             else
                 for (int e = 0; e < 4 && j + e <= jmax; ++e) dst[e] = v[e];
         }
@@ -219,11 +219,11 @@ __global__ __launch_bounds__(256, TM == 2 ? 2 : 1) void gemm_direct_kernel(const
             const int i = i0 + 32 * (b / TN) + q8, j = j0 + 32 * (b % TN) + r32;
             const int e0 = diag_tile ? max(0, j + 1 - i) : 0, e1 = min(4, P.M - i);
             if (j >= P.N || e0 >= e1) continue;
-            float *dst = mbase + (long long)j * ldm + i;
+            const Global<float> dst = mbase + (long long)j * ldm + i;
             gd_floatx4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = part[gd_place(b, q8 + e, r32)];
-            if (e0 == 0 && e1 == 4) *(gd_floatx4_u *)dst = v;
+            if (e0 == 0 && e1 == 4) *(Global<gd_floatx4_u>)dst = v;
             else
                 for (int e = e0; e < e1; ++e) dst[e] = v[e];
         }

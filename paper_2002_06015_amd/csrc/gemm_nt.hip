@@ -66,7 +66,7 @@ __device__ __forceinline__ void store_slab(const GemmProblem &P, float *T, int g
     constexpr int LDT = COLS + 1;
     const bool sym = (P.flags & GEMM_SYM) != 0;
     const float alpha = P.alpha, beta = P.beta;
-    float *mbase = !sym ? P.Ct : gi0 - gj0 - (COLS - 1) < P.mirror_band ? P.C : nullptr;
+    const Global<float> C = global(P.C), mbase = global(!sym ? P.Ct : gi0 - gj0 - (COLS - 1) < P.mirror_band ? P.C : nullptr);
     // direct pass: a thread owns 4 adjacent columns of one row.  The old values (beta != 0) of all its rows are requested
     // before the first store: a load issued behind a store to the same matrix waits for it, and load - store pairs then
     // cost one memory round trip per row.
@@ -81,7 +81,7 @@ __device__ __forceinline__ void store_slab(const GemmProblem &P, float *T, int g
                 const int r = rr + q * RPP, i = gi0 + r;
                 const int jmax = min(diag_tile ? i : P.N - 1, P.N - 1);
                 old[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (r < ROWS && i < P.M && j + 3 <= jmax) old[q] = *(const floatx4_st *)(P.C + (long long)i * P.ldc + j);
+                if (r < ROWS && i < P.M && j + 3 <= jmax) old[q] = *(Global<const floatx4_st>)(C + (long long)i * P.ldc + j);
             }
         }
 #pragma unroll
@@ -90,13 +90,13 @@ __device__ __forceinline__ void store_slab(const GemmProblem &P, float *T, int g
             if (r >= ROWS || i >= P.M || j >= P.N) continue;
             const int jmax = min(diag_tile ? i : P.N - 1, P.N - 1);   // last column this row may write
             if (j > jmax) continue;
-            float *dst = P.C + (long long)i * P.ldc + j;
+            const Global<float> dst = C + (long long)i * P.ldc + j;
             float *t = T + r * LDT + c;
             if (j + 3 <= jmax) {
                 floatx4 v = {alpha * t[0], alpha * t[1], alpha * t[2], alpha * t[3]};
                 if (beta != 0.0f)
                     for (int e = 0; e < 4; ++e) v[e] = fmaf(beta, old[q][e], v[e]);   // same rounding in every path
-                *(floatx4_st *)dst = v;
+                *(Global<floatx4_st>)dst = v;
                 if (mbase)
                     for (int e = 0; e < 4; ++e) t[e] = v[e];
             } else {
@@ -125,9 +125,9 @@ __device__ __forceinline__ void store_slab(const GemmProblem &P, float *T, int g
             const int e0 = (sym && diag_tile) ? max(0, j + 1 - i) : 0;
             const int e1 = min(4, P.M - i);
             if (e0 >= e1) continue;
-            float *dst = mbase + (long long)j * ldm + i;
+            const Global<float> dst = mbase + (long long)j * ldm + i;
             const float *t = T + r * LDT + c;
-            if (e0 == 0 && e1 == 4) *(floatx4_st *)dst = floatx4{t[0], t[LDT], t[2 * LDT], t[3 * LDT]};
+            if (e0 == 0 && e1 == 4) *(Global<floatx4_st>)dst = floatx4{t[0], t[LDT], t[2 * LDT], t[3 * LDT]};
             else
                 for (int e = e0; e < e1; ++e) dst[e] = t[e * LDT];
         }
@@ -138,15 +138,15 @@ __device__ __forceinline__ void store_slab(const GemmProblem &P, float *T, int g
 // of the operand, and the corner from the contraction length.
 __device__ __forceinline__ void store_border(const GemmProblem &P, int row, float sum)
 {
-    float *pr = P.C + (long long)P.M * P.ldc + row;
+    const Global<float> C = global(P.C), pr = C + (long long)P.M * P.ldc + row;
     float v = P.alpha * sum;
     if (P.beta != 0.0f) v = fmaf(P.beta, *pr, v);
     *pr = v;
-    P.C[(long long)row * P.ldc + P.M] = v;
+    C[(long long)row * P.ldc + P.M] = v;
 }
 __device__ __forceinline__ void store_corner(const GemmProblem &P)
 {
-    float *pc = P.C + (long long)P.M * P.ldc + P.M;
+    const Global<float> pc = global(P.C) + (long long)P.M * P.ldc + P.M;
     float v = P.alpha * (float)P.ones;
     if (P.beta != 0.0f) v = fmaf(P.beta, *pc, v);
     *pc = v;
@@ -309,7 +309,7 @@ __device__ __forceinline__ void finish_row_sums(const GemmProblem &P, float *lds
     if (tid < BM) {
         const float total = lds[tid] + rs_rem;
         const int row = tm * BM + tid;
-        if (P.splits > 1) P.partial_rs[((long long)tm * P.splits + split) * BM + tid] = total;
+        if (P.splits > 1) global(P.partial_rs)[((long long)tm * P.splits + split) * BM + tid] = total;
         else if (row < P.M) store_border(P, row, total);
     }
     if (tile == 0 && tid == 0 && P.splits == 1) store_corner(P);
@@ -813,7 +813,7 @@ __device__ __forceinline__ bool half_scales(const GemmProblem &P, int tm, int tn
     if (P.kdiag) {
         int hi = 0, lo = 0;
         for (int k = k0 + tid; k < k0 + klen; k += 256) {
-            const int e = (int)((__float_as_uint(P.kdiag[(long long)k * P.kdiag_step]) >> 23) & 255);
+            const int e = (int)((__float_as_uint(global(P.kdiag)[(long long)k * P.kdiag_step]) >> 23) & 255);
             hi = max(hi, e);
             lo = max(lo, 255 - e);
         }
@@ -1157,8 +1157,8 @@ __device__ __forceinline__ int half_doubts(const floatx16 (&acc)[TM][TN], const 
 }
 
 // The listed sums in fp32, four per wavefront at a time, into their places in `out` (rows of ld elements).
-template <int BM, int BN>
-__device__ __forceinline__ void half_settle(const GemmProblem &P, const int *doubts, int n, int tm, int tn, int k0, int k1, int tid, float *out, int ld)
+template <int BM, int BN, typename Out>
+__device__ __forceinline__ void half_settle(const GemmProblem &P, const int *doubts, int n, int tm, int tn, int k0, int k1, int tid, Out out, int ld)
 {
     constexpr int U = 4;
     const int lane = tid & 63, end4 = k0 + ((k1 - k0) & ~3);
@@ -1379,7 +1379,7 @@ __device__ __forceinline__ void finish_row_sums_trans(const GemmProblem &P, floa
 #pragma unroll
         for (int q = 0; q < PARTS; ++q) total += lds[q * BM + tid];
         const int row = tm * BM + tid;
-        if (P.splits > 1) P.partial_rs[((long long)tm * P.splits + split) * BM + tid] = total;
+        if (P.splits > 1) global(P.partial_rs)[((long long)tm * P.splits + split) * BM + tid] = total;
         else if (row < P.M) store_border(P, row, total);
     }
     if (tile == 0 && tid == 0 && P.splits == 1) store_corner(P);
@@ -1456,7 +1456,7 @@ __device__ __forceinline__ void gemm_nt_f32_body(const GemmProblem *__restrict__
     // accumulator layout of the 32x32 block: column = lane % 32,
     // row = 8 * (v / 4) + 4 * (lane / 32) + v % 4 for register v = 0..15
     if (part_of_k) {
-        float *part = P.partial + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
+        const Global<float> part = global(P.partial) + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1617,7 +1617,7 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_k
     // accumulator layout of the 32x32 block: column = lane % 32,
     // row = 8 * (v / 4) + 4 * (lane / 32) + v % 4 for register v = 0..15
     if (part_of_k) {
-        float *part = P.partial + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
+        const Global<float> part = global(P.partial) + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -2180,7 +2180,7 @@ __device__ __forceinline__ void gemm_nt_bf16_body(const GemmProblem &P, int loca
     }
 
     if (part_of_k) {
-        float *part = P.partial + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
+        const Global<float> part = global(P.partial) + ((long long)(tile - P.split_from) * P.splits + split) * (BM * BN);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -2223,7 +2223,7 @@ __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int 
     static_assert(B % ROWS == 0 && ROWS % 4 == 0 && ROWS <= kRedRows && B <= 128, "slabs of a tile, in T");
     static_assert((ROWS * B / 4) % 256 == 0 || 256 % (ROWS * B / 4) == 0, "whole passes, or whole groups of threads");
     const bool diag_tile = (P.flags & GEMM_SYM) && tm == tn;
-    const float *part = P.partial + (long long)(tile - P.split_from) * P.splits * (B * B) + slab * ROWS * B;
+    const Global<const float> part = global((const float *)P.partial) + (long long)(tile - P.split_from) * P.splits * (B * B) + slab * ROWS * B;
     // ROWS * B elements, 4 per thread per pass; where they are fewer than 4 per thread, `groups` groups of threads take every
     // groups-th split.  A thread's U splits in flight go into U partial sums.
     constexpr int VECS = ROWS * B / 4, PASSES = VECS >= 256 ? VECS / 256 : 1, GROUPS = VECS >= 256 ? 1 : 256 / VECS;
@@ -2242,7 +2242,7 @@ __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int 
             for (int p = 0; p < PASSES; ++p) {
                 v[p][k] = floatx4{0.f, 0.f, 0.f, 0.f};
                 if (q + k * GROUPS < P.splits)
-                    v[p][k] = __builtin_nontemporal_load((const floatx4 *)(part + (long long)(q + k * GROUPS) * (B * B) + vec * 4 + p * 1024));
+                    v[p][k] = __builtin_nontemporal_load((Global<const floatx4>)(part + (long long)(q + k * GROUPS) * (B * B) + vec * 4 + p * 1024));
             }
 #pragma unroll
         for (int k = 0; k < U; ++k)
@@ -2275,7 +2275,7 @@ __device__ __forceinline__ void reduce_slab(const GemmProblem &P, int tile, int 
         // splits of its row is a chain of memory latencies: 79 of them cost 15 us)
         constexpr int RG = 256 / ROWS;
         const int r = threadIdx.x % ROWS, g = threadIdx.x / ROWS;
-        const float *prs = P.partial_rs + (long long)tm * P.splits * B + slab * ROWS + r;
+        const Global<const float> prs = global((const float *)P.partial_rs) + (long long)tm * P.splits * B + slab * ROWS + r;
         float sum = 0.f;
         for (int q = g; q < P.splits; q += RG) sum += prs[(long long)q * B];
         float *part_sums = (float *)sums;

@@ -23,8 +23,8 @@ __global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const LayoutJob *__re
     const int n = local / (tc * th);
     local -= n * tc * th;
     const int h0 = (local / tc) * 64, c0 = (local % tc) * 64;
-    const T *src = (const T *)J->src + (long long)n * HW * C;
-    T *dst = (T *)J->dst + (long long)n * HW * C;
+    const Global<const T> src = global((const T *)J->src) + (long long)n * HW * C;
+    const Global<T> dst = global((T *)J->dst) + (long long)n * HW * C;
     const int g = threadIdx.x & 15, r = threadIdx.x >> 4;
     // read: rows of the tile are positions hw, 16 groups of 4 channels each
     if ((C & 3) == 0) {
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const LayoutJob *__re
         for (int q = 0; q < 4; ++q) {
             const int h = h0 + r + 16 * q, c = c0 + 4 * g;
             in[q] = h < HW && c < C;
-            if (in[q]) v[q] = __builtin_nontemporal_load((const vec4 *)(src + (long long)h * C + c));
+            if (in[q]) v[q] = __builtin_nontemporal_load((Global<const vec4>)(src + (long long)h * C + c));
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const LayoutJob *__re
                 vec4 v;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = tile[r + 16 * q][4 * g + i];
-                *(vec4 *)(dst + (long long)c * HW + h) = v;
+                *(Global<vec4>)(dst + (long long)c * HW + h) = v;
             }
         }
     } else {

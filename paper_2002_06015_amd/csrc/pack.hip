@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256) void pack_upper_kernel(const PackJob *__restri
     typedef unsigned short h4 __attribute__((ext_vector_type(4), aligned(2)));
     const PackJob *J = &pack_find(jobs, n_jobs, blockIdx.x);
     const int d = J->d;
-    const float *X = J->X;
+    const Global<const float> X = global(J->X);
     const long long tri = (long long)d * (d + 1) / 2, off = J->off;
     const long long p0 = (long long)(blockIdx.x - J->wg_start) * kPackChunk;
     v4 v[4];
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void pack_upper_kernel(const PackJob *__restri
         while (r > 0 && pack_row_start(r, d) > p) --r;
         int c = r + (int)(p - pack_row_start(r, d));
         if (c + 3 < d) {
-            v[g] = __builtin_nontemporal_load((const v4 *)(X + (long long)r * d + c));
+            v[g] = __builtin_nontemporal_load((Global<const v4>)(X + (long long)r * d + c));
         } else {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void unpack_upper_kernel(const PackJob *__rest
     int tr, tc;
     pack_tile_of(blockIdx.x - J.wg_start, J.tiles, tr, tc);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float *X = const_cast<float *>(J.X);
+    const Global<float> X = global(const_cast<float *>(J.X));
     const int c = 64 * tc + lane;
     float v[16];
     bool in[16];

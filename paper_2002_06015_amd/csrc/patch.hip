@@ -13,13 +13,13 @@ template <typename T>
 __device__ __forceinline__ void patch_plane(const PatchJob &J, int plane, int t0, int t1, int lane)
 {
     const int n = plane / J.c_in, c = plane - n * J.c_in;
-    const T *src = (const T *)J.src + (long long)plane * J.h_in * J.w_in;
+    const Global<const T> src = global((const T *)J.src) + (long long)plane * J.h_in * J.w_in;
     const int hw = J.h * J.w;
     const int kk = J.k * J.k;
-    T *dst_row0 = (T *)J.dst + (long long)c * kk * J.ld + (long long)n * hw;
+    const Global<T> dst_row0 = global((T *)J.dst) + (long long)c * kk * J.ld + (long long)n * hw;
     for (int tap = 0; tap < kk; ++tap) {
         const int ky = tap / J.k, kx = tap - ky * J.k;
-        T *dst = dst_row0 + (long long)tap * J.ld;
+        const Global<T> dst = dst_row0 + (long long)tap * J.ld;
         for (int t = t0 + lane; t < t1; t += 64) {
             const int y = J.magic_w ? (int)__umulhi((unsigned)t, J.magic_w) : t / J.w;
             const int x = t - y * J.w;
@@ -39,10 +39,10 @@ __device__ __forceinline__ void patch_plane_vec4(const PatchJob &J, int plane, i
 {
     typedef T vec4 __attribute__((ext_vector_type(4)));
     const int n = plane / J.c_in, c = plane - n * J.c_in;
-    const T *src = (const T *)J.src + (long long)plane * J.h_in * J.w_in;
+    const Global<const T> src = global((const T *)J.src) + (long long)plane * J.h_in * J.w_in;
     const int hw = J.h * J.w;
     const int kk = J.k * J.k;
-    T *dst_row0 = (T *)J.dst + (long long)c * kk * J.ld + (long long)n * hw;
+    const Global<T> dst_row0 = global((T *)J.dst) + (long long)c * kk * J.ld + (long long)n * hw;
     for (int t = t0 + 4 * lane; t < t1; t += 256) {
         const int y0 = J.magic_w ? (int)__umulhi((unsigned)t, J.magic_w) : t / J.w;
         const int x0 = t - y0 * J.w;
@@ -63,7 +63,7 @@ __device__ __forceinline__ void patch_plane_vec4(const PatchJob &J, int plane, i
                     if (yy >= 0 && yy < J.h_in && xx >= 0 && xx < J.w_in) u = src[yy * J.w_in + xx];
                     v[e] = u;
                 }
-                __builtin_nontemporal_store(v, (vec4 *)(dst_row0 + (long long)(ky * J.k + kx) * J.ld + t));
+                __builtin_nontemporal_store(v, (Global<vec4>)(dst_row0 + (long long)(ky * J.k + kx) * J.ld + t));
             }
     }
 }
@@ -78,9 +78,9 @@ __device__ __forceinline__ void patch_plane_window(const PatchJob &J, int plane,
     typedef T vec4 __attribute__((ext_vector_type(4)));
     constexpr int WIN = 3 * S + K;
     const int n = plane / J.c_in, c = plane - n * J.c_in;
-    const T *src = (const T *)J.src + (long long)plane * J.h_in * J.w_in;
+    const Global<const T> src = global((const T *)J.src) + (long long)plane * J.h_in * J.w_in;
     const int hw = J.h * J.w;
-    T *dst_row0 = (T *)J.dst + (long long)c * (K * K) * J.ld + (long long)n * hw;
+    const Global<T> dst_row0 = global((T *)J.dst) + (long long)c * (K * K) * J.ld + (long long)n * hw;
     for (int t = t0 + 4 * lane; t < t1; t += 256) {
         const int y0 = J.magic_w ? (int)__umulhi((unsigned)t, J.magic_w) : t / J.w;
         const int x0 = t - y0 * J.w;
@@ -89,7 +89,7 @@ __device__ __forceinline__ void patch_plane_window(const PatchJob &J, int plane,
         for (int ky = 0; ky < K; ++ky) {
             const int iy = y0 * S - J.pad + ky;
             const bool row_in = iy >= 0 && iy < J.h_in;
-            const T *line = src + (row_in ? iy : 0) * J.w_in;
+            const Global<const T> line = src + (row_in ? iy : 0) * J.w_in;
             T win[WIN];
 #pragma unroll
             for (int j = 0; j < WIN; ++j) {
@@ -99,7 +99,7 @@ __device__ __forceinline__ void patch_plane_window(const PatchJob &J, int plane,
 #pragma unroll
             for (int kx = 0; kx < K; ++kx) {
                 const vec4 v = {win[kx], win[S + kx], win[2 * S + kx], win[3 * S + kx]};
-                __builtin_nontemporal_store(v, (vec4 *)(dst_row0 + (long long)(ky * K + kx) * J.ld + t));
+                __builtin_nontemporal_store(v, (Global<vec4>)(dst_row0 + (long long)(ky * K + kx) * J.ld + t));
             }
         }
     }
@@ -120,12 +120,12 @@ __device__ __forceinline__ void patch_flat(const PatchJob &J, int local)
     const long long row = idx >> 32 ? (long long)(idx / groups) : (long long)((unsigned)idx / groups);
     if (row >= J.c_in) return;
     const int m = V * (int)(idx - row * groups), n = m / hw, t = m - n * hw;
-    const T *src = (const T *)J.src + ((long long)n * J.c_in + row) * hw;
-    T *dst = (T *)J.dst + row * J.ld + m;
+    const Global<const T> src = global((const T *)J.src) + ((long long)n * J.c_in + row) * hw;
+    const Global<T> dst = global((T *)J.dst) + row * J.ld + m;
     const int next = (J.c_in - 1) * hw;           // from the end of a plane to the same channel of the next sample
     vec v;
     if (t + V <= hw) {                            // (then m + V <= M, too)
-        v = *(const vec *)(src + t);
+        v = *(Global<const vec>)(src + t);
     } else {
         long long o = t;
         int left = hw - t;
@@ -136,7 +136,7 @@ __device__ __forceinline__ void patch_flat(const PatchJob &J, int local)
             if (--left == 0) { o += next; left = hw; }
         }
     }
-    if (m + V <= M) *(vec *)dst = v;
+    if (m + V <= M) *(Global<vec>)dst = v;
     else
         for (int e = 0; e < V && m + e < M; ++e) dst[e] = v[e];
 }

@@ -52,9 +52,9 @@ __device__ __forceinline__ void stale_partial_chunk(const StaleJob &J, int local
         in[g] = e + 4 <= e1;
         x[g] = p[g] = q[g] = stale_vec4{0.f, 0.f, 0.f, 0.f};
         if (in[g]) {
-            x[g] = __builtin_nontemporal_load((const stale_vec4 *)(J.X + e));
-            if (J.P) p[g] = __builtin_nontemporal_load((const stale_vec4 *)(J.P + e));
-            if (J.Q) q[g] = __builtin_nontemporal_load((const stale_vec4 *)(J.Q + e));
+            x[g] = __builtin_nontemporal_load((Global<const stale_vec4>)(global(J.X) + e));
+            if (J.P) p[g] = __builtin_nontemporal_load((Global<const stale_vec4>)(global(J.P) + e));
+            if (J.Q) q[g] = __builtin_nontemporal_load((Global<const stale_vec4>)(global(J.Q) + e));
         }
     }
 #pragma unroll
@@ -73,7 +73,7 @@ __device__ __forceinline__ void stale_partial_chunk(const StaleJob &J, int local
     const long long tail0 = e0 + ((e1 - e0) & ~3LL);
     if (threadIdx.x < (unsigned)(e1 - tail0)) {
         const long long e = tail0 + threadIdx.x;
-        const double xv = (double)J.X[e], pv = J.P ? (double)J.P[e] : 0.0, qv = J.Q ? (double)J.Q[e] : 0.0;
+        const double xv = (double)global(J.X)[e], pv = J.P ? (double)global(J.P)[e] : 0.0, qv = J.Q ? (double)global(J.Q)[e] : 0.0;
         acc[0] = fma(xv - pv, xv - pv, acc[0]);
         acc[1] = fma(pv, pv, acc[1]);
         acc[2] = fma(xv - qv, xv - qv, acc[2]);
@@ -81,7 +81,7 @@ __device__ __forceinline__ void stale_partial_chunk(const StaleJob &J, int local
     }
     block_sum4(acc, red);
     if (threadIdx.x == 0) {
-        double *out = J.partial + 4LL * local;
+        const Global<double> out = global(J.partial) + 4LL * local;
         out[0] = acc[0]; out[1] = acc[1]; out[2] = acc[2]; out[3] = acc[3];
     }
 }
@@ -111,14 +111,15 @@ __device__ __forceinline__ void stale_final_job(const StaleJob &J, double (*red)
 {
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int w = threadIdx.x; w < J.wgs; w += 256) {
-        const double *part = J.partial + 4LL * w;
+        const Global<const double> part = global((const double *)J.partial) + 4LL * w;
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[k] += part[k];
     }
     block_sum4(acc, red);
     if (threadIdx.x == 0) {
-        J.out[0] = stale_ratio(J.P != nullptr, acc[0], acc[1]);
-        J.out[1] = stale_ratio(J.Q != nullptr, acc[2], acc[3]);
+        const Global<double> out = global(J.out);
+        out[0] = stale_ratio(J.P != nullptr, acc[0], acc[1]);
+        out[1] = stale_ratio(J.Q != nullptr, acc[2], acc[3]);
     }
 }
 

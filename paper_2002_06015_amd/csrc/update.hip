@@ -33,6 +33,8 @@ __global__ __launch_bounds__(256) void update_step_kernel(const UpdateJob *__res
     const int local = blockIdx.x - J.wg_start;
     const long long e0 = (long long)local * kUpdateChunk;
     const long long e1 = e0 + kUpdateChunk < J.n ? e0 + kUpdateChunk : J.n;
+    const Global<float> W = global(J.W), W_prev = global(J.W_prev);
+    const Global<const float> U = global(J.U);
     double ss = 0.0;
     constexpr int GROUPS = kUpdateChunk / 4 / 256;
     upd_vec4 w[GROUPS], wp[GROUPS], u[GROUPS];
@@ -42,9 +44,9 @@ __global__ __launch_bounds__(256) void update_step_kernel(const UpdateJob *__res
         const long long e = e0 + 4LL * ((int)threadIdx.x + 256 * g);
         in[g] = e + 4 <= e1;
         if (in[g]) {
-            w[g] = *(const upd_vec4 *)(J.W + e);
-            wp[g] = *(const upd_vec4 *)(J.W_prev + e);
-            u[g] = __builtin_nontemporal_load((const upd_vec4 *)(J.U + e));
+            w[g] = *(Global<const upd_vec4>)(W + e);
+            wp[g] = *(Global<const upd_vec4>)(W_prev + e);
+            u[g] = __builtin_nontemporal_load((Global<const upd_vec4>)(U + e));
         }
     }
 #pragma unroll
@@ -57,17 +59,17 @@ __global__ __launch_bounds__(256) void update_step_kernel(const UpdateJob *__res
             nw[k] = upd_one(w[g][k], wp[g][k], u[g][k], eta, momentum);
             ss = fma((double)nw[k], (double)nw[k], ss);
         }
-        *(upd_vec4 *)(J.W + e) = nw;
-        *(upd_vec4 *)(J.W_prev + e) = w[g];
+        *(Global<upd_vec4>)(W + e) = nw;
+        *(Global<upd_vec4>)(W_prev + e) = w[g];
     }
     const long long tail0 = e0 + ((e1 - e0) & ~3LL);
     if (threadIdx.x < (unsigned)(e1 - tail0)) {
         const long long e = tail0 + threadIdx.x;
-        const float wv = J.W[e];
-        const float nw = upd_one(wv, J.W_prev[e], J.U[e], eta, momentum);
+        const float wv = W[e];
+        const float nw = upd_one(wv, W_prev[e], U[e], eta, momentum);
         ss = fma((double)nw, (double)nw, ss);
-        J.W[e] = nw;
-        J.W_prev[e] = wv;
+        W[e] = nw;
+        W_prev[e] = wv;
     }
     if (!J.partial) return;   // no rescaling: the sums are not needed
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(256) void update_step_kernel(const UpdateJob *__res
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
     if (lane == 0) red[wave] = ss;
     __syncthreads();
-    if (threadIdx.x == 0) J.partial[local] = ((red[0] + red[1]) + red[2]) + red[3];
+    if (threadIdx.x == 0) global(J.partial)[local] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 __global__ __launch_bounds__(256) void update_scale_kernel(const UpdateJob *__restrict__ jobs, int n_jobs, float eps)
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(256) void update_scale_kernel(const UpdateJob *__re
     const UpdateJob J = jobs[blockIdx.x];
     if (!J.partial) return;
     double ss = 0.0;
-    for (int w = threadIdx.x; w < J.wgs; w += 256) ss += J.partial[w];
+    for (int w = threadIdx.x; w < J.wgs; w += 256) ss += global(J.partial)[w];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
@@ -92,7 +94,7 @@ __global__ __launch_bounds__(256) void update_scale_kernel(const UpdateJob *__re
     __syncthreads();
     if (threadIdx.x == 0) {
         const double norm = sqrt(((red[0] + red[1]) + red[2]) + red[3]);
-        *J.scale = (float)(sqrt(2.0 * (double)J.d_out) / (norm + (double)eps));
+        *global(J.scale) = (float)(sqrt(2.0 * (double)J.d_out) / (norm + (double)eps));
     }
 }
 
@@ -100,7 +102,8 @@ __global__ __launch_bounds__(256) void update_rescale_kernel(const UpdateJob *__
 {
     const UpdateJob J = upd_find(jobs, n_jobs, blockIdx.x);
     if (!J.partial) return;
-    const float sc = *J.scale;
+    const float sc = *global(J.scale);
+    const Global<float> W = global(J.W);
     const long long e0 = (long long)(blockIdx.x - J.wg_start) * kUpdateChunk;
     const long long e1 = e0 + kUpdateChunk < J.n ? e0 + kUpdateChunk : J.n;
     constexpr int GROUPS = kUpdateChunk / 4 / 256;
@@ -110,16 +113,16 @@ __global__ __launch_bounds__(256) void update_rescale_kernel(const UpdateJob *__
     for (int g = 0; g < GROUPS; ++g) {
         const long long e = e0 + 4LL * ((int)threadIdx.x + 256 * g);
         in[g] = e + 4 <= e1;
-        if (in[g]) w[g] = *(const upd_vec4 *)(J.W + e);
+        if (in[g]) w[g] = *(Global<const upd_vec4>)(W + e);
     }
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) {
         if (!in[g]) continue;
         const long long e = e0 + 4LL * ((int)threadIdx.x + 256 * g);
-        *(upd_vec4 *)(J.W + e) = w[g] * sc;
+        *(Global<upd_vec4>)(W + e) = w[g] * sc;
     }
     const long long tail0 = e0 + ((e1 - e0) & ~3LL);
-    if (threadIdx.x < (unsigned)(e1 - tail0)) J.W[tail0 + threadIdx.x] *= sc;
+    if (threadIdx.x < (unsigned)(e1 - tail0)) W[tail0 + threadIdx.x] *= sc;
 }
 
 hipError_t launch_update(const UpdateJob *jobs_dev, int n_jobs, int total_wgs, int pass, float eta, float momentum,
