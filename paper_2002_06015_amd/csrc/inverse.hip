@@ -12,6 +12,40 @@
 namespace kfac {
 
 // ------------------------------------------------------------------ trace / pi / damping
+__device__ __forceinline__ double pi_of(const TraceJob &J, double trA, double trG)
+{
+    return trA > 0.0 && trG > 0.0 ? sqrt((trA / J.dA) / (trG / J.dG)) : 1.0;
+}
+__device__ __forceinline__ void write_damping(const TraceJob &J, double pi, float gamma, float *damp, float *pi_out)
+{
+    damp[3 * J.idx + 0] = (float)pi;
+    damp[3 * J.idx + 1] = (float)(pi * (double)gamma);   // added to A
+    damp[3 * J.idx + 2] = (float)((double)gamma / pi);   // added to G
+    if (pi_out) pi_out[J.idx] = (float)pi;
+}
+// The traces of a layer over the THREADS threads of a workgroup, in two halves: their parts per wavefront into parts[2][THREADS / 64]
+// (then a barrier), and the damping of A or G from these.  Layers of up to kInlineTrace rows in both factors: a launch of its own
+// takes 7 us and a gap, this one memory latency.
+template <int THREADS>
+__device__ __forceinline__ void trace_parts(const TraceJob &J, double *parts)
+{
+    const Global<const float> A = global(J.A), G = global(J.G);
+    const int tid = threadIdx.x;
+    double sa = 0.0, sg = 0.0;
+    for (int i = tid; i < J.dA; i += THREADS) sa += (double)A[(long long)i * J.dA + i];
+    for (int i = tid; i < J.dG; i += THREADS) sg += (double)G[(long long)i * J.dG + i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { sa += __shfl_xor(sa, o); sg += __shfl_xor(sg, o); }
+    if ((tid & 63) == 0) { parts[tid >> 6] = sa; parts[THREADS / 64 + (tid >> 6)] = sg; }
+}
+template <int THREADS>
+__device__ __forceinline__ double pi_from_parts(const TraceJob &J, const double *parts)
+{
+    double sa = 0.0, sg = 0.0;
+    for (int w = 0; w < THREADS / 64; ++w) { sa += parts[w]; sg += parts[THREADS / 64 + w]; }
+    return pi_of(J, sa, sg);
+}
+
 __global__ __launch_bounds__(256) void trace_kernel(const TraceJob *__restrict__ jobs, float gamma,
                                                     float *__restrict__ damp, float *__restrict__ pi_out)
 {
@@ -31,15 +65,7 @@ __global__ __launch_bounds__(256) void trace_kernel(const TraceJob *__restrict__
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const double trA = red[0][0], trG = red[1][0];
-        double pi = 1.0;
-        if (trA > 0.0 && trG > 0.0) pi = sqrt((trA / J.dA) / (trG / J.dG));
-        damp[3 * J.idx + 0] = (float)pi;
-        damp[3 * J.idx + 1] = (float)(pi * (double)gamma);   // added to A
-        damp[3 * J.idx + 2] = (float)((double)gamma / pi);   // added to G
-        if (pi_out) pi_out[J.idx] = (float)pi;
-    }
+    if (threadIdx.x == 0) write_damping(J, pi_of(J, red[0][0], red[1][0]), gamma, damp, pi_out);
 }
 
 hipError_t launch_trace(const TraceJob *jobs_dev, int n_layers, float gamma, float *damp_dev,
@@ -55,9 +81,9 @@ hipError_t launch_trace(const TraceJob *jobs_dev, int n_layers, float gamma, flo
 // inverted as leaves: a row is copied up to kLeafMax columns past the diagonal (ResNet-50's factors: 232 -> 153 us).
 constexpr int COPY_ROWS = 8;
 
-__global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restrict__ jobs, int n_jobs,
-                                                        const float *__restrict__ damp)
+__global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restrict__ jobs, int n_jobs, Damping D)
 {
+    __shared__ double parts[2 * 4];
     const int wg = blockIdx.x;
     int lo = 0, hi = n_jobs;
     while (hi - lo > 1) {
@@ -65,7 +91,18 @@ __global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restric
         if (jobs[mid].wg_start <= wg) lo = mid; else hi = mid;
     }
     const CopyJob J = jobs[lo];
-    const float d = (J.damp_idx >= 0) ? damp[J.damp_idx] : 0.f;
+    float d = 0.f;
+    if (D.layers) {
+        const TraceJob L = D.layers[J.layer];
+        trace_parts<256>(L, parts);
+        __syncthreads();
+        const double pi = pi_from_parts<256>(L, parts);
+        const bool of_A = J.damp_idx == 3 * L.idx + 1;
+        d = (float)(of_A ? pi * (double)D.gamma : (double)D.gamma / pi);
+        if (of_A && wg == J.wg_start && threadIdx.x == 0) write_damping(L, pi, D.gamma, D.damp, D.pi_out);
+    } else if (J.damp_idx >= 0) {
+        d = D.damp[J.damp_idx];
+    }
     const int r0 = (wg - J.wg_start) * COPY_ROWS;
     const Global<const float> src = global(J.src);
     const Global<float> dst = global(J.dst);
@@ -108,11 +145,10 @@ __global__ __launch_bounds__(256) void copy_damp_kernel(const CopyJob *__restric
     }
 }
 
-hipError_t launch_copy_damp(const CopyJob *jobs_dev, int n_jobs, int total_wgs, const float *damp_dev,
-                            hipStream_t s)
+hipError_t launch_copy_damp(const CopyJob *jobs_dev, int n_jobs, int total_wgs, const Damping &damping, hipStream_t s)
 {
     if (total_wgs <= 0) return hipSuccess;
-    copy_damp_kernel<<<dim3(total_wgs), dim3(256), 0, s>>>(jobs_dev, n_jobs, damp_dev);
+    copy_damp_kernel<<<dim3(total_wgs), dim3(256), 0, s>>>(jobs_dev, n_jobs, damping);
     return hipGetLastError();
 }
 
@@ -250,8 +286,9 @@ constexpr int LB_DP = 2 * 2048;                         // planes of D, form F
 constexpr int LB_TOP = 14;                              // a scaled block has its largest element in [2^14, 2^15)
 constexpr int LB_LDS_D = 2 * LB_PANEL, LB_LDS_DIAG = LB_LDS_D + 2 * LB_DP,
               LB_LDS_SC = LB_LDS_DIAG + 2 * 4096, LB_LDS_UN = LB_LDS_SC + 32 * LB_MAXT * 4,
-              LB_LDS_BYTES = LB_LDS_UN + 2 * 16 * 4;   // UN: reciprocal scales of two panels' blocks, of I and (LB_UN_D) of D
+              LB_LDS_BYTES = LB_LDS_UN + 2 * LB_THREADS / 64 * 8;   // UN: reciprocal scales of two panels' blocks, of I and (LB_UN_D) of D
 constexpr int LB_UN_D = LB_IDENT + 1;
+static_assert(2 * 16 * 4 <= 2 * LB_THREADS / 64 * 8 && LB_LDS_UN % 8 == 0, "the traces' parts lie in the same place");
 static_assert(LB_LDS_BYTES <= 160 * 1024 - 64, "one compute unit's LDS");
 constexpr int LB_STAGE = 36;                            // row length of the staging tiles (16-byte accesses spread over the banks)
 static_assert(LB_LDS_D >= LB_MAXT * 2 * 32 * LB_STAGE * 4, "the staging tiles of the final store fit into the panels");
@@ -478,9 +515,8 @@ __device__ __forceinline__ int leaf_chain_sweep(lb_floatx16 &t, int lane)
     return first;
 }
 
-__global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *__restrict__ jobs,
-                                                          const float *__restrict__ damp,
-                                                          int32_t *__restrict__ info)
+__global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *__restrict__ jobs, Damping D,
+                                                               int32_t *__restrict__ info)
 {
     extern __shared__ __attribute__((aligned(16))) char lb_lds[];
     float *sc = (float *)(lb_lds + LB_LDS_SC);       // [32 T] diagonal scaling
@@ -492,7 +528,22 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32_ = lane & 31, h_ = lane >> 5;
-    const float d = (J.damp_idx >= 0) ? damp[J.damp_idx] : 0.f;
+    float d = 0.f;
+    const bool find_damping = D.layers && J.layer >= 0;
+    const TraceJob *layer = D.layers + max(J.layer, 0);
+    double *parts = (double *)(lb_lds + LB_LDS_UN);   // (until the first scale is written there)
+    if (find_damping) trace_parts<LB_THREADS>(*layer, parts);
+    else if (J.damp_idx >= 0) d = D.damp[J.damp_idx];
+    // called by all wavefronts once their loads are under way
+    auto wait_for_damping = [&]() {
+        if (!find_damping) return;
+        __syncthreads();
+        const double pi = pi_from_parts<LB_THREADS>(*layer, parts);
+        const bool of_A = J.damp_idx == 3 * layer->idx + 1;
+        d = (float)(of_A ? pi * (double)D.gamma : (double)D.gamma / pi);
+        if (of_A && tid == 0) write_damping(*layer, pi, D.gamma, D.damp, D.pi_out);
+        __syncthreads();
+    };
     const unsigned lds = (unsigned)J.lds, ldd = (unsigned)J.ldd;
     const Global<const float> src = global(J.src);
     const Global<float> dst = global(J.dst);
@@ -569,6 +620,7 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
     if (w == LB_CHAIN) {
         lb_floatx16 t;
         load_tile(t, 0, 0, true);
+        wait_for_damping();
         __syncthreads();
         scale_tile(t, 0, 0, true, true);
         __builtin_amdgcn_s_setprio(3);
@@ -610,7 +662,10 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
 #pragma unroll
             for (int q = 0; q < 16; ++q) t[q] = fmaf(c[q], un, t[q]);
         }
-        if (bad != 0 && lane == 0 && info && J.info_idx >= 0) atomicCAS(&info[J.info_idx], 0, J.pivot_base + bad);
+        if (lane == 0 && info && J.info_idx >= 0) {
+            if (J.pivot_base == 0) info[J.info_idx] = bad;
+            else if (bad != 0) atomicCAS(&info[J.info_idx], 0, J.pivot_base + bad);
+        }
         __syncthreads();
         return;
     }
@@ -622,6 +677,7 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
         for (int q = 0; q < 16; ++q) acc[s][q] = 0.f;
         if (j_[s] >= 0) load_tile(acc[s], j_[s], v_, false);
     }
+    wait_for_damping();
     scales();
     if (w < 8) {   // the identity: wavefront w writes step fragments w % 2 of plane (w / 2) % 2 of panel w / 4
         const int u = w & 1, q = (w >> 1) & 1;
@@ -785,7 +841,7 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
     }
 }
 
-hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, const float *damp_dev, int32_t *info, hipStream_t s)
+hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, const Damping &damping, int32_t *info, hipStream_t s)
 {
     if (n_jobs <= 0) return hipSuccess;
     constexpr size_t lds_bytes = LB_LDS_BYTES;
@@ -795,7 +851,7 @@ hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, const float *damp_de
         if (e != hipSuccess) return e;
         configured = true;
     }
-    leaf_block_kernel<<<dim3(n_jobs), dim3(LB_THREADS), lds_bytes, s>>>(jobs_dev, damp_dev, info);
+    leaf_block_kernel<<<dim3(n_jobs), dim3(LB_THREADS), lds_bytes, s>>>(jobs_dev, damping, info);
     return hipGetLastError();
 }
 

@@ -178,7 +178,7 @@ struct Launch {
     int n, total_wgs, cfg, dtype;
     int k_max;             // L_GEMM: longest contraction
     float f0, f1;
-    void *p0, *p1;
+    void *p0, *p1, *p2;
     double flops, bytes;   // algorithmic counts (profiling only)
     int stream;            // 0: the context's stream; 1..3: auxiliary streams (ordered by L_RECORD / L_WAIT)
 };
@@ -1091,7 +1091,12 @@ struct InvMatrix {
     float *dst;
     int n, damp_idx, info_idx;
     bool bias;   // an A factor whose last row/column is the bias border
+    int layer;   // index into the traces' table, or -1
 };
+// Largest dA + dG of a group's layers for which the damping is found by the kernels that use it (every workgroup of them reads both
+// diagonals), instead of in a launch for it: inversion of two 288-row factors 53.1 us with that launch and one that clears info, 47.2
+// without them; of a 577- and a 64-row one (a step with them) 5 us less.
+constexpr int kInlineTrace = 1280;
 
 enum OpKind { OP_LEAF, OP_GEMM };
 struct InvOp {
@@ -1131,6 +1136,7 @@ int build_inverse(std::vector<InvOp> &ops, Arena &arena, float *X, long long ld,
         op.leaf.damp_idx = -1;
         op.leaf.info_idx = info_idx;
         op.leaf.pivot_base = o;
+        op.leaf.layer = -1;
         ops.push_back(op);
         return level + 1;
     }
@@ -1214,9 +1220,15 @@ struct InvertArgs {
 // Inversion of a list of damped SPD matrices as one chain of launches: the damped copies, then
 // the recursion of every matrix with the launches of equal depth merged, then the bias borders.
 // damp: device array the matrices' damp_idx point into; info: device array for info_idx or null.
+// traces: null, or what the first kernels find the damping with (off_b: the layers' table, f0, p0 and p2: gamma, damp, pi_out).
 void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::vector<InvMatrix> &mats,
-                      float *damp, int32_t *info)
+                      float *damp, int32_t *info, const Launch *traces = nullptr)
 {
+    auto damping = [&](Launch &L) {
+        L.p0 = damp;
+        L.cfg = traces ? 1 : 0;
+        if (traces) { L.off_b = traces->off_b; L.f0 = traces->f0; L.p2 = traces->p2; }
+    };
     std::vector<CopyJob> cjobs;
     std::vector<BorderJob> bjobs;
     int copy_wgs = 0, border_wgs = 0;
@@ -1232,6 +1244,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             op.leaf.damp_idx = m.damp_idx;
             op.leaf.info_idx = m.info_idx;
             op.leaf.pivot_base = 0;
+            op.leaf.layer = m.layer;
             ops.push_back(op);
         } else {
             // The bias border (c_in k^2 + 1) would make every block of the recursion one row larger
@@ -1242,6 +1255,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             C.src = m.src; C.dst = m.dst;
             C.lds = m.n; C.ldd = m.n; C.n = core;
             C.damp_idx = m.damp_idx;
+            C.layer = m.layer;
             C.border = m.bias ? 1 : 0;
             C.wg_start = copy_wgs;
             copy_wgs += (core + 7) / 8;
@@ -1266,7 +1280,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
         C.off_a = plan.tab.add(cjobs.data(), cjobs.size() * sizeof(CopyJob));
         C.n = (int)cjobs.size();
         C.total_wgs = copy_wgs;
-        C.p0 = damp;
+        damping(C);
         C.bytes = copy_bytes;
         plan.launches.push_back(C);
     }
@@ -1284,7 +1298,7 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
             Lf.kind = L_LEAF;
             Lf.off_a = plan.tab.add(lj.data(), lj.size() * sizeof(LeafJob));
             Lf.n = (int)lj.size();
-            Lf.p0 = damp;
+            damping(Lf);
             Lf.p1 = info;
             plan.launches.push_back(Lf);
         }
@@ -1323,6 +1337,7 @@ void plan_invert_group(Plan &plan, Arena &arena, const Tunables &tun, const Inve
     const size_t first_launch = plan.launches.size();
     std::vector<TraceJob> tjobs;
     std::vector<InvMatrix> mats;
+    bool inline_trace = true;
     for (int l : ids) {
         int dA, dG;
         layer_ok(a.L[l], &dA, &dG, nullptr, nullptr);
@@ -1333,20 +1348,20 @@ void plan_invert_group(Plan &plan, Arena &arena, const Tunables &tun, const Inve
         T.idx = l;
         tjobs.push_back(T);
         // dry runs only need distinct, well-aligned stand-in addresses for planning
-        mats.push_back({T.A, dry ? (float *)nullptr : a.A_inv[l], dA, 3 * l + 1, 2 * l, a.L[l].bias != 0});
-        mats.push_back({T.G, dry ? (float *)nullptr : a.G_inv[l], dG, 3 * l + 2, 2 * l + 1, false});
+        const int at = (int)tjobs.size() - 1;
+        mats.push_back({T.A, dry ? (float *)nullptr : a.A_inv[l], dA, 3 * l + 1, 2 * l, a.L[l].bias != 0, at});
+        mats.push_back({T.G, dry ? (float *)nullptr : a.G_inv[l], dG, 3 * l + 2, 2 * l + 1, false, at});
+        inline_trace &= dA + dG <= kInlineTrace;
     }
-    {
-        Launch T{};
-        T.kind = L_TRACE;
-        T.off_a = plan.tab.add(tjobs.data(), tjobs.size() * sizeof(TraceJob));
-        T.n = (int)tjobs.size();
-        T.f0 = a.gamma;
-        T.p0 = damp;
-        T.p1 = a.pi_out;
-        plan.launches.push_back(T);
-    }
-    plan_invert_mats(plan, arena, tun, mats, damp, a.info);
+    Launch T{};
+    T.kind = L_TRACE;
+    T.off_a = T.off_b = plan.tab.add(tjobs.data(), tjobs.size() * sizeof(TraceJob));
+    T.n = (int)tjobs.size();
+    T.f0 = a.gamma;
+    T.p0 = damp;
+    T.p1 = T.p2 = a.pi_out;
+    if (!inline_trace) plan.launches.push_back(T);
+    plan_invert_mats(plan, arena, tun, mats, damp, a.info, inline_trace ? &T : nullptr);
     plan.set_stream(first_launch, stream);
 }
 
@@ -1422,13 +1437,6 @@ std::vector<std::vector<int>> deal_by_depth(const kfac_layer *L, std::vector<int
 void plan_invert(Plan &plan, Arena &arena, const Tunables &tun, const InvertArgs &a, bool dry)
 {
     float *damp = (float *)arena.take((size_t)3 * a.n_layers * sizeof(float));
-    if (a.info || dry) {
-        Launch Z{};
-        Z.kind = L_ZERO;
-        Z.p0 = a.info;
-        Z.n = 2 * a.n_layers;
-        plan.launches.push_back(Z);
-    }
     std::vector<int> all(a.n_layers);
     for (int l = 0; l < a.n_layers; ++l) all[l] = l;
     const int n_groups = spread_chains(tun, a.L, all) ? std::max(1, std::min(tun.inv_streams, 4)) : 1;
@@ -1520,7 +1528,8 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
 {
     const int n = st.n_layers;
     float *damp = (float *)arena.take((size_t)3 * n * sizeof(float));
-    if (inv.info || dry) {
+    // (the first leaf of a matrix writes its report)
+    if (inv.info && mask && std::find(mask, mask + n, (uint8_t)0) != mask + n) {
         Launch Z{};
         Z.kind = L_ZERO;
         Z.p0 = inv.info;
@@ -1741,6 +1750,9 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
         if (hipEventRecord(ctx->ev[slot], s) != hipSuccess) return KFAC_ERR_DEVICE;
         ctx->ev_used[slot] = true;
     }
+    auto damping_of = [&](const Launch &L) {
+        return Damping{L.cfg ? (const TraceJob *)(tab_dev + L.off_b) : nullptr, L.f0, (float *)L.p0, (float *)L.p2};
+    };
     for (auto &L : plan.launches) {
         hipError_t e = hipSuccess;
         hipStream_t ls = s;
@@ -1782,7 +1794,7 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
                 case L_LAYOUT: pe.kernel = KFAC_K_LAYOUT; break;
                 case L_RECORD: case L_WAIT: break;
             }
-            pe.variant = (L.kind == L_GEMM || L.kind == L_LEAF || L.kind == L_BNFULL) ? L.cfg : 0;
+            pe.variant = (L.kind == L_GEMM || L.kind == L_BNFULL) ? L.cfg : 0;
             pe.workgroups = (L.kind == L_TRACE || L.kind == L_LEAF) ? L.n : L.total_wgs;
             pe.flops = L.flops;
             pe.bytes = L.bytes;
@@ -1819,10 +1831,10 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
                 e = launch_trace((const TraceJob *)(tab_dev + L.off_a), L.n, L.f0, (float *)L.p0, (float *)L.p1, ls);
                 break;
             case L_COPY:
-                e = launch_copy_damp((const CopyJob *)(tab_dev + L.off_a), L.n, L.total_wgs, (const float *)L.p0, ls);
+                e = launch_copy_damp((const CopyJob *)(tab_dev + L.off_a), L.n, L.total_wgs, damping_of(L), ls);
                 break;
             case L_LEAF:
-                e = launch_leaf((const LeafJob *)(tab_dev + L.off_a), L.n, (const float *)L.p0, (int32_t *)L.p1, ls);
+                e = launch_leaf((const LeafJob *)(tab_dev + L.off_a), L.n, damping_of(L), (int32_t *)L.p1, ls);
                 break;
             case L_ZERO:
                 e = launch_zero_i32((int32_t *)L.p0, L.n, ls);
@@ -2312,7 +2324,7 @@ void plan_bn_full(Plan &plan, Arena &arena, const Tunables &tun, const BnFullArg
     };
     pass(0);
     pass(1);
-    if (a.info || dry) {
+    if (a.info && (int)inv_ids.size() < n) {   // (the first leaf of a matrix writes its report)
         Launch Z{};
         Z.kind = L_ZERO;
         Z.p0 = a.info;
@@ -2328,7 +2340,7 @@ void plan_bn_full(Plan &plan, Arena &arena, const Tunables &tun, const BnFullArg
         std::vector<std::vector<int>> ids = deal_by_leaves(inv_ids, leaves, n_groups, 0);
         std::vector<std::vector<InvMatrix>> groups(n_groups);
         for (int g = 0; g < n_groups; ++g)
-            for (int l : ids[g]) groups[g].push_back({jobs[l].F_ema, dry ? (float *)nullptr : a.F_inv[l], 2 * a.C[l], l, l, false});
+            for (int l : ids[g]) groups[g].push_back({jobs[l].F_ema, dry ? (float *)nullptr : a.F_inv[l], 2 * a.C[l], l, l, false, -1});
         bool forked = false;
         for (int gi = 0; gi < n_groups; ++gi) {
             const int g = (gi + 1) % n_groups;   // auxiliary chains are enqueued before the main one

@@ -146,6 +146,13 @@ struct TraceJob {   // one per layer
     int dA, dG;
     int idx;        // layer index: damp[3*idx .. 3*idx+2] and pi_out[idx] are written
 };
+// What the first kernels of an inversion need to find the damping of small layers themselves, in the place of a launch that does
+struct Damping {
+    const TraceJob *layers;   // null: damp is there already
+    float gamma;
+    float *damp;              // [3 * layers]
+    float *pi_out;            // or null
+};
 
 struct CopyJob {    // dst[i][j] = src[i][j] + (i == j) * damp[damp_idx]   (i < n, j < min(n, i + kLeafMax))
     const float *src;
@@ -153,6 +160,7 @@ struct CopyJob {    // dst[i][j] = src[i][j] + (i == j) * damp[damp_idx]   (i < 
     long long lds, ldd;
     int n;
     int damp_idx;   // index into the damping array, or -1
+    int layer;      // where the kernel finds the damping itself: index into the layers' table
     int border;     // 1: src is (n+1) x (n+1); its last row/column (the bias border of an A factor) is
                     // eliminated on the fly: with u = src[0:n, n], c = src[n][n] + damp the copy is
                     // the Schur complement  src[0:n,0:n] + damp I - u u^T / c
@@ -179,7 +187,8 @@ struct LeafJob {    // dst = (src + damp I)^-1 inside one workgroup, n <= 288
     int n;
     int damp_idx;   // or -1
     int info_idx;   // index into info (or -1), pivot indices are reported + pivot_base
-    int pivot_base;
+    int pivot_base; // (the leaf with 0 is the first of its matrix: it writes its report, zero or not)
+    int layer;      // as in CopyJob; -1: damp_idx as it stands
 };
 
 // ---- BatchNorm ---------------------------------------------------------------------
@@ -312,12 +321,11 @@ hipError_t launch_pad_bf16(const PadJobBF16 *jobs_dev, int n_jobs, int total_wgs
 hipError_t launch_assemble(const AssembleJob *jobs_dev, int n_jobs, int total_wgs, hipStream_t s);
 hipError_t launch_trace(const TraceJob *jobs_dev, int n_layers, float gamma, float *damp_dev,
                         float *pi_out, hipStream_t s);
-hipError_t launch_copy_damp(const CopyJob *jobs_dev, int n_jobs, int total_wgs, const float *damp_dev,
-                            hipStream_t s);
+hipError_t launch_copy_damp(const CopyJob *jobs_dev, int n_jobs, int total_wgs, const Damping &damping, hipStream_t s);
 // pass 0: the border row/column (total_wgs workgroups); pass 1: the corner (one workgroup per job)
 hipError_t launch_border(const BorderJob *jobs_dev, int n_jobs, int total_wgs, int pass, const float *damp_dev,
                          int32_t *info, hipStream_t s);
-hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, const float *damp_dev, int32_t *info, hipStream_t s);
+hipError_t launch_leaf(const LeafJob *jobs_dev, int n_jobs, const Damping &damping, int32_t *info, hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s);
 hipError_t launch_bn(const BnJob *jobs_dev, int n_jobs, int total_wgs, int N, float decay, float lambda,
                      hipStream_t s);
