@@ -461,7 +461,8 @@ typedef enum {
 
 typedef struct {
     int32_t kernel;    /* kfac_kernel */
-    int32_t variant;   /* GEMM: 0 = 128x128 tiles, 1 = 64x64 tiles, 2 / 3 = 32x32 / 64x64 without LDS staging */
+    int32_t variant;   /* GEMM: 0 = 128x128 tiles, 1 = 64x64 tiles, 2 / 3 = 32x32 / 64x64 without LDS staging,
+                        * 4 = the displaced products of one image together */
     int32_t workgroups;
     float ms;
     double flops;

@@ -710,6 +710,16 @@ __device__ __forceinline__ float max_abs(float m, const floatx4 &v)
     return fmaxf(fmaxf(m, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
 }
 
+// The floor that the counts of 32 sampled elements give, see RowSample::floor_of.
+__device__ __forceinline__ float half_floor(float f, float most)
+{
+    const float n_small = floorf(f * 0x1p-16f);
+    f -= n_small * 0x1p16f;
+    const float n_larger = floorf(f * 0x1p-10f);
+    f -= n_larger * 0x1p10f;
+    return most * (n_larger <= 1.f ? 2.f : n_larger < kHalfFew ? 1.f : fminf(fmaxf(1.f / 128, n_small / (4.f * f)), 1.f));
+}
+
 // Largest sampled magnitudes of the thread's rows over [k0, k0 + klen): request() issues the loads of four chunks per row and lane,
 // finish() waits for them, so that both operands' loads are in flight together.
 template <int BR>
@@ -753,11 +763,7 @@ struct RowSample {
         f += __shfl_xor(f, 1);
         f += __shfl_xor(f, 2);
         f += __shfl_xor(f, 4);
-        const float n_small = floorf(f * 0x1p-16f);
-        f -= n_small * 0x1p16f;
-        const float n_larger = floorf(f * 0x1p-10f);
-        f -= n_larger * 0x1p10f;
-        return most * (n_larger <= 1.f ? 2.f : n_larger < kHalfFew ? 1.f : fminf(fmaxf(1.f / 128, n_small / (4.f * f)), 1.f));
+        return half_floor(f, most);
     }
 };
 // over the 8 lanes of a row
@@ -1510,22 +1516,13 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_f32_split_trans_kernel(const G
 // three planes 143).  Eight places of a row and the floors of the rows take 2 to 5 % (without them 268, 274 and 318).  Tiles of 256 x 128 by eight wavefronts were 5 % faster on 4096^3 and too coarse for the rest; 256 x 256 spills.
 // (Two wavefronts per SIMD, four of the small tile: the register allocation is held to 256 and 128.)
 template <int TM, int TN>
-__global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_kernel(const GemmProblem *__restrict__ probs,
-                                                                            const int *__restrict__ tile_start, int n_probs)
+__device__ __forceinline__ void gemm_nt_f32_split_tile(const GemmProblem &P, int tile, int split, bool part_of_k, float *lds)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
-    extern __shared__ __attribute__((aligned(16))) float lds[];   // operand stages, then slabs of the output tile; scales behind
     float *sc = lds + split_lds_bytes<TM, TN>() / sizeof(float) - (2 * (BM + BN) + 2 + 1 + kMaxDoubts);
     int *doubts = (int *)(sc + 2 * (BM + BN) + 2);
     unsigned short *l16 = (unsigned short *)lds;
-
-    const int wg = blockIdx.x;
-    const int pi = find_problem(tile_start, n_probs, wg);
-    const GemmProblem &P = probs[pi];
-    const int local = wg - tile_start[pi];
-    if (local >= n_workgroups(P)) return;   // padding up to the next problem
-    int tile, split, tm, tn;
-    const bool part_of_k = locate_tile(P, local, tile, split);   // neighbours: neighbouring tiles of the same K range
+    int tm, tn;
     decode_tile(P, tile, tm, tn);
     const int k0 = split * P.k_per_split;
     const int k1 = part_of_k ? min(P.K, k0 + P.k_per_split) : P.K;
@@ -1654,6 +1651,21 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_k
         }
         store_slab<BM, BN>(P, lds, tm * BM, tn * BN, diag_tile, tid);
     }
+}
+
+template <int TM, int TN>
+__global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void gemm_nt_f32_split_kernel(const GemmProblem *__restrict__ probs,
+                                                                            const int *__restrict__ tile_start, int n_probs)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // operand stages, then the output tile; scales behind
+    const int wg = blockIdx.x;
+    const int pi = find_problem(tile_start, n_probs, wg);
+    const GemmProblem &P = probs[pi];
+    const int local = wg - tile_start[pi];
+    if (local >= n_workgroups(P)) return;   // padding up to the next problem
+    int tile, split;
+    const bool part_of_k = locate_tile(P, local, tile, split);   // neighbours: neighbouring tiles of the same K range
+    gemm_nt_f32_split_tile<TM, TN>(P, tile, split, part_of_k, lds);
 }
 
 // ------------------------------------------------------------------ bf16 operand loader
@@ -2347,6 +2359,303 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_trans_kernel(const GemmProbl
     gemm_nt_bf16_body<TM, TN, false, true>(P, local, lds);
 }
 
+// ------------------------------------------------------------------ the displaced products of one image together
+// The 13 products of a padded image of up to 64 channels with itself displaced by (dy, dx) (corr.hip), as parts of their
+// contraction (the partial tiles of gemm_reduce_kernel).  One by one, as 64-row tiles, each of them read its two operands from
+// memory: 26 times the tensor, which bound them (64 channels at 56 x 56, 32 samples, bf16: 1.36 GB and 165 us for three layers;
+// fp32: 26 conversions of every element as well).  Here a workgroup stages the rows of the image and of six displaced ones in LDS
+// and forms seven (or six) products out of them: two workgroups, on the same XCD, share a part.  7 x 16 accumulators leave
+// two workgroups to a compute unit (all thirteen in one: 208, one workgroup, and half the parts).
+// Three images of 64 channels at 56 x 56: fp32 187 -> 132 us with 32 samples, 469 -> 233 with 64 and 959 -> 438 with 128 (315
+// TFLOP/s, where two planes stop at the power limit), bf16 130 -> 126 with 32, 362 -> 242 with 64.  Bound: fp32 by power; bf16 by the loads of a step, which wait for its barrier (one stage: two would leave
+// one workgroup to a compute unit).  Errors of the factors against 64 bits, over batches of 8 to 128, 17 to 64 channels and 28 to 112
+// positions a side: fp32 0.88, bf16 0.96 of those of single products.
+// A thread loads and stores 16 bytes of two rows of every staged tile: the tiles differ by a uniform base address only.  (The planes
+// of a padded image have at least 28 positions in fp32 and 40 in bf16, so that a step wraps twice at most.)
+constexpr int DISP_TILES = 7, DISP_TILE_BYTES = 8192, DISP_STAGE = DISP_TILES * DISP_TILE_BYTES;
+constexpr size_t displaced_lds_bytes()
+{
+    const size_t own = DISP_STAGE + (2 * 128 + 2 + 1 + kMaxDoubts + 1) * sizeof(float), one_by_one = split_lds_bytes<1, 1>();
+    return own > one_by_one ? own : one_by_one;
+}
+
+// Position of a thread's chunk in the contraction.
+struct DisplacedCursor {
+    unsigned at;               // byte offset from a tile's base address
+    int t, m;
+    __device__ __forceinline__ void seek(const Operand &op, int row, int m_, int esize)
+    {
+        m = m_;
+        const int n = m / op.hw;
+        t = m - n * op.hw;
+        at = (unsigned)((n * op.batch_stride + (long long)row * op.row_stride + t) * esize);
+    }
+    // by `step` < 2 hw positions; beyond kend: where it is (what is read there counts as zero)
+    __device__ __forceinline__ void advance(const Operand &op, int step, int kend, int esize)
+    {
+        m += step;
+        if (m >= kend) return;
+        t += step;
+        at += (unsigned)(step * esize);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bool wrap = t >= op.hw;
+            t -= wrap ? op.hw : 0;
+            at += wrap ? (unsigned)((op.batch_stride - op.hw) * esize) : 0u;
+        }
+    }
+};
+
+// Scales and floors of the 64 rows in [k0, k0 + klen), as half_scales makes them: 32 sampled elements of each for the floor.  False:
+// the two planes do not serve.
+__device__ __forceinline__ bool displaced_scales(const Operand &op, int k0, int klen, float *sc, int tid)
+{
+    const int row = tid >> 2, kq = 4 * (tid & 3);
+    const Global<const char> base = global((const char *)op.base);
+    floatx4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        DisplacedCursor at;
+        at.seek(op, min(row, op.rows - 1), k0 + kq + (q == 7 ? klen - 16 : ((klen - 16) / 7 * q) & ~3), 4);
+        v[q] = *(Global<const floatx4_u>)(base + at.at);
+    }
+    float mx = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) mx = max_abs(mx, v[q]);
+    mx = fmaxf(mx, __shfl_xor(mx, 1));
+    mx = fmaxf(mx, __shfl_xor(mx, 2));
+    float scale = half_scale(mx, kHalfTop), f = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const float y = fabsf(v[q][0]) * scale;
+        f += fminf(y, 16.f) + (y >= kHalfExact ? 0x1p10f : y != 0.f ? 0x1p16f : 0.f);
+    }
+    f += __shfl_xor(f, 1);
+    f += __shfl_xor(f, 2);
+    const float floor = half_floor(f, kHalfFloor);
+    const bool zero = mx == 0.f, dead = row >= op.rows;
+    if ((tid & 3) == 0) {
+        sc[row] = sc[64 + row] = zero && !dead ? 0.f : scale;
+        sc[128 + row] = sc[192 + row] = dead ? kNoFloor : floor;
+    }
+    const bool odd = !dead && floor > kHalfFloor;
+    if (__syncthreads_or(odd)) {
+        if (__syncthreads_count(odd && (tid & 3) == 0) > 16) return false;
+        for (int r = tid >> 6; r < 64; r += 4) {      // rows that sampled as zero are read on until an element is not
+            if (sc[r] != 0.f) continue;
+            float most = 0.f;
+            walk_row(op, r, k0, klen, tid & 63, [&](const auto &x) {
+#pragma unroll
+                for (const floatx4 &y : x) most = max_abs(most, y);
+                for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
+                return most != 0.f;
+            });
+            if ((tid & 63) == 0) {
+                sc[r] = sc[64 + r] = half_scale(most, kHalfTop);
+                if (most == 0.f) sc[128 + r] = sc[192 + r] = kNoFloor;
+            }
+        }
+        __syncthreads();
+    }
+    return true;
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProblem *__restrict__ probs, const int *__restrict__ start, int n_groups)
+{
+    constexpr int KS = BF16 ? 64 : 32, CHUNK = KS / 8, ESIZE = BF16 ? 2 : 4;   // positions a step, a thread's chunk
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    char *stage = (char *)lds;
+    float *sc = lds + DISP_STAGE / 4;
+    int *doubts = (int *)(sc + 258), *redo = doubts + 1 + kMaxDoubts;
+    const int wg = blockIdx.x, g = find_problem(start, n_groups, wg), local = wg - start[g];
+    const GemmProblem *Q = probs + 13 * g;
+    const Operand op = Q->a;
+    const int second = (local >> 3) & 1, split = (local & 7) + 8 * (local >> 4);   // (workgroups of a part: the same XCD)
+    if (split >= Q->splits) return;
+    const int k0 = split * Q->k_per_split, k1 = min(Q->K, k0 + Q->k_per_split);
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int wave_m = wid >> 1, wave_n = wid & 1, l32 = lane & 31, half = lane >> 5;
+    const bool live = 32 * wave_m < op.rows && 32 * wave_n < op.rows;
+    const int row = tid >> 3, chunk = tid & 7;            // a thread: this chunk of rows `row` and row + 32
+
+    // tile 0: the image; tile j: the image as displacement 6 * second + j displaces it
+    Global<const char> base[DISP_TILES];
+    base[0] = global((const char *)op.base);
+#pragma unroll
+    for (int j = 1; j < DISP_TILES; ++j) base[j] = global((const char *)Q[6 * second + j].b.base);
+
+    float scale[2] = {1.f, 1.f};
+    bool one_by_one = false;
+    if constexpr (!BF16) {
+        if (tid == 0) { doubts[0] = 0; *redo = 0; }
+        one_by_one = !displaced_scales(op, k0, k1 - k0, sc, tid);
+        scale[0] = sc[row];
+        scale[1] = sc[row + 32];
+    }
+    floatx16 acc[DISP_TILES];
+    float rs[2] = {0.f, 0.f};
+    if (!one_by_one) {
+        typedef std::conditional_t<BF16, ushortx8, floatx4> chunk_t;
+        typedef std::conditional_t<BF16, ushortx8, floatx4_u> chunk_mem_t;
+        chunk_t reg[DISP_TILES][2];
+        DisplacedCursor at;
+        at.seek(op, min(row, op.rows - 1), min(k0 + CHUNK * chunk, k1 - CHUNK), ESIZE);
+        at.m = k0 + CHUNK * chunk;
+        const unsigned down = (unsigned)((min(row + 32, op.rows - 1) - min(row, op.rows - 1)) * op.row_stride * ESIZE);
+        bool in = at.m < k1;                              // what the registers hold counts
+        auto load = [&]() {
+#pragma unroll
+            for (int j = 0; j < DISP_TILES; ++j) {
+                reg[j][0] = *(Global<const chunk_mem_t>)(base[j] + at.at);
+                reg[j][1] = *(Global<const chunk_mem_t>)(base[j] + (at.at + down));
+            }
+        };
+        // 16-byte chunks of a row are permuted so that fragment reads spread over the banks (32 rows further down alike)
+        const int to = BF16 ? row * 128 + ((chunk ^ (row & 7)) << 4) : row * 64 + (((chunk >> 1) ^ half_swz(row)) << 4) + 8 * (chunk & 1);
+        auto store = [&](int j, int s) {
+            char *dst = stage + j * DISP_TILE_BYTES + to + s * (BF16 ? 4096 : 2048);
+            chunk_t x = reg[j][s];
+            if (j == 0 && !in)
+#pragma unroll
+                for (int e = 0; e < CHUNK; ++e) x[e] = 0;
+            if constexpr (BF16) {
+                if (j == 0)
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) rs[s] += __uint_as_float((unsigned)x[e] << 16) + __uint_as_float((unsigned)x[e + 1] << 16);
+                *(ushortx8 *)dst = x;
+            } else {
+                if (j == 0) rs[s] += (x[0] + x[1]) + (x[2] + x[3]);
+                uint2 h, l;
+                split_half_pair(x[0], x[1], scale[s], h.x, l.x);
+                split_half_pair(x[2], x[3], scale[s], h.y, l.y);
+                *(uint2 *)dst = h;
+                *(uint2 *)(dst + 4096) = l;
+            }
+        };
+        // fragments of 32 rows of a tile: bf16 the four 16-wide parts of the step; fp32 its two, of both planes
+        struct Frag { ushortx8 v[4]; };
+        auto read = [&](int j, int r0) {
+            const int r = r0 + l32;
+            Frag f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                f.v[u] = *(const ushortx8 *)(stage + j * DISP_TILE_BYTES +
+                                             (BF16 ? r * 128 + (((2 * u + half) ^ (r & 7)) << 4) : r * 64 + (((2 * (u & 1) + half) ^ half_swz(r)) << 4) + 4096 * (u >> 1)));
+            return f;
+        };
+        auto multiply = [&](floatx16 &c, const Frag &a, const Frag &b) {
+            if constexpr (BF16) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.v[u]), __builtin_bit_cast(bf16x8, b.v[u]), c, 0, 0, 0);
+            } else {
+                auto h = [](const ushortx8 &v) { return __builtin_bit_cast(halfx8, v); };
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(h(a.v[u]), h(b.v[u]), c, 0, 0, 0);
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(h(a.v[u]), h(b.v[u + 2]), c, 0, 0, 0);
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(h(a.v[u + 2]), h(b.v[u]), c, 0, 0, 0);
+                }
+            }
+        };
+        auto partial = [&](int j) { return global(Q[j == 0 ? 0 : 6 * second + j].partial) + (long long)split * 4096 + (32 * wave_m + 4 * half) * 64 + 32 * wave_n + l32; };
+        auto at_row = [](int v) { return (8 * (v >> 2) + (v & 3)) * 64; };
+        // No chain of sums over more positions than the split rule gives a part (128 parts, 512 to 4096 positions): such lengths are added up in the partial tile
+        // (9 to 20 us more where there are two; without it the errors against 64 bits grew by a tenth).
+        const int steps = (k1 - k0 + KS - 1) / KS, longest = (min(4096, max(512, (Q->K + 127) / 128)) + KS - 1) / KS;
+        const int chains = (steps + longest - 1) / longest, chain = (steps + chains - 1) / chains;
+        int left = chain;
+        bool first = true;                                // nothing in the partial tiles yet
+        load();
+#pragma unroll
+        for (int j = 0; j < DISP_TILES; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        for (int k = k0; k < k1; k += KS) {
+            __syncthreads();                              // the step before has been read
+#pragma unroll
+            for (int j = 0; j < DISP_TILES; ++j) {
+                store(j, 0);
+                store(j, 1);
+            }
+            at.advance(op, KS, k1, ESIZE);
+            in = at.m < k1;
+            load();                                       // (behind the last step: the same again)
+            __syncthreads();
+            if (!live) continue;
+            const Frag a = read(0, 32 * wave_m);
+            Frag b = read(0, 32 * wave_n);
+#pragma unroll
+            for (int j = 0; j < DISP_TILES; ++j) {
+                Frag next = b;
+                if (j + 1 < DISP_TILES) next = read(j + 1, 32 * wave_n);
+                __builtin_amdgcn_sched_barrier(0);
+                if (j > 0 || !second) multiply(acc[j], a, b);
+                __builtin_amdgcn_sched_barrier(0);
+                b = next;
+            }
+            if (--left > 0 || k + KS >= k1) continue;
+            left = chain;
+#pragma unroll
+            for (int j = 0; j < DISP_TILES; ++j) {
+                if (j == 0 && second) continue;
+                const Global<float> part = partial(j);
+                if (!first)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[j][v] += part[at_row(v)];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part[at_row(v)] = acc[j][v];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+            }
+            first = false;
+        }
+        if (!second) {                                     // the border: sums of the rows
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                rs[s] += __shfl_xor(rs[s], 1);
+                rs[s] += __shfl_xor(rs[s], 2);
+                rs[s] += __shfl_xor(rs[s], 4);
+                if (chunk == 0 && (Q->flags & GEMM_BORDER)) global(Q->partial_rs)[(long long)split * 64 + row + 32 * s] = rs[s];
+            }
+        }
+        unsigned again = 0;
+#pragma unroll
+        for (int j = 0; j < DISP_TILES; ++j) {
+            if (!live || (j == 0 && second)) continue;
+            const Global<float> part = partial(j);
+            if (!first)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j][v] += part[at_row(v)];
+            floatx16 one[1][1] = {{acc[j]}};
+            if constexpr (!BF16) {
+                if (half_doubts<1, 1>(one, sc, doubts, wave_m, wave_n, l32, half)) again |= 1u << j;
+                half_unscale_tile<1, 1>(one, sc, wave_m, wave_n, l32, half);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) part[at_row(v)] = one[0][0][v];
+        }
+        if constexpr (!BF16) {
+            if (again) atomicOr(redo, (int)again);
+            __syncthreads();
+        }
+    } else if (tid == 0) {
+        *redo = (1 << DISP_TILES) - 1;
+    }
+    if constexpr (!BF16) {
+        // where sums are in doubt or not finite, or the two planes do not serve: as products of their own
+        __syncthreads();
+        const int again = *redo;
+        __syncthreads();
+        for (int j = second; j < DISP_TILES; ++j) {
+            if (!((again >> j) & 1)) continue;
+            gemm_nt_f32_split_tile<1, 1>(Q[j == 0 ? 0 : 6 * second + j], 0, split, true, lds);
+            __syncthreads();
+        }
+    }
+}
+
 template <typename Kernel>
 static hipError_t launch_one(Kernel kernel, bool &configured, size_t lds_bytes, const GemmProblem *probs_dev,
                              const int *tile_start_dev, int n_probs, int total_wgs, hipStream_t s)
@@ -2381,6 +2690,13 @@ hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, 
     }
     if (tile_cfg == 0) return go(gemm_nt_f32_split_kernel<2, 2>, split_lds_bytes<2, 2>());
     return go(gemm_nt_f32_split_kernel<1, 1>, split_lds_bytes<1, 1>());
+}
+
+hipError_t launch_gemm_displaced(const GemmProblem *probs_dev, const int *start_dev, int n_groups, int total_wgs, int bf16, hipStream_t s)
+{
+    static bool configured[2];
+    auto kernel = bf16 ? gemm_displaced_kernel<true> : gemm_displaced_kernel<false>;
+    return launch_one(kernel, configured[bf16 != 0], displaced_lds_bytes(), probs_dev, start_dev, n_groups, total_wgs, s);
 }
 
 hipError_t launch_gemm_reduce(const GemmProblem *probs_dev, const int *red_start_dev, int n_probs,

@@ -222,6 +222,8 @@ struct GemmGroup {   // problems that go into one phase (no dependencies among t
     std::vector<GemmProblem> probs;
 };
 
+constexpr int kDisplacedCfg = 4;       // of a launch: gemm_displaced_kernel (64-row tiles)
+constexpr int kDisplacedParts = 256;
 int tile_edge(int cfg) { return cfg == 0 ? 128 : cfg == 2 ? 32 : 64; }
 
 // Rough time model (matrix-pipe cycles) of one problem under a tile configuration: the
@@ -305,40 +307,51 @@ int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun)
 // launches, on a stream it chooses).
 // align: every problem starts at a multiple of that many workgroups (8: see locate_tile; not where the padding could push a
 // launch past a whole number of rounds).
+// displaced: so many problems at the front, in groups of 13, have a launch of their own (gemm_displaced_kernel).
 void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmProblem> &sel, int cfg, int dtype, int align,
-                      std::vector<Launch> *deferred = nullptr)
+                      std::vector<Launch> *deferred = nullptr, size_t displaced = 0)
 {
     if (sel.empty()) return;
     const int B = tile_edge(cfg);
-    std::vector<int> start(sel.size() + 1, 0), rstart(sel.size() + 1, 0);
+    std::vector<int> start(sel.size() - displaced + 1, 0), rstart(sel.size() + 1, 0), dstart(displaced / 13 + 1, 0);
+    for (size_t g = 0; g < displaced / 13; ++g) dstart[g + 1] = dstart[g] + (sel[13 * g].splits + 7) / 8 * 16;
     bool any_split = false;
     for (size_t i = 0; i < sel.size(); ++i) {
         const GemmProblem &P = sel[i];
-        start[i + 1] = start[i] + (P.split_from + (P.n_tiles - P.split_from) * P.splits + align - 1) / align * align;
+        if (i >= displaced)
+            start[i - displaced + 1] = start[i - displaced] + (P.split_from + (P.n_tiles - P.split_from) * P.splits + align - 1) / align * align;
         rstart[i + 1] = rstart[i] + (P.splits > 1 ? (P.n_tiles - P.split_from) * (B / red_rows(P.splits)) : 0);
         any_split |= P.splits > 1;
     }
-    Launch L{};
-    L.kind = L_GEMM;
-    for (auto &P : sel) L.k_max = std::max(L.k_max, P.K);
-    for (auto &P : sel)
-        if (P.flags & GEMM_SYM) {
-            const double d = P.M + ((P.flags & GEMM_BORDER) ? 1.0 : 0.0);
-            L.flops += (double)P.K * d * (d + 1.0);
-        } else {
-            L.flops += 2.0 * P.M * (double)P.N * P.K;
+    const size_t off = plan.tab.add(sel.data(), sel.size() * sizeof(GemmProblem));
+    auto matrix_launch = [&](size_t first, size_t last, const std::vector<int> &at, int kernel) {
+        if (first == last) return;
+        Launch L{};
+        L.kind = L_GEMM;
+        for (size_t i = first; i < last; ++i) {
+            const GemmProblem &P = sel[i];
+            L.k_max = std::max(L.k_max, P.K);
+            if (P.flags & GEMM_SYM) {
+                const double d = P.M + ((P.flags & GEMM_BORDER) ? 1.0 : 0.0);
+                L.flops += (double)P.K * d * (d + 1.0);
+            } else {
+                L.flops += 2.0 * P.M * (double)P.N * P.K;
+            }
         }
-    L.off_a = plan.tab.add(sel.data(), sel.size() * sizeof(GemmProblem));
-    L.off_b = plan.tab.add(start.data(), start.size() * sizeof(int));
-    L.n = (int)sel.size();
-    L.total_wgs = start.back();
-    L.cfg = cfg;
-    L.dtype = (dtype == 0 && tun.split) ? 2 : dtype;
-    plan.launches.push_back(L);
+        L.off_a = off + first * sizeof(GemmProblem);
+        L.off_b = plan.tab.add(at.data(), at.size() * sizeof(int));
+        L.n = (int)at.size() - 1;
+        L.total_wgs = at.back();
+        L.cfg = kernel;
+        L.dtype = (dtype == 0 && tun.split) ? 2 : dtype;
+        plan.launches.push_back(L);
+    };
+    matrix_launch(0, displaced, dstart, kDisplacedCfg);
+    matrix_launch(displaced, sel.size(), start, cfg);
     if (any_split) {
         Launch R{};
         R.kind = L_REDUCE;
-        R.off_a = L.off_a;
+        R.off_a = off;
         R.off_b = plan.tab.add(rstart.data(), rstart.size() * sizeof(int));
         R.n = (int)sel.size();
         R.total_wgs = rstart.back();
@@ -346,6 +359,46 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
             if (P.splits > 1) R.bytes += 4.0 * (P.n_tiles - P.split_from) * B * B * (P.splits + 1.0);
         if (deferred) deferred->push_back(R);
         else plan.launches.push_back(R);
+    }
+}
+
+// Takes the displaced products of images of up to 64 channels out of `sel` and splits them for gemm_displaced_kernel: into at most
+// 256 parts in all (two workgroups each, two to a compute unit), a multiple of 8 of each image (an XCD more of them than its 64
+// slots hold is a second round: 85 parts of three images 242 us, 80 132), within the limits of the split rule, which are those of the
+// workspace bound.
+// The rule: where the split rule allows the images 256 parts together.  With fewer (one image, or short contractions) a compute
+// unit holds one workgroup, which waits for its own loads; that, a launch more and no gain in the lines and corners make it the
+// slower way.  Products of one layer each at 56 x 56, together with those of its lines and corners, one by one against this way:
+//   fp32  64 channels, 32 samples: one image 78 us against 87; two 142, 103; three 212, 157.  64 samples: one 137, 132; three 494, 258;
+//                      128 samples: three 984, 463
+//   fp32  32 channels, 32 samples: three 148, 119;  50 channels at 28 x 28, 27 samples: two 47, 69
+//   bf16  64 channels, 32 samples: one 45, 47; two 80, 70; three 145, 139.  64 samples: one 75, 69; three 377, 257
+void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> &sel, std::vector<GemmProblem> &displaced)
+{
+    std::vector<GemmProblem> rest;
+    // (a part may be twice as long as the rule's: its sums are chains of at most max_k_per_wg)
+    auto least = [&](const GemmProblem &P) { return (P.K + 2 * tun.max_k_per_wg - 1) / (2 * tun.max_k_per_wg); };
+    auto most = [&](const GemmProblem &P) { return std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P.K / tun.min_k_per_split)); };
+    double k_all = 0;
+    int allowed = 0;
+    for (size_t i = 0; i < sel.size(); ++i) {
+        bool together = (sel[i].flags & GEMM_DISPLACED) && i + 13 <= sel.size() && most(sel[i]) >= 2;
+        for (size_t q = 1; together && q < 13; ++q) together = sel[i + q].a.base == sel[i].a.base && sel[i + q].K == sel[i].K;
+        if (!together) { rest.push_back(sel[i]); continue; }
+        displaced.insert(displaced.end(), sel.begin() + i, sel.begin() + i + 13);
+        k_all += sel[i].K;
+        allowed += most(sel[i]);
+        i += 12;
+    }
+    if (allowed < kDisplacedParts) { displaced.clear(); return; }
+    sel = rest;
+    for (GemmProblem &P : displaced) {
+        const int share = (int)(kDisplacedParts * (double)P.K / k_all);
+        const int parts = std::min(most(P), std::max({2, least(P), share >= 8 ? share / 8 * 8 : share}));
+        P.k_per_split = ((P.K + parts - 1) / parts + 31) / 32 * 32;
+        P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
+        P.partial = (float *)arena.take((size_t)P.splits * 64 * 64 * sizeof(float));
+        if (P.flags & GEMM_BORDER) P.partial_rs = (float *)arena.take((size_t)P.splits * 64 * sizeof(float));
     }
 }
 
@@ -392,6 +445,9 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
         if (sel.empty()) continue;
         const int B = tile_edge(cfg);
         int align = 1;
+        std::vector<GemmProblem> displaced;
+        if (cfg == 1 && (dtype == 1 || (dtype == 0 && tun.split)) && !tun.chosen_rule && !tun.worst_case_splits)
+            take_displaced(arena, tun, sel, displaced);
         if (cfg < 2) {
             // Per problem (independent of what else is in the launch, so that the workspace need of
             // a layer list does not depend on which of its inputs are present): enough splits for
@@ -422,7 +478,8 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
         std::stable_sort(sel.begin(), sel.end(), [](const GemmProblem &x, const GemmProblem &y) {
             return std::min(x.K, x.k_per_split) > std::min(y.K, y.k_per_split);
         });
-        push_gemm_launch(plan, tun, sel, cfg, dtype, align, deferred);
+        sel.insert(sel.begin(), displaced.begin(), displaced.end());
+        push_gemm_launch(plan, tun, sel, cfg, dtype, align, deferred, displaced.size());
     }
 }
 
@@ -945,6 +1002,7 @@ void plan_stats(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &
                 const int dy = slot < 3 ? 0 : (slot - 3) / 5 + 1, dx = slot < 3 ? slot : (slot - 3) % 5 - 2;
                 gram(img, image_op(dy, dx), N * PP, slot == 0, &S.full[slot], &S.full_t[slot], &S.ld_full[slot]);
             }
+            if (C <= 64 && (double)N * C * PP * esize < 4e9) probs[probs.size() - 13].flags |= GEMM_DISPLACED;   // (32-bit offsets)
             for (int which = 0; which < 2; ++which)
                 for (int d = 0; d < 3; ++d) {
                     gram(row_op(which, 0), row_op(which, d), N * Lw, d == 0, &S.rows[which][d], &S.rows_t[which][d], &S.ld_rows[which][d]);
@@ -1807,6 +1865,11 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
         }
         switch (L.kind) {
             case L_GEMM:
+                if (L.cfg == kDisplacedCfg) {
+                    e = launch_gemm_displaced((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b), L.n, L.total_wgs,
+                                              L.dtype == 1, ls);
+                    break;
+                }
                 e = L.cfg >= 2 ? launch_gemm_direct((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b),
                                                     L.n, L.total_wgs, L.cfg, L.k_max, ls)
                                : launch_gemm((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b), L.n,

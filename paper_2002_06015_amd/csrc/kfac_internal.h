@@ -41,7 +41,8 @@ struct Operand {
 //              comes from row sums taken while the diagonal tiles stage their operand,
 //              and C[M][M] = alpha * ones + beta * old.
 // GEMM_TRANS:  both operands are stored transposed (Operand::trans).
-enum : int { GEMM_SYM = 1, GEMM_BORDER = 2, GEMM_TRANS = 4 };
+// GEMM_DISPLACED: the first of the 13 products of a padded image with itself displaced (corr.hip), the others follow it.
+enum : int { GEMM_SYM = 1, GEMM_BORDER = 2, GEMM_TRANS = 4, GEMM_DISPLACED = 8 };
 
 struct GemmProblem {
     Operand a, b;
@@ -313,6 +314,8 @@ hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, 
 // small products of plain fp32 matrices (tile_cfg 2, 3), three-plane product mode
 hipError_t launch_gemm_direct(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, int total_wgs,
                               int tile_cfg, int k_max, hipStream_t s);
+// groups of 13 problems: the displaced products of padded images of up to 64 channels (dtype fp32 through planes, or bf16), all split
+hipError_t launch_gemm_displaced(const GemmProblem *probs_dev, const int *start_dev, int n_groups, int total_wgs, int bf16, hipStream_t s);
 hipError_t launch_gemm_reduce(const GemmProblem *probs_dev, const int *red_start_dev, int n_probs,
                               int total_wgs, hipStream_t s);
 hipError_t launch_patch(const PatchJob *jobs_dev, int n_jobs, int total_wgs, hipStream_t s);

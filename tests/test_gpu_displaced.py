@@ -1,0 +1,147 @@
+"""The 13 displaced products of 3x3 convolutions of up to 64 channels, which share a launch: channel counts around the wavefronts'
+32 rows, planes that no step of the contraction divides, short last parts, several layers in one call, and values that lead
+single products, or all of them, to the general kernel.  They do so where the split rule (512 positions to a part, 128 parts to a
+product) allows the images of a call 256 parts: a small layer stands in the list as often as that takes."""
+import pytest
+import torch
+
+from paper_2002_06015_amd import kfac, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _times(L):
+    return -(-256 // min(128, L.N * (L.h_in + 2) * (L.w_in + 2) // 512))
+
+
+def _factor(layers, dtype, acts, decay=0.75, nhwc=False):
+    gen = torch.Generator(device="cuda").manual_seed(len(layers))
+    A = [torch.randn(L.dA, L.dA, device="cuda", generator=gen) for L in layers]
+    A = [(a + a.t()).contiguous() for a in A]
+    A0 = [a.double() for a in A]
+    G = [torch.empty(L.dG, L.dG, device="cuda") for L in layers]
+    ctx = kfac.Context(layers, dtype)
+    kfac.kfac_profile_enable(ctx, True)
+    kfac.kfac_stats(ctx, layers, dtype, acts, None, decay, True, A, G, nhwc=nhwc)
+    torch.cuda.synchronize()
+    together = sum(e["variant"] == 4 and "gemm" in e["kernel"] for e in kfac.kfac_profile_read(ctx))
+    ctx.close()
+    return A, A0, together
+
+
+def _check(L, x, A, A0, decay=0.75):
+    m = torch.nn.functional.unfold(x.double(), 3, padding=1).permute(1, 0, 2).reshape(9 * L.c_in, -1)
+    if L.bias:
+        m = torch.cat([m, torch.ones(1, m.shape[1], device="cuda", dtype=torch.float64)])
+    ref = decay * A0 + (1 - decay) * (m @ m.t()) / m.shape[1]
+    # parts of at most 4096 terms, sums of at most 128 parts, 2^-22 a product, and an image's sums less those of its border lines
+    # and plus those of its corners (three times the sum of an image at most), three roundings of the running average
+    bound = 3 * (4096 + 128 + 4) * 2.0 ** -24 * (1 - decay) * (m.abs() @ m.abs().t()) / m.shape[1] + 2.0 ** -22 * A0.abs()
+    assert bool(((A.double() - ref).abs() <= bound).all())
+    assert bool((A == A.t()).all())
+
+
+# (N, c, h, w): K from two parts up; 5 x 5 planes of 49 (fp32: padded so that 4 divides them), last parts of a few positions
+@pytest.mark.parametrize("shape", [(21, 1, 5, 5), (60, 3, 5, 6), (5, 31, 17, 13), (3, 32, 28, 28), (4, 33, 19, 23), (2, 50, 32, 24),
+                                   (3, 63, 30, 31), (2, 64, 56, 56), (1, 64, 33, 35), (27, 64, 14, 14)])
+@pytest.mark.parametrize("dtype", [kfac.KFAC_F32, kfac.KFAC_BF16])
+@pytest.mark.parametrize("bias", [0, 1])
+def test_shapes(shape, dtype, bias):
+    N, c, h, w = shape
+    L = wl.Layer(N, c, 8, 3, 1, 1, h, w, bias)
+    gen = torch.Generator(device="cuda").manual_seed(sum(shape))
+    x = torch.randn(N, c, h, w, device="cuda", generator=gen).clamp_(min=0)
+    if dtype == kfac.KFAC_BF16:
+        x = x.bfloat16()
+    A, A0, together = _factor([L] * _times(L), dtype, [x] * _times(L))
+    assert together == 1
+    _check(L, x, A[0], A0[0])
+    _check(L, x, A[-1], A0[-1])
+
+
+def test_what_stays_apart():
+    """Contractions of one part, 65 channels, and fewer than 256 parts."""
+    for N, c, h, w, times in ((2, 64, 14, 14, 256), (4, 65, 28, 28, 40), (32, 64, 56, 56, 1), (4, 32, 30, 30, 31)):
+        L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
+        x = torch.randn(N, c, h, w, device="cuda").clamp_(min=0)
+        A, A0, together = _factor([L] * times, kfac.KFAC_F32, [x] * times)
+        assert together == 0
+        _check(L, x, A[-1], A0[-1])
+
+
+@pytest.mark.parametrize("dtype", [kfac.KFAC_F32, kfac.KFAC_BF16])
+@pytest.mark.parametrize("nhwc", [False, True])
+def test_several_layers(dtype, nhwc):
+    layers = [wl.Layer(6, 40, 8, 3, 1, 1, 28, 28, 1), wl.Layer(6, 64, 8, 3, 1, 1, 20, 22, 0), wl.Layer(6, 16, 8, 1, 1, 0, 9, 9, 1), wl.Layer(6, 5, 8, 3, 1, 1, 60, 17, 1)]
+    layers += 10 * layers            # 10 + 5 + 13 parts each time
+    xs = [torch.randn(L.N, L.c_in, L.h_in, L.w_in, device="cuda").clamp_(min=0) for L in layers]
+    if dtype == kfac.KFAC_BF16:
+        xs = [x.bfloat16() for x in xs]
+    acts = [x.permute(0, 2, 3, 1).contiguous() if nhwc else x for x in xs]
+    A, A0, together = _factor(layers, dtype, acts, nhwc=nhwc)
+    assert together == 1
+    for l, (L, x) in enumerate(zip(layers, xs)):
+        if L.k == 3:
+            _check(L, x, A[l], A0[l])
+
+
+@pytest.mark.parametrize("dtype", [kfac.KFAC_F32, kfac.KFAC_BF16])
+def test_long_parts(dtype):
+    """Parts of 4864 positions, in two chains."""
+    L = wl.Layer(100, 2, 8, 3, 1, 1, 60, 60, 1)
+    x = torch.randn(L.N, L.c_in, L.h_in, L.w_in, device="cuda").clamp_(min=0)
+    if dtype == kfac.KFAC_BF16:
+        x = x.bfloat16()
+    A, A0, together = _factor([L] * 3, dtype, [x] * 3)
+    assert together == 1
+    _check(L, x, A[0], A0[0])
+
+
+# signed: sums near zero, in doubt; dead: rows of zeros; half: too many of them; sparse: rows that sample as zero and are not; scales:
+# images of very different size; steep: a row that leaves the range of fp16; far: rows near the ends of fp32
+@pytest.mark.parametrize("kind", ["signed", "dead", "half", "sparse", "scales", "steep", "far", "zero"])
+@pytest.mark.parametrize("c", [20, 64])
+def test_values(kind, c):
+    N, h, w = 9, 24, 26
+    gen = torch.Generator(device="cuda").manual_seed(c)
+    x = torch.randn(N, c, h, w, device="cuda", generator=gen)
+    if kind != "signed":
+        x.clamp_(min=0)
+    if kind == "dead":
+        x[:, 3] = 0
+    elif kind == "half":
+        x[:, ::2] = 0
+    elif kind == "sparse":
+        x[:, 1] = 0
+        x[N - 1, 1, h - 1, 5] = 2.0
+        x[:, 7] *= (torch.rand(N, h, w, device="cuda", generator=gen) < 0.01)
+    elif kind == "scales":
+        x *= torch.exp(4 * torch.randn(N, 1, 1, 1, device="cuda", generator=gen))
+    elif kind == "steep":
+        x[4, 2, 11, 13] = 2.0 ** 30
+    elif kind == "far":
+        x[:, 2] *= 2.0 ** 50
+        x[:, 5] *= 2.0 ** -50
+    elif kind == "zero":
+        x.zero_()
+    L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
+    A, A0, together = _factor([L] * _times(L), kfac.KFAC_F32, [x] * _times(L))
+    assert together == 1
+    _check(L, x, A[0], A0[0])
+
+
+def test_infinities():
+    """Where an operand is infinite the products are not finite, the others are what they are without it."""
+    N, c, h, w = 9, 24, 24, 26
+    x = torch.randn(N, c, h, w, device="cuda").clamp_(min=0)
+    L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
+    whole, _, _ = _factor([L] * _times(L), kfac.KFAC_F32, [x] * _times(L))
+    x[3, 6, 10, 10] = float("inf")
+    A, _, together = _factor([L] * _times(L), kfac.KFAC_F32, [x] * _times(L))
+    assert together == 1
+    rows = torch.zeros(L.dA, dtype=torch.bool, device="cuda")
+    rows[6 * 9:7 * 9] = True
+    touched = rows[:, None] | rows[None, :]
+    assert not bool(torch.isfinite(A[0][touched]).any())
+    assert bool(torch.isfinite(A[0][~touched]).all())
+    assert bool(((A[0] - whole[0])[~touched].abs() <= 1e-5 * whole[0][~touched].abs() + 1e-6).all())
