@@ -249,6 +249,12 @@ hipError_t launch_pad_bf16(const PadJobBF16 *jobs_dev, int n_jobs, int total_wgs
 // round is read from the transposed copy the GEMM wrote alongside, so every read is along a
 // row of a Gram matrix and every write along the row of A (the interleaving of the nine k'
 // goes through LDS).
+//
+// What bounds it is the time of a workgroup, a chain of memory latencies (eight of them share a compute unit: 512 channels are 2.2
+// rounds).  So a thread issues all loads of a channel, nine products, up to seven corrections and the old elements of A, before it
+// waits for one, and the rows of a channel share an XCD.  512 channels in fp32 88 -> 73 us (222 MB, 3.0 TB/s), ResNet-50's 3x3
+// layers 130 -> 93 (with a branch and a wait per correction, and rows dealt out in order).  Sources from scalar registers instead of the
+// table are four levels of dependent loads: 110, and 64 channels 1 us more.
 struct CorrSource {
     Global<const float> full, row, col, corner;   // row / col / corner: null if no such correction
     int ld_full, ld_row, ld_col;
@@ -307,7 +313,10 @@ __global__ __launch_bounds__(256) void assemble_kernel(const AssembleJob *__rest
     }
     const AssembleJob &J = jobs[lo];
     const int d0 = 9 * J.C;
-    const int i = wg - J.wg_start;          // row of A
+    int i = wg - J.wg_start;                // row of A
+    // the nine rows of a channel, which read the same rows of the products, go to one XCD (as far as 8 divides the channels); not
+    // where the products fit an L2 and the launch is one round of latencies (64 channels: 10.2 us without, 11.1 with)
+    if (J.C >= 256 && i < J.C / 8 * 72) i = 9 * (i / 72 * 8 + (i & 7)) + (i / 8) % 9;
     const Global<float> out_row = global(J.A) + (long long)i * J.ldA;
     if (i < d0) {
         const int c = i / 9, k = i - 9 * c, ky = k / 3, kx = k - 3 * ky;
@@ -316,34 +325,49 @@ __global__ __launch_bounds__(256) void assemble_kernel(const AssembleJob *__rest
         __shared__ float vals[9][257];   // 256 channels c' at a time: [k'][c']
         if (threadIdx.x < 9) src[threadIdx.x] = corr_source(J, ky, kx, threadIdx.x / 3, threadIdx.x % 3);
         __syncthreads();
-        // Reads go along rows of the Gram matrices (consecutive threads, consecutive c'), writes along
-        // the row of A (consecutive threads, consecutive (c', k')); LDS does the interleaving.
         for (int cp0 = 0; cp0 < J.C; cp0 += 256) {
-            const int cp = cp0 + threadIdx.x;
+            const int cp = cp0 + threadIdx.x, nout = 9 * min(256, J.C - cp0);
+            const Global<float> dst = out_row + 9 * cp0;
+            float full[9], row[3], col[3], corner = 0.f;
+            v4 old[3];
+            if (cp < J.C) {
+#pragma unroll
+                for (int kp = 0; kp < 9; ++kp) full[kp] = src[kp].full[(long long)c * src[kp].ld_full + cp];
+                if (ky != 1)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) row[q] = src[3 * ky + q].row[(long long)c * src[3 * ky + q].ld_row + cp];
+                if (kx != 1)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) col[q] = src[3 * q + kx].col[(long long)c * src[3 * q + kx].ld_col + cp];
+                if (ky != 1 && kx != 1) corner = src[k].corner[(long long)c * J.ld_corner + cp];
+            }
+            if (J.beta != 0.f)
+#pragma unroll
+                for (int m = 0; m < 3; ++m) {
+                    const int e = 4 * threadIdx.x + 1024 * m;
+                    if (e + 3 < nout) old[m] = *(Global<const v4>)(dst + e);
+                }
             if (cp < J.C) {
 #pragma unroll
                 for (int kp = 0; kp < 9; ++kp) {
-                    const CorrSource S = src[kp];
-                    float v = S.full[(long long)c * S.ld_full + cp];
-                    if (S.row) v -= S.row[(long long)c * S.ld_row + cp];
-                    if (S.col) v -= S.col[(long long)c * S.ld_col + cp];
-                    if (S.corner) v += S.corner[(long long)c * J.ld_corner + cp];
+                    float v = full[kp];
+                    if (ky != 1 && kp / 3 == ky) v -= row[kp % 3];
+                    if (kx != 1 && kp % 3 == kx) v -= col[kp / 3];
+                    if (ky != 1 && kx != 1 && kp == k) v += corner;
                     vals[kp][threadIdx.x] = v;
                 }
             }
             __syncthreads();
-            const int nout = 9 * min(256, J.C - cp0);
-            const Global<float> dst = out_row + 9 * cp0;
-            for (int e = 4 * threadIdx.x; e < nout; e += 1024) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                const int e = 4 * threadIdx.x + 1024 * m;
                 if (e + 3 < nout) {
                     v4 r;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) r[q] = J.alpha * vals[(e + q) % 9][(e + q) / 9];
-                    if (J.beta != 0.f) {
-                        const v4 o = *(Global<const v4>)(dst + e);
+                    if (J.beta != 0.f)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) r[q] = fmaf(J.beta, o[q], r[q]);
-                    }
+                        for (int q = 0; q < 4; ++q) r[q] = fmaf(J.beta, old[m][q], r[q]);
                     *(Global<v4>)(dst + e) = r;
                 } else {
                     for (int q = 0; e + q < nout; ++q) corr_store(J, dst + e + q, vals[(e + q) % 9][(e + q) / 9]);
