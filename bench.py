@@ -245,7 +245,7 @@ def main():
     del pjob
     kernels = {}
     for e in entries:
-        name = e["kernel"] + ("_tile%s" % ("128", "64", "32_direct", "64_direct")[e["variant"]] if e["kernel"].startswith("gemm_f") or
+        name = e["kernel"] + ("_tile%s" % ("128", "64", "32_direct", "64_direct", "64_displaced")[e["variant"]] if e["kernel"].startswith("gemm_f") or
                               e["kernel"] == "gemm_bf16" else "")
         k = kernels.setdefault(name, {"launches": 0, "ms": 0.0, "flops": 0.0, "bytes": 0.0})
         k["launches"] += 1
