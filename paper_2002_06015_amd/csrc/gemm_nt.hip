@@ -2406,8 +2406,8 @@ struct DisplacedCursor {
     }
 };
 
-// Scales and floors of the 64 rows in [k0, k0 + klen), as half_scales makes them: 32 sampled elements of each for the floor.  False:
-// the two planes do not serve.
+// Scales and floors of the 64 rows in [k0, k0 + klen), klen > 16, as half_scales makes them: 32 sampled elements of each for the floor.
+// False: the two planes do not serve.
 __device__ __forceinline__ bool displaced_scales(const Operand &op, int k0, int klen, float *sc, int tid)
 {
     const int row = tid >> 2, kq = 4 * (tid & 3);
@@ -2489,7 +2489,8 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
     bool one_by_one = false;
     if constexpr (!BF16) {
         if (tid == 0) { doubts[0] = 0; *redo = 0; }
-        one_by_one = !displaced_scales(op, k0, k1 - k0, sc, tid);
+        // (the samples of a last part of up to one step, of any four positions more, would reach beyond it; see gemm_nt_f32_split_tile)
+        one_by_one = k1 - k0 <= KT || !displaced_scales(op, k0, k1 - k0, sc, tid);
         scale[0] = sc[row];
         scale[1] = sc[row + 32];
     }

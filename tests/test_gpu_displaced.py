@@ -1,5 +1,5 @@
 """The 13 displaced products of 3x3 convolutions of up to 64 channels, which share a launch: channel counts around the wavefronts'
-32 rows, planes that no step of the contraction divides, short last parts, several layers in one call, and values that lead
+32 rows, planes that no step of the contraction divides, last parts of a few positions, several layers in one call, and values that lead
 single products, or all of them, to the general kernel.  They do so where the split rule (512 positions to a part, 128 parts to a
 product) allows the images of a call 256 parts: a small layer stands in the list as often as that takes."""
 import pytest
@@ -14,13 +14,27 @@ def _times(L):
     return -(-256 // min(128, L.N * (L.h_in + 2) * (L.w_in + 2) // 512))
 
 
-def _factor(layers, dtype, acts, decay=0.75, nhwc=False):
+def _parts(L, times):
+    """Contraction length, length of a part and of the last part of an fp32 layer that stands `times` times in a list: the rule of
+    take_displaced (kfac_api.hip) over planes padded as plan_stats pads them."""
+    plane = min((L.h_in + a) * (L.w_in + b) for a in range(2, 6) for b in range(2, 6) if (L.h_in + a) * (L.w_in + b) % 4 == 0)
+    K = L.N * plane
+    most, share = max(-(-K // 4096), min(128, K // 512)), 256 // times
+    assert times * most >= 256
+    parts = min(most, max(2, -(-K // 8192), share // 8 * 8 if share >= 8 else share))
+    part = -(-(-(-K // parts)) // 32) * 32
+    return K, part, (K - 1) % part + 1
+
+
+def _factor(layers, dtype, acts, decay=0.75, nhwc=False, fill=None):
     gen = torch.Generator(device="cuda").manual_seed(len(layers))
     A = [torch.randn(L.dA, L.dA, device="cuda", generator=gen) for L in layers]
     A = [(a + a.t()).contiguous() for a in A]
     A0 = [a.double() for a in A]
     G = [torch.empty(L.dG, L.dG, device="cuda") for L in layers]
     ctx = kfac.Context(layers, dtype)
+    if fill is not None:
+        ctx.workspace.fill_(fill)
     kfac.kfac_profile_enable(ctx, True)
     kfac.kfac_stats(ctx, layers, dtype, acts, None, decay, True, A, G, nhwc=nhwc)
     torch.cuda.synchronize()
@@ -41,7 +55,7 @@ def _check(L, x, A, A0, decay=0.75):
     assert bool((A == A.t()).all())
 
 
-# (N, c, h, w): K from two parts up; 5 x 5 planes of 49 (fp32: padded so that 4 divides them), last parts of a few positions
+# (N, c, h, w): K from two parts up; 5 x 5 planes of 49 (fp32: padded so that 4 divides them)
 @pytest.mark.parametrize("shape", [(21, 1, 5, 5), (60, 3, 5, 6), (5, 31, 17, 13), (3, 32, 28, 28), (4, 33, 19, 23), (2, 50, 32, 24),
                                    (3, 63, 30, 31), (2, 64, 56, 56), (1, 64, 33, 35), (27, 64, 14, 14)])
 @pytest.mark.parametrize("dtype", [kfac.KFAC_F32, kfac.KFAC_BF16])
@@ -95,6 +109,26 @@ def test_long_parts(dtype):
     A, A0, together = _factor([L] * 3, dtype, [x] * 3)
     assert together == 1
     _check(L, x, A[0], A0[0])
+
+
+@pytest.mark.parametrize("shape,times,last", [((97, 64, 28, 28), 2, 4), ((97, 3, 28, 28), 2, 4), ((27, 33, 51, 51), 2, 12), ((59, 20, 28, 28), 3, 12),
+                                              ((27, 40, 40, 40), 4, 12), ((9, 50, 72, 72), 3, 4), ((43, 64, 28, 28), 6, 12), ((12, 17, 59, 61), 3, 32),
+                                              ((47, 6, 37, 37), 3, 8), ((9, 7, 47, 47), 6, 36)])
+def test_short_last_parts(shape, times, last):
+    """Too few positions to take samples from.  Nothing behind the image is read: the same bits whatever the workspace held."""
+    N, c, h, w = shape
+    L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
+    assert _parts(L, times)[2] == last
+    gen = torch.Generator(device="cuda").manual_seed(sum(shape))
+    x = torch.randn(N, c, h, w, device="cuda", generator=gen).clamp_(min=0)
+    bits = []
+    for fill in (0, 0x7f, 0xff):            # zeros, 3.4e38, NaN
+        A, A0, together = _factor([L] * times, kfac.KFAC_F32, [x] * times, fill=fill)
+        assert together == 1
+        bits.append(A)
+    _check(L, x, bits[0][0], A0[0])
+    for l in range(times):
+        assert torch.equal(bits[1][l], bits[0][l]) and torch.equal(bits[2][l], bits[0][l])
 
 
 # signed: sums near zero, in doubt; dead: rows of zeros; half: too many of them; sparse: rows that sample as zero and are not; scales:
