@@ -2406,9 +2406,11 @@ struct DisplacedCursor {
     }
 };
 
-// Scales and floors of the 64 rows in [k0, k0 + klen), klen > 16, as half_scales makes them: 32 sampled elements of each for the floor.
-// False: the two planes do not serve.
-__device__ __forceinline__ bool displaced_scales(const Operand &op, int k0, int klen, float *sc, int tid)
+// Scales and floors of the 64 rows, as half_scales makes them: 32 sampled elements of each for the floor.  Both sides of the products
+// share them, so they are those of [k0, k0 + klen), klen > 16: the rows' own part, which ends at k1, and what the displaced images
+// have behind it, up to 2 Wp + 2 positions (what is behind an image is zero there).  take_displaced keeps parts at least twice as long
+// as that, so that the samples are those of every displaced image.  False: the two planes do not serve.
+__device__ __forceinline__ bool displaced_scales(const Operand &op, int k0, int k1, int klen, float *sc, int tid)
 {
     const int row = tid >> 2, kq = 4 * (tid & 3);
     const Global<const char> base = global((const char *)op.base);
@@ -2444,15 +2446,20 @@ __device__ __forceinline__ bool displaced_scales(const Operand &op, int k0, int 
         for (int r = tid >> 6; r < 64; r += 4) {      // rows that sampled as zero are read on until an element is not
             if (sc[r] != 0.f) continue;
             float most = 0.f;
-            walk_row(op, r, k0, klen, tid & 63, [&](const auto &x) {
+            auto walk = [&](int from, int to) {
+                walk_row(op, r, from, to - from, tid & 63, [&](const auto &x) {
 #pragma unroll
-                for (const floatx4 &y : x) most = max_abs(most, y);
-                for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
-                return most != 0.f;
-            });
+                    for (const floatx4 &y : x) most = max_abs(most, y);
+                    for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
+                    return most != 0.f;
+                });
+                return most == 0.f;
+            };
+            const bool none = walk(k0, k1), none_behind = none && walk(k1, k0 + klen);
             if ((tid & 63) == 0) {
                 sc[r] = sc[64 + r] = half_scale(most, kHalfTop);
-                if (most == 0.f) sc[128 + r] = sc[192 + r] = kNoFloor;
+                if (none) sc[128 + r] = kNoFloor;              // as a row of its own part it is zero
+                if (none_behind) sc[192 + r] = kNoFloor;
             }
         }
         __syncthreads();
@@ -2490,7 +2497,8 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
     if constexpr (!BF16) {
         if (tid == 0) { doubts[0] = 0; *redo = 0; }
         // (the samples of a last part of up to one step, of any four positions more, would reach beyond it; see gemm_nt_f32_split_tile)
-        one_by_one = k1 - k0 <= KT || !displaced_scales(op, k0, k1 - k0, sc, tid);
+        const int to = min(Q->K, (k1 + (int)((base[DISP_TILES - 1] - base[0]) / ESIZE) + 3) & ~3);
+        one_by_one = k1 - k0 <= KT || !displaced_scales(op, k0, k1, to - k0, sc, tid);
         scale[0] = sc[row];
         scale[1] = sc[row + 32];
     }

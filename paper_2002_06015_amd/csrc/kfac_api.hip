@@ -373,28 +373,37 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
 //                      128 samples: three 984, 463
 //   fp32  32 channels, 32 samples: three 148, 119;  50 channels at 28 x 28, 27 samples: two 47, 69
 //   bf16  64 channels, 32 samples: one 45, 47; two 80, 70; three 145, 139.  64 samples: one 75, 69; three 377, 257
-void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> &sel, std::vector<GemmProblem> &displaced)
+// fp32: parts at least twice as long as the last displacement reaches (2 Wp + 2), for one scale of a row to serve all of them.
+void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> &sel, std::vector<GemmProblem> &displaced, bool fp32)
 {
     std::vector<GemmProblem> rest;
+    auto reach = [](const GemmProblem *P) { return (int)((const float *)P[12].b.base - (const float *)P[0].a.base); };
     // (a part may be twice as long as the rule's: its sums are chains of at most max_k_per_wg)
     auto least = [&](const GemmProblem &P) { return (P.K + 2 * tun.max_k_per_wg - 1) / (2 * tun.max_k_per_wg); };
-    auto most = [&](const GemmProblem &P) { return std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P.K / tun.min_k_per_split)); };
+    auto most = [&](const GemmProblem &P, int shortest) {
+        return std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P.K / std::max(shortest, tun.min_k_per_split)));
+    };
+    std::vector<int> at_most;
     double k_all = 0;
     int allowed = 0;
     for (size_t i = 0; i < sel.size(); ++i) {
-        bool together = (sel[i].flags & GEMM_DISPLACED) && i + 13 <= sel.size() && most(sel[i]) >= 2;
+        bool together = (sel[i].flags & GEMM_DISPLACED) && i + 13 <= sel.size();
+        const int shortest = together && fp32 ? 2 * reach(&sel[i]) : 0, parts = most(sel[i], shortest);
+        together = together && parts >= 2 && shortest <= tun.max_k_per_wg;
         for (size_t q = 1; together && q < 13; ++q) together = sel[i + q].a.base == sel[i].a.base && sel[i + q].K == sel[i].K;
         if (!together) { rest.push_back(sel[i]); continue; }
         displaced.insert(displaced.end(), sel.begin() + i, sel.begin() + i + 13);
         k_all += sel[i].K;
-        allowed += most(sel[i]);
+        allowed += parts;
+        at_most.push_back(parts);
         i += 12;
     }
     if (allowed < kDisplacedParts) { displaced.clear(); return; }
     sel = rest;
-    for (GemmProblem &P : displaced) {
+    for (size_t i = 0; i < displaced.size(); ++i) {
+        GemmProblem &P = displaced[i];
         const int share = (int)(kDisplacedParts * (double)P.K / k_all);
-        const int parts = std::min(most(P), std::max({2, least(P), share >= 8 ? share / 8 * 8 : share}));
+        const int parts = std::min(at_most[i / 13], std::max({2, least(P), share >= 8 ? share / 8 * 8 : share}));
         P.k_per_split = ((P.K + parts - 1) / parts + 31) / 32 * 32;
         P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
         P.partial = (float *)arena.take((size_t)P.splits * 64 * 64 * sizeof(float));
@@ -447,7 +456,7 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
         int align = 1;
         std::vector<GemmProblem> displaced;
         if (cfg == 1 && (dtype == 1 || (dtype == 0 && tun.split)) && !tun.chosen_rule && !tun.worst_case_splits)
-            take_displaced(arena, tun, sel, displaced);
+            take_displaced(arena, tun, sel, displaced, dtype == 0);
         if (cfg < 2) {
             // Per problem (independent of what else is in the launch, so that the workspace need of
             // a layer list does not depend on which of its inputs are present): enough splits for

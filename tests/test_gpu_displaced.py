@@ -14,12 +14,17 @@ def _times(L):
     return -(-256 // min(128, L.N * (L.h_in + 2) * (L.w_in + 2) // 512))
 
 
+def _padded(L):
+    """Lines and columns of an fp32 image's plane, as plan_stats pads it."""
+    return min(((L.h_in + a, L.w_in + b) for a in range(2, 6) for b in range(2, 6) if (L.h_in + a) * (L.w_in + b) % 4 == 0), key=lambda s: s[0] * s[1])
+
+
 def _parts(L, times):
     """Contraction length, length of a part and of the last part of an fp32 layer that stands `times` times in a list: the rule of
-    take_displaced (kfac_api.hip) over planes padded as plan_stats pads them."""
-    plane = min((L.h_in + a) * (L.w_in + b) for a in range(2, 6) for b in range(2, 6) if (L.h_in + a) * (L.w_in + b) % 4 == 0)
-    K = L.N * plane
-    most, share = max(-(-K // 4096), min(128, K // 512)), 256 // times
+    take_displaced (kfac_api.hip)."""
+    Hp, Wp = _padded(L)
+    K = L.N * Hp * Wp
+    most, share = max(-(-K // 4096), min(128, K // max(512, 4 * Wp + 4))), 256 // times
     assert times * most >= 256
     parts = min(most, max(2, -(-K // 8192), share // 8 * 8 if share >= 8 else share))
     part = -(-(-(-K // parts)) // 32) * 32
@@ -43,15 +48,17 @@ def _factor(layers, dtype, acts, decay=0.75, nhwc=False, fill=None):
     return A, A0, together
 
 
-def _check(L, x, A, A0, decay=0.75):
+def _check(L, x, A, A0, decay=0.75, terms=4096, rows=None):
+    """rows: only these, whose products have at most `terms` terms that are not zero."""
     m = torch.nn.functional.unfold(x.double(), 3, padding=1).permute(1, 0, 2).reshape(9 * L.c_in, -1)
     if L.bias:
         m = torch.cat([m, torch.ones(1, m.shape[1], device="cuda", dtype=torch.float64)])
     ref = decay * A0 + (1 - decay) * (m @ m.t()) / m.shape[1]
     # parts of at most 4096 terms, sums of at most 128 parts, 2^-22 a product, and an image's sums less those of its border lines
     # and plus those of its corners (three times the sum of an image at most), three roundings of the running average
-    bound = 3 * (4096 + 128 + 4) * 2.0 ** -24 * (1 - decay) * (m.abs() @ m.abs().t()) / m.shape[1] + 2.0 ** -22 * A0.abs()
-    assert bool(((A.double() - ref).abs() <= bound).all())
+    bound = 3 * (terms + 128 + 4) * 2.0 ** -24 * (1 - decay) * (m.abs() @ m.abs().t()) / m.shape[1] + 2.0 ** -22 * A0.abs()
+    rows = slice(None) if rows is None else slice(0, rows)
+    assert bool(((A.double() - ref).abs() <= bound)[rows].all())
     assert bool((A == A.t()).all())
 
 
@@ -129,6 +136,47 @@ def test_short_last_parts(shape, times, last):
     _check(L, x, bits[0][0], A0[0])
     for l in range(times):
         assert torch.equal(bits[1][l], bits[0][l]) and torch.equal(bits[2][l], bits[0][l])
+
+
+# (values that fp16 loses without a scale of their own, beside others of all sizes; more such rows than single products are spared for)
+@pytest.mark.parametrize("value", [2.0 ** -60, 2.0 ** -30, 1e-4, 3e5])
+@pytest.mark.parametrize("rows", [1, 10, 40])
+@pytest.mark.parametrize("other", [1.0, 2.0 ** -40])
+def test_rows_that_begin_behind_a_part(value, rows, other):
+    """Channels that are zero all through a part of the contraction and not just behind it: the displaced products of the part
+    meet elements that the image itself has in the next one only."""
+    N, c, h, w, times = 32, 64, 40, 38, 3
+    L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
+    K, part, _ = _parts(L, times)
+    Hp, Wp = _padded(L)
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    x = other * torch.randn(N, c, h, w, device="cuda", generator=gen).clamp_(min=0)
+    x[:, :rows] = 0
+    found = 0
+    for p in range(1, K // part):
+        n, at = divmod(p * part, Hp * Wp)
+        y, at = at // Wp - (Hp - h), at % Wp - (Wp - w)      # first position of the part, in the image
+        if 1 <= y < h and 0 <= at < w - 6:
+            x[n, :rows, y, at:at + 6] = value * (1 + torch.rand(rows, 6, device="cuda", generator=gen))
+            found += 1
+    assert found > 10
+    A, A0, together = _factor([L] * times, kfac.KFAC_F32, [x] * times, decay=0.0)
+    assert together == 1
+    _check(L, x, A[0], A0[0], decay=0.0)
+    _check(L, x, A[0], A0[0], decay=0.0, terms=6 * found, rows=9 * rows)
+
+
+@pytest.mark.parametrize("shape,times,expected", [((3, 20, 12, 300), 30, 1), ((4, 64, 30, 1000), 8, 1), ((3, 5, 8, 1100), 40, 0), ((2, 40, 200, 210), 8, 1)])
+def test_wide_images(shape, times, expected):
+    """The displaced images reach hundreds of positions behind a part: parts at least twice as long, or products of their own."""
+    N, c, h, w = shape
+    L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
+    gen = torch.Generator(device="cuda").manual_seed(sum(shape))
+    x = torch.randn(N, c, h, w, device="cuda", generator=gen).clamp_(min=0)
+    x *= torch.exp(4 * torch.randn(N, 1, h, 1, device="cuda", generator=gen))
+    A, A0, together = _factor([L] * times, kfac.KFAC_F32, [x] * times)
+    assert together == expected
+    _check(L, x, A[0], A0[0])
 
 
 # signed: sums near zero, in doubt; dead: rows of zeros; half: too many of them; sparse: rows that sample as zero and are not; scales:
