@@ -2373,11 +2373,9 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_trans_kernel(const GemmProbl
 // A thread loads and stores 16 bytes of two rows of every staged tile: the tiles differ by a uniform base address only.  (The planes
 // of a padded image have at least 28 positions in fp32 and 40 in bf16, so that a step wraps twice at most.)
 constexpr int DISP_TILES = 7, DISP_TILE_BYTES = 8192, DISP_STAGE = DISP_TILES * DISP_TILE_BYTES;
-constexpr size_t displaced_lds_bytes()
-{
-    const size_t own = DISP_STAGE + (2 * 128 + 2 + 1 + kMaxDoubts + 1) * sizeof(float), one_by_one = split_lds_bytes<1, 1>();
-    return own > one_by_one ? own : one_by_one;
-}
+constexpr int DISP_SCALES = DISP_STAGE / 4, DISP_DOUBTS = DISP_SCALES + 256, DISP_REDO = DISP_DOUBTS + DISP_TILES * (1 + kMaxDoubts);   // in LDS, words
+constexpr size_t displaced_lds_bytes() { return (DISP_REDO + 1) * sizeof(float); }
+static_assert(split_lds_bytes<1, 1>() <= DISP_STAGE, "single products leave the lists of sums in doubt as they are");
 
 // Position of a thread's chunk in the contraction.
 struct DisplacedCursor {
@@ -2473,8 +2471,8 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
     constexpr int KS = BF16 ? 64 : 32, CHUNK = KS / 8, ESIZE = BF16 ? 2 : 4;   // positions a step, a thread's chunk
     extern __shared__ __attribute__((aligned(16))) float lds[];
     char *stage = (char *)lds;
-    float *sc = lds + DISP_STAGE / 4;
-    int *doubts = (int *)(sc + 258), *redo = doubts + 1 + kMaxDoubts;
+    float *sc = lds + DISP_SCALES;
+    int *doubts = (int *)lds + DISP_DOUBTS, *redo = (int *)lds + DISP_REDO;   // doubts: a list for each product
     const int wg = blockIdx.x, g = find_problem(start, n_groups, wg), local = wg - start[g];
     const GemmProblem *Q = probs + 13 * g;
     const Operand op = Q->a;
@@ -2495,7 +2493,8 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
     float scale[2] = {1.f, 1.f};
     bool one_by_one = false;
     if constexpr (!BF16) {
-        if (tid == 0) { doubts[0] = 0; *redo = 0; }
+        if (tid < DISP_TILES) doubts[tid * (1 + kMaxDoubts)] = 0;
+        if (tid == 0) *redo = 0;
         // (the samples of a last part of up to one step, of any four positions more, would reach beyond it; see gemm_nt_f32_split_tile)
         const int to = min(Q->K, (k1 + (int)((base[DISP_TILES - 1] - base[0]) / ESIZE) + 3) & ~3);
         one_by_one = k1 - k0 <= KT || !displaced_scales(op, k0, k1, to - k0, sc, tid);
@@ -2639,7 +2638,7 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
                 for (int v = 0; v < 16; ++v) acc[j][v] += part[at_row(v)];
             floatx16 one[1][1] = {{acc[j]}};
             if constexpr (!BF16) {
-                if (half_doubts<1, 1>(one, sc, doubts, wave_m, wave_n, l32, half)) again |= 1u << j;
+                if (half_doubts<1, 1>(one, sc, doubts + j * (1 + kMaxDoubts), wave_m, wave_n, l32, half) & 2) again |= 1u << j;
                 half_unscale_tile<1, 1>(one, sc, wave_m, wave_n, l32, half);
             }
 #pragma unroll
@@ -2653,14 +2652,20 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
         *redo = (1 << DISP_TILES) - 1;
     }
     if constexpr (!BF16) {
-        // where sums are in doubt or not finite, or the two planes do not serve: as products of their own
+        // where sums are not finite, many are in doubt (the limit of gemm_nt_f32_split_tile), or the two planes do not serve: as products
+        // of their own, one after the other; a few sums in doubt (of rows of random sign, one product in fourteen has some) by themselves
         __syncthreads();
         const int again = *redo;
-        __syncthreads();
         for (int j = second; j < DISP_TILES; ++j) {
-            if (!((again >> j) & 1)) continue;
-            gemm_nt_f32_split_tile<1, 1>(Q[j == 0 ? 0 : 6 * second + j], 0, split, true, lds);
-            __syncthreads();
+            const GemmProblem &P = Q[j == 0 ? 0 : 6 * second + j];
+            const int *list = doubts + j * (1 + kMaxDoubts);
+            const int n = one_by_one ? 0 : list[0];
+            if (((again >> j) & 1) || n > min(kMaxDoubts, 24 + (k1 - k0) / 32)) {
+                __syncthreads();
+                gemm_nt_f32_split_tile<1, 1>(P, 0, split, true, lds);
+            } else if (n) {
+                half_settle<64, 64>(P, list, n, 0, 0, k0, k1, tid, global(P.partial) + (long long)split * 4096, 64);
+            }
         }
     }
 }
