@@ -380,22 +380,23 @@ void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> 
     auto reach = [](const GemmProblem *P) { return (int)((const float *)P[12].b.base - (const float *)P[0].a.base); };
     // (a part may be twice as long as the rule's: its sums are chains of at most max_k_per_wg)
     auto least = [&](const GemmProblem &P) { return (P.K + 2 * tun.max_k_per_wg - 1) / (2 * tun.max_k_per_wg); };
-    auto most = [&](const GemmProblem &P, int shortest) {
-        return std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P.K / std::max(shortest, tun.min_k_per_split)));
+    auto most = [&](const GemmProblem &P, int least_k) {
+        return std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P.K / std::max(least_k, tun.min_k_per_split)));
     };
-    std::vector<int> at_most;
+    std::vector<int> at_most, shortest;
     double k_all = 0;
     int allowed = 0;
     for (size_t i = 0; i < sel.size(); ++i) {
         bool together = (sel[i].flags & GEMM_DISPLACED) && i + 13 <= sel.size();
-        const int shortest = together && fp32 ? 2 * reach(&sel[i]) : 0, parts = most(sel[i], shortest);
-        together = together && parts >= 2 && shortest <= tun.max_k_per_wg;
+        const int least_k = together && fp32 ? 2 * reach(&sel[i]) : 0, parts = most(sel[i], least_k);
+        together = together && parts >= 2 && least_k <= tun.max_k_per_wg;
         for (size_t q = 1; together && q < 13; ++q) together = sel[i + q].a.base == sel[i].a.base && sel[i + q].K == sel[i].K;
         if (!together) { rest.push_back(sel[i]); continue; }
         displaced.insert(displaced.end(), sel.begin() + i, sel.begin() + i + 13);
         k_all += sel[i].K;
         allowed += parts;
         at_most.push_back(parts);
+        shortest.push_back(least_k);
         i += 12;
     }
     if (allowed < kDisplacedParts) { displaced.clear(); return; }
@@ -405,6 +406,11 @@ void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> 
         const int share = (int)(kDisplacedParts * (double)P.K / k_all);
         const int parts = std::min(at_most[i / 13], std::max({2, least(P), share >= 8 ? share / 8 * 8 : share}));
         P.k_per_split = ((P.K + parts - 1) / parts + 31) / 32 * 32;
+        // (fp32: the last part one and a half times as long, or a single step: in a shorter one the last displaced images have hardly a
+        // position before they end, and nearly all sums come out in doubt.  50 channels at 32 x 24, 27 samples, 8 images 439 us with a
+        // last part of 60 positions, 190 without)
+        auto last = [&]() { return (P.K - 1) % P.k_per_split + 1; };
+        while (last() > 32 && last() < shortest[i / 13] / 4 * 3) P.k_per_split += 32;
         P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
         P.partial = (float *)arena.take((size_t)P.splits * 64 * 64 * sizeof(float));
         if (P.flags & GEMM_BORDER) P.partial_rs = (float *)arena.take((size_t)P.splits * 64 * sizeof(float));

@@ -28,6 +28,8 @@ def _parts(L, times):
     assert times * most >= 256
     parts = min(most, max(2, -(-K // 8192), share // 8 * 8 if share >= 8 else share))
     part = -(-(-(-K // parts)) // 32) * 32
+    while 32 < (K - 1) % part + 1 < 3 * Wp + 3:
+        part += 32
     return K, part, (K - 1) % part + 1
 
 
@@ -120,9 +122,10 @@ def test_long_parts(dtype):
 
 @pytest.mark.parametrize("shape,times,last", [((97, 64, 28, 28), 2, 4), ((97, 3, 28, 28), 2, 4), ((27, 33, 51, 51), 2, 12), ((59, 20, 28, 28), 3, 12),
                                               ((27, 40, 40, 40), 4, 12), ((9, 50, 72, 72), 3, 4), ((43, 64, 28, 28), 6, 12), ((12, 17, 59, 61), 3, 32),
-                                              ((47, 6, 37, 37), 3, 8), ((9, 7, 47, 47), 6, 36)])
+                                              ((47, 6, 37, 37), 3, 8), ((9, 7, 47, 47), 6, 4), ((27, 50, 32, 24), 8, 668)])
 def test_short_last_parts(shape, times, last):
-    """Too few positions to take samples from.  Nothing behind the image is read: the same bits whatever the workspace held."""
+    """Too few positions to take samples from; and lengths behind those that parts are lengthened to avoid.  Nothing behind the image is
+    read: the same bits whatever the workspace held."""
     N, c, h, w = shape
     L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
     assert _parts(L, times)[2] == last
