@@ -2473,11 +2473,12 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
     char *stage = (char *)lds;
     float *sc = lds + DISP_SCALES;
     int *doubts = (int *)lds + DISP_DOUBTS, *redo = (int *)lds + DISP_REDO;   // doubts: a list for each product
-    const int wg = blockIdx.x, g = find_problem(start, n_groups, wg), local = wg - start[g];
+    // the parts of all images in a row, start[]: each image's first (two workgroups of a part on the same XCD, as many parts on each)
+    const int wg = blockIdx.x, second = (wg >> 3) & 1, part_of_all = (wg & 7) + 8 * (wg >> 4);
+    if (part_of_all >= start[n_groups]) return;
+    const int g = find_problem(start, n_groups, part_of_all), split = part_of_all - start[g];
     const GemmProblem *Q = probs + 13 * g;
     const Operand op = Q->a;
-    const int second = (local >> 3) & 1, split = (local & 7) + 8 * (local >> 4);   // (workgroups of a part: the same XCD)
-    if (split >= Q->splits) return;
     const int k0 = split * Q->k_per_split, k1 = min(Q->K, k0 + Q->k_per_split);
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wave_m = wid >> 1, wave_n = wid & 1, l32 = lane & 31, half = lane >> 5;

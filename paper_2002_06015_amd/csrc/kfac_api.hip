@@ -314,7 +314,7 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
     if (sel.empty()) return;
     const int B = tile_edge(cfg);
     std::vector<int> start(sel.size() - displaced + 1, 0), rstart(sel.size() + 1, 0), dstart(displaced / 13 + 1, 0);
-    for (size_t g = 0; g < displaced / 13; ++g) dstart[g + 1] = dstart[g] + (sel[13 * g].splits + 7) / 8 * 16;
+    for (size_t g = 0; g < displaced / 13; ++g) dstart[g + 1] = dstart[g] + sel[13 * g].splits;
     bool any_split = false;
     for (size_t i = 0; i < sel.size(); ++i) {
         const GemmProblem &P = sel[i];
@@ -324,7 +324,7 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
         any_split |= P.splits > 1;
     }
     const size_t off = plan.tab.add(sel.data(), sel.size() * sizeof(GemmProblem));
-    auto matrix_launch = [&](size_t first, size_t last, const std::vector<int> &at, int kernel) {
+    auto matrix_launch = [&](size_t first, size_t last, const std::vector<int> &at, int kernel, int wgs) {
         if (first == last) return;
         Launch L{};
         L.kind = L_GEMM;
@@ -341,13 +341,13 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
         L.off_a = off + first * sizeof(GemmProblem);
         L.off_b = plan.tab.add(at.data(), at.size() * sizeof(int));
         L.n = (int)at.size() - 1;
-        L.total_wgs = at.back();
+        L.total_wgs = wgs;
         L.cfg = kernel;
         L.dtype = (dtype == 0 && tun.split) ? 2 : dtype;
         plan.launches.push_back(L);
     };
-    matrix_launch(0, displaced, dstart, kDisplacedCfg);
-    matrix_launch(displaced, sel.size(), start, cfg);
+    matrix_launch(0, displaced, dstart, kDisplacedCfg, (dstart.back() + 7) / 8 * 16);   // (two a part)
+    matrix_launch(displaced, sel.size(), start, cfg, start.back());
     if (any_split) {
         Launch R{};
         R.kind = L_REDUCE;
@@ -363,9 +363,10 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
 }
 
 // Takes the displaced products of images of up to 64 channels out of `sel` and splits them for gemm_displaced_kernel: into at most
-// 256 parts in all (two workgroups each, two to a compute unit), a multiple of 8 of each image (an XCD more of them than its 64
-// slots hold is a second round: 85 parts of three images 242 us, 80 132), within the limits of the split rule, which are those of the
-// workspace bound.
+// 256 parts in all (two workgroups each, two to a compute unit; one workgroup more is a second round), or, where these would be longer
+// than twice the split rule's (the sums are chains of its length), into as many for each of several rounds; of each image at most as
+// many as the split rule allows, which is what the workspace bound counts.  (Seven images of 6 channels at 105 x 105, 26 samples, fp32:
+// 259 parts 948 us (as single products 705), 504 parts 580.)
 // The rule: where the split rule allows the images 256 parts together.  With fewer (one image, or short contractions) a compute
 // unit holds one workgroup, which waits for its own loads; that, a launch more and no gain in the lines and corners make it the
 // slower way.  Products of one layer each at 56 x 56, together with those of its lines and corners, one by one against this way:
@@ -378,8 +379,6 @@ void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> 
 {
     std::vector<GemmProblem> rest;
     auto reach = [](const GemmProblem *P) { return (int)((const float *)P[12].b.base - (const float *)P[0].a.base); };
-    // (a part may be twice as long as the rule's: its sums are chains of at most max_k_per_wg)
-    auto least = [&](const GemmProblem &P) { return (P.K + 2 * tun.max_k_per_wg - 1) / (2 * tun.max_k_per_wg); };
     auto most = [&](const GemmProblem &P, int least_k) {
         return std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P.K / std::max(least_k, tun.min_k_per_split)));
     };
@@ -401,10 +400,10 @@ void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> 
     }
     if (allowed < kDisplacedParts) { displaced.clear(); return; }
     sel = rest;
+    const double all_parts = kDisplacedParts * std::ceil(k_all / (2.0 * tun.max_k_per_wg * kDisplacedParts));
     for (size_t i = 0; i < displaced.size(); ++i) {
         GemmProblem &P = displaced[i];
-        const int share = (int)(kDisplacedParts * (double)P.K / k_all);
-        const int parts = std::min(at_most[i / 13], std::max({2, least(P), share >= 8 ? share / 8 * 8 : share}));
+        const int parts = std::min(at_most[i / 13], std::max(2, (int)(all_parts * P.K / k_all)));
         P.k_per_split = ((P.K + parts - 1) / parts + 31) / 32 * 32;
         // (fp32: the last part one and a half times as long, or a single step: in a shorter one the last displaced images have hardly a
         // position before they end, and nearly all sums come out in doubt.  50 channels at 32 x 24, 27 samples, 8 images 439 us with a
