@@ -374,46 +374,61 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
 //                      128 samples: three 984, 463
 //   fp32  32 channels, 32 samples: three 148, 119;  50 channels at 28 x 28, 27 samples: two 47, 69
 //   bf16  64 channels, 32 samples: one 45, 47; two 80, 70; three 145, 139.  64 samples: one 75, 69; three 377, 257
+// bf16 with more than 32 channels: where the parts have at least 900 positions and 13 lines.  Shorter ones, and lines that long, wait for
+// the six displaced lines of a step from beyond the caches that single products keep busy.  112 x 112, 8 samples, 64 channels: two images
+// 133 us one by one against 152 (7 lines a part), three 218, 243 (11), five 399, 367 (18); 79 x 79, 11 samples, 58 channels: three 167,
+// 184 (10); 100 x 44, 10 samples, 49 channels: three 120, 131 (576 positions).
 // fp32: parts at least twice as long as the last displacement reaches (2 Wp + 2), for one scale of a row to serve all of them.
 void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> &sel, std::vector<GemmProblem> &displaced, bool fp32)
 {
-    std::vector<GemmProblem> rest;
-    auto reach = [](const GemmProblem *P) { return (int)((const float *)P[12].b.base - (const float *)P[0].a.base); };
-    auto most = [&](const GemmProblem &P, int least_k) {
-        return std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P.K / std::max(least_k, tun.min_k_per_split)));
-    };
-    std::vector<int> at_most, shortest;
+    struct Image { size_t at; int line, parts, shortest; };   // its first product; length of a line; most parts; least of a part
+    std::vector<Image> images;
     double k_all = 0;
-    int allowed = 0;
-    for (size_t i = 0; i < sel.size(); ++i) {
-        bool together = (sel[i].flags & GEMM_DISPLACED) && i + 13 <= sel.size();
-        const int least_k = together && fp32 ? 2 * reach(&sel[i]) : 0, parts = most(sel[i], least_k);
-        together = together && parts >= 2 && least_k <= tun.max_k_per_wg;
-        for (size_t q = 1; together && q < 13; ++q) together = sel[i + q].a.base == sel[i].a.base && sel[i + q].K == sel[i].K;
-        if (!together) { rest.push_back(sel[i]); continue; }
-        displaced.insert(displaced.end(), sel.begin() + i, sel.begin() + i + 13);
-        k_all += sel[i].K;
-        allowed += parts;
-        at_most.push_back(parts);
-        shortest.push_back(least_k);
+    for (size_t i = 0; i + 13 <= sel.size(); ++i) {
+        const GemmProblem *P = &sel[i];
+        bool together = (P->flags & GEMM_DISPLACED) != 0;
+        for (size_t q = 1; together && q < 13; ++q) together = P[q].a.base == P->a.base && P[q].K == P->K;
+        if (!together) continue;
+        const int line = (int)(((const char *)P[5].b.base - (const char *)P->b.base) / (fp32 ? 4 : 2));   // (displaced by (1, 0))
+        const int shortest = fp32 ? 2 * (2 * line + 2) : 0;
+        const int parts = std::max((P->K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, std::min(tun.target_wgs, P->K / std::max(shortest, tun.min_k_per_split)));
+        if (parts >= 2 && shortest <= tun.max_k_per_wg) {
+            images.push_back({i, line, parts, shortest});
+            k_all += P->K;
+        }
         i += 12;
     }
-    if (allowed < kDisplacedParts) { displaced.clear(); return; }
-    sel = rest;
+    if (!fp32)
+        images.erase(std::remove_if(images.begin(), images.end(), [&](const Image &m) {
+            return sel[m.at].M > 32 && k_all < (double)kDisplacedParts * std::max(900, 13 * m.line);
+        }), images.end());
+    int allowed = 0;
+    k_all = 0;
+    for (const Image &m : images) { allowed += m.parts; k_all += sel[m.at].K; }
+    if (allowed < kDisplacedParts) return;
     const double all_parts = kDisplacedParts * std::ceil(k_all / (2.0 * tun.max_k_per_wg * kDisplacedParts));
-    for (size_t i = 0; i < displaced.size(); ++i) {
-        GemmProblem &P = displaced[i];
-        const int parts = std::min(at_most[i / 13], std::max(2, (int)(all_parts * P.K / k_all)));
-        P.k_per_split = ((P.K + parts - 1) / parts + 31) / 32 * 32;
-        // (fp32: the last part one and a half times as long, or a single step: in a shorter one the last displaced images have hardly a
-        // position before they end, and nearly all sums come out in doubt.  50 channels at 32 x 24, 27 samples, 8 images 439 us with a
-        // last part of 60 positions, 190 without)
-        auto last = [&]() { return (P.K - 1) % P.k_per_split + 1; };
-        while (last() > 32 && last() < shortest[i / 13] / 4 * 3) P.k_per_split += 32;
-        P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
-        P.partial = (float *)arena.take((size_t)P.splits * 64 * 64 * sizeof(float));
-        if (P.flags & GEMM_BORDER) P.partial_rs = (float *)arena.take((size_t)P.splits * 64 * sizeof(float));
+    std::vector<GemmProblem> rest;
+    size_t next = 0;
+    for (const Image &m : images) {
+        rest.insert(rest.end(), sel.begin() + next, sel.begin() + m.at);
+        next = m.at + 13;
+        for (size_t q = 0; q < 13; ++q) {
+            GemmProblem P = sel[m.at + q];
+            const int parts = std::min(m.parts, std::max(2, (int)(all_parts * P.K / k_all)));
+            P.k_per_split = ((P.K + parts - 1) / parts + 31) / 32 * 32;
+            // (fp32: the last part one and a half times as long, or a single step: in a shorter one the last displaced images have hardly a
+            // position before they end, and nearly all sums come out in doubt.  50 channels at 32 x 24, 27 samples, 8 images 439 us with a
+            // last part of 60 positions, 190 without)
+            auto last = [&]() { return (P.K - 1) % P.k_per_split + 1; };
+            while (last() > 32 && last() < m.shortest / 4 * 3) P.k_per_split += 32;
+            P.splits = (P.K + P.k_per_split - 1) / P.k_per_split;
+            P.partial = (float *)arena.take((size_t)P.splits * 64 * 64 * sizeof(float));
+            if (P.flags & GEMM_BORDER) P.partial_rs = (float *)arena.take((size_t)P.splits * 64 * sizeof(float));
+            displaced.push_back(P);
+        }
     }
+    rest.insert(rest.end(), sel.begin() + next, sel.end());
+    sel = rest;
 }
 
 // Emits the launches of one phase by the split rule (factor products; all products where a caller chose the rule): per tile

@@ -1,7 +1,8 @@
 """The 13 displaced products of 3x3 convolutions of up to 64 channels, which share a launch: channel counts around the wavefronts'
 32 rows, planes that no step of the contraction divides, last parts of a few positions, several layers in one call, and values that lead
 single products, or all of them, to the general kernel.  They do so where the split rule (512 positions to a part, 128 parts to a
-product) allows the images of a call 256 parts: a small layer stands in the list as often as that takes."""
+product) allows the images of a call 256 parts, and, with more than 32 channels in bf16, where these are long: a small layer stands in
+the list as often as that takes."""
 import pytest
 import torch
 
@@ -10,8 +11,11 @@ from paper_2002_06015_amd import kfac, workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-def _times(L):
-    return -(-256 // min(128, L.N * (L.h_in + 2) * (L.w_in + 2) // 512))
+def _times(L, dtype=kfac.KFAC_F32):
+    line = -(-(L.w_in + 2) // 8) * 8                    # of a bf16 plane
+    K = L.N * (L.h_in + 2) * line
+    long = -(-256 * max(900, 13 * line) // K) if dtype == kfac.KFAC_BF16 and L.c_in > 32 else 0
+    return max(-(-256 // min(128, L.N * (L.h_in + 2) * (L.w_in + 2) // 512)), long)
 
 
 def _padded(L):
@@ -76,7 +80,8 @@ def test_shapes(shape, dtype, bias):
     x = torch.randn(N, c, h, w, device="cuda", generator=gen).clamp_(min=0)
     if dtype == kfac.KFAC_BF16:
         x = x.bfloat16()
-    A, A0, together = _factor([L] * _times(L), dtype, [x] * _times(L))
+    times = _times(L, dtype)
+    A, A0, together = _factor([L] * times, dtype, [x] * times)
     assert together == 1
     _check(L, x, A[0], A0[0])
     _check(L, x, A[-1], A0[-1])
@@ -90,13 +95,17 @@ def test_what_stays_apart():
         A, A0, together = _factor([L] * times, kfac.KFAC_F32, [x] * times)
         assert together == 0
         _check(L, x, A[-1], A0[-1])
+    L = wl.Layer(8, 64, 8, 3, 1, 1, 112, 112, 1)         # bf16: short parts of many channels
+    x = torch.randn(8, 64, 112, 112, device="cuda").clamp_(min=0).bfloat16()
+    assert _factor([L] * 3, kfac.KFAC_BF16, [x] * 3)[2] == 0
+    assert _factor([L] * 4, kfac.KFAC_BF16, [x] * 4)[2] == 1
 
 
 @pytest.mark.parametrize("dtype", [kfac.KFAC_F32, kfac.KFAC_BF16])
 @pytest.mark.parametrize("nhwc", [False, True])
 def test_several_layers(dtype, nhwc):
     layers = [wl.Layer(6, 40, 8, 3, 1, 1, 28, 28, 1), wl.Layer(6, 64, 8, 3, 1, 1, 20, 22, 0), wl.Layer(6, 16, 8, 1, 1, 0, 9, 9, 1), wl.Layer(6, 5, 8, 3, 1, 1, 60, 17, 1)]
-    layers += 10 * layers            # 10 + 5 + 13 parts each time
+    layers += 15 * layers            # at most 10 + 5 + 13 parts each time
     xs = [torch.randn(L.N, L.c_in, L.h_in, L.w_in, device="cuda").clamp_(min=0) for L in layers]
     if dtype == kfac.KFAC_BF16:
         xs = [x.bfloat16() for x in xs]
@@ -110,7 +119,7 @@ def test_several_layers(dtype, nhwc):
 
 @pytest.mark.parametrize("dtype", [kfac.KFAC_F32, kfac.KFAC_BF16])
 def test_long_parts(dtype):
-    """Parts of 4864 positions, in two chains."""
+    """Parts of more than 4096 positions, in two chains."""
     L = wl.Layer(100, 2, 8, 3, 1, 1, 60, 60, 1)
     x = torch.randn(L.N, L.c_in, L.h_in, L.w_in, device="cuda").clamp_(min=0)
     if dtype == kfac.KFAC_BF16:
