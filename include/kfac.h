@@ -94,7 +94,8 @@ typedef struct kfac_ctx kfac_ctx;
 typedef enum {
     KFAC_PRODUCTS_SPLIT_BF16 = 0, /* fp32 operands split into two fp16 or three bf16 planes, three or six matrix
                                      instructions per block product, fp32 accumulation (default) */
-    KFAC_PRODUCTS_FP32_MFMA = 1   /* the fp32 matrix instruction */
+    KFAC_PRODUCTS_FP32_MFMA = 1   /* the fp32 matrix instruction; inverses of up to 288 rows, and those that larger ones
+                                     start from, go through planes here too */
 } kfac_products;
 
 typedef struct {

@@ -261,8 +261,11 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s)
 // scales that are exact: a panel block and D take the power of two that brings their largest element to [2^14, 2^15), P_v one per
 // row (a lane).  Nothing overflows, and elements down to 2^-16 of the largest of their block lose nothing.  The sum of a product
 // is scaled back into the tile with one fma, so a tile is rounded once per step (six times as the accumulator of bf16 planes):
-// inverses of 10 to 288 rows err 0.66 of what they did, those of 289 to 4609 rows 0.52 (128 and 87 factors of random layers);
-// rows that are nearly parallel lose: pairs correlated by 0.9995 2.9e-3 against 1.2e-3 at 288 rows, 0.95^|i-j| 0.9 of before.
+// inverses of 5 to 288 rows err 0.65 of what they did with three bf16 planes, those of 289 to 4609 rows 0.52 (127 and 87 factors of
+// random layers).  P also takes the product of the low planes (two instructions a step more, 36 before; 0.5 us at n = 288): where rows
+// are nearly parallel D is large and its products with R cancel, and what that product leaves out does not.  Pairs correlated by 0.9995,
+// 288 rows: 1.0e-3 with it, 2.9e-3 without, 1.2e-3 with three bf16 planes; 0.95^|i-j| 1.7e-5, 3.1e-5, 3.4e-5; patches of smooth
+// images 2.6e-5, 5.1e-5, 4.5e-5; 0.999^|i-j| 0.21, 0.49, 0.21.
 //
 // n = 288: 40.9 us (51.8 with fifteen wavefronts, three bf16 planes and an address per element), 224: 29.6 (35.9), 160: 20.0
 // (23.4), 64: 11.2 (11.2).  In-kernel cycles at n = 288: loads and scales 8400, a step 7650, stores 9000.  Of a step, the chain
@@ -323,12 +326,17 @@ __device__ __forceinline__ LbFrag lb_split8(const lb_floatx16 &t, int u, float s
     split_half_pair(t[8 * u + 6], t[8 * u + 7], scale, h.w, l.w);
     return {__builtin_bit_cast(halfx8, h), __builtin_bit_cast(halfx8, l)};
 }
-// product of two blocks (fragments of both 16-wide steps), the small terms first
+// product of two blocks (fragments of both 16-wide steps), the small terms first; FOUR: with the product of the low planes
+template <bool FOUR>
 __device__ __forceinline__ lb_floatx16 lb_mma(const LbFrag (&a)[2], const LbFrag (&b)[2])
 {
     lb_floatx16 c;
 #pragma unroll
     for (int q = 0; q < 16; ++q) c[q] = 0.f;
+    if constexpr (FOUR) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0].l, b[0].l, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1].l, b[1].l, c, 0, 0, 0);
+    }
     c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0].l, b[0].h, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0].h, b[0].l, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1].l, b[1].h, c, 0, 0, 0);
@@ -655,10 +663,10 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
 #pragma unroll
                 for (int e = 0; e < 4; ++e) t[4 * g + e] = x[e];
             }
-            const lb_floatx16 p = lb_mma(d, r);      // P^T = D R^T
+            const lb_floatx16 p = lb_mma<true>(d, r);      // P^T = D R^T
             const float scale = half_scale(__uint_as_float(lb_max_halves(__float_as_uint(lb_max_abs(p)))), LB_TOP), un = lb_reciprocal(scale) * un_d * un_r * un_r;
             const LbFrag pf[2] = {lb_split8(p, 0, scale), lb_split8(p, 1, scale)};
-            const lb_floatx16 c = lb_mma(r, pf);
+            const lb_floatx16 c = lb_mma<false>(r, pf);
 #pragma unroll
             for (int q = 0; q < 16; ++q) t[q] = fmaf(c[q], un, t[q]);
         }
@@ -756,7 +764,7 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
                 if (j_[s] >= 0 && j_[s] != k) lb_read_panel(f[(s + 1) & 1], panel, j_[s], lb_form_f(T, j_[s], k), l64);
             };
             read_tile(1);
-            const lb_floatx16 p = lb_mma(dq, f[1]);
+            const lb_floatx16 p = lb_mma<true>(dq, f[1]);
             const float scale = half_scale(__uint_as_float(lb_max_halves(__float_as_uint(lb_max_abs(p)))), LB_TOP), un_v = lb_reciprocal(scale) * un_p;
             dq[0] = lb_split8(p, 0, scale);
             dq[1] = lb_split8(p, 1, scale);
@@ -774,7 +782,7 @@ __global__ __launch_bounds__(LB_THREADS) void leaf_block_kernel(const LeafJob *_
                 __builtin_amdgcn_sched_barrier(0);
                 if (j == k) continue;
                 const float u = un_v * un_j[s];
-                const lb_floatx16 c = lb_mma(f[(s + 1) & 1], dq);
+                const lb_floatx16 c = lb_mma<false>(f[(s + 1) & 1], dq);
                 __builtin_amdgcn_sched_barrier(0);
                 if (v_ == k) {
 #pragma unroll
