@@ -1630,6 +1630,7 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
     };
     std::vector<int> inverted_ids;
     double later_gf = 0, all_n3 = 0;
+    double class_load[2] = {0, 0};                      // (of the whole list)
     bool early = false;
     for (int l = 0; l < n; ++l) {
         const bool inverted = !mask || mask[l];
@@ -1637,15 +1638,24 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
         layer_ok(st.L[l], &dA, &dG, nullptr, nullptr);
         if (inverted) inverted_ids.push_back(l);
         if (std::max(dA, dG) < tun.early_n) later_gf += factor_gf(l);
-        else early |= inverted;
+        else {
+            early |= inverted;
+            class_load[std::max(dA, dG) >= 2 * tun.early_n ? 0 : 1] += chain_load(st.L[l]);
+        }
         all_n3 += 1e-9 * chain_load(st.L[l]);
     }
     // ... also below 10 GFLOP where one long chain runs under contractions that take longer than it: 2048 -> 500 units (8.7
     // GFLOP) beside one, four 64-channel 3x3 layers at 56 x 56, 64 samples 930, 1500 us against 980, 1625 on one stream; beside 0.3 GFLOP
-    // of contractions 805 against 747.  (Of the whole list, whatever is inverted: a mask never takes streams, and scratch,
-    // that the whole list would not.)
+    // of contractions 805 against 747.  (Of the whole list, whatever is inverted, like the limit below: a mask never takes streams,
+    // and scratch, that the whole list would not.)
     const bool under_contractions = early && later_gf >= 4.0 * all_n3;
     int n_aux = under_contractions || spread_chains(tun, st.L, inverted_ids) ? std::max(0, std::min(tun.inv_streams, 4) - 1) : 0;
+    // With two classes each gets one stream where the second one's n^3 are less than two thirds of the first one's: on two streams its
+    // chains disturb the longest ones more than they hide.  More of them take two.  Two streams against one on 50 random lists and on
+    // ResNet-50 (v1, v1.5, 8 to 128 samples, fp32, bf16): ratio up to 0.64 (ResNet-50: 0.46) 1.01 times the time on average, up to
+    // 1.025 (ResNet-50, 32 samples 7200 us, 7070 on one); above 0.7 0.97, down to 0.89 (nine factors of up to 3803 rows beside two of
+    // 4096 or more: 5330 us, 6020 on one).  Not where the caller chose the schedule.
+    if (!tun.chosen_schedule && class_load[1] > 0 && 3 * class_load[1] < 2 * class_load[0]) n_aux = std::min(n_aux, 2);
     std::vector<int> cls[2], late, late_inv;
     for (int l = 0; l < n; ++l) {
         int dA, dG;
@@ -1660,9 +1670,6 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
     }
     if (cls[0].empty()) std::swap(cls[0], cls[1]);
     // auxiliary streams per class: with two classes the first (few, longest chains) gets one
-    // (and the second class one, too, unless the caller chose: on two streams its chains disturbed the longest ones more than they
-    // hid, ResNet-50 at 32 samples 7530 us against 7300, bf16 6450 against 6330)
-    if (!tun.chosen_schedule && !cls[0].empty() && !cls[1].empty()) n_aux = std::min(n_aux, 2);
     int aux_of[2][2] = {{1, n_aux}, {0, -1}};   // [class][first, last]
     if (!cls[1].empty()) {
         if (n_aux >= 2) { aux_of[0][1] = 1; aux_of[1][0] = 2; aux_of[1][1] = n_aux; }
@@ -1673,7 +1680,8 @@ void plan_step(Plan &plan, Arena &arena, const Tunables &tun, const StatsArgs &s
     // operand rewrites of the next phase run (on the last auxiliary stream, idle until its chain
     // starts) under the matrix launches of the current one, and what follows the matrix launches
     // of a class runs at the head of the first stream of its chains, under the matrix launches
-    // of the next phase.  Each phase then needs scratch of its own.
+    // of the next phase.  Each phase then needs scratch of its own.  (Where the second class has one stream, that is the last one
+    // too: the third phase's rewrites wait there behind the second class's matrix launches.  On a third stream they gained nothing.)
     //   event 6: the call's tables are on the device (recorded first on the context's stream)
     //   events 7, 8: rewrites of the second / third phase done
     //   events 9 + c: matrix launches of class c done;  events 4 + c: factors of class c complete

@@ -58,6 +58,16 @@ def test_default_schedule():
     assert _streams(_profile(LONG_CHAIN + CONTRACTIONS, [False] + [True] * 4)[0]) == {0}
 
 
+@pytest.mark.parametrize("second,streams", [((2100, 2200, 2300), {0, 1, 2}), ((3400, 3500, 3600), {0, 1, 2, 3})])
+def test_streams_of_two_classes(second, streams):
+    """The second class (2048 to 4095 rows) on one stream where it is much less than the first, on two otherwise; a mask takes no stream
+    that the whole list does not."""
+    layers = [wl.fc_layer(64, 4200, 16)] + [wl.fc_layer(64, n, 16) for n in second] + [wl.fc_layer(64, 60, 30)]
+    assert _streams(_profile(layers)[0]) == streams
+    for mask in ([0, 1, 1, 1, 1], [0, 1, 1, 1, 0], [0, 1, 0, 1, 1], [1, 0, 0, 0, 0], [1, 0, 1, 0, 1]):
+        assert _streams(_profile(layers, mask)[0]) <= streams, mask
+
+
 def test_factor_launches_in_parts():
     def factor_launches(**fields):
         return sum(e["kernel"] == "gemm_f32_split" and e["stream"] == 0 for e in _profile(SMALL, early_n=100, **fields)[0])
