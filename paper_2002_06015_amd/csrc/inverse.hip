@@ -4,7 +4,7 @@
 //     bias border of an A factor eliminated on the way (Schur complement), and border_kernel,
 //     which puts the border back into the finished inverse;
 //   - leaf_block_kernel: (X + damp I)^-1 for n <= 288 by a blocked symmetric sweep held in the
-//     registers of one 1024-thread workgroup, block products on the matrix cores (one matrix per
+//     registers of one 768-thread workgroup, block products on the matrix cores (one matrix per
 //     workgroup, many matrices per launch).
 #include "kfac_internal.h"
 
@@ -24,8 +24,9 @@ __device__ __forceinline__ void write_damping(const TraceJob &J, double pi, floa
     if (pi_out) pi_out[J.idx] = (float)pi;
 }
 // The traces of a layer over the THREADS threads of a workgroup, in two halves: their parts per wavefront into parts[2][THREADS / 64]
-// (then a barrier), and the damping of A or G from these.  Layers of up to kInlineTrace rows in both factors: a launch of its own
-// takes 7 us and a gap, this one memory latency.
+// (then a barrier), and the damping of A or G from these.  Layers of up to kInlineTrace rows in both factors: one memory latency in
+// the place of a launch of its own.  (The order of the sums is that of the workgroup: A and G of a layer, and a launch of its own, may
+// differ in the last place of pi as a double.)
 template <int THREADS>
 __device__ __forceinline__ void trace_parts(const TraceJob &J, double *parts)
 {
@@ -267,8 +268,8 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s)
 // 288 rows: 1.0e-3 with it, 2.9e-3 without, 1.2e-3 with three bf16 planes; 0.95^|i-j| 1.7e-5, 3.1e-5, 3.4e-5; patches of smooth
 // images 2.6e-5, 5.1e-5, 4.5e-5; 0.999^|i-j| 0.21, 0.49, 0.21.
 //
-// n = 288: 40.9 us (51.8 with fifteen wavefronts, three bf16 planes and an address per element), 224: 29.6 (35.9), 160: 20.0
-// (23.4), 64: 11.2 (11.2).  In-kernel cycles at n = 288: loads and scales 8400, a step 7650, stores 9000.  Of a step, the chain
+// n = 288: 42 us (52 with fifteen wavefronts, three bf16 planes and an address per element), 224: 30.4 (36.3), 160: 20.4
+// (23.8), 64: 11.2 (11.3), 42: 12.0 (11.4: stores of partial tiles).  In-kernel cycles, before the product of the low planes at n = 288: loads and scales 8400, a step 7650, stores 9000.  Of a step, the chain
 // needs 5600 (sweep 3640, D into planes 850, operand reads 260, P and update 900); a SIMD with three stars 3460 for its matrix
 // instructions and 5800 for the vector ones.
 typedef float lb_floatx16 __attribute__((ext_vector_type(16)));

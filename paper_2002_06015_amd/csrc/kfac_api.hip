@@ -369,11 +369,13 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
 // 259 parts 948 us (as single products 705), 504 parts 580.)
 // The rule: where the split rule allows the images 256 parts together.  With fewer (one image, or short contractions) a compute
 // unit holds one workgroup, which waits for its own loads; that, a launch more and no gain in the lines and corners make it the
-// slower way.  Products of one layer each at 56 x 56, together with those of its lines and corners, one by one against this way:
-//   fp32  64 channels, 32 samples: one image 78 us against 87; two 142, 103; three 212, 157.  64 samples: one 137, 132; three 494, 258;
-//                      128 samples: three 984, 463
-//   fp32  32 channels, 32 samples: three 148, 119;  50 channels at 28 x 28, 27 samples: two 47, 69
-//   bf16  64 channels, 32 samples: one 45, 47; two 80, 70; three 145, 139.  64 samples: one 75, 69; three 377, 257
+// slower way (the products of one image of 64 channels at 56 x 56, 32 samples, with those of its lines and corners 78 us one by one, 87
+// this way; of two of 50 channels at 28 x 28, 27 samples 47 and 69).  From 256 parts on, calls of kfac_stats for the A factors at 56 x 56,
+// one by one and this way:
+//   fp32  64 channels, 32 samples: two images 190 us, 158; three 278, 226.  64 samples: two 333, 242; three 607, 363.  128: three 1180, 638
+//         32 channels, 32 samples: three 210, 182;  17 channels at 40 x 40, 32 samples: five 207, 165
+//   bf16  64 channels, 32 samples: two 145, 134; three 256, 245.  64 samples: two 329, 278; three 553, 427.  128: three 1157, 836
+// (Over 110 random lists in fp32 the least gain is 1.0, over 160 in bf16 0.98.)
 // bf16 with more than 32 channels: where the parts have at least 900 positions and 13 lines.  Shorter ones, and lines that long, wait for
 // the six displaced lines of a step from beyond the caches that single products keep busy.  112 x 112, 8 samples, 64 channels: two images
 // 133 us one by one against 152 (7 lines a part), three 218, 243 (11), five 399, 367 (18); 79 x 79, 11 samples, 58 channels: three 167,
@@ -1374,8 +1376,8 @@ void plan_invert_mats(Plan &plan, Arena &arena, const Tunables &tun, const std::
     int max_level = -1;
     for (auto &op : ops) max_level = std::max(max_level, op.level);
     for (int lv = 0; lv <= max_level; ++lv) {
-        // One launch per level, by the kernel of its largest leaf and the largest first: a leaf is a serial chain on one compute
-        // unit, and one launch per size class ran chains of 21, 34 and 41 us one after the other that fit beside each other.
+        // One launch per level, the largest leaf first: a leaf is a serial chain on one compute unit, and chains of 21, 34 and 41 us
+        // fit beside each other.
         std::vector<LeafJob> lj;
         for (auto &op : ops)
             if (op.level == lv && op.kind == OP_LEAF) lj.push_back(op.leaf);
