@@ -24,8 +24,8 @@ def _padded(L):
 
 
 def _parts(L, times):
-    """Contraction length, length of a part and of the last part of an fp32 layer that stands `times` times in a list: the rule of
-    take_displaced (kfac_api.hip)."""
+    """Contraction length, length of a part and of the last part of an fp32 layer that stands `times` times in a list, for the last one of
+    them (parts that are left over go to the first ones): the rule of take_displaced (kfac_api.hip)."""
     Hp, Wp = _padded(L)
     K = L.N * Hp * Wp
     most, rounds = max(-(-K // 4096), min(128, K // max(512, 4 * Wp + 4))), -(-times * K // (8192 * 256))
@@ -218,6 +218,7 @@ def test_short_last_parts(shape, times, last):
         assert together == 1
         bits.append(A)
     _check(L, x, bits[0][0], A0[0])
+    _check(L, x, bits[0][-1], A0[-1])
     for l in range(times):
         assert torch.equal(bits[1][l], bits[0][l]) and torch.equal(bits[2][l], bits[0][l])
 
@@ -246,8 +247,8 @@ def test_rows_that_begin_behind_a_part(value, rows, other):
     assert found > 10
     A, A0, together = _factor([L] * times, kfac.KFAC_F32, [x] * times, decay=0.0)
     assert together == 1
-    _check(L, x, A[0], A0[0], decay=0.0)
-    _check(L, x, A[0], A0[0], decay=0.0, terms=6 * found, rows=9 * rows)
+    _check(L, x, A[-1], A0[-1], decay=0.0)
+    _check(L, x, A[-1], A0[-1], decay=0.0, terms=6 * found, rows=9 * rows)
 
 
 @pytest.mark.parametrize("shape,times,expected", [((3, 20, 12, 300), 30, 1), ((4, 64, 30, 1000), 8, 1), ((3, 5, 8, 1100), 40, 0), ((2, 40, 200, 210), 8, 1)])
