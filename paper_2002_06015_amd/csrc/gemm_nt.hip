@@ -2374,9 +2374,8 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_trans_kernel(const GemmProbl
 // A thread loads and stores 16 bytes of two rows of every staged tile: the tiles differ by a uniform base address only.  (The planes
 // of a padded image have at least 28 positions in fp32 and 40 in bf16, so that a step wraps twice at most.)
 constexpr int DISP_TILES = 7, DISP_TILE_BYTES = 8192, DISP_STAGE = DISP_TILES * DISP_TILE_BYTES;
-constexpr int DISP_SCALES = DISP_STAGE / 4, DISP_DOUBTS = DISP_SCALES + 256, DISP_REDO = DISP_DOUBTS + DISP_TILES * (1 + kMaxDoubts);   // in LDS, words
-constexpr size_t displaced_lds_bytes() { return (DISP_REDO + 1) * sizeof(float); }
-static_assert(split_lds_bytes<1, 1>() <= DISP_STAGE, "single products leave the lists of sums in doubt as they are");
+constexpr int DISP_SCALES = DISP_STAGE / 4, DISP_DOUBTS = DISP_SCALES + 384, DISP_INFINITE = DISP_DOUBTS + DISP_TILES * (1 + kMaxDoubts);   // in LDS, words
+constexpr size_t displaced_lds_bytes() { return (DISP_INFINITE + 1) * sizeof(float); }
 
 // Position of a thread's chunk in the contraction.
 struct DisplacedCursor {
@@ -2410,7 +2409,9 @@ struct DisplacedCursor {
 // have behind it, up to 2 Wp + 2 positions (what is behind an image is zero there).  take_displaced keeps parts at least twice as long
 // as that, so that the samples are those of every displaced image.  The eight places are unevenly spread and the element of a chunk that
 // counts for the floor changes: even steps of nearly a plane's length met little but the zero lines above its image (seven images of 3 to 49
-// channels, 57 samples, 14 x 14 planes among them: 311 us, 100 without).  False: the two planes do not serve.
+// channels, 57 samples, 14 x 14 planes among them: 311 us, 100 without).  sc[0 .. 256): scales of rows and columns and their floors;
+// sc[256 .. 384): floors for the product of the image with itself.  False: the two planes do not serve, since more than 16 rows have
+// hardly an element, and nearly all sums of theirs would come out in doubt.
 __device__ __forceinline__ bool displaced_scales(const Operand &op, int k0, int k1, int klen, float *sc, int tid)
 {
     const int row = tid >> 2, kq = 4 * (tid & 3);
@@ -2440,43 +2441,44 @@ __device__ __forceinline__ bool displaced_scales(const Operand &op, int k0, int 
     const bool zero = mx == 0.f, dead = row >= op.rows;
     if ((tid & 3) == 0) {
         sc[row] = sc[64 + row] = zero && !dead ? 0.f : scale;
-        sc[128 + row] = sc[192 + row] = dead ? kNoFloor : floor;
+        sc[128 + row] = sc[192 + row] = sc[256 + row] = sc[320 + row] = dead ? kNoFloor : floor;
     }
     const bool odd = !dead && floor > kHalfFloor;
-    if (__syncthreads_or(odd)) {
-        if (__syncthreads_count(odd && (tid & 3) == 0) > 16) return false;
-        for (int r = tid >> 6; r < 64; r += 4) {      // rows that sampled as zero are read on until an element is not
-            if (sc[r] != 0.f) continue;
+    if (!__syncthreads_or(odd)) return true;
+    if (__syncthreads_count(odd && !zero && (tid & 3) == 0) > 16) return false;
+    for (int r = tid >> 6; r < 64; r += 4) {              // rows that sampled as zero are read on until an element is not
+        if (sc[r] != 0.f) continue;
+        auto largest = [&](int to) {
             float most = 0.f;
-            auto walk = [&](int from, int to) {
-                walk_row(op, r, from, to - from, tid & 63, [&](const auto &x) {
+            walk_row(op, r, k0, to - k0, tid & 63, [&](const auto &x) {
 #pragma unroll
-                    for (const floatx4 &y : x) most = max_abs(most, y);
-                    for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
-                    return most != 0.f;
-                });
-                return most == 0.f;
-            };
-            const bool none = walk(k0, k1), none_behind = none && walk(k1, k0 + klen);
-            if ((tid & 63) == 0) {
-                sc[r] = sc[64 + r] = half_scale(most, kHalfTop);
-                if (none) sc[128 + r] = kNoFloor;              // as a row of its own part it is zero
-                if (none_behind) sc[192 + r] = kNoFloor;
-            }
+                for (const floatx4 &y : x) most = max_abs(most, y);
+                for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
+                return most != 0.f;
+            });
+            return most;
+        };
+        const float most = largest(k0 + klen);
+        const bool none = most == 0.f || largest(k1) == 0.f;   // none of its own part
+        if ((tid & 63) == 0) {
+            sc[r] = sc[64 + r] = half_scale(most, kHalfTop);
+            if (none) sc[128 + r] = sc[256 + r] = sc[320 + r] = kNoFloor;
+            if (most == 0.f) sc[192 + r] = kNoFloor;
         }
-        __syncthreads();
     }
-    return true;
+    __syncthreads();
+    return __syncthreads_count(tid < 64 && sc[192 + (tid & 63)] > kHalfFloor) <= 16;
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProblem *__restrict__ probs, const int *__restrict__ start, int n_groups)
+__global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProblem *__restrict__ probs, const int *__restrict__ start, int n_groups,
+                                                                int *__restrict__ left)
 {
     constexpr int KS = BF16 ? 64 : 32, CHUNK = KS / 8, ESIZE = BF16 ? 2 : 4;   // positions a step, a thread's chunk
     extern __shared__ __attribute__((aligned(16))) float lds[];
     char *stage = (char *)lds;
     float *sc = lds + DISP_SCALES;
-    int *doubts = (int *)lds + DISP_DOUBTS, *redo = (int *)lds + DISP_REDO;   // doubts: a list for each product
+    int *doubts = (int *)lds + DISP_DOUBTS, *infinite = (int *)lds + DISP_INFINITE;   // doubts: a list for each product
     // the parts of all images in a row, start[]: each image's first (two workgroups of a part on the same XCD, as many parts on each)
     const int wg = blockIdx.x, second = (wg >> 3) & 1, part_of_all = (wg & 7) + 8 * (wg >> 4);
     if (part_of_all >= start[n_groups]) return;
@@ -2499,7 +2501,7 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
     bool one_by_one = false;
     if constexpr (!BF16) {
         if (tid < DISP_TILES) doubts[tid * (1 + kMaxDoubts)] = 0;
-        if (tid == 0) *redo = 0;
+        if (tid == 0) *infinite = 0;
         // (the samples of a last part of up to one step, of any four positions more, would reach beyond it; see gemm_nt_f32_split_tile)
         const int to = min(Q->K, (k1 + (int)((base[DISP_TILES - 1] - base[0]) / ESIZE) + 3) & ~3);
         one_by_one = k1 - k0 <= KT || !displaced_scales(op, k0, k1, to - k0, sc, tid);
@@ -2633,7 +2635,7 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
                 if (chunk == 0 && (Q->flags & GEMM_BORDER)) global(Q->partial_rs)[(long long)split * 64 + row + 32 * s] = rs[s];
             }
         }
-        unsigned again = 0;
+        unsigned mine = 0;
 #pragma unroll
         for (int j = 0; j < DISP_TILES; ++j) {
             if (!live || (j == 0 && second)) continue;
@@ -2643,48 +2645,73 @@ __global__ __launch_bounds__(256, 2) void gemm_displaced_kernel(const GemmProble
                 for (int v = 0; v < 16; ++v) acc[j][v] += part[at_row(v)];
             floatx16 one[1][1] = {{acc[j]}};
             if constexpr (!BF16) {
-                if (half_doubts<1, 1>(one, sc, doubts + j * (1 + kMaxDoubts), wave_m, wave_n, l32, half) & 2) again |= 1u << j;
+                if (half_doubts<1, 1>(one, j == 0 ? sc + 128 : sc, doubts + j * (1 + kMaxDoubts), wave_m, wave_n, l32, half) & 2) mine |= 1u << j;
                 half_unscale_tile<1, 1>(one, sc, wave_m, wave_n, l32, half);
             }
 #pragma unroll
             for (int v = 0; v < 16; ++v) part[at_row(v)] = one[0][0][v];
         }
         if constexpr (!BF16) {
-            if (again) atomicOr(redo, (int)again);
-            __syncthreads();
+            if (mine) atomicOr(infinite, (int)mine);
         }
-    } else if (tid == 0) {
-        *redo = (1 << DISP_TILES) - 1;
     }
     if constexpr (!BF16) {
-        // where sums are not finite, many are in doubt (the limit of gemm_nt_f32_split_tile), or the two planes do not serve: as products
-        // of their own, one after the other; a few sums in doubt (of rows of random sign, one product in fourteen has some) by themselves
+        // A few sums in doubt (of rows of random sign, one product in fourteen has some) are formed again here.  Products with more than a
+        // single tile settles, or with sums that are not finite, and all of them where the two planes do not serve, are left to the
+        // next launch: one after the other here, the few of a launch took up to 100 us, all of them 230.
         __syncthreads();
-        const int again = *redo;
-        for (int j = second; j < DISP_TILES; ++j) {
-            const GemmProblem &P = Q[j == 0 ? 0 : 6 * second + j];
-            const int *list = doubts + j * (1 + kMaxDoubts);
-            const int n = one_by_one ? 0 : list[0];
-            if (((again >> j) & 1) || n > min(kMaxDoubts, 24 + (k1 - k0) / 32)) {
-                __syncthreads();
-                gemm_nt_f32_split_tile<1, 1>(P, 0, split, true, lds);
-            } else if (n) {
-                half_settle<64, 64>(P, list, n, 0, 0, k0, k1, tid, global(P.partial) + (long long)split * 4096, 64);
+        int alone = (1 << DISP_TILES) - 1;
+        if (!one_by_one) {
+            alone = *infinite;
+            for (int j = second; j < DISP_TILES; ++j) {
+                const int *list = doubts + j * (1 + kMaxDoubts), n = list[0];
+                if ((alone >> j) & 1) continue;
+                const GemmProblem &P = Q[j == 0 ? 0 : 6 * second + j];
+                if (n > min(kMaxDoubts, 24 + (k1 - k0) / 32)) alone |= 1 << j;
+                else if (n) half_settle<64, 64>(P, list, n, 0, 0, k0, k1, tid, global(P.partial) + (long long)split * 4096, 64);
             }
         }
+        if (tid == 0) global(left)[2 * part_of_all + second] = alone;
     }
 }
 
-template <typename Kernel>
-static hipError_t launch_one(Kernel kernel, bool &configured, size_t lds_bytes, const GemmProblem *probs_dev,
-                             const int *tile_start_dev, int n_probs, int total_wgs, hipStream_t s)
+// The products of a launch on 64-row tiles, and behind them a workgroup for each part of each displaced product, which ends at once
+// where gemm_displaced_kernel has not left it: the thirteen of a part one after the other on one XCD.  (Workgroups that take what is left
+// in turn would be fewer, but the loop around a tile spills 175 registers; those that end at once cost nothing that can be measured.)
+__global__ __launch_bounds__(256, 4) void gemm_nt_f32_split_rest_kernel(const GemmProblem *__restrict__ probs, const int *__restrict__ tile_start,
+                                                                        int n_probs, Displaced d)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int own = tile_start[n_probs], wg = blockIdx.x;
+    const GemmProblem *P;
+    int tile = 0, split;
+    bool part_of_k = true;
+    if (wg < own) {
+        const int pi = find_problem(tile_start, n_probs, wg), local = wg - tile_start[pi];
+        P = probs + pi;
+        if (local >= n_workgroups(*P)) return;   // padding up to the next problem
+        part_of_k = locate_tile(*P, local, tile, split);
+    } else {
+        const int at = (wg >> 3) - ((own + 7) >> 3);
+        if (at < 0) return;
+        const int q = 8 * (at / 13) + (wg & 7), r = at % 13;
+        if (q >= d.start[d.n_groups] || !((d.left[2 * q + (r > 6)] >> (r > 6 ? r - 6 : r)) & 1)) return;
+        const int g = find_problem(d.start, d.n_groups, q);
+        P = d.probs + 13 * g + r;
+        split = q - d.start[g];
+    }
+    gemm_nt_f32_split_tile<1, 1>(*P, tile, split, part_of_k, lds);
+}
+
+template <typename Kernel, typename... Args>
+static hipError_t launch_one(Kernel kernel, bool &configured, size_t lds_bytes, int total_wgs, hipStream_t s, Args... args)
 {
     if (!configured) {   // the attribute is per function, set once per process
         hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    kernel<<<dim3(total_wgs), dim3(256), lds_bytes, s>>>(probs_dev, tile_start_dev, n_probs);
+    kernel<<<dim3(total_wgs), dim3(256), lds_bytes, s>>>(args...);
     return hipGetLastError();
 }
 
@@ -2698,7 +2725,7 @@ hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, 
     if (total_wgs <= 0) return hipSuccess;
     static bool configured[5][2];
     auto go = [&](auto kernel, size_t lds_bytes) {
-        return launch_one(kernel, configured[dtype][tile_cfg == 0], lds_bytes, probs_dev, tile_start_dev, n_probs, total_wgs, s);
+        return launch_one(kernel, configured[dtype][tile_cfg == 0], lds_bytes, total_wgs, s, probs_dev, tile_start_dev, n_probs);
     };
     constexpr size_t big = gemm_lds_bytes<2, 2>(), small = gemm_lds_bytes<1, 1>();
     switch (dtype) {
@@ -2711,11 +2738,17 @@ hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, 
     return go(gemm_nt_f32_split_kernel<1, 1>, split_lds_bytes<1, 1>());
 }
 
-hipError_t launch_gemm_displaced(const GemmProblem *probs_dev, const int *start_dev, int n_groups, int total_wgs, int bf16, hipStream_t s)
+hipError_t launch_gemm_displaced(const Displaced &d, int total_wgs, int bf16, hipStream_t s)
 {
     static bool configured[2];
-    auto kernel = bf16 ? gemm_displaced_kernel<true> : gemm_displaced_kernel<false>;
-    return launch_one(kernel, configured[bf16 != 0], displaced_lds_bytes(), probs_dev, start_dev, n_groups, total_wgs, s);
+    return launch_one(bf16 ? gemm_displaced_kernel<true> : gemm_displaced_kernel<false>, configured[bf16 != 0], displaced_lds_bytes(), total_wgs, s,
+                      d.probs, d.start, d.n_groups, d.left);
+}
+
+hipError_t launch_gemm_rest(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, const Displaced &d, int total_wgs, hipStream_t s)
+{
+    static bool configured;
+    return launch_one(gemm_nt_f32_split_rest_kernel, configured, split_lds_bytes<1, 1>(), total_wgs, s, probs_dev, tile_start_dev, n_probs, d);
 }
 
 hipError_t launch_gemm_reduce(const GemmProblem *probs_dev, const int *red_start_dev, int n_probs,

@@ -179,6 +179,8 @@ struct Launch {
     int k_max;             // L_GEMM: longest contraction
     float f0, f1;
     void *p0, *p1, *p2;
+    size_t off_c, off_d;   // L_GEMM with displaced products beside it, and their own launch: their problems, first parts,
+    int n_groups;          // and groups of 13; p0: what is left of them (Displaced)
     double flops, bytes;   // algorithmic counts (profiling only)
     int stream;            // 0: the context's stream; 1..3: auxiliary streams (ordered by L_RECORD / L_WAIT)
 };
@@ -307,9 +309,10 @@ int choose_direct(const std::vector<GemmProblem> &probs, const Tunables &tun)
 // launches, on a stream it chooses).
 // align: every problem starts at a multiple of that many workgroups (8: see locate_tile; not where the padding could push a
 // launch past a whole number of rounds).
-// displaced: so many problems at the front, in groups of 13, have a launch of their own (gemm_displaced_kernel).
+// displaced: so many problems at the front, in groups of 13, have a launch of their own (gemm_displaced_kernel); left: fp32, where it
+// reports what it leaves to the other one, which then has a workgroup for each part of each of them.
 void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmProblem> &sel, int cfg, int dtype, int align,
-                      std::vector<Launch> *deferred = nullptr, size_t displaced = 0)
+                      std::vector<Launch> *deferred = nullptr, size_t displaced = 0, int *left = nullptr)
 {
     if (sel.empty()) return;
     const int B = tile_edge(cfg);
@@ -324,8 +327,9 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
         any_split |= P.splits > 1;
     }
     const size_t off = plan.tab.add(sel.data(), sel.size() * sizeof(GemmProblem));
+    const size_t off_d = displaced ? plan.tab.add(dstart.data(), dstart.size() * sizeof(int)) : 0;
     auto matrix_launch = [&](size_t first, size_t last, const std::vector<int> &at, int kernel, int wgs) {
-        if (first == last) return;
+        if (wgs == 0) return;
         Launch L{};
         L.kind = L_GEMM;
         for (size_t i = first; i < last; ++i) {
@@ -343,11 +347,15 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
         L.n = (int)at.size() - 1;
         L.total_wgs = wgs;
         L.cfg = kernel;
+        L.off_c = off;
+        L.off_d = off_d;
+        L.n_groups = (int)displaced / 13;
+        L.p0 = left;
         L.dtype = (dtype == 0 && tun.split) ? 2 : dtype;
         plan.launches.push_back(L);
     };
     matrix_launch(0, displaced, dstart, kDisplacedCfg, (dstart.back() + 7) / 8 * 16);   // (two a part)
-    matrix_launch(displaced, sel.size(), start, cfg, start.back());
+    matrix_launch(displaced, sel.size(), start, cfg, left ? (start.back() + 7) / 8 * 8 + 13 * ((dstart.back() + 7) / 8 * 8) : start.back());
     if (any_split) {
         Launch R{};
         R.kind = L_REDUCE;
@@ -381,7 +389,8 @@ void push_gemm_launch(Plan &plan, const Tunables &tun, const std::vector<GemmPro
 // 133 us one by one against 152 (7 lines a part), three 218, 243 (11), five 399, 367 (18); 79 x 79, 11 samples, 58 channels: three 167,
 // 184 (10); 100 x 44, 10 samples, 49 channels: three 120, 131 (576 positions).
 // fp32: parts at least twice as long as the last displacement reaches (2 Wp + 2), for one scale of a row to serve all of them.
-void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> &sel, std::vector<GemmProblem> &displaced, bool fp32)
+void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> &sel, std::vector<GemmProblem> &displaced, bool fp32,
+                    int **left_of)
 {
     struct Image { size_t at; int K, line, most, shortest, parts; };   // its first product; length of a line; most parts; least of a part
     std::vector<Image> images;
@@ -441,6 +450,10 @@ void take_displaced(Arena &arena, const Tunables &tun, std::vector<GemmProblem> 
     }
     rest.insert(rest.end(), sel.begin() + next, sel.end());
     sel = rest;
+    if (!fp32) return;
+    int parts = 0;
+    for (size_t i = 0; i < displaced.size(); i += 13) parts += displaced[i].splits;
+    *left_of = (int *)arena.take(2 * (size_t)parts * sizeof(int));
 }
 
 // Emits the launches of one phase by the split rule (factor products; all products where a caller chose the rule): per tile
@@ -487,8 +500,12 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
         const int B = tile_edge(cfg);
         int align = 1;
         std::vector<GemmProblem> displaced;
+        int *left = nullptr;
+        if (tun.worst_case_splits && cfg == 1 && dtype == 0)   // (beyond the partial tiles: what take_displaced takes besides)
+            for (auto &P : sel)
+                if (P.flags & GEMM_DISPLACED) arena.take(2 * sizeof(int) * std::max((P.K + tun.max_k_per_wg - 1) / tun.max_k_per_wg, tun.target_wgs));
         if (cfg == 1 && (dtype == 1 || (dtype == 0 && tun.split)) && !tun.chosen_rule && !tun.worst_case_splits)
-            take_displaced(arena, tun, sel, displaced, dtype == 0);
+            take_displaced(arena, tun, sel, displaced, dtype == 0, &left);
         if (cfg < 2) {
             // Per problem (independent of what else is in the launch, so that the workspace need of
             // a layer list does not depend on which of its inputs are present): enough splits for
@@ -520,7 +537,7 @@ void emit_gemm_phase(Plan &plan, Arena &arena, const Tunables &tun, std::vector<
             return std::min(x.K, x.k_per_split) > std::min(y.K, y.k_per_split);
         });
         sel.insert(sel.begin(), displaced.begin(), displaced.end());
-        push_gemm_launch(plan, tun, sel, cfg, dtype, align, deferred, displaced.size());
+        push_gemm_launch(plan, tun, sel, cfg, dtype, align, deferred, displaced.size(), left);
     }
 }
 
@@ -1914,10 +1931,13 @@ kfac_status run_plan(kfac_ctx *ctx, Plan &plan, Arena &arena)
         }
         switch (L.kind) {
             case L_GEMM:
-                if (L.cfg == kDisplacedCfg) {
-                    e = launch_gemm_displaced((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b), L.n, L.total_wgs,
-                                              L.dtype == 1, ls);
-                    break;
+                if (L.n_groups) {
+                    const Displaced d{(const GemmProblem *)(tab_dev + L.off_c), (const int *)(tab_dev + L.off_d), L.n_groups, (int *)L.p0};
+                    if (L.cfg == kDisplacedCfg || L.p0) {
+                        e = L.cfg == kDisplacedCfg ? launch_gemm_displaced(d, L.total_wgs, L.dtype == 1, ls)
+                                                   : launch_gemm_rest((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b), L.n, d, L.total_wgs, ls);
+                        break;
+                    }
                 }
                 e = L.cfg >= 2 ? launch_gemm_direct((const GemmProblem *)(tab_dev + L.off_a), (const int *)(tab_dev + L.off_b),
                                                     L.n, L.total_wgs, L.cfg, L.k_max, ls)

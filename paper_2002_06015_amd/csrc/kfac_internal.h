@@ -314,8 +314,16 @@ hipError_t launch_gemm(const GemmProblem *probs_dev, const int *tile_start_dev, 
 // small products of plain fp32 matrices (tile_cfg 2, 3), three-plane product mode
 hipError_t launch_gemm_direct(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, int total_wgs,
                               int tile_cfg, int k_max, hipStream_t s);
-// groups of 13 problems: the displaced products of padded images of up to 64 channels (dtype fp32 through planes, or bf16), all split
-hipError_t launch_gemm_displaced(const GemmProblem *probs_dev, const int *start_dev, int n_groups, int total_wgs, int bf16, hipStream_t s);
+// the displaced products of padded images of up to 64 channels (fp32 through planes, or bf16), all split
+struct Displaced {
+    const GemmProblem *probs;   // n_groups times 13
+    const int *start;           // [n_groups + 1]: the first part of each group, of the parts of all in a row
+    int n_groups;
+    int *left;                  // fp32: [2 * parts], which products of a part (7 and 6 of them, bits) are left to launch_gemm_rest
+};
+hipError_t launch_gemm_displaced(const Displaced &d, int total_wgs, int bf16, hipStream_t s);
+// fp32 products through planes on 64-row tiles, and those that launch_gemm_displaced has left
+hipError_t launch_gemm_rest(const GemmProblem *probs_dev, const int *tile_start_dev, int n_probs, const Displaced &d, int total_wgs, hipStream_t s);
 hipError_t launch_gemm_reduce(const GemmProblem *probs_dev, const int *red_start_dev, int n_probs,
                               int total_wgs, hipStream_t s);
 hipError_t launch_patch(const PatchJob *jobs_dev, int n_jobs, int total_wgs, hipStream_t s);

@@ -265,8 +265,10 @@ def test_wide_images(shape, times, expected):
 
 
 # signed: sums near zero, in doubt; dead: rows of zeros; half: too many of them; sparse: rows that sample as zero and are not; scales:
-# images of very different size; steep: a row that leaves the range of fp16; far: rows near the ends of fp32
-@pytest.mark.parametrize("kind", ["signed", "dead", "half", "sparse", "scales", "steep", "far", "zero"])
+# images of very different size; steep: a row that leaves the range of fp16; far: rows near the ends of fp32; late: images that are black
+# down to their middle, so that parts are zero in all rows, or in their own positions only; thin: one element of twenty, no two planes
+# in any part; fifth: rows that a few elements dominate
+@pytest.mark.parametrize("kind", ["signed", "dead", "half", "sparse", "scales", "steep", "far", "zero", "late", "thin", "fifth"])
 @pytest.mark.parametrize("c", [20, 64])
 def test_values(kind, c):
     N, h, w = 9, 24, 26
@@ -291,6 +293,12 @@ def test_values(kind, c):
         x[:, 5] *= 2.0 ** -50
     elif kind == "zero":
         x.zero_()
+    elif kind == "late":
+        x[:, :, :h // 2] = 0
+    elif kind == "thin":
+        x *= torch.rand(N, c, h, w, device="cuda", generator=gen) < 0.1
+    elif kind == "fifth":
+        x = x ** 5
     L = wl.Layer(N, c, 8, 3, 1, 1, h, w, 1)
     A, A0, together = _factor([L] * _times(L), kfac.KFAC_F32, [x] * _times(L))
     assert together == 1
