@@ -2366,7 +2366,7 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_trans_kernel(const GemmProbl
 // fp32: 26 conversions of every element as well).  Here a workgroup stages the rows of the image and of six displaced ones in LDS
 // and forms seven (or six) products out of them: two workgroups, on the same XCD, share a part.  7 x 16 accumulators leave
 // two workgroups to a compute unit (all thirteen in one: 208, one workgroup, and half the parts).
-// Three images of 64 channels at 56 x 56: fp32 187 -> 136 us with 32 samples (252 TFLOP/s), 959 -> 440 with 128 (312), 500 once the
+// Three images of 64 channels at 56 x 56: fp32 187 -> 135 us with 32 samples (255 TFLOP/s), 959 -> 437 with 128 (315), 500 once the
 // clock has gone down to 1.9 GHz; bf16 130 -> 127 with 32, 414 (365 TFLOP/s) with 128.  Bound: fp32 by power, at that clock with the matrix
 // unit busy 0.39 to 0.47 of the time; bf16 (0.13 to 0.16, at 2.2 GHz, wavefronts waiting 0.7 of the time) by the loads of a step, which wait
 // for its barrier (one stage: two would leave one workgroup to a compute unit).  Errors of the factors against 64 bits, over batches of 8 to 128, 17 to 64 channels and 28 to 112
